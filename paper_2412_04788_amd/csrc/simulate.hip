@@ -6,18 +6,19 @@
 // here is documented in guide.h.  The engine state is kept in aggregated form:
 //   - admission is FCFS, so admitted requests are the index range [.., next);
 //   - prompt chunks are handed out in admission order, so at most the head of
-//     the prefill queue [pf_head, next) is partially prefilled;
+//     the prefill queue [comp, next) is partially prefilled;
 //   - a request that finished its prompt decodes on every later step, so its
 //     finishing step is known when its prompt completes: decoders live in a
 //     per-lane 4-ary min-heap keyed by finishing step (root in registers, the
-//     rest in global memory, one cache line per node's children), and their
-//     number and total context are two running integers.
-// One step therefore costs one pass-time evaluation plus O(1) integer updates;
-// heap traffic is O(log n) per request, not per step.
+//     rest in LDS as far as it goes), and their number and total context are
+//     two running numbers.
+// A request therefore costs a few pass-time evaluations and O(log n) heap
+// traffic; the steps in between cost an addition to the clock or less.
 #include <type_traits>
 
 #include "kernels.hpp"
 #include "perf_model.hpp"
+#include "reduce.hpp"
 
 namespace guide {
 
@@ -25,16 +26,14 @@ namespace {
 
 constexpr uint32_t kSimBlock = 256;      // one block per compute unit: the trace is staged once, the rest of LDS holds heaps
 constexpr uint32_t kPctBlock = 256;
-constexpr size_t kSimStaticLds = 2 * kSimBlock * 4 + 64;   // the simulation kernel's own static LDS (segment tables)
+constexpr size_t kSimStaticLds = 64;     // the simulation kernel's own static LDS (wave totals)
 
-struct SimLds {
-    uint32_t axis[kNumAxes][GUIDE_MAX_AXIS_VALUES];
-    guide_model models[GUIDE_MAX_MODELS];
-    double arrival[GUIDE_MAX_REQUESTS];
-    uint32_t n_in[GUIDE_MAX_REQUESTS];
-    uint32_t n_out[GUIDE_MAX_REQUESTS];
+struct RequestsLds {
+    double arrival[GUIDE_MAX_REQUESTS];      // at unit rate
+    uint2 len[GUIDE_MAX_REQUESTS];           // prompt and generated tokens
 };
 
+constexpr uint32_t kHeapWidth = 4;     // children per heap node
 constexpr uint32_t kKeyBins = 1024;      // buckets of the expected-step-count ordering
 
 // Workspace: heap[position][node] (u64 keys), first[cfg][req] and fin[cfg][req] (time of the first and of the
@@ -72,39 +71,54 @@ __device__ inline bool decode_sim_index(const uint32_t (*axis)[GUIDE_MAX_AXIS_VA
     return bad;
 }
 
-// Lanes of a wave run until their slowest configuration ends, so configurations
-// are launched in order of a rough estimate of their engine steps: generated
-// tokens / concurrency, with concurrency from Little's law (arrival rate x
-// latency of a lone request), clamped to [1, sequence cap].  Only the order
-// depends on it, never a result.
+// Lanes of a wave run until their slowest configuration ends, and a lane's heap wants as much LDS as it has
+// sequences running, so configurations are ordered by an estimate of their concurrency: Little's law (arrival
+// rate x latency), with the latency at that concurrency, clamped to [1, what the sequence cap and the KV pool let
+// in].  Buckets of a hundredth of an octave.  Only the order and the shares of LDS depend on it, never a result.
+__device__ inline uint32_t bucket_of(float conc) {
+    const int k = (int)(__log2f(fmaxf(conc, 1.0f)) * 100.0f);
+    return (uint32_t)(k > (int)kKeyBins - 1 ? (int)kKeyBins - 1 : k);
+}
+__device__ inline float expected_of(uint32_t bucket) { return exp2f((float)bucket * 0.01f); }
+// Counting and scattering go through a histogram per block in LDS: the buckets in use are few, and one global atomic
+// per configuration serialises on them (197 + 195 us for 65 536 configurations).
+constexpr uint32_t kOrderBlock = 1024;
+static_assert(kOrderBlock == kKeyBins, "a thread per bucket");
 template <bool ADDITIVE>
-__global__ __launch_bounds__(kBlock) void sim_order_count_kernel(GridDesc g, const DevTables *__restrict__ tab,
-                                                                 uint32_t n_req,
-                                                                 const uint32_t *__restrict__ cfg_idx,
-                                                                 const double *__restrict__ rate_in, uint32_t n_cfg,
-                                                                 SimWs ws, double sum_in, double sum_out) {
-    const double s_sum[2] = {sum_in, sum_out};      // prompt / generated tokens of the whole trace
-    const uint32_t c = blockIdx.x * kBlock + threadIdx.x;
-    if (c >= n_cfg) return;
-    uint32_t v[kNumAxes];
-    const bool bad = decode_sim_index(tab->axis_vals, g, cfg_idx[c], v);
-    uint32_t b = 0;
-    const double rate = rate_in[c];
-    if (!bad && rate > 0.0) {
-        const guide_hw hw = tab->hw[v[AX_HW]];
-        const Coef cf = make_coef(tab->models[v[AX_MODEL]], v[AX_TP], v[AX_WBITS]);
-        const TimeCoef tc = make_time_coef(cf, 1.0 / hw.peak_flops, 1.0 / hw.hbm_bw, 1.0 / hw.link_bw, hw.link_lat);
-        const double mean_in = s_sum[0] / (double)n_req, mean_out = s_sum[1] / (double)n_req;
-        const double ctx = mean_in + 0.5 * mean_out;
-        const double lone = mean_out * pass_time<ADDITIVE>(tc, 1.0, ctx, ctx, 1.0) +
-                            pass_time<ADDITIVE>(tc, mean_in, mean_in * mean_in, mean_in, 1.0);
-        const double conc = fmin(fmax(rate * lone, 1.0), (double)v[AX_BATCH]);
-        const float steps = (float)(s_sum[1] / conc);
-        const int k = (int)((__log2f(fmaxf(steps, 1.0f)) - 6.0f) * 64.0f);
-        b = (uint32_t)(k < 0 ? 0 : (k > (int)kKeyBins - 1 ? (int)kKeyBins - 1 : k));
+__global__ __launch_bounds__(kOrderBlock) void sim_order_count_kernel(GridDesc g, const DevTables *__restrict__ tab,
+                                                                      uint32_t n_req,
+                                                                      const uint32_t *__restrict__ cfg_idx,
+                                                                      const double *__restrict__ rate_in, uint32_t n_cfg,
+                                                                      SimWs ws, double sum_in, double sum_out) {
+    __shared__ uint32_t s_n[kKeyBins];
+    s_n[threadIdx.x] = 0;
+    __syncthreads();
+    const uint32_t c = blockIdx.x * kOrderBlock + threadIdx.x;
+    if (c < n_cfg) {
+        uint32_t v[kNumAxes];
+        const bool bad = decode_sim_index(tab->axis_vals, g, cfg_idx[c], v);
+        uint32_t b = 0;
+        const double rate = rate_in[c];
+        if (!bad && rate > 0.0) {
+            const guide_hw hw = tab->hw[v[AX_HW]];
+            const Coef cf = make_coef(tab->models[v[AX_MODEL]], v[AX_TP], v[AX_WBITS]);
+            const TimeCoef tc = make_time_coef(cf, 1.0 / hw.peak_flops, 1.0 / hw.hbm_bw, 1.0 / hw.link_bw, hw.link_lat);
+            const double mean_in = sum_in / (double)n_req, mean_out = sum_out / (double)n_req;
+            const double ctx = mean_in + 0.5 * mean_out;
+            const double pool = floor(fmax(hw.cap_bytes - cf.w_gpu, 0.0) / ((mean_in + mean_out + 0.5 * (double)v[AX_BLK]) * cf.kv_tok));
+            const double most = fmin(fmin((double)v[AX_BATCH], (double)n_req), fmax(pool, 1.0));
+            // twice the share of time that prompts take holds the decoders up
+            const double busy = fmin(2.0 * rate * pass_time<ADDITIVE>(tc, mean_in, mean_in * mean_in, mean_in, 1.0), 0.95);
+            double conc = 1.0;
+            for (int it = 0; it < 8; ++it)
+                conc = fmin(fmax(rate * mean_out * pass_time<ADDITIVE>(tc, conc, conc * ctx, conc * ctx, conc) / (1.0 - busy), 1.0), most);
+            b = bucket_of((float)conc);
+        }
+        ws.bucket[c] = b;
+        atomicAdd(&s_n[b], 1u);
     }
-    ws.bucket[c] = b;
-    atomicAdd(&ws.bins[b], 1u);
+    __syncthreads();
+    if (s_n[threadIdx.x]) atomicAdd(&ws.bins[threadIdx.x], s_n[threadIdx.x]);
 }
 
 __global__ __launch_bounds__(kKeyBins) void sim_order_scan_kernel(SimWs ws) {
@@ -118,141 +132,286 @@ __global__ __launch_bounds__(kKeyBins) void sim_order_scan_kernel(SimWs ws) {
         s[t] += o;
         __syncthreads();
     }
-    // longest first: bucket b starts after all higher buckets
-    ws.bins[t] = s[kKeyBins - 1] - s[t];
+    ws.bins[t] = t ? s[t - 1] : 0;              // bucket t starts after all lower buckets
 }
 
-__global__ __launch_bounds__(kBlock) void sim_order_scatter_kernel(uint32_t n_cfg, SimWs ws) {
-    const uint32_t c = blockIdx.x * kBlock + threadIdx.x;
-    if (c < n_cfg) ws.perm[atomicAdd(&ws.bins[ws.bucket[c]], 1u)] = c;
+__global__ __launch_bounds__(kOrderBlock) void sim_order_scatter_kernel(uint32_t n_cfg, SimWs ws) {
+    __shared__ uint32_t s_n[kKeyBins], s_at[kKeyBins];
+    s_n[threadIdx.x] = 0;
+    __syncthreads();
+    const uint32_t c = blockIdx.x * kOrderBlock + threadIdx.x;
+    const uint32_t b = c < n_cfg ? ws.bucket[c] : 0u;
+    uint32_t rank = 0;
+    if (c < n_cfg) rank = atomicAdd(&s_n[b], 1u);
+    __syncthreads();
+    if (s_n[threadIdx.x]) s_at[threadIdx.x] = atomicAdd(&ws.bins[threadIdx.x], s_n[threadIdx.x]);
+    __syncthreads();
+    if (c < n_cfg) ws.perm[s_at[b] + rank] = c;
 }
 
 __global__ __launch_bounds__(kKeyBins) void sim_order_clear_kernel(SimWs ws) { ws.bins[threadIdx.x] = 0; }
 
-// Heap of the decoders' finishing steps, one per lane.  Node 0 lives in a register, nodes 1 .. cap in the lane's
-// segment of LDS, deeper nodes in global memory.  4-ary: the children of node i are 4i+1 .. 4i+4.
+// Heap of the decoders' finishing steps, one per lane.  The root lives in a register, node i = 1, 2, .. at position i - 1
+// of the lane's LDS segment (cap positions), deeper nodes in global memory.  D-ary: the children of node i are nodes
+// D i + 1 .. D i + D at positions D i .. D i + D - 1, so siblings are aligned 16-byte reads (cap is a multiple of D and at
+// least D: siblings never straddle the segment's end).  Unused LDS positions hold the largest key.  (Eight children per
+// node, which need fewer levels of longer comparisons, measured the same: 6.43 against 6.41 ms.)
 // Key = finishing step << 10 | request; 32-bit keys when every finishing step fits 22 bits (twice the nodes in LDS).
+// While the nodes of all lanes in action are in LDS, which is nearly always, the branches that look at global memory
+// are left out by a choice that is uniform over the wave.
 template <typename KeyT>
 struct LaneHeap {
-    KeyT top;
-    KeyT *lds;            // node i (1 <= i <= cap) at lds[i - 1]
-    KeyT *mem;            // node i (i > cap) at mem[i]
+    static constexpr KeyT kEmpty = (KeyT)~(KeyT)0;
+    KeyT top;             // kEmpty when there is none: above every key
+    KeyT *lds;            // position j < cap
+    KeyT *mem;            // position j >= cap at mem[j]
     uint32_t cap, n;
-    __device__ KeyT get(uint32_t i) const { return i <= cap ? lds[i - 1] : mem[i]; }
-    __device__ void set(uint32_t i, KeyT k) {
-        if (i <= cap) lds[i - 1] = k; else mem[i] = k;
-    }
-    __device__ void push(KeyT key) {                // the new node rises from the end
-        uint32_t i = n++;
-        while (i > 0) {
-            const uint32_t par = (i - 1) >> 2;
-            const KeyT pk = par == 0 ? top : get(par);
-            if (pk <= key) break;
-            set(i, pk);
-            i = par;
+    static constexpr uint32_t D = kHeapWidth;
+    struct alignas(16) Children {
+        KeyT k[D];
+    };
+    // Waits for the global loads above it.  Where a branch that is hardly ever taken loads from global memory, the
+    // wait belongs inside it: left to the value's use after the join, every lane's way there would wait for all
+    // of the wave's global accesses, the stores of finishing times (a microsecond or two) among them.
+    static __device__ void wait_here() { __builtin_amdgcn_s_waitcnt(0x0F70); }      // vmcnt(0)
+    __device__ KeyT get(uint32_t j) const {
+        KeyT k = kEmpty;
+        if (j < cap) k = lds[j];
+        if (j >= cap) {
+            k = mem[j];
+            wait_here();
         }
-        if (i == 0) top = key; else set(i, key);
+        return k;
+    }
+    __device__ void set(uint32_t j, KeyT k) {
+        if (j < cap) lds[j] = k;
+        if (j >= cap) mem[j] = k;
+    }
+    // the least of the children and which it is (keys differ)
+    static __device__ KeyT least(const Children &c, uint32_t &at) {
+        KeyT m = c.k[0];
+#pragma unroll
+        for (uint32_t j = 1; j < D; ++j) m = c.k[j] < m ? c.k[j] : m;
+        at = 0;
+#pragma unroll
+        for (uint32_t j = 1; j < D; ++j) at = c.k[j] == m ? j : at;
+        return m;
+    }
+    __device__ void push(KeyT key) {                // the new node rises from the end; a new least key takes the root's place
+        const KeyT old = top;
+        top = key < old ? key : old;
+        key = key < old ? old : key;
+        const uint32_t i0 = n++;                    // the new node
+        if (i0 == 0) return;                        // (key is kEmpty then)
+        uint32_t i = i0;
+        if (__ballot(i0 > cap) == 0) {
+            while (i > D) {                         // nodes 1 .. D are the root's children
+                const uint32_t par = (i - 1) / D;
+                const KeyT pk = lds[par - 1];
+                if (pk <= key) break;
+                lds[i - 1] = pk;
+                i = par;
+            }
+            lds[i - 1] = key;
+        } else {
+            while (i > D) {
+                const uint32_t par = (i - 1) / D;
+                const KeyT pk = get(par - 1);
+                if (pk <= key) break;
+                set(i - 1, pk);
+                i = par;
+            }
+            set(i - 1, key);
+        }
     }
     __device__ void pop() {                         // the last node sinks from the root
         --n;
-        if (n == 0) {
-            top = (KeyT)~(KeyT)0;
-            return;
-        }
-        const KeyT last = get(n);
-        uint32_t i = 0;
-        for (;;) {
-            const uint32_t c0 = 4 * i + 1;
-            if (c0 >= n) break;
-            KeyT k[4];
+        const uint32_t end = n ? n - 1 : 0u;        // its position (with no node left: position 0, which is unused)
+        uint32_t hole = 0, at;
+        KeyT last;
+        if (__ballot(n > cap) == 0) {
+            last = lds[end];
+            lds[end] = kEmpty;
+            const Children k0 = *(const Children *)lds;
+            KeyT best = least(k0, at);
+            top = best < last ? best : last;
+            if (!(best < last)) return;
+            hole = at;
+            for (;;) {
+                const uint32_t g = D * hole + D;    // the children's positions; position end - 1 is the last in use
+                const bool inside = g < end;
+                const Children k = *(const Children *)(lds + (inside ? g : 0u));
+                best = least(k, at);
+                const bool go = inside && best < last;
+                lds[hole] = go ? best : last;
+                if (!go) break;
+                hole = g + at;
+            }
+        } else {
+            last = get(end);
+            if (end < cap) lds[end] = kEmpty;
+            const Children k0 = *(const Children *)lds;
+            KeyT best = least(k0, at);
+            top = best < last ? best : last;
+            if (!(best < last)) return;
+            hole = at;
+            for (;;) {
+                const uint32_t g = D * hole + D;
+                if (g >= end) break;
+                Children k;
+                if (g < cap) k = *(const Children *)(lds + g);
+                if (g >= cap) {
 #pragma unroll
-            for (uint32_t j = 0; j < 4; ++j) k[j] = get(c0 + j < n ? c0 + j : c0);      // all four requested at once
-            KeyT best = k[0];
-            uint32_t bi = c0;
-#pragma unroll
-            for (uint32_t j = 1; j < 4; ++j)
-                if (c0 + j < n && k[j] < best) { best = k[j]; bi = c0 + j; }
-            if (best >= last) break;
-            if (i == 0) top = best; else set(i, best);
-            i = bi;
+                    for (uint32_t j = 0; j < D; ++j) k.k[j] = g + j < end ? mem[g + j] : kEmpty;
+                    wait_here();
+                }
+                best = least(k, at);
+                if (!(best < last)) break;
+                set(hole, best);
+                hole = g + at;
+            }
+            set(hole, last);
         }
-        if (i == 0) top = last; else set(i, last);
     }
 };
 
-// Time of r consecutive decode-only steps of T decoders whose total context is C0 before the first one:
-// r * (everything but attention) + L * (attention over contexts C0, C0 + T, ..), the latter in closed form.
+// Pass times of one configuration with the number of layers multiplied into the layers' coefficients once.
+struct LaneTimes {
+    double c[N_LINEAR], m0[N_LINEAR], m1[N_LINEAR];
+    double lin1, lin0;                      // norms and all-reduces: per token, per pass
+    double c_lm, m0_lm, m1_lm;
+    double c_att, m_att_t, m_att_k;
+    double E, k;
+};
+__device__ inline LaneTimes lane_times(const TimeCoef &t) {
+    LaneTimes r;
+#pragma unroll
+    for (int i = 0; i < N_LINEAR; ++i) {
+        r.c[i] = t.L * t.c[i];
+        r.m0[i] = t.L * t.m0[i];
+        r.m1[i] = t.L * t.m1[i];
+    }
+    r.lin1 = t.L * fma(2.0, t.ar1, t.m_nm);
+    r.lin0 = t.L * (2.0 * t.ar0);
+    r.c_lm = t.c_lm; r.m0_lm = t.m0_lm; r.m1_lm = t.m1_lm;
+    r.c_att = t.L * t.c_att; r.m_att_t = t.L * t.m_att_t; r.m_att_k = t.L * t.m_att_k;
+    r.E = t.E; r.k = t.k;
+    return r;
+}
+// A pass of T tokens with n_lm LM-head rows, without attention.
 template <bool ADDITIVE>
-__device__ inline double run_time(const TimeCoef &tc, double step_const, double T, double r_T, double C0, double r) {
-    const double att = attention_series<ADDITIVE>(tc.c_att, tc.m_att_k, T * tc.m_att_t, C0 - T, T, r_T, r);
-    return fma(r, step_const, tc.L * att);
+__device__ inline double pass_base(const LaneTimes &t, double T, double n_lm) {
+    const double eld = fmin(t.E, t.k * T);   // experts whose weights are read
+    double s = fma(T, t.lin1, t.lin0);
+    s += op_time<ADDITIVE>(T * t.c[OP_QKV], fma(T, t.m1[OP_QKV], t.m0[OP_QKV]));
+    s += op_time<ADDITIVE>(T * t.c[OP_OPROJ], fma(T, t.m1[OP_OPROJ], t.m0[OP_OPROJ]));
+    s += op_time<ADDITIVE>(T * t.c[OP_UP], fma(T, t.m1[OP_UP], eld * t.m0[OP_UP]));
+    s += op_time<ADDITIVE>(T * t.c[OP_DOWN], fma(T, t.m1[OP_DOWN], eld * t.m0[OP_DOWN]));
+    s += op_time<ADDITIVE>(T * t.c[OP_ROUTER], fma(T, t.m1[OP_ROUTER], t.m0[OP_ROUTER]));
+    s += n_lm > 0.0 ? op_time<ADDITIVE>(n_lm * t.c_lm, fma(n_lm, t.m1_lm, t.m0_lm)) : 0.0;
+    return s;
 }
 
-// CLOSED_RUNS: runs of decode-only steps are advanced by run_time() in one go (GUIDE_SIM_CLOSED_FORM_RUNS);
-// otherwise step by step with the general step's own arithmetic.
-// ordered: configurations run in the order ws.perm (longest expected first); otherwise as given.
-// heap_slots: keys that the LDS behind the staged tables holds for the whole block; they are shared out among the
-// block's lanes in proportion to the most decoders each can have (its sequence cap), so that a lane that can
-// run a thousand sequences gets a long segment and a lane capped at four next to nothing.
+// The least r in 1 .. r_max with arr <= now + time_of(r), r_max when there is none; time_of grows with r.
+// guess: a first estimate.  An estimate that is right or one off takes two evaluations, any other a bisection.
+template <typename F>
+__device__ inline uint32_t least_steps(double now, double arr, uint32_t r_max, float guess, F &&time_of) {
+    uint32_t lo = 0, hi = r_max, r = guess >= 1.0f ? (guess < (float)r_max ? (uint32_t)guess : r_max) : 1u;
+    bool near = true;
+    while (hi - lo > 1) {
+        r = r <= lo ? lo + 1 : (r >= hi ? hi - 1 : r);
+        const bool reached = arr <= now + time_of((double)r);
+        if (reached) hi = r; else lo = r;
+        r = near ? (reached ? r - 1 : r + 1) : lo + (hi - lo) / 2;
+        near = false;
+    }
+    return hi;
+}
+
+// What the host knows about the trace.
+struct TraceSums {
+    double out;             // generated tokens
+    uint64_t tokens;        // prompt and generated tokens
+    uint32_t longest;       // most prompt + generated tokens of one request
+};
+
+// One configuration per lane, `lanes` of them per wave (64, or fewer when there are not enough configurations for
+// the chip's waves: the paths of the lanes of a wave are executed one after the other, so fewer lanes make a
+// shorter instruction stream, which is what bounds the kernel: every SIMD holds one wave).
+// A round of the loop does at most one of each kind of thing: one decoder leaves, one request enters, one prompt chunk is
+// scheduled, a pass with prompts runs, one prompt turns into a decoder, a run of decode-only steps advances up to
+// and including the step that retires the next decoder.  A lane with one event at a time takes one round per request;
+// a lane with bursts takes a round per request as well, while the other lanes go on with theirs (loops over a burst
+// make the whole wave wait for every lane's bursts in turn: 7000 loop turns per 1024 requests).
+// CLOSED_RUNS: the run is advanced in closed form (GUIDE_SIM_CLOSED_FORM_RUNS); otherwise the clock walks through it.  A
+// step's time is linear in the context while attention is bound by reading the cache at any context (every lane of
+// nearly every wave), so the walk takes strides of 64 and 8 steps, whose times are in arithmetic progression, as long
+// as the last step of the stride starts before the arrival that would end the run, and single steps after that.
+// (The stride's sum has one rounding where 64 additions to a clock of hundreds of seconds have 64: against 80-bit
+// sums over runs of up to 2000 steps the clock is 2.2e-16 off, step by step 7.0e-16.)
+// What bounds the kernel: a wave is a serial stream of about 560 instructions per round, 7 cycles each with one wave
+// per SIMD (40 % of the cycles wait for LDS, 55 % issue), and the longest wave takes 2000 - 3200 rounds.
+// 65 536 configurations x 1024 requests: 7.1 ms stepped, 5.8 ms with closed-form runs; 1999 x 97: 0.69 ms.
+// Before (loops over every kind of event, two rounds per request, four predicated steps of 65 instructions at a time,
+// heap segments by sequence cap, finishing times waited for by every heap read): 41.9, 13.9 and 4.1 ms.
+// heap_slots: keys that the LDS behind the staged trace holds for the whole block (whole groups of siblings); they are
+// shared out among the block's lanes in proportion to the most decoders each can have (its sequence cap), so that a
+// lane that can run a thousand sequences gets a long segment and a lane capped at four next to nothing.
 template <bool ADDITIVE, bool PREFILL_FIRST, bool CLOSED_RUNS, typename KeyT>
 __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const DevTables *__restrict__ tab,
                                                              const TraceDev *__restrict__ trace, uint32_t n_req,
                                                              const uint32_t *__restrict__ cfg_idx,
                                                              const double *__restrict__ rate_in, uint32_t n_cfg,
-                                                             guide_sim_out out, SimWs ws, uint32_t max_run,
-                                                             uint32_t heap_slots, uint32_t ordered) {
+                                                             guide_sim_out out, SimWs ws, TraceSums sums, uint32_t lanes,
+                                                             uint32_t heap_slots) {
+    // With 32-bit keys the whole trace is below 2^30 tokens, so blocks, budgets and steps fit 32 bits as well
+    using Int = typename std::conditional<sizeof(KeyT) == 4, int32_t, long long>::type;
+    constexpr Int kIntMax = sizeof(KeyT) == 4 ? (Int)0x7FFFFFFF : (Int)(1ll << 62);
     extern __shared__ __align__(16) unsigned char s_raw[];
-    SimLds &s = *(SimLds *)s_raw;
-    KeyT *s_heap = (KeyT *)(s_raw + sizeof(SimLds));
-    __shared__ uint32_t s_cap[kSimBlock], s_off[kSimBlock];
-    __shared__ uint32_t s_total[kSimBlock / kWave];
-    for (uint32_t i = threadIdx.x; i < kNumAxes * GUIDE_MAX_AXIS_VALUES; i += blockDim.x)
-        (&s.axis[0][0])[i] = (&tab->axis_vals[0][0])[i];
-    for (uint32_t i = threadIdx.x; i < g.n_models * 8u; i += blockDim.x)
-        ((uint32_t *)s.models)[i] = ((const uint32_t *)tab->models)[i];
+    RequestsLds &req = *(RequestsLds *)s_raw;
+    KeyT *s_heap = (KeyT *)(s_raw + sizeof(RequestsLds));
+    __shared__ uint2 s_total[kSimBlock / kWave];
     for (uint32_t i = threadIdx.x; i < n_req; i += blockDim.x) {
-        s.arrival[i] = trace->arrival[i];
-        s.n_in[i] = trace->n_in[i];
-        s.n_out[i] = trace->n_out[i];
+        req.arrival[i] = trace->arrival[i];
+        req.len[i] = uint2{trace->n_in[i], trace->n_out[i]};
     }
-    __syncthreads();
-    const uint32_t pos = blockIdx.x * kSimBlock + threadIdx.x;     // launch position
-    const bool in_range = pos < n_cfg;
-    const uint32_t c = in_range ? (ordered ? ws.perm[pos] : pos) : 0u;      // its configuration
+    for (uint32_t i = threadIdx.x; i < heap_slots / (16 / sizeof(KeyT)); i += blockDim.x)
+        ((uint4 *)s_heap)[i] = uint4{~0u, ~0u, ~0u, ~0u};
+    const uint32_t wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    // Configurations are in order of their expected concurrency, and wave w of a block takes its lanes from the
+    // w-th quarter of them: lanes of a wave behave alike, and every block has waves with short and with long heaps.  The
+    // last quarter, where heaps reach hundreds of keys, is dealt out lane by lane, so that no block has more of
+    // the longest ones than its LDS holds (consecutive lanes there: 7.9 instead of 6.5 ms).
+    const uint32_t in_part = wave & 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+    const uint32_t pos = wave == kSimBlock / kWave - 1 ? (wave * lanes + lane) * gridDim.x + in_part
+                                                       : (wave * gridDim.x + in_part) * lanes + lane;
+    const bool in_range = lane < lanes && pos < n_cfg;
+    const uint32_t c = in_range ? ws.perm[pos] : 0u;              // the lane's configuration
 
     uint32_t v[kNumAxes];
     bool alive = false;                                           // this lane has a simulation to run
-    uint32_t max_seqs = 1, blk = 1, mbt = 1;
-    double rate = 1.0, c_avail = 0.0, tokens = 0.0;
-    uint64_t step_bound = n_req;
-    long long n_blk = 0;
-    Coef cf;
-    TimeCoef tc;
+    uint32_t max_seqs = 1, mbt = 1;
+    double rate = 1.0;
+    Int n_blk = 0;
+    LaneTimes lt;
     Div32 dblk = make_div32(1);
     // KV blocks of a request of `tok` >= 1 tokens: ceil(tok / blk) without the 32-bit overflow of tok + blk - 1
-    auto blocks_of = [&](uint32_t tok) { return (long long)div32(tok - 1, dblk) + 1; };
+    auto blocks_of = [&](uint32_t tok) { return (Int)div32(tok - 1, dblk) + 1; };
     if (in_range) {
-        const bool bad_index = decode_sim_index(s.axis, g, cfg_idx[c], v);
-        max_seqs = v[AX_BATCH]; blk = v[AX_BLK]; mbt = v[AX_MBT];
+        const bool bad_index = decode_sim_index(tab->axis_vals, g, cfg_idx[c], v);
+        max_seqs = v[AX_BATCH]; mbt = v[AX_MBT];
         const guide_hw hw = tab->hw[v[AX_HW]];
         rate = rate_in[c];
-        cf = make_coef(s.models[v[AX_MODEL]], v[AX_TP], v[AX_WBITS]);
-        tc = make_time_coef(cf, 1.0 / hw.peak_flops, 1.0 / hw.hbm_bw, 1.0 / hw.link_bw, hw.link_lat);
-        dblk = make_div32(blk);
+        const Coef cf = make_coef(tab->models[v[AX_MODEL]], v[AX_TP], v[AX_WBITS]);
+        lt = lane_times(make_time_coef(cf, 1.0 / hw.peak_flops, 1.0 / hw.hbm_bw, 1.0 / hw.link_bw, hw.link_lat));
+        dblk = make_div32(v[AX_BLK]);
         // KV pool in blocks; every request must fit on its own
-        c_avail = hw.cap_bytes - cf.w_gpu;
-        uint32_t max_tok = 0;
-        for (uint32_t i = 0; i < n_req; ++i) {
-            const uint32_t t = s.n_in[i] + s.n_out[i];
-            max_tok = t > max_tok ? t : max_tok;
-            step_bound += t;
-            tokens += (double)s.n_out[i];
-        }
+        const double c_avail = hw.cap_bytes - cf.w_gpu;
         if (c_avail > 0.0) {
-            const double nb = floor(c_avail / ((double)blk * cf.kv_tok));
-            n_blk = nb >= 9.0e18 ? 0x7FFFFFFFFFFFFFFFll : (long long)nb;
+            const double nb = floor(c_avail / ((double)v[AX_BLK] * cf.kv_tok));
+            n_blk = nb >= (double)kIntMax ? kIntMax : (Int)nb;
         }
-        if (bad_index || !(c_avail > 0.0) || blocks_of(max_tok) > n_blk || !(rate > 0.0)) {
+        if (bad_index || !(c_avail > 0.0) || blocks_of(sums.longest) > n_blk || !(rate > 0.0)) {
             out.ttft_p50[c] = INFINITY; out.ttft_p99[c] = INFINITY; out.mean_tpot[c] = INFINITY; out.tokens_s[c] = 0.0;
             out.status[c] = (bad_index || !(rate > 0.0)) ? GUIDE_SIM_BAD_INPUT : GUIDE_SIM_INFEASIBLE;
             out.n_steps[c] = 0; out.n_request_steps[c] = 0;
@@ -263,232 +422,283 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
 
     // LDS segments of the heaps: a lane can have at most min(sequence cap, requests) decoders, one of them in a
     // register; when the block's lanes want more than the LDS holds, every segment shrinks by the same factor
-    const uint32_t want = alive ? (max_seqs < n_req ? max_seqs : n_req) - 1u : 0u;
+    LaneHeap<KeyT> heap;
     {
-        uint32_t t = want;
-        for (int off = kWave / 2; off > 0; off >>= 1) t += __shfl_xor(t, off, kWave);
-        if (threadIdx.x % kWave == 0) s_total[threadIdx.x / kWave] = t;
-        __syncthreads();
-        uint32_t total = 0;
-        for (uint32_t w = 0; w < kSimBlock / kWave; ++w) total += s_total[w];
-        uint32_t cap = want;
-        if (total > heap_slots) cap = (uint32_t)((double)want * ((double)heap_slots / (double)total) * (1.0 - 0x1p-30));
-        s_cap[threadIdx.x] = cap;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            uint32_t run = 0;
-            for (uint32_t i = 0; i < kSimBlock; ++i) {
-                s_off[i] = run;
-                run += s_cap[i];
-            }
+        const uint32_t most = max_seqs < n_req ? max_seqs : n_req;
+        // most - 1 positions at most, and not many more than the pool holds requests of average length; three times
+        // the expected concurrency first, what is left over in proportion to the rest
+        const float mean_blocks = (float)sums.tokens / (float)n_req / (float)dblk.d + 0.5f;
+        const float pool = fminf(1.5f * (float)n_blk / mean_blocks + 4.0f, 2048.0f);
+        auto groups = [](uint32_t x) { return (x + kHeapWidth - 1) / kHeapWidth * kHeapWidth; };
+        const uint32_t bound = groups((most < (uint32_t)pool ? most : (uint32_t)pool) - 1u);
+        const uint32_t likely = groups((uint32_t)(3.0f * expected_of(alive ? ws.bucket[c] : 0u)) + 16u);
+        const uint32_t full = alive ? (bound < kHeapWidth ? kHeapWidth : bound) : 0u, want = alive && likely < full ? likely : full;
+        const uint32_t wave_want = wave_sum(want), wave_full = wave_sum(full);
+        if (lane == 0) s_total[wave] = uint2{wave_want, wave_full};
+        __syncthreads();                                // the trace and the empty heaps are staged as well
+        uint32_t total = 0, total_full = 0;
+        for (uint32_t w = 0; w < kSimBlock / kWave; ++w) {
+            total += s_total[w].x;
+            total_full += s_total[w].y;
         }
+        // (heap_slots is at least a group per thread whenever the wants do not fit, so every lane in use keeps one)
+        uint32_t cap = want;
+        if (total > heap_slots)
+            cap = kHeapWidth + (uint32_t)((double)(want - kHeapWidth) * ((double)(heap_slots - kHeapWidth * kSimBlock) / (double)total)) /
+                                   kHeapWidth * kHeapWidth;
+        else if (total_full > total)
+            cap = want + (uint32_t)((double)(full - want) * fmin((double)(heap_slots - total) / (double)(total_full - total), 1.0)) /
+                             kHeapWidth * kHeapWidth;
+        if (!alive) cap = 0;
+        const uint32_t incl = wave_scan_sum(cap);
         __syncthreads();
+        if (lane == kWave - 1) s_total[wave].x = incl;
+        __syncthreads();
+        uint32_t off = incl - cap;
+        for (uint32_t w = 0; w < wave; ++w) off += s_total[w].x;
+        heap.lds = s_heap + off;
+        heap.cap = cap;
     }
+    // attention bound by reading the cache at every context, for every lane of the wave: step times are linear
+    const bool wave_linear = ADDITIVE || __ballot(alive && !(lt.c_att <= lt.m_att_k)) == 0;
     if (!alive) return;
 
-    LaneHeap<KeyT> heap;
-    heap.top = (KeyT)~(KeyT)0;
-    heap.lds = s_heap + s_off[threadIdx.x];
+    heap.top = LaneHeap<KeyT>::kEmpty;
     heap.mem = (KeyT *)(ws.heap + (size_t)pos * n_req);
-    heap.cap = s_cap[threadIdx.x];
     heap.n = 0;
     double *first = ws.first + (size_t)c * n_req, *fin = ws.fin + (size_t)c * n_req;
 
-    double now = 0.0, max_fin = -INFINITY;
-    uint32_t next = 0, pf_head = 0, pf_done = 0, n_dec = 0, n_done = 0;
-    uint64_t s_ctx = 0, step = 0, dstep = 0, n_rs = 0;   // dstep counts the steps in which decoders ran
-    long long free_blk = n_blk;
+    // arrival / rate: the reciprocal's product with one correction step has the division's rounding; rates and traces at the
+    // ends of the range are divided
+    const double last_arrival = req.arrival[n_req - 1];
+    const bool plain_rate = rate >= 0x1p-400 && rate <= 0x1p400 && last_arrival <= 0x1p400;
+    const bool wave_plain = __ballot(!plain_rate) == 0;
+    const double r_rate = 1.0 / rate;
+    auto arrival_of = [&](double a) {
+        const double q = a * r_rate;
+        double t = fma(fma(-q, rate, a), r_rate, q);
+        if (!wave_plain) {
+            asm volatile("");                           // keeps the division out of the other lanes' way
+            t = plain_rate ? t : a / rate;
+        }
+        return t;
+    };
+    const Int budget_full = (uint64_t)mbt > (uint64_t)(kIntMax / 2) ? kIntMax / 2 : (Int)mbt;   // beyond every trace
+
+    double now = 0.0, max_fin = -INFINITY, s_ctx = 0.0;     // s_ctx: total context, an integer far below 2^53
+    // prompts [comp, next) are admitted and have not emitted their first token; the next one to schedule is h, of which
+    // `done` tokens have been computed; pend: prompts from comp on whose last chunk was in the pass just run
+    uint32_t next = 0, comp = 0, h = 0, done = 0, pend = 0, n_dec = 0, n_done = 0;
+    double c_T = 0.0, c_Q = 0.0, c_K = 0.0;                 // chunks scheduled for the next pass: tokens, workload, context
+    uint32_t chunks = 0, n_full = 0;                        // their number, and prompts that they complete
+    Int used = 0;                                           // their tokens
+    uint64_t step = 0, n_rs = 0;
+    KeyT dstep = 0;                                         // steps in which decoders ran
+    Int free_blk = n_blk;
     uint32_t status = GUIDE_SIM_OK;
-    double arr_next = s.arrival[0] / rate;   // arrival time of request `next`
-    long long need_next = blocks_of(s.n_in[0] + s.n_out[0]);
-    double kept_base = 0.0, kept_lm = 0.0;   // layer_base / lm_head for kept_dec decode tokens (a pure function of the count)
+    const uint64_t step_bound = (uint64_t)n_req + sums.tokens;      // every step consumes at least one token of some request
+    const uint32_t last_req = n_req - 1;
+    auto at_most = [&](uint32_t r) { return r < last_req ? r : last_req; };
+    double arr_next = arrival_of(req.arrival[0]);           // arrival time of request `next`
+    Int need_next = blocks_of(req.len[0].x + req.len[0].y);
+    double kept_base = 0.0;                                 // pass_base of kept_dec decode tokens
     uint32_t kept_dec = 0;
 
-    while (n_done < n_req) {
-        // Run of decode-only steps: no prompt is waiting for chunks, and nothing changes until the first
-        // decoder finishes or a request that could be admitted arrives.
-        if (pf_head == next && n_dec > 0) {
+    for (;;) {
+        // everything that the steps below read from LDS, requested together
+        const uint2 l_h = req.len[at_most(h)], l_comp = req.len[at_most(comp)], l_next = req.len[at_most(next + 1)];
+        const double a_next = req.arrival[at_most(next + 1)];
+        bool moved = false;
+        // 1. a decoder that has emitted its last token leaves (an empty heap's top is beyond every step)
+        if ((heap.top >> 10) == dstep) {
+            const uint32_t r = (uint32_t)(heap.top & 1023u);
+            const uint2 len = req.len[r];
+            heap.pop();
+            free_blk += blocks_of(len.x + len.y);
+            --n_dec;
+            s_ctx -= (double)(len.x + len.y);
+            ++n_done;
+            fin[r] = now;
+            max_fin = now;
+            moved = true;
+        }
+        if (n_done == n_req) break;
+        // 2. idle: jump to the next arrival
+        const uint32_t n_active = (next - comp) + n_dec;
+        if (n_active == 0 && next < n_req) now = arr_next > now ? arr_next : now;
+        // 3. FCFS admission of one request, if it can enter.  (Decoders that still have to leave, or prompts that turn into
+        // decoders, only make room: whoever enters before would enter after.)
+        auto admissible = [&](uint32_t active) {
+            return next < n_req && active < max_seqs && arr_next <= now && need_next <= free_blk;
+        };
+        if (admissible(n_active)) {
+            free_blk -= need_next;
+            ++next;
+            arr_next = next < n_req ? arrival_of(a_next) : INFINITY;
+            need_next = blocks_of(l_next.x + l_next.y);
+            moved = true;
+        }
+        const bool leaving = (heap.top >> 10) == dstep;
+        // 4. schedule one prompt chunk.  Split-fuse: the budget that the decoders leave, whose number is final once nobody
+        // leaves or joins any more; a whole prompt may go in before when it fits for sure.  Prefill-first:
+        // whole prompts, as many as fit the budget, the first always.
+        {
+            const Int rem = (Int)(l_h.x - done);
+            const Int left = PREFILL_FIRST ? budget_full - used : budget_full - (Int)(n_dec + pend) - used;
+            const bool fits = PREFILL_FIRST ? (chunks == 0 || rem <= left)
+                                            : (rem <= left || (left > 0 && !leaving && pend == 0));
+            if (h < next && fits) {
+                const Int ch = PREFILL_FIRST ? rem : (rem < left ? rem : left);
+                used += ch;
+                done += (uint32_t)ch;
+                const double C = (double)ch, ctx = (double)done;
+                c_T += C;
+                c_Q = fma(C, ctx, c_Q);
+                c_K += ctx;
+                ++chunks;
+                if (ch == rem) {
+                    ++n_full;
+                    ++h;
+                    done = 0;
+                }
+                moved = true;
+            }
+        }
+        // 5. a pass with prompts, once nothing is left to be done before it: one token per decoder (prefill-first:
+        // the decoders pause) and the scheduled chunks
+        const bool settled = !leaving && pend == 0 && !admissible((next - comp) + n_dec);
+        if (settled && comp < next) {
+            const bool more = h < next && (PREFILL_FIRST ? (Int)(req.len[at_most(h)].x) <= budget_full - used
+                                                         : budget_full - (Int)n_dec - used > 0);
+            if (!more) {
+                const double d = PREFILL_FIRST ? 0.0 : (double)n_dec, ctx = PREFILL_FIRST ? 0.0 : s_ctx;
+                const double T = c_T + d, Q = c_Q + ctx, K = c_K + ctx;
+                now += pass_base<ADDITIVE>(lt, T, d + (double)n_full) +
+                       op_time<ADDITIVE>(Q * lt.c_att, fma(K, lt.m_att_k, T * lt.m_att_t));
+                ++step;
+                n_rs += chunks;
+                if (!PREFILL_FIRST) {
+                    n_rs += n_dec;
+                    if (n_dec > 0) ++dstep;
+                    s_ctx += d;
+                }
+                pend = n_full;
+                c_T = c_Q = c_K = 0.0;
+                chunks = n_full = 0;
+                used = 0;
+                moved = true;
+            }
+        }
+        // 6. a prompt completed in the last pass emits its first token
+        if (pend > 0) {
+            const uint32_t r = comp;
+            first[r] = now;
+            if (l_comp.y == 1) {
+                free_blk += blocks_of(l_comp.x + 1);
+                ++n_done;
+                fin[r] = now;
+                max_fin = now;
+            } else {
+                ++n_dec;
+                s_ctx += (double)(l_comp.x + 1);
+                heap.push((KeyT)(((dstep + (KeyT)(l_comp.y - 1)) << 10) | r));
+            }
+            ++comp;
+            --pend;
+            moved = true;
+        }
+        // 7. run of decode-only steps: no prompt is waiting, and nothing changes until the first decoder emits its
+        // last token or a request that could be admitted arrives.
+        if (comp == next && n_dec > 0 && (heap.top >> 10) != dstep) {
+            const double T = (double)n_dec;
             if (kept_dec != n_dec) {
-                kept_base = layer_base<ADDITIVE>(tc, (double)n_dec);
-                kept_lm = lm_head<ADDITIVE>(tc, (double)n_dec);
+                kept_base = pass_base<ADDITIVE>(lt, T, T);
                 kept_dec = n_dec;
             }
             const bool can_admit = next < n_req && n_dec < max_seqs && need_next <= free_blk;
-            const double arr_stop = can_admit ? arr_next : INFINITY;
-            const uint64_t stop = (uint64_t)(heap.top >> 10); // the step whose book-keeping retires a decoder
-            // steps left before that one (stop > dstep: its last token is still to come)
-            const uint64_t left = stop - dstep - 1;
-            const double T = (double)n_dec;
-            double ctx = (double)s_ctx;                       // integers below 2^53: exact in fp64
+            const double arr_stop = can_admit ? arr_next : __builtin_nan("");      // compares false: nothing ends the run early
+            const uint32_t total = (uint32_t)((heap.top >> 10) - dstep);  // steps up to the one that retires a decoder
+            // time of a step at context c: base + max(c_att c, m_att_k c + T m_att_t)
+            const double base = kept_base, base_m = fma(T, lt.m_att_t, base);
+            const double slope = ADDITIVE ? lt.c_att + lt.m_att_k : lt.m_att_k;
+            auto step_time = [&](double ctx) {
+                const double tm = fma(ctx, slope, base_m);
+                return wave_linear ? tm : fmax(fma(ctx, lt.c_att, base), tm);
+            };
             uint32_t run = 0;
             if (CLOSED_RUNS) {
-                // The run takes r = min(left, least r with arrival <= now + time of r steps) steps.  The search
-                // walks up from r = 0 without overshooting: the steps still to come each take at most the time
-                // of the last one that could be needed, so floor(remaining / that) of them fit for sure.
-                const uint32_t r_max = left < 0x40000000ull ? (uint32_t)left : 0x40000000u;
-                const double step_const = fma(tc.L, kept_base, kept_lm), r_T = fast_recip(T);
-                auto t_at = [&](double j) {
-                    const double cj = fma(j, T, ctx);
-                    return fma(tc.L, attention<ADDITIVE>(tc, T, cj, cj), step_const);
-                };
-                double s_run = 0.0;
-                if (!can_admit) {
+                // all steps before the retiring one, or the least number after which the arrival has come
+                const uint32_t r_max = total - 1;
+                if (r_max > 0 && !(arr_stop <= now)) {
+                    const double h_T = 0.5 * T;
+                    auto linear_time = [&](double r) { return r * fma(slope, fma(h_T, r - 1.0, s_ctx), base_m); };
+                    auto any_time = [&](double r) {
+                        return fma(r, base, attention_series<ADDITIVE>(lt.c_att, lt.m_att_k, T * lt.m_att_t, s_ctx - T, T,
+                                                                       fast_recip(T), r));
+                    };
                     run = r_max;
-                    s_run = run_time<ADDITIVE>(tc, step_const, T, r_T, ctx, (double)run);
-                } else {
-                    for (;;) {
-                        const double rem = arr_stop - (now + s_run);
-                        if (!(rem > 0.0) || run == r_max) break;
-                        const double room = (double)(r_max - run);
-                        const double ub = fmin(ceil(rem * fast_recip(t_at((double)run))), room);
-                        const double t_hi = t_at((double)run + fmax(ub, 1.0) - 1.0);
-                        const double q = fmin(fmax(floor(rem * fast_recip(t_hi)), 1.0), room);
-                        run += (uint32_t)q;
-                        s_run = run_time<ADDITIVE>(tc, step_const, T, r_T, ctx, (double)run);
+                    if (can_admit) {
+                        // time(r) = p r + q r^2 up to rounding; its root in single precision is the first guess
+                        const double rem = arr_stop - now;
+                        const float q = (float)(slope * h_T), p = (float)fma(slope, s_ctx - h_T, base_m), rf = (float)rem;
+                        const float guess = ceilf(2.0f * rf * __builtin_amdgcn_rcpf(p + __builtin_amdgcn_sqrtf(fmaf(p, p, 4.0f * q * rf))));
+                        run = wave_linear ? least_steps(now, arr_stop, r_max, guess, linear_time)
+                                          : least_steps(now, arr_stop, r_max, guess, any_time);
                     }
+                    now += wave_linear ? linear_time((double)run) : any_time((double)run);
                 }
-                now += s_run;
-            } else {
-                const uint32_t r_cap = left < max_run ? (uint32_t)left : max_run;
-                auto step_time = [&](double cj) { return fma(tc.L, kept_base + attention<ADDITIVE>(tc, T, cj, cj), kept_lm); };
-                // Four steps at a time without a branch between them: the times after each step are formed in
-                // step order (n1 = now + t1, n2 = n1 + t2, ..), and the run stops after the first k steps whose
-                // starting time is still before the arrival -- times only grow, so k is a count of compares.
-                // Each step is the general step below with its invariant parts left out: the same operations
-                // in the same order on the same values.
+                if (run == r_max && !(arr_stop <= now)) {
+                    now += step_time(fma((double)run, T, s_ctx));
+                    ++run;
+                }
+            } else if (wave_linear) {
+                const double dt = slope * T;
+                double t0 = fma(s_ctx, slope, base_m);
+                // strides of 64, then of 8 steps, whose times are in arithmetic progression, while the last step
+                // of the stride would still start before the arrival; then step by step
+                auto stride = [&](auto steps) {
+                    constexpr double kS = decltype(steps)::value;
+                    while (run + (uint32_t)kS <= total) {
+                        const double to_last = now + fma(0.5 * (kS - 1.0) * (kS - 2.0), dt, (kS - 1.0) * t0);
+                        if (arr_stop <= to_last) break;
+                        now += fma(0.5 * kS * (kS - 1.0), dt, kS * t0);
+                        t0 = fma(kS, dt, t0);
+                        run += (uint32_t)kS;
+                    }
+                };
+                stride(std::integral_constant<int, 64>{});
+                t0 = fma(fma((double)run, T, s_ctx), slope, base_m);
+                stride(std::integral_constant<int, 8>{});
+                t0 = fma(fma((double)run, T, s_ctx), slope, base_m);
                 bool go = true;
-                while (go && run + 4 <= r_cap) {
-                    const double c2 = ctx + T, c3 = c2 + T, c4 = c3 + T;
-                    const double n1 = now + step_time(ctx), n2 = n1 + step_time(c2), n3 = n2 + step_time(c3),
-                                 n4 = n3 + step_time(c4);
-                    const uint32_t k = arr_stop <= now ? 0u : arr_stop <= n1 ? 1u : arr_stop <= n2 ? 2u : arr_stop <= n3 ? 3u : 4u;
-                    now = k == 0 ? now : k == 1 ? n1 : k == 2 ? n2 : k == 3 ? n3 : n4;
-                    ctx = k == 0 ? ctx : k == 1 ? c2 : k == 2 ? c3 : k == 3 ? c4 : c4 + T;
-                    run += k;
-                    go = k == 4;
+#pragma unroll
+                for (int j = 0; j < 7; ++j) {
+                    go = go && run < total && !(arr_stop <= now);
+                    const double n = now + fma((double)j, dt, t0);
+                    now = go ? n : now;
+                    run += go ? 1u : 0u;
                 }
-                while (go && run < r_cap && !(arr_stop <= now)) {
+            } else {
+                double ctx = s_ctx;
+                while (run < total && !(arr_stop <= now)) {
                     now += step_time(ctx);
                     ctx += T;
                     ++run;
                 }
             }
             step += run;
-            dstep += run;
+            dstep += (KeyT)run;
             n_rs += (uint64_t)run * n_dec;
-            s_ctx += (uint64_t)run * n_dec;
+            s_ctx = fma((double)run, T, s_ctx);
+            moved = moved || run > 0;
         }
-        uint32_t n_active = (next - pf_head) + n_dec;
-        // 1. idle jump to the next arrival
-        if (n_active == 0 && next < n_req) now = arr_next > now ? arr_next : now;
-        // 2. FCFS admission; stop at the first request that cannot enter
-        while (next < n_req && n_active < max_seqs && arr_next <= now && need_next <= free_blk) {
-            free_blk -= need_next;
-            ++next;
-            ++n_active;
-            if (next < n_req) {
-                arr_next = s.arrival[next] / rate;
-                need_next = blocks_of(s.n_in[next] + s.n_out[next]);
-            } else {
-                arr_next = INFINITY;
-            }
-        }
-        // 3. schedule.  Split-fuse: one token per decoder, then prompt chunks in admission order under
-        // the remaining budget.  Prefill-first: while prompts wait, whole prompts only (as many as fit the
-        // budget, the first always) and the decoders pause.
-        const bool decoders_run = !(PREFILL_FIRST && pf_head < next);
-        double T = 0.0, Q = 0.0, K = 0.0, n_lm = 0.0;
-        if (decoders_run) {
-            T = (double)n_dec; Q = (double)s_ctx; K = (double)s_ctx; n_lm = (double)n_dec;
-        }
-        long long budget = (long long)mbt - (long long)n_dec;
-        uint32_t h = pf_head, done = pf_done, chunks = 0;
-        if (PREFILL_FIRST) {
-            long long used = 0;
-            while (h < next && (chunks == 0 || used + (long long)s.n_in[h] <= (long long)mbt)) {
-                const double len = (double)s.n_in[h];
-                used += (long long)s.n_in[h];
-                T += len;
-                Q = fma(len, len, Q);
-                K += len;
-                n_lm += 1.0;
-                ++chunks;
-                ++h;
-            }
-            budget = 0;
-        }
-        while (h < next && budget > 0) {
-            const long long rem = (long long)(s.n_in[h] - done);
-            const long long ch = rem < budget ? rem : budget;
-            budget -= ch;
-            const double C = (double)ch, ctx = (double)(done + (uint32_t)ch);
-            T += C;
-            Q = fma(C, ctx, Q);
-            K += ctx;
-            ++chunks;
-            if (ch == rem) {
-                n_lm += 1.0;
-                ++h;
-                done = 0;
-            } else {
-                done += (uint32_t)ch;
-            }
-        }
-        // 4. one engine step.  A step with decode tokens only repeats the previous step's token count
-        // unless a request joined or left, so the part of the pass that depends on the token count alone
-        // is kept from step to step (same operations, same rounding, as evaluating the whole pass)
-        if (chunks == 0) {
-            if (n_dec != kept_dec) {
-                kept_base = layer_base<ADDITIVE>(tc, T);
-                kept_lm = lm_head<ADDITIVE>(tc, n_lm);
-                kept_dec = n_dec;
-            }
-            now += fma(tc.L, kept_base + attention<ADDITIVE>(tc, T, Q, K), kept_lm);
-        } else {
-            now += pass_time<ADDITIVE>(tc, T, Q, K, n_lm);
-        }
-        ++step;
-        n_rs += (decoders_run ? n_dec : 0u) + chunks;
-        // 5. book-keeping: decoders emitted a token; those at their last one leave
-        if (decoders_run) {
-            ++dstep;
-            s_ctx += n_dec;
-        }
-        while (decoders_run && heap.n > 0 && (uint64_t)(heap.top >> 10) == dstep) {
-            const uint32_t r = (uint32_t)(heap.top & 1023u);
-            heap.pop();
-            const uint32_t r_tok = s.n_in[r] + s.n_out[r];
-            free_blk += blocks_of(r_tok);
-            --n_dec;
-            s_ctx -= (uint64_t)r_tok;
-            ++n_done;
-            fin[r] = now;
-            max_fin = now;
-        }
-        // prompts completed in this step emit their first token
-        for (uint32_t r = pf_head; r < h; ++r) {
-            const uint32_t r_in = s.n_in[r], r_out = s.n_out[r];
-            first[r] = now;
-            if (r_out == 1) {
-                free_blk += blocks_of(r_in + 1);
-                ++n_done;
-                fin[r] = now;
-                max_fin = now;
-            } else {
-                ++n_dec;
-                s_ctx += (uint64_t)r_in + 1;
-                heap.push((KeyT)(((dstep + r_out - 1) << 10) | r));
-            }
-        }
-        pf_head = h;
-        pf_done = done;
-        if (step > step_bound) {   // every step consumes at least one token of some request
+        if (step > step_bound || !moved) {                  // a round always moves something
             status = GUIDE_SIM_INTERNAL;
             break;
         }
     }
 
-    out.tokens_s[c] = status == GUIDE_SIM_OK ? tokens / (max_fin - s.arrival[0] / rate) : 0.0;
+    out.tokens_s[c] = status == GUIDE_SIM_OK ? sums.out / (max_fin - req.arrival[0] / rate) : 0.0;
     out.status[c] = status;
     out.n_steps[c] = step;
     out.n_request_steps[c] = n_rs;
@@ -613,43 +823,40 @@ size_t simulate_workspace_bytes(uint32_t n_cfg, uint32_t n_req) {
 hipError_t launch_simulate(const GridDesc &g, const DevTables *tab, const TraceDev *trace, uint32_t n_req,
                            const uint32_t *cfg_idx, const double *rate, uint32_t n_cfg, bool additive,
                            bool prefill_first, bool closed_runs, const guide_sim_out &out, void *ws_, hipStream_t stream,
-                           double sum_in, double sum_out) {
+                           double sum_in, double sum_out, uint32_t longest) {
     const SimWs ws = sim_ws(ws_, n_cfg, n_req);
-    // Stepped runs: lanes wait for the longest run of their wave before the next general step, so runs are
-    // capped (64 steps measured best among 4..1024 on the 65 536-configuration mix; stopping a run once few
-    // lanes of the wave are still in it measured worse at every setting tried).
-    const uint32_t max_run = 64;
-    // LDS beyond the staged tables holds heap nodes of the block's lanes; 32-bit keys when every finishing step
-    // (at most the trace's generated tokens) fits 22 bits
-    const bool key32 = sum_out < 4194303.0;
+    const TraceSums sums{sum_out, (uint64_t)(sum_in + sum_out), longest};
+    // Lanes in use per wave: 64 once the configurations fill a wave per SIMD, otherwise as few as still give every
+    // SIMD at most one wave.
+    const uint32_t simds = device_cus() * 4;
+    uint32_t lanes = kWave;
+    while (lanes > 1 && (uint64_t)n_cfg <= (uint64_t)(lanes / 2) * simds) lanes /= 2;
+    const uint32_t per_block = kSimBlock / kWave * lanes;
+    // LDS beyond the staged trace holds heap nodes of the block's lanes; 32-bit keys when every finishing step
+    // (at most the trace's generated tokens) fits 22 bits and the trace's tokens fit 30
+    const bool key32 = sum_out < 4194303.0 && sum_in < 1073700000.0;
     const size_t key_bytes = key32 ? sizeof(uint32_t) : sizeof(uint64_t);
     int dev = 0, lds_max = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
     if (e != hipSuccess) return e;
-    const size_t fixed = sizeof(SimLds) + kSimStaticLds;
-    if ((size_t)lds_max < fixed) return hipErrorInvalidValue;
+    const size_t staged = sizeof(RequestsLds), fixed = staged + kSimStaticLds;
+    if ((size_t)lds_max < fixed + kSimBlock * kHeapWidth * key_bytes) return hipErrorInvalidValue;
     size_t heap_bytes = (size_t)lds_max - fixed;
-    const size_t most = (size_t)kSimBlock * n_req * key_bytes;          // no lane needs more than n_req - 1 nodes
+    const size_t most = (size_t)per_block * (n_req + 2 * kHeapWidth) * key_bytes;      // no lane needs more
     heap_bytes = heap_bytes < most ? heap_bytes : most;
-    heap_bytes -= heap_bytes % 16;
+    heap_bytes -= heap_bytes % (kHeapWidth * sizeof(uint64_t));
     const uint32_t heap_slots = (uint32_t)(heap_bytes / key_bytes);
-    const size_t lds_bytes = sizeof(SimLds) + heap_bytes;
-    const dim3 grid((n_cfg + kSimBlock - 1) / kSimBlock), block(kSimBlock);
-    const dim3 ogrid((n_cfg + kBlock - 1) / kBlock), oblock(kBlock);
-    // Stepped runs: configurations run longest first, so that the lanes of a wave end together.  With closed-form
-    // runs every lane does about the same number of rounds (one per event), and the order given mixes lanes with
-    // short and long heaps in a block, which is what the shared LDS wants.
-    const uint32_t ordered = closed_runs ? 0u : 1u;
-    if (ordered) {
-        hipLaunchKernelGGL(sim_order_clear_kernel, dim3(1), dim3(kKeyBins), 0, stream, ws);
-        if (additive)
-            hipLaunchKernelGGL(sim_order_count_kernel<true>, ogrid, oblock, 0, stream, g, tab, n_req, cfg_idx, rate, n_cfg, ws, sum_in, sum_out);
-        else
-            hipLaunchKernelGGL(sim_order_count_kernel<false>, ogrid, oblock, 0, stream, g, tab, n_req, cfg_idx, rate, n_cfg, ws, sum_in, sum_out);
-        hipLaunchKernelGGL(sim_order_scan_kernel, dim3(1), dim3(kKeyBins), 0, stream, ws);
-        hipLaunchKernelGGL(sim_order_scatter_kernel, ogrid, oblock, 0, stream, n_cfg, ws);
-    }
+    const size_t lds_bytes = staged + heap_bytes;
+    const dim3 grid((n_cfg + per_block - 1) / per_block), block(kSimBlock);
+    const dim3 ogrid((n_cfg + kOrderBlock - 1) / kOrderBlock), oblock(kOrderBlock);
+    hipLaunchKernelGGL(sim_order_clear_kernel, dim3(1), dim3(kKeyBins), 0, stream, ws);
+    if (additive)
+        hipLaunchKernelGGL(sim_order_count_kernel<true>, ogrid, oblock, 0, stream, g, tab, n_req, cfg_idx, rate, n_cfg, ws, sum_in, sum_out);
+    else
+        hipLaunchKernelGGL(sim_order_count_kernel<false>, ogrid, oblock, 0, stream, g, tab, n_req, cfg_idx, rate, n_cfg, ws, sum_in, sum_out);
+    hipLaunchKernelGGL(sim_order_scan_kernel, dim3(1), dim3(kKeyBins), 0, stream, ws);
+    hipLaunchKernelGGL(sim_order_scatter_kernel, ogrid, oblock, 0, stream, n_cfg, ws);
     const int variant = (additive ? 8 : 0) | (prefill_first ? 4 : 0) | (closed_runs ? 2 : 0) | (key32 ? 1 : 0);
 #define GUIDE_SIM(A, P, C, K32)                                                                                    \
     case ((A ? 8 : 0) | (P ? 4 : 0) | (C ? 2 : 0) | (K32 ? 1 : 0)): {                                               \
@@ -657,7 +864,7 @@ hipError_t launch_simulate(const GridDesc &g, const DevTables *tab, const TraceD
         e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);    \
         if (e != hipSuccess) return e;                                                                              \
         hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, g, tab, trace, n_req, cfg_idx, rate, n_cfg, out, ws, \
-                           max_run, heap_slots, ordered);                                                           \
+                           sums, lanes, heap_slots);                                                                \
         break;                                                                                                      \
     }
     switch (variant) {
