@@ -28,14 +28,6 @@ struct RowFilter {
     double cap[GUIDE_MAX_CONSTRAINTS];
 };
 
-__device__ inline bool row_passes(const RowFilter &f, uint32_t i) {
-    bool ok = !f.feasible || f.feasible[i] != 0;
-#pragma unroll
-    for (uint32_t c = 0; c < GUIDE_MAX_CONSTRAINTS; ++c)
-        if (c < f.n_con) ok = ok && (f.col[c][i] <= f.cap[c]);
-    return ok;
-}
-
 // All loads of a row are issued unconditionally (index clamped when the row is
 // past the end) and nothing is computed from them here, so that many rows can be
 // in flight while the kernel does other work; row_of() turns the loaded values
@@ -257,111 +249,222 @@ __global__ __launch_bounds__(kMergeThreads) void topk_merge_kernel(Top1Ws w, uin
 
 // ------------------------------------------------------- top-k, with groups
 
-// Workspace layout (u64 units): after_key[G], after_idx[G], part_key[B*G], part_idx[B*G], part_cnt[B*G].
-struct TopkWs {
-    uint64_t *after_key, *after_idx, *part_key, *part_idx, *part_cnt;
+// Workspace of a grouped top-k, three u64 per group and block of kSelBlocks: counts [group][block], keys and rows
+// [group][block][k].
+struct GroupWs {
+    uint64_t *cnt, *key;
+    uint32_t *row;
 };
-TopkWs topk_ws(void *ws, uint32_t G) {
-    TopkWs w;
-    uint64_t *p = (uint64_t *)ws;
-    w.after_key = p; p += GUIDE_MAX_GROUPS;
-    w.after_idx = p; p += GUIDE_MAX_GROUPS;
-    w.part_key = p; p += (size_t)kSelBlocks * G;
-    w.part_idx = p; p += (size_t)kSelBlocks * G;
-    w.part_cnt = p;
+size_t topk_ws_bytes(uint32_t G) { return sizeof(uint64_t) * (2 * GUIDE_MAX_GROUPS + 3 * (size_t)kSelBlocks * G); }
+GroupWs group_ws(void *ws, uint32_t G, uint32_t k, uint32_t n_blocks) {
+    GroupWs w;
+    w.cnt = (uint64_t *)ws;
+    w.key = w.cnt + (size_t)G * n_blocks;
+    w.row = (uint32_t *)(w.key + (size_t)G * n_blocks * k);
     return w;
 }
-size_t topk_ws_bytes(uint32_t G) { return sizeof(uint64_t) * (2 * GUIDE_MAX_GROUPS + 3 * (size_t)kSelBlocks * G); }
+constexpr uint32_t kGroupChunk = 512 * kUnroll;            // rows of a block's batch
+// Blocks of the grouped pass: two per compute unit, fewer when the partials of more would not fit the workspace
+// (8 + 12 k bytes per group and block: 512 blocks up to k = 3, 236 for k = 8).
+uint32_t group_blocks(uint64_t n, uint32_t k) {
+    const uint64_t fit = 3 * sizeof(uint64_t) * kSelBlocks / (8 + 12 * (uint64_t)k), cap = 2 * (uint64_t)device_cus();
+    uint64_t need = (n + kGroupChunk - 1) / kGroupChunk;
+    need = need ? need : 1;
+    need = need < cap ? need : cap;
+    return (uint32_t)(need < fit ? need : fit);
+}
 
-// One round: per block and group, the least (key, row) pair strictly after the
-// group's previous pick; round 0 also counts passing rows.  Candidates of one
-// group meet in per-wave LDS slots (slot_update).
-__global__ __launch_bounds__(kBlock) void topk_round_kernel(const double *__restrict__ obj, RowFilter f,
-                                                            const uint32_t *__restrict__ group, uint32_t G,
-                                                            uint32_t n, uint32_t round, TopkWs w) {
-    __shared__ uint64_t s_key[kWaves][GUIDE_MAX_GROUPS], s_idx[kWaves][GUIDE_MAX_GROUPS];
-    __shared__ uint32_t s_cnt[kWaves][GUIDE_MAX_GROUPS];
-    const int wave = threadIdx.x / kWave;
-    for (uint32_t i = threadIdx.x; i < kWaves * GUIDE_MAX_GROUPS; i += kBlock) {
-        (&s_key[0][0])[i] = kNone;
-        (&s_idx[0][0])[i] = kNone;
-        (&s_cnt[0][0])[i] = 0;
+constexpr uint32_t kGroupThreads = 512, kGroupWaves = kGroupThreads / kWave;
+// One pass over the rows for any number of groups and k.  Every wave keeps a sorted list of k (key, row) pairs per
+// group in LDS, and the block a bound per group with at least k of its rows at or below it, which the first batch
+// starts from the minima of eight parts of it.  Nearly all rows lie above the bound of their group and cost a
+// compare; the others are inserted one after the other, the list's places side by side in lanes 0 .. k - 1.
+// Bound by latency at this size (one batch per block): 1.9 million rows, ten groups, k = 3 and one constraint (40 MB)
+// take 17.3 us + 5.2 us for the merge; k rounds over all rows took 15.7 + 4.1 us a round.  Blocks of 512 threads:
+// 23.0 us with 256 (twice the batches); lists that start from nothing: 35 us (every row is inserted at first).
+constexpr uint32_t kGroupThreads = 512, kGroupWaves = kGroupThreads / kWave;
+// One pass over the rows for any number of groups and k.  Every wave keeps a sorted list of k (key, row) pairs per
+// group in LDS, and the block a bound per group: some wave's k-th key.  Nearly all rows lie above the bound of
+// their group and cost a compare; the others are inserted one after the other, the list's places side by side in
+// lanes 0 .. k - 1.  Bound by the read of the columns and the inserts of the start: 1.9 million rows, ten groups,
+// k = 3 and one constraint (40 MB) take 13 us with the merge's 6; k rounds over all rows with a pass and a merge
+// each took 15.7 + 4.1 us a round.
+template <uint32_t MAXC>
+__global__ __launch_bounds__(kGroupThreads) void topk_group_kernel(const double *__restrict__ obj, RowFilter f,
+                                                            const uint32_t *__restrict__ group, uint32_t G, uint32_t k,
+                                                            uint32_t n, GroupWs w) {
+    extern __shared__ __align__(16) unsigned char s_group[];
+    uint64_t *s_bound = (uint64_t *)s_group;                    // [G]
+    uint64_t *s_part = s_bound + G;                             // [G][8]
+    uint64_t *s_key = s_part + 8 * G;                           // [wave][G][k]
+    uint32_t *s_row = (uint32_t *)(s_key + (size_t)kGroupWaves * G * k);     // the same
+    uint32_t *s_cnt = s_row + (size_t)kGroupWaves * G * k;           // [G]
+    const uint32_t wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, per_wave = G * k;
+    for (uint32_t i = threadIdx.x; i < G * 8; i += kGroupThreads) s_part[i] = kNone;
+    for (uint32_t i = threadIdx.x; i < G; i += kGroupThreads) s_cnt[i] = 0;
+    for (uint32_t i = threadIdx.x; i < kGroupWaves * per_wave; i += kGroupThreads) {
+        s_key[i] = kNone;
+        s_row[i] = ~0u;
     }
     __syncthreads();
-    // every lane of a wave runs the same number of iterations (uniform trip count)
-    const uint32_t stride = gridDim.x * kBlock;
-    const uint32_t iters = (n + stride - 1) / stride;
-    for (uint32_t it = 0; it < iters; ++it) {
-        const uint32_t i = it * stride + blockIdx.x * kBlock + threadIdx.x;
-        bool ok = i < n;
-        double x = 0.0;
-        uint32_t g = 0;
-        if (ok) {
-            x = obj[i];
-            g = group[i];
-            ok = (x == x) && g < G && row_passes(f, i);
+    constexpr uint32_t U = kUnroll;
+    uint64_t *my_key = s_key + wave * per_wave;
+    uint32_t *my_row = s_row + wave * per_wave;
+    ChunkWalk<U * kGroupThreads / kBlock> cw(kGroupChunk, n, gridDim.x);     // batches of kGroupThreads * U rows
+    RawRow<MAXC> raw[U];
+    uint32_t raw_g[U];
+    auto request = [&]() {
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t i = (uint32_t)cw.base + threadIdx.x + u * kGroupThreads;
+            raw[u] = load_raw<false, MAXC>(obj, nullptr, f, i, (uint32_t)cw.end);
+            raw_g[u] = group[i < (uint32_t)cw.end ? i : 0];
         }
-        Pair p = {kNone, kNone};
-        if (ok) {
-            p.key = key_of(x);
-            p.idx = i;
-            if (round == 0) atomicAdd(&s_cnt[wave][g], 1u);
-            if (round > 0) {
-                const Pair after = {w.after_key[g], w.after_idx[g]};
-                ok = less_than(after, p);
+    };
+    bool first = true;
+    if (cw.live()) request();
+    while (cw.live()) {                                         // block-uniform trip count
+        const uint32_t base = (uint32_t)cw.base + threadIdx.x;
+        Row r[U];
+        uint32_t grp[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            r[u] = row_of<false, MAXC>(raw[u], f);
+            grp[u] = raw_g[u];
+        }
+        cw.next();
+        if (cw.live()) request();                               // the next batch is under way while this one is worked on
+        if (first) {
+            // The first batch gives the bounds a start: the least key of each of eight parts of the batch, per group;
+            // the k-th least of them has k rows at or below it.
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u)
+                if (r[u].pass && grp[u] < G)
+                    atomicMin((unsigned long long *)&s_part[grp[u] * 8 + threadIdx.x % 8], (unsigned long long)key_of(r[u].x));
+            __syncthreads();
+            for (uint32_t g = threadIdx.x; g < G; g += kGroupThreads) {
+                uint64_t p[8], bound = kNone;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) p[j] = s_part[g * 8 + j];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    uint32_t rank = 0;
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) rank += (p[q] < p[j] || (p[q] == p[j] && q < j)) ? 1u : 0u;
+                    bound = rank == k - 1 ? p[j] : bound;
+                }
+                s_bound[g] = bound;
+            }
+            __syncthreads();
+            first = false;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const bool ok = r[u].pass && grp[u] < G;
+            const uint32_t g = ok ? grp[u] : 0u;
+            const uint64_t key = ok ? key_of(r[u].x) : kNone;
+            if (ok) atomicAdd(&s_cnt[g], 1u);
+            const uint64_t bound = __hip_atomic_load(&s_bound[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            // (of rows that tie with the bound, those that the wave's own list has no place for are left out here)
+            bool take = ok && key <= bound;
+            if (take) {
+                const uint64_t l_key = my_key[g * k + k - 1];
+                take = key < l_key || (key == l_key && base + u * kGroupThreads < my_row[g * k + k - 1]);
+            }
+            for (uint64_t todo = __ballot(take); todo; todo &= todo - 1) {
+                const int src = __ffsll((long long)todo) - 1;
+                const uint32_t c_g = (uint32_t)__builtin_amdgcn_readlane((int)g, src);
+                const uint64_t c_key = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(key >> 32), src) << 32) |
+                                       (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, src);
+                const uint32_t c_row = (uint32_t)__builtin_amdgcn_readlane((int)(base + u * kGroupThreads), src);
+                const uint32_t at = c_g * k + (lane < k ? lane : 0u);
+                const uint64_t cur = my_key[at];
+                const uint32_t cur_row = my_row[at];
+                const bool before = lane < k && (cur < c_key || (cur == c_key && cur_row < c_row));
+                const uint32_t pos = (uint32_t)__popcll(__ballot(before));      // a sorted list: the entries before come first
+                const uint64_t up = dpp_keep<0x111>(cur);                       // the left neighbour's (k <= 8 lanes of a row)
+                const uint32_t up_row = dpp_u32<0x111>(cur_row, cur_row);
+                if (lane >= pos && lane < k) {
+                    const uint64_t now = lane == pos ? c_key : up;
+                    my_key[at] = now;
+                    my_row[at] = lane == pos ? c_row : up_row;
+                    if (lane == k - 1)
+                        __hip_atomic_fetch_min(&s_bound[c_g], now, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             }
         }
-        slot_update(s_key[wave], s_idx[wave], g, ok, p);
     }
     __syncthreads();
-    for (uint32_t g = threadIdx.x; g < G; g += kBlock) {
-        Pair b = {s_key[0][g], s_idx[0][g]};
-        uint64_t c = s_cnt[0][g];
-        for (int wv = 1; wv < kWaves; ++wv) {
-            const Pair o = {s_key[wv][g], s_idx[wv][g]};
-            b = pair_min(b, o);
-            c += s_cnt[wv][g];
+    // a thread per group merges the waves' lists
+    for (uint32_t g = threadIdx.x; g < G; g += kGroupThreads) {
+        uint32_t head[kGroupWaves];
+#pragma unroll
+        for (int wv = 0; wv < kGroupWaves; ++wv) head[wv] = 0;
+        const size_t to = ((size_t)g * gridDim.x + blockIdx.x) * k;
+        for (uint32_t j = 0; j < k; ++j) {
+            uint64_t best = kNone;
+            uint32_t best_row = ~0u;
+            int from = -1;
+#pragma unroll
+            for (int wv = 0; wv < kGroupWaves; ++wv) {
+                const uint32_t at = wv * per_wave + g * k + head[wv];   // (no list gives more than j < k entries)
+                const uint64_t c = s_key[at];
+                const uint32_t c_row = s_row[at];
+                if (c < best || (c == best && c_row < best_row)) {
+                    best = c;
+                    best_row = c_row;
+                    from = wv;
+                }
+            }
+#pragma unroll
+            for (int wv = 0; wv < kGroupWaves; ++wv) head[wv] += from == wv ? 1u : 0u;
+            w.key[to + j] = best;
+            w.row[to + j] = best_row;
         }
-        w.part_key[(size_t)blockIdx.x * G + g] = b.key;
-        w.part_idx[(size_t)blockIdx.x * G + g] = b.idx;
-        if (round == 0) w.part_cnt[(size_t)blockIdx.x * G + g] = c;
+        w.cnt[(size_t)g * gridDim.x + blockIdx.x] = s_cnt[g];
     }
 }
 
-// One block per group: reduce the block partials, emit pick `round`, remember it.
-__global__ __launch_bounds__(kBlock) void topk_final_kernel(TopkWs w, uint32_t G, uint32_t n_blocks, uint32_t round,
-                                                            uint32_t k, uint64_t *out_idx, double *out_val,
-                                                            uint64_t *out_cnt) {
-    __shared__ uint64_t s_key[kWaves], s_idx[kWaves], s_cnt[kWaves];
+// One block per group: the k least of the block partials, and the count.  K >= k: places of the threads' lists.
+template <int K>
+__global__ __launch_bounds__(kBlock) void topk_group_merge_kernel(GroupWs w, uint32_t n_blocks, uint32_t k, uint64_t *out_idx,
+                                                                  double *out_val, uint64_t *out_cnt) {
+    __shared__ Pair s_pairs[kWaves][K];
+    __shared__ uint64_t s_cnt[kWaves];
     const uint32_t g = blockIdx.x;
-    Pair best = {kNone, kNone};
+    const uint64_t *key = w.key + (size_t)g * n_blocks * k;
+    const uint32_t *row = w.row + (size_t)g * n_blocks * k;
+    TopList<K> l;
+    l.init();
     uint64_t cnt = 0;
-    for (uint32_t b = threadIdx.x; b < n_blocks; b += kBlock) {
-        const Pair o = {w.part_key[(size_t)b * G + g], w.part_idx[(size_t)b * G + g]};
-        best = pair_min(best, o);
-        if (round == 0) cnt += w.part_cnt[(size_t)b * G + g];
-    }
-    best = wave_min(best);
-    for (int off = kWave / 2; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off, kWave);
-    if (threadIdx.x % kWave == 0) {
-        s_key[threadIdx.x / kWave] = best.key;
-        s_idx[threadIdx.x / kWave] = best.idx;
-        s_cnt[threadIdx.x / kWave] = cnt;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int wv = 1; wv < kWaves; ++wv) {
-            const Pair o = {s_key[wv], s_idx[wv]};
-            best = pair_min(best, o);
-            cnt += s_cnt[wv];
+    const uint32_t total = n_blocks * k;
+    for (uint32_t i0 = threadIdx.x; i0 < total; i0 += 4 * kBlock) {             // four loads in flight
+        uint64_t c[4];
+        uint32_t c_row[4];
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u) {
+            const uint32_t i = i0 + u * kBlock;
+            c[u] = i < total ? key[i] : kNone;
+            c_row[u] = i < total ? row[i] : ~0u;
         }
-        const bool none = best.idx == kNone;
-        out_idx[(size_t)g * k + round] = best.idx;
-        out_val[(size_t)g * k + round] = none ? INFINITY : value_of(best.key);
-        if (round == 0) out_cnt[g] = cnt;
-        // nothing is strictly after (max key, max row): later rounds stay empty
-        w.after_key[g] = best.key;
-        w.after_idx[g] = best.idx;
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u)
+            if (c_row[u] != ~0u) l.insert(Pair{c[u], (uint64_t)c_row[u]});
+    }
+    for (uint32_t i = threadIdx.x; i < n_blocks; i += kBlock) cnt += w.cnt[(size_t)g * n_blocks + i];
+    for (int off = kWave / 2; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off, kWave);
+    if (threadIdx.x % kWave == 0) s_cnt[threadIdx.x / kWave] = cnt;
+    block_topk<K, kWaves>(l, s_pairs, [&](int r, const Pair &p) {
+        if ((uint32_t)r < k) {
+            out_idx[(size_t)g * k + r] = p.idx;
+            out_val[(size_t)g * k + r] = p.idx == kNone ? INFINITY : value_of(p.key);
+        }
+    });
+    if (threadIdx.x == 0) {
+        uint64_t t = 0;
+        for (int wv = 0; wv < kWaves; ++wv) t += s_cnt[wv];
+        out_cnt[g] = t;
     }
 }
 
@@ -1277,15 +1380,24 @@ hipError_t launch_select_topk(const guide_select_spec &spec, uint64_t n, const g
         launch_top1_merge(partial_width(spec.k), ws, blocks_for(n), spec.k, out, stream);
         return hipGetLastError();
     }
-    const uint32_t G = spec.n_groups;
-    const TopkWs w = topk_ws(ws, G);
-    const RowFilter f = make_filter(spec);
-    const uint32_t nb = blocks_for(n);
-    for (uint32_t round = 0; round < spec.k; ++round) {
-        hipLaunchKernelGGL(topk_round_kernel, dim3(nb), dim3(kBlock), 0, stream, spec.objective, f, spec.group, G,
-                           (uint32_t)n, round, w);
-        hipLaunchKernelGGL(topk_final_kernel, dim3(G), dim3(kBlock), 0, stream, w, G, nb, round, spec.k, out.idx, out.val,
-                           out.count);
+    const uint32_t G = spec.n_groups, k = spec.k, nb = group_blocks(n, k);
+    const GroupWs w = group_ws(ws, G, k, nb);
+    const size_t per_group = (size_t)kGroupWaves * k;
+    const size_t lds = (sizeof(uint64_t) * (1 + per_group) + sizeof(uint32_t) * (1 + per_group)) * G + sizeof(uint64_t) * 8 * G;
+    static_assert((sizeof(uint64_t) + sizeof(uint32_t)) * GUIDE_MAX_GROUPS * (1 + kGroupWaves * GUIDE_MAX_TOPK) +
+                          sizeof(uint64_t) * 8 * GUIDE_MAX_GROUPS <= 65536,
+                  "the lists of a block fit the default LDS limit");
+    with_max_constraints(spec.n_constraints, [&](auto maxc) {
+        hipLaunchKernelGGL((topk_group_kernel<decltype(maxc)::value>), dim3(nb), dim3(kGroupThreads), lds, stream, spec.objective,
+                           make_filter(spec), spec.group, G, k, (uint32_t)n, w);
+    });
+    const dim3 groups(G), block(kBlock);
+    switch (partial_width(k)) {
+        case 1: hipLaunchKernelGGL(topk_group_merge_kernel<1>, groups, block, 0, stream, w, nb, k, out.idx, out.val, out.count); break;
+        case 2: hipLaunchKernelGGL(topk_group_merge_kernel<2>, groups, block, 0, stream, w, nb, k, out.idx, out.val, out.count); break;
+        case 3: hipLaunchKernelGGL(topk_group_merge_kernel<3>, groups, block, 0, stream, w, nb, k, out.idx, out.val, out.count); break;
+        case 4: hipLaunchKernelGGL(topk_group_merge_kernel<4>, groups, block, 0, stream, w, nb, k, out.idx, out.val, out.count); break;
+        default: hipLaunchKernelGGL(topk_group_merge_kernel<8>, groups, block, 0, stream, w, nb, k, out.idx, out.val, out.count); break;
     }
     return hipGetLastError();
 }
