@@ -65,34 +65,6 @@ __device__ inline double cost_of(const Knobs &kn, double t_batch) {
     return (double)kn.p * t_batch / 3600.0 * 1.0e6 / ((double)kn.b * (double)kn.s_out);
 }
 
-template <bool ADDITIVE>
-__global__ __launch_bounds__(kBlock) void eval_grid_kernel(GridDesc g, const DevTables *__restrict__ tab,
-                                                           uint32_t first, uint32_t count, double re_c, double re_b,
-                                                           guide_metrics out) {
-    __shared__ GridLds s;
-    stage_grid_tables(s, g, tab);
-    __syncthreads();
-    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < count; i += gridDim.x * kBlock) {
-        const Candidate c = decode_index(s, g, first + i);
-        const Coef cf = make_coef(s.models[c.model], c.kn.p, c.kn.wbits);
-        const HwRecip hw = s.hw[c.hw];
-        const TimeCoef tc = make_time_coef(cf, hw.r_peak * re_c, hw.r_bw * re_b, hw.r_link, hw.lat);
-        const EvalResult r = evaluate_times<ADDITIVE>(tc, c.kn);
-        const MemResult m = memory_check(cf, hw.cap, c.kn.b, c.kn.s_in, c.kn.s_out, c.kn.blk);
-        const double t_batch = r.t_prefill + r.t_decode;
-        if (out.t_prefill) out.t_prefill[i] = r.t_prefill;
-        if (out.t_decode) out.t_decode[i] = r.t_decode;
-        if (out.t_batch) out.t_batch[i] = t_batch;
-        if (out.decode_tok_s) {
-            const double n = (double)(c.kn.s_out - 1);
-            out.decode_tok_s[i] = c.kn.s_out > 1 ? (double)c.kn.b * n / r.t_decode : 0.0;
-        }
-        if (out.cost) out.cost[i] = cost_of(c.kn, t_batch);
-        if (out.b_max) out.b_max[i] = m.b_max;
-        if (out.feasible) out.feasible[i] = m.feasible ? 1 : 0;
-    }
-}
-
 // ---------------------------------------------------------------- tiled variant
 //
 // The two fastest axes (KV block, max batched tokens) change only part of the
@@ -622,66 +594,259 @@ __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const
     }
 }
 
-// Cluster-level columns under a GPU budget (one index per lane; not on the timed path).
-template <bool ADDITIVE>
-__global__ __launch_bounds__(kBlock) void eval_extras_kernel(GridDesc g, const DevTables *__restrict__ tab,
-                                                             uint32_t first, uint32_t count, uint32_t n_gpus,
-                                                             guide_extras out) {
-    __shared__ GridLds s;
-    stage_grid_tables(s, g, tab);
+// ---------------------------------------------------------------- expanded variants
+//
+// Where a lane cannot own a whole tile (more than four values on one of the two fastest axes) or hardly any column varies
+// inside one (the cluster-level columns), a block takes a run of tiles, works out into LDS what depends on the tile,
+// on (tile, token budget) and on (tile, block size), and then writes the rows from there, each wave 64 consecutive
+// rows of every column.
+
+constexpr uint32_t kExpandTiles = 256;          // most tiles of a run
+constexpr uint32_t kExpandParts = 1024;         // most (tile, block size) and (tile, token budget) pairs of a run
+struct ExpandTile {
+    uint32_t row;                               // (model, tp, precision) row of coefficients
+    uint32_t model, hw, b, d_sin, s_in, s_out, d_tp, p, wbits;
+};
+__device__ inline ExpandTile expand_tile(const GridLds &s, const GridDesc &g, uint32_t tile) {
+    uint32_t dg[AX_BLK], rem = tile;
+#pragma unroll
+    for (int a = AX_BLK - 1; a > 0; --a) {
+        const uint32_t q = div32(rem, g.div[a]);
+        dg[a] = rem - q * g.div[a].d;
+        rem = q;
+    }
+    dg[0] = rem;
+    ExpandTile t;
+    t.row = (dg[AX_MODEL] * g.div[AX_TP].d + dg[AX_TP]) * g.div[AX_WBITS].d + dg[AX_WBITS];
+    t.model = s.axis[AX_MODEL][dg[AX_MODEL]];
+    t.hw = s.axis[AX_HW][dg[AX_HW]];
+    t.b = s.axis[AX_BATCH][dg[AX_BATCH]];
+    t.d_sin = dg[AX_SIN];
+    t.s_in = s.axis[AX_SIN][dg[AX_SIN]];
+    t.s_out = s.axis[AX_SOUT][dg[AX_SOUT]];
+    t.d_tp = dg[AX_TP];
+    t.p = s.axis[AX_TP][dg[AX_TP]];
+    t.wbits = s.axis[AX_WBITS][dg[AX_WBITS]];
+    return t;
+}
+template <bool STREAM, typename T>
+__device__ inline void put(T *col, uint32_t i, T v) {
+    if (STREAM) __builtin_nontemporal_store(v, &col[i]);
+    else col[i] = v;
+}
+
+// Evaluation of grids with more than four values on one of the two fastest axes.  per_run: tiles of a run.
+// Bound by arithmetic and launch at ordinary sizes: 443 211 rows of a grid with five block sizes and six token
+// budgets (20 MB), additive times: 7.5 us; one index per lane, which repeats the decode series and the prefill for
+// every row: 20.1 us.
+template <bool ADDITIVE, bool STREAM>
+__global__ __launch_bounds__(kBlock) void eval_wide_kernel(GridDesc g, uint32_t first, uint32_t count, double re_c,
+                                                           double re_b, guide_metrics out,
+                                                           const TileLds *__restrict__ derived, uint32_t per_run) {
+    __shared__ TileLds s;
+    __shared__ ExpandTile s_tile[kExpandTiles];
+    __shared__ double s_dec[kExpandTiles], s_tok[kExpandTiles], s_cost[kExpandTiles], s_pre[kExpandParts];
+    __shared__ uint32_t s_bmax[kExpandParts];
+    __shared__ uint8_t s_feas[kExpandParts];
+    const uint32_t n_rows = g.div[AX_MODEL].d * g.div[AX_TP].d * g.div[AX_WBITS].d;
+    const bool coef_in_lds = n_rows <= kCoefRows;
+    {
+        const uint32_t vecs = (uint32_t)(offsetof(TileLds, coef) + (coef_in_lds ? n_rows : 0u) * sizeof(Coef) + 15) / 16;
+        for (uint32_t i = threadIdx.x; i < vecs; i += kBlock) ((uint4 *)&s)[i] = ((const uint4 *)derived)[i];
+    }
     __syncthreads();
-    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < count; i += gridDim.x * kBlock) {
-        const Candidate c = decode_index(s, g, first + i);
-        const HwRecip hw = s.hw[c.hw];
-        const Coef cf = make_coef(s.models[c.model], c.kn.p, c.kn.wbits);
-        const uint32_t dp = n_gpus / c.kn.p;
-        const double n = (double)(c.kn.s_out - 1);
-        double tok_s = 0.0, tok_s1 = 0.0;
-        if (c.kn.s_out > 1 && (out.cluster_tok_s || out.paper_tok_s)) {
-            const TimeCoef tc = make_time_coef(cf, hw.r_peak, hw.r_bw, hw.r_link, hw.lat);
-            tok_s = (double)c.kn.b * n / decode_time<ADDITIVE>(tc, c.kn.b, c.kn.s_in, c.kn.s_out - 1);
-            if (out.paper_tok_s) {
-                const Coef c1 = make_coef(s.models[c.model], 1u, c.kn.wbits);      // the same candidate on one GPU
-                const TimeCoef t1 = make_time_coef(c1, hw.r_peak, hw.r_bw, hw.r_link, hw.lat);
-                tok_s1 = (double)c.kn.b * n / decode_time<ADDITIVE>(t1, c.kn.b, c.kn.s_in, c.kn.s_out - 1);
+    const uint32_t NB = g.div[AX_BLK].d, NM = g.div[AX_MBT].d, TS = NB * NM;
+    const uint32_t t_first = first / TS, last = first + count, n_tiles = (last - 1) / TS - t_first + 1;
+    for (uint64_t run64 = (uint64_t)blockIdx.x * per_run; run64 < n_tiles; run64 += (uint64_t)gridDim.x * per_run) {
+        const uint32_t run = (uint32_t)run64, tiles = n_tiles - run < per_run ? n_tiles - run : per_run;
+        for (uint32_t t = threadIdx.x; t < tiles; t += kBlock) s_tile[t] = expand_tile(s.g, g, t_first + run + t);
+        __syncthreads();
+        // items: a decode series per tile, a prefill per (tile, token budget), a memory check per (tile, block size)
+        const uint32_t n_pre = tiles * NM, n_mem = tiles * NB, n_items = tiles + n_pre + n_mem;
+        for (uint32_t i = threadIdx.x; i < n_items; i += kBlock) {
+            uint32_t t, part = 0;
+            if (i < n_pre) {
+                t = div32(i, g.div[AX_MBT]);
+                part = i - t * NM;
+            } else if (i < n_pre + tiles) {
+                t = i - n_pre;
+            } else {
+                t = div32(i - n_pre - tiles, g.div[AX_BLK]);
+                part = i - n_pre - tiles - t * NB;
+            }
+            const ExpandTile tl = s_tile[t];
+            const Coef cf = coef_in_lds ? s.coef[tl.row] : make_coef(s.g.models[tl.model], tl.p, tl.wbits, s.r_tp[tl.d_tp]);
+            const HwRecip hw = s.g.hw[tl.hw];
+            if (i < n_pre + tiles) {
+                const TimeCoef tc = make_time_coef(cf, hw.r_peak * re_c, hw.r_bw * re_b, hw.r_link, hw.lat);
+                if (i < n_pre) {
+                    s_pre[i] = prefill_time_fast<ADDITIVE>(tc, tl.b, tl.s_in, s.g.axis[AX_MBT][part], s.r_sin[tl.d_sin],
+                                                           s.r_mbt[part]);
+                } else {
+                    const double t_dec = decode_time_fast<ADDITIVE>(tc, tl.b, tl.s_in, tl.s_out - 1);
+                    s_dec[t] = t_dec;
+                    s_tok[t] = tl.s_out > 1 ? (double)tl.b * (double)(tl.s_out - 1) * fast_recip(t_dec) : 0.0;
+                    s_cost[t] = (double)tl.p * (1.0e6 / 3600.0) * fast_recip((double)tl.b * (double)tl.s_out);
+                }
+            } else {
+                const double c_avail = hw.cap - cf.w_gpu;
+                const uint32_t blk = s.g.axis[AX_BLK][part];
+                const uint32_t tok_req = floor_div(tl.s_in + tl.s_out + blk - 1, s.r_blk[part]) * blk;
+                const double kv_req = (double)tok_req * cf.kv_tok;
+                const double q = floor(c_avail / kv_req);
+                const bool room = c_avail > 0.0;
+                s_bmax[t * NB + part] = !room ? 0u : (q >= 4294967295.0 ? 4294967295u : (uint32_t)q);
+                s_feas[t * NB + part] = room && (double)tl.b * kv_req <= c_avail ? 1 : 0;
             }
         }
-        const double c_avail = hw.cap - cf.w_gpu;
-        const double q = floor(c_avail / ((double)c.kn.b * cf.kv_tok));
-        const uint32_t s_max = !(c_avail > 0.0) ? 0u : (q >= 4294967295.0 ? 4294967295u : (uint32_t)q);
-        if (out.s_max) out.s_max[i] = s_max;
-        if (out.dp_max) out.dp_max[i] = dp;
-        const MemResult m = memory_check(cf, hw.cap, c.kn.b, c.kn.s_in, c.kn.s_out, c.kn.blk);
-        if (out.max_parallelism) out.max_parallelism[i] = (uint64_t)dp * (uint64_t)m.b_max;
-        if (out.b_adj) out.b_adj[i] = c.kn.b < m.b_max ? c.kn.b : m.b_max;
-        const bool long_prompt = c.kn.s_in > c.kn.mbt;
-        if (out.n_sub_batches) {
-            uint32_t split = c.kn.mbt / c.kn.s_in;                    // prompts per pass (0 for a long prompt)
-            split = split < c.kn.b ? split : c.kn.b;
-            out.n_sub_batches[i] = long_prompt ? c.kn.b : (c.kn.b + split - 1) / split;
+        __syncthreads();
+        const uint32_t row0 = (t_first + run) * TS;             // grid index of the run's first row
+        const uint32_t lo = row0 > first ? row0 : first;
+        const uint32_t skip = lo - row0, in_run = tiles * TS - skip, n = last - lo < in_run ? last - lo : in_run;
+        for (uint32_t j = threadIdx.x; j < n; j += kBlock) {
+            const uint32_t rel = skip + j, tk = div32(rel, g.div[AX_MBT]), m = rel - tk * NM, t = div32(tk, g.div[AX_BLK]);
+            const uint32_t i = lo - first + j;
+            const double t_pre = s_pre[t * NM + m], t_dec = s_dec[t], t_batch = t_pre + t_dec;
+            if (out.t_prefill) put<STREAM>(out.t_prefill, i, t_pre);
+            if (out.t_decode) put<STREAM>(out.t_decode, i, t_dec);
+            if (out.t_batch) put<STREAM>(out.t_batch, i, t_batch);
+            if (out.decode_tok_s) put<STREAM>(out.decode_tok_s, i, s_tok[t]);
+            if (out.cost) put<STREAM>(out.cost, i, t_batch * s_cost[t]);
+            if (out.b_max) out.b_max[i] = s_bmax[tk];
+            if (out.feasible) out.feasible[i] = s_feas[tk];
         }
-        if (out.n_segments) out.n_segments[i] = long_prompt ? (c.kn.s_in - 1) / c.kn.mbt + 1 : 1u;
-        if (out.s_adj) {
-            const uint32_t len = c.kn.s_in + c.kn.s_out;              // both below 2^31
-            out.s_adj[i] = len < s_max ? len : s_max;
-        }
-        if (out.b_max_kept || out.feasible_kept || out.s_max_kept) {
-            // a KV-cache reduction that keeps the fraction kv_keep of every request's entries
-            const double keep = out.kv_keep == 0.0 ? 1.0 : out.kv_keep;
-            const uint32_t len = c.kn.s_in + c.kn.s_out;
-            const uint64_t kept = (uint64_t)ceil(keep * (double)len);
-            const uint64_t tok_req = (kept + c.kn.blk - 1) / c.kn.blk * c.kn.blk;
-            const double kv_req = (double)tok_req * cf.kv_tok;
-            const bool room = c_avail > 0.0;
-            const double qb = floor(c_avail / kv_req), qs = floor(q / keep);
-            if (out.b_max_kept) out.b_max_kept[i] = !room ? 0u : (qb >= 4294967295.0 ? 4294967295u : (uint32_t)qb);
-            if (out.feasible_kept) out.feasible_kept[i] = (room && (double)c.kn.b * kv_req <= c_avail) ? 1 : 0;
-            if (out.s_max_kept) out.s_max_kept[i] = !room ? 0u : (qs >= 4294967295.0 ? 4294967295u : (uint32_t)qs);
-        }
-        if (out.cluster_tok_s) out.cluster_tok_s[i] = (double)dp * tok_s;
-        if (out.paper_tok_s)
-            out.paper_tok_s[i] = ((double)dp * (double)c.kn.p) * tok_s1 / (1.0 + log2((double)c.kn.p));
+        __syncthreads();                                        // the run's values have been read
     }
+}
+
+// Cluster-level columns under a GPU budget: every one depends on the tile, on (tile, block size) or on (tile, token
+// budget) alone, so the rows are copies.  Bound by the stores: the full grid's twelve columns (57 bytes a row, 108 MB)
+// take 25 us; one index per lane with everything worked out per row (571 instructions) took 44 us.
+template <bool ADDITIVE, bool STREAM>
+__global__ __launch_bounds__(kBlock) void eval_extras_kernel(GridDesc g, const DevTables *__restrict__ tab,
+                                                             uint32_t first, uint32_t count, uint32_t n_gpus,
+                                                             guide_extras out, uint32_t per_run) {
+    __shared__ GridLds s;
+    __shared__ ExpandTile s_tile[kExpandTiles];
+    __shared__ double s_avail[kExpandTiles], s_kv[kExpandTiles], s_cluster[kExpandTiles], s_paper[kExpandTiles];
+    __shared__ uint32_t s_smax[kExpandTiles], s_dp[kExpandTiles], s_sadj[kExpandTiles], s_skept[kExpandTiles];
+    __shared__ uint64_t s_par[kExpandParts];
+    __shared__ uint32_t s_badj[kExpandParts], s_bkept[kExpandParts], s_sub[kExpandParts], s_seg[kExpandParts];
+    __shared__ uint8_t s_fkept[kExpandParts];
+    stage_grid_tables(s, g, tab);
+    __syncthreads();
+    const uint32_t NB = g.div[AX_BLK].d, NM = g.div[AX_MBT].d, TS = NB * NM;
+    const uint32_t t_first = first / TS, last = first + count, n_tiles = (last - 1) / TS - t_first + 1;
+    const double keep = out.kv_keep == 0.0 ? 1.0 : out.kv_keep;
+    const bool any_tok = out.cluster_tok_s || out.paper_tok_s, any_kept = out.b_max_kept || out.feasible_kept;
+    for (uint64_t run64 = (uint64_t)blockIdx.x * per_run; run64 < n_tiles; run64 += (uint64_t)gridDim.x * per_run) {
+        const uint32_t run = (uint32_t)run64, tiles = n_tiles - run < per_run ? n_tiles - run : per_run;
+        for (uint32_t t = threadIdx.x; t < tiles; t += kBlock) {
+            const ExpandTile tl = expand_tile(s, g, t_first + run + t);
+            const HwRecip hw = s.hw[tl.hw];
+            const Coef cf = make_coef(s.models[tl.model], tl.p, tl.wbits);
+            const uint32_t dp = n_gpus / tl.p;
+            double tok_s = 0.0, tok_s1 = 0.0;
+            if (tl.s_out > 1 && any_tok) {
+                const double n = (double)tl.b * (double)(tl.s_out - 1);
+                const TimeCoef tc = make_time_coef(cf, hw.r_peak, hw.r_bw, hw.r_link, hw.lat);
+                tok_s = n / decode_time<ADDITIVE>(tc, tl.b, tl.s_in, tl.s_out - 1);
+                if (out.paper_tok_s) {
+                    const Coef c1 = make_coef(s.models[tl.model], 1u, tl.wbits);   // the same candidate on one GPU
+                    const TimeCoef t1 = make_time_coef(c1, hw.r_peak, hw.r_bw, hw.r_link, hw.lat);
+                    tok_s1 = n / decode_time<ADDITIVE>(t1, tl.b, tl.s_in, tl.s_out - 1);
+                }
+            }
+            const double c_avail = hw.cap - cf.w_gpu;
+            const bool room = c_avail > 0.0;
+            const double q = floor(c_avail / ((double)tl.b * cf.kv_tok)), qs = floor(q / keep);
+            const uint32_t s_max = !room ? 0u : (q >= 4294967295.0 ? 4294967295u : (uint32_t)q);
+            const uint32_t len = tl.s_in + tl.s_out;                    // both below 2^31
+            s_tile[t] = tl;
+            s_avail[t] = c_avail;
+            s_kv[t] = cf.kv_tok;
+            s_cluster[t] = (double)dp * tok_s;
+            s_paper[t] = ((double)dp * (double)tl.p) * tok_s1 / (1.0 + log2((double)tl.p));
+            s_smax[t] = s_max;
+            s_dp[t] = dp;
+            s_sadj[t] = len < s_max ? len : s_max;
+            s_skept[t] = !room ? 0u : (qs >= 4294967295.0 ? 4294967295u : (uint32_t)qs);
+        }
+        __syncthreads();
+        const uint32_t n_mem = tiles * NB, n_pre = tiles * NM;
+        for (uint32_t i = threadIdx.x; i < n_mem + n_pre; i += kBlock) {
+            if (i < n_mem) {
+                const uint32_t t = div32(i, g.div[AX_BLK]), blk = s.axis[AX_BLK][i - t * NB];
+                const ExpandTile tl = s_tile[t];
+                const double c_avail = s_avail[t];
+                const bool room = c_avail > 0.0;
+                const uint32_t len = tl.s_in + tl.s_out;
+                const uint32_t tok_req = (len + blk - 1) / blk * blk;
+                const double qb = floor(c_avail / ((double)tok_req * s_kv[t]));
+                const uint32_t b_max = !room ? 0u : (qb >= 4294967295.0 ? 4294967295u : (uint32_t)qb);
+                s_par[i] = (uint64_t)s_dp[t] * (uint64_t)b_max;
+                s_badj[i] = tl.b < b_max ? tl.b : b_max;
+                if (any_kept) {
+                    // a KV-cache reduction that keeps the fraction kv_keep of every request's entries
+                    const uint64_t kept = (uint64_t)ceil(keep * (double)len);
+                    const double kv_req = (double)((kept + blk - 1) / blk * blk) * s_kv[t];
+                    const double qk = floor(c_avail / kv_req);
+                    s_bkept[i] = !room ? 0u : (qk >= 4294967295.0 ? 4294967295u : (uint32_t)qk);
+                    s_fkept[i] = (room && (double)tl.b * kv_req <= c_avail) ? 1 : 0;
+                }
+            } else {
+                const uint32_t j = i - n_mem, t = div32(j, g.div[AX_MBT]), mbt = s.axis[AX_MBT][j - t * NM];
+                const uint32_t b = s_tile[t].b, s_in = s_tile[t].s_in;
+                const bool long_prompt = s_in > mbt;
+                uint32_t split = mbt / s_in;                            // prompts per pass (0 for a long prompt)
+                split = split < b ? split : b;
+                s_sub[j] = long_prompt ? b : (b + split - 1) / split;
+                s_seg[j] = long_prompt ? (s_in - 1) / mbt + 1 : 1u;
+            }
+        }
+        __syncthreads();
+        const uint32_t row0 = (t_first + run) * TS;
+        const uint32_t lo = row0 > first ? row0 : first;
+        const uint32_t skip = lo - row0, in_run = tiles * TS - skip, n = last - lo < in_run ? last - lo : in_run;
+        for (uint32_t j = threadIdx.x; j < n; j += kBlock) {
+            const uint32_t rel = skip + j, tk = div32(rel, g.div[AX_MBT]), m = rel - tk * NM, t = div32(tk, g.div[AX_BLK]);
+            const uint32_t i = lo - first + j, tm = t * NM + m;
+            if (out.s_max) put<STREAM>(out.s_max, i, s_smax[t]);
+            if (out.dp_max) put<STREAM>(out.dp_max, i, s_dp[t]);
+            if (out.max_parallelism) put<STREAM>(out.max_parallelism, i, s_par[tk]);
+            if (out.cluster_tok_s) put<STREAM>(out.cluster_tok_s, i, s_cluster[t]);
+            if (out.paper_tok_s) put<STREAM>(out.paper_tok_s, i, s_paper[t]);
+            if (out.b_adj) put<STREAM>(out.b_adj, i, s_badj[tk]);
+            if (out.n_sub_batches) put<STREAM>(out.n_sub_batches, i, s_sub[tm]);
+            if (out.n_segments) put<STREAM>(out.n_segments, i, s_seg[tm]);
+            if (out.s_adj) put<STREAM>(out.s_adj, i, s_sadj[t]);
+            if (out.b_max_kept) put<STREAM>(out.b_max_kept, i, s_bkept[tk]);
+            if (out.s_max_kept) put<STREAM>(out.s_max_kept, i, s_skept[t]);
+            if (out.feasible_kept) out.feasible_kept[i] = s_fkept[tk];
+        }
+        __syncthreads();                                        // the run's values have been read
+    }
+}
+
+// Tiles of a run and blocks of the launch.  Two blocks per compute unit (what the LDS of both kernels allows at 160 KB;
+// three with half the runs' length: 27 against 25 us for the full grid's twelve columns), every block the same number
+// of full runs, and runs of whole multiples of 64 tiles when they are that long: their rows then start on line
+// boundaries of every column (2.9 TB/s when two blocks share the lines at their ends, 4.3 TB/s like this).
+struct ExpandPlan {
+    uint32_t per_run, blocks;
+};
+static ExpandPlan expand_plan(const GridDesc &g, uint32_t first, uint32_t count) {
+    const uint32_t nb = g.div[AX_BLK].d, nm = g.div[AX_MBT].d, ts = nb * nm, widest = nb > nm ? nb : nm;
+    const uint32_t n_tiles = (first + count - 1) / ts - first / ts + 1, most = device_cus() * 2;
+    const uint32_t cap = kExpandParts / widest < kExpandTiles ? kExpandParts / widest : kExpandTiles;
+    const uint32_t per_block = (uint32_t)(((uint64_t)n_tiles + most - 1) / most), rounds = (per_block + cap - 1) / cap;
+    uint32_t per_run = (per_block + rounds - 1) / rounds;
+    if (per_run >= 64) {
+        const uint32_t up = (per_run + 63) / 64 * 64;
+        per_run = up <= cap ? up : per_run / 64 * 64;
+    }
+    const uint32_t runs = (uint32_t)(((uint64_t)n_tiles + per_run - 1) / per_run);
+    return ExpandPlan{per_run, runs < most ? runs : most};
 }
 
 static uint32_t blocks_for(uint32_t count) {
@@ -707,6 +872,11 @@ constexpr uint64_t kStreamBytes = 64ull << 20;      // twice the 8 x 4 MB of L2:
 constexpr uint32_t kRiderBlocks = kSampleRows / kBlock;     // sample blocks appended to a plain evaluation
 static_assert(kRiderBlocks == kSampleBlocks, "the scratch holds one sample front per sample block");
 
+static uint32_t n_f64_columns(const guide_metrics &out) {
+    return (out.t_prefill ? 1u : 0u) + (out.t_decode ? 1u : 0u) + (out.t_batch ? 1u : 0u) + (out.decode_tok_s ? 1u : 0u) +
+           (out.cost ? 1u : 0u);
+}
+
 template <bool ADDITIVE, int NB, int NM>
 static void launch_tile(const GridDesc &g, const DevTables *tab, const void *tile_tables, uint32_t first,
                         uint32_t count, double re_c, double re_b, const guide_metrics &out, const FusedSelect *fs,
@@ -721,9 +891,7 @@ static void launch_tile(const GridDesc &g, const DevTables *tab, const void *til
     // launch more room (20M rows: 163 - 166 us against 178 - 179 us; 1.9M rows inside an evaluate-and-select step:
     // 17.4 against 17.8 us, the filter pass after it 13.4 against 13.1 us; smaller outputs stay cached for their readers).
     // (a kernel of its own: a run-time choice between the two kinds of store compiles to the plain one)
-    const uint32_t n_f64 = (out.t_prefill ? 1u : 0u) + (out.t_decode ? 1u : 0u) + (out.t_batch ? 1u : 0u) +
-                           (out.decode_tok_s ? 1u : 0u) + (out.cost ? 1u : 0u);
-    const bool stream_stores = (uint64_t)count * 8 * n_f64 >= kStreamBytes;
+    const bool stream_stores = (uint64_t)count * 8 * n_f64_columns(out) >= kStreamBytes;
     auto launch = [&](auto kernel) {
         // with timing events the launch goes through the extended call, which attaches them to the dispatch
         if (tm.start)
@@ -737,8 +905,8 @@ static void launch_tile(const GridDesc &g, const DevTables *tab, const void *til
     else launch(eval_tile_kernel<ADDITIVE, NB, NM, false, false>);
 }
 
-// Tile shapes with a compiled kernel (up to four values on each of the two fastest axes); other grids take the
-// one-index-per-lane kernel.
+// Tile shapes with a compiled kernel (up to four values on each of the two fastest axes); other grids take
+// eval_wide_kernel.
 #define GUIDE_TILE_SHAPES(X)                                                                     \
     X(2, 3) X(1, 1) X(1, 2) X(1, 3) X(1, 4) X(2, 1) X(2, 2) X(2, 4) X(3, 1) X(3, 2) X(3, 3) X(3, 4) \
     X(4, 1) X(4, 2) X(4, 3) X(4, 4)
@@ -794,7 +962,7 @@ hipError_t launch_eval_grid_fused(const GridDesc &g, const DevTables *tab, const
 hipError_t launch_eval_grid(const GridDesc &g, const DevTables *tab, const void *tile_tables, uint32_t first,
                             uint32_t count, double e_c, double e_b, bool additive, const guide_metrics &out,
                             hipStream_t stream, LaunchTiming tm, const FusedSelect *sample, bool *sampled) {
-    const dim3 grid(blocks_for(count)), block(kBlock);
+    const dim3 block(kBlock);
     const double re_c = 1.0 / e_c, re_b = 1.0 / e_b;
     FusedSelect rider;
     const FusedSelect *fs = nullptr;
@@ -809,26 +977,39 @@ hipError_t launch_eval_grid(const GridDesc &g, const DevTables *tab, const void 
     if (additive ? dispatch_tile<true>(g, tab, tile_tables, first, count, re_c, re_b, out, fs, stream, nullptr, tm)
                  : dispatch_tile<false>(g, tab, tile_tables, first, count, re_c, re_b, out, fs, stream, nullptr, tm))
         return hipGetLastError();
-    if (additive && tm.start)
-        hipExtLaunchKernelGGL(eval_grid_kernel<true>, grid, block, 0, stream, tm.start, tm.stop, 0, g, tab, first, count,
-                              re_c, re_b, out);
-    else if (additive)
-        hipLaunchKernelGGL(eval_grid_kernel<true>, grid, block, 0, stream, g, tab, first, count, re_c, re_b, out);
-    else if (tm.start)
-        hipExtLaunchKernelGGL(eval_grid_kernel<false>, grid, block, 0, stream, tm.start, tm.stop, 0, g, tab, first, count,
-                              re_c, re_b, out);
-    else
-        hipLaunchKernelGGL(eval_grid_kernel<false>, grid, block, 0, stream, g, tab, first, count, re_c, re_b, out);
+    const ExpandPlan plan = expand_plan(g, first, count);
+    const bool stream_stores = (uint64_t)count * 8 * n_f64_columns(out) >= kStreamBytes;
+    auto launch = [&](auto kernel) {
+        const TileLds *tables = (const TileLds *)tile_tables;
+        if (tm.start)
+            hipExtLaunchKernelGGL(kernel, dim3(plan.blocks), block, 0, stream, tm.start, tm.stop, 0, g, first, count, re_c, re_b,
+                                  out, tables, plan.per_run);
+        else
+            hipLaunchKernelGGL(kernel, dim3(plan.blocks), block, 0, stream, g, first, count, re_c, re_b, out, tables,
+                               plan.per_run);
+    };
+    if (additive && stream_stores) launch(eval_wide_kernel<true, true>);
+    else if (additive) launch(eval_wide_kernel<true, false>);
+    else if (stream_stores) launch(eval_wide_kernel<false, true>);
+    else launch(eval_wide_kernel<false, false>);
     return hipGetLastError();
 }
 
 hipError_t launch_eval_extras(const GridDesc &g, const DevTables *tab, uint32_t first, uint32_t count, uint32_t n_gpus,
                               bool additive, const guide_extras &out, hipStream_t stream) {
-    const dim3 grid(blocks_for(count)), block(kBlock);
-    if (additive)
-        hipLaunchKernelGGL(eval_extras_kernel<true>, grid, block, 0, stream, g, tab, first, count, n_gpus, out);
-    else
-        hipLaunchKernelGGL(eval_extras_kernel<false>, grid, block, 0, stream, g, tab, first, count, n_gpus, out);
+    const ExpandPlan plan = expand_plan(g, first, count);
+    auto bytes = [](const void *p, uint64_t width) { return p ? width : 0; };
+    const uint64_t per_row = bytes(out.s_max, 4) + bytes(out.dp_max, 4) + bytes(out.max_parallelism, 8) + bytes(out.cluster_tok_s, 8) +
+                             bytes(out.paper_tok_s, 8) + bytes(out.b_adj, 4) + bytes(out.n_sub_batches, 4) +
+                             bytes(out.n_segments, 4) + bytes(out.s_adj, 4) + bytes(out.b_max_kept, 4) + bytes(out.s_max_kept, 4);
+    const bool stream_stores = count * per_row >= kStreamBytes;
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(plan.blocks), dim3(kBlock), 0, stream, g, tab, first, count, n_gpus, out, plan.per_run);
+    };
+    if (additive && stream_stores) launch(eval_extras_kernel<true, true>);
+    else if (additive) launch(eval_extras_kernel<true, false>);
+    else if (stream_stores) launch(eval_extras_kernel<false, true>);
+    else launch(eval_extras_kernel<false, false>);
     return hipGetLastError();
 }
 
