@@ -478,10 +478,15 @@ struct ExtremeK {
 #pragma unroll
         for (int i = 0; i < kRankMax; ++i) v[i] = w[1 + i];
     }
-    __device__ double at(uint32_t r) const {   // r-th from the extreme end, 0-based
+    // r-th from the extreme end, 0-based: the least extreme of the first r + 1.  (A chain of selects r == i ? v[i] : x
+    // is turned into an indexed read, which puts the list into scratch memory.)
+    __device__ double at(uint32_t r) const {
         double x = v[0];
 #pragma unroll
-        for (int i = 1; i < kRankMax; ++i) x = r == (uint32_t)i ? v[i] : x;
+        for (int i = 1; i < kRankMax; ++i) {
+            const double y = LARGEST ? fmin(x, v[i]) : fmax(x, v[i]);
+            x = (uint32_t)i <= r ? y : x;
+        }
         return x;
     }
 };
@@ -501,108 +506,7 @@ __device__ inline void sort_group(double (&a)[kSweepGroup]) {
     cx(a[3], a[4]);
 }
 
-// Efficiency sweep.  Neither latency depends on the KV block size, so one lane evaluates the samples
-// for all block sizes of a configuration at once (rows that differ only in the kv_block digit) and
-// only the memory check is repeated per block size; the split of the prefill into passes does not
-// depend on the sample and is planned once.
-// Two waves per SIMD: the register budget that asks for costs a few spills, and measured 0.44 ms against 0.56 ms
-// with one wave (three and four waves spill far more: 1.5 and 2.7 ms).
-template <bool ADDITIVE>
-__global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const DevTables *__restrict__ tab,
-                                                            uint32_t first, uint32_t count, uint32_t n_eff,
-                                                            guide_stats out) {
-    __shared__ GridLds s;
-    __shared__ double s_rec[GUIDE_MAX_EFF], s_reb[GUIDE_MAX_EFF];
-    stage_grid_tables(s, g, tab);
-    for (uint32_t i = threadIdx.x; i < n_eff; i += blockDim.x) {
-        s_rec[i] = 1.0 / tab->eff_c[i];
-        s_reb[i] = 1.0 / tab->eff_b[i];
-    }
-    __syncthreads();
-    // nearest rank: p10 = sorted[ceil(n/10) - 1]; p90 = sorted[ceil(9n/10) - 1] = (n - ceil(9n/10))-th largest, 0-based
-    const uint32_t r_lo = (n_eff + 9) / 10 - 1;
-    const uint32_t r_hi = n_eff - (9 * n_eff + 9) / 10;
-    // work item u = (index with the kv_block digit removed): rows (hi * NB + k) * NM + m for k < NB
-    const uint32_t NB = g.div[AX_BLK].d, NM = g.div[AX_MBT].d, TS = NB * NM;
-    const uint32_t t_first = first / TS;
-    const uint32_t n_items = ((first + count - 1) / TS - t_first + 1) * NM;
-    const uint32_t last = first + count;
-    for (uint32_t u = blockIdx.x * kBlock + threadIdx.x; u < n_items; u += gridDim.x * kBlock) {
-        const uint32_t hi = t_first + u / NM, m_digit = u % NM;
-        const uint32_t row0 = hi * TS + m_digit;                  // the row with kv_block digit 0
-        // none of this item's rows inside [first, last)?  (only at the ragged ends)
-        if (row0 + (NB - 1) * NM < first || row0 >= last) continue;
-        const Candidate c = decode_index(s, g, row0);
-        const Coef cf = make_coef(s.models[c.model], c.kn.p, c.kn.wbits);
-        const HwRecip hw = s.hw[c.hw];
-        const PrefillPlan plan = make_prefill_plan(c.kn.b, c.kn.s_in, c.kn.mbt, recip_up(1.0 / (double)c.kn.s_in),
-                                                   recip_up(1.0 / (double)c.kn.mbt));
-        ExtremeK<false> lo_p, lo_b;
-        ExtremeK<true> hi_p, hi_b;
-        lo_p.init(); hi_p.init(); lo_b.init(); hi_b.init();
-        double sum_p = 0.0, sum_b = 0.0;
-        auto sample = [&](uint32_t e, double &tp, double &tb) {
-            const TimeCoef tc = make_time_coef(cf, hw.r_peak * s_rec[e], hw.r_bw * s_reb[e], hw.r_link, hw.lat);
-            tp = prefill_time_plan<ADDITIVE>(tc, plan, c.kn.b);
-            tb = tp + decode_time_fast<ADDITIVE>(tc, c.kn.b, c.kn.s_in, c.kn.s_out - 1);
-            sum_p += tp;
-            sum_b += tb;
-        };
-        // Whole groups of eight samples are sorted once (shared by the list of the smallest and the list of
-        // the largest) and merged into the lists: 12.5 instead of 28 minimum / maximum operations per sample
-        // and metric.  The eight evaluations of a group are unrolled: they are independent, which gives the one
-        // or two waves a SIMD holds something to issue while an earlier result is on its way (0.55 against
-        // 0.62 ms with the group's samples parked in LDS and the evaluation not unrolled).
-        uint32_t e = 0;
-        for (; e + kSweepGroup <= n_eff; e += kSweepGroup) {
-            double a[kSweepGroup], bb[kSweepGroup];
-#pragma unroll
-            for (int q = 0; q < kSweepGroup; ++q) sample(e + q, a[q], bb[q]);
-            sort_group(a);
-            lo_p.merge(a);
-            hi_p.merge(a);
-            sort_group(bb);
-            lo_b.merge(bb);
-            hi_b.merge(bb);
-        }
-        for (; e < n_eff; ++e) {
-            double tp, tb;
-            sample(e, tp, tb);
-            lo_p.push(tp); hi_p.push(tp);
-            lo_b.push(tb); hi_b.push(tb);
-        }
-        const double mean_p = sum_p / (double)n_eff, mean_b = sum_b / (double)n_eff;
-        const double p10_p = lo_p.at(r_lo), p90_p = hi_p.at(r_hi), p10_b = lo_b.at(r_lo), p90_b = hi_b.at(r_hi);
-        const double cost = cost_of(c.kn, mean_b);
-        for (uint32_t k = 0; k < NB; ++k) {
-            const uint32_t row = row0 + k * NM;
-            if (row < first || row >= last) continue;
-            const uint32_t i = row - first;
-            if (out.ttft_mean) out.ttft_mean[i] = mean_p;
-            if (out.ttft_p10) out.ttft_p10[i] = p10_p;
-            if (out.ttft_p90) out.ttft_p90[i] = p90_p;
-            if (out.t_batch_mean) out.t_batch_mean[i] = mean_b;
-            if (out.t_batch_p10) out.t_batch_p10[i] = p10_b;
-            if (out.t_batch_p90) out.t_batch_p90[i] = p90_b;
-            if (out.cost) out.cost[i] = cost;
-            if (out.b_max || out.feasible) {
-                const MemResult mem = memory_check(cf, hw.cap, c.kn.b, c.kn.s_in, c.kn.s_out, s.axis[AX_BLK][k]);
-                if (out.b_max) out.b_max[i] = mem.b_max;
-                if (out.feasible) out.feasible[i] = mem.feasible ? 1 : 0;
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------- expanded variants
-//
-// Where a lane cannot own a whole tile (more than four values on one of the two fastest axes) or hardly any column varies
-// inside one (the cluster-level columns), a block takes a run of tiles, works out into LDS what depends on the tile,
-// on (tile, token budget) and on (tile, block size), and then writes the rows from there, each wave 64 consecutive
-// rows of every column.
-
-constexpr uint32_t kExpandTiles = 256;          // most tiles of a run
-constexpr uint32_t kExpandParts = 1024;         // most (tile, block size) and (tile, token budget) pairs of a run
+// One setting of the seven slower axes.
 struct ExpandTile {
     uint32_t row;                               // (model, tp, precision) row of coefficients
     uint32_t model, hw, b, d_sin, s_in, s_out, d_tp, p, wbits;
@@ -629,6 +533,272 @@ __device__ inline ExpandTile expand_tile(const GridLds &s, const GridDesc &g, ui
     t.wbits = s.axis[AX_WBITS][dg[AX_WBITS]];
     return t;
 }
+
+// Efficiency sweep.  Neither latency depends on the KV block size, so one lane evaluates the samples
+// for all block sizes of a configuration at once (rows that differ only in the kv_block digit) and
+// only the memory check is repeated per block size.
+//
+// A sample scales every compute time by x = 1 / e_c and every read time by y = 1 / e_b.  A configuration's time is a sum of
+// terms max(F x, B y) -- one per task and pass, with the passes' counts multiplied in -- plus the transfers.  Over the
+// ratios x / y of all samples most terms are bound by the same side throughout: those are added up once per
+// configuration, and a sample costs two multiply-adds for all of them.  The others (a few per wave: neighbouring
+// configurations have them in common) are kept as pairs and evaluated per sample, skipped by branches that are uniform
+// over the wave.
+constexpr int kPassTerms = N_LINEAR + 2;                // the linear tasks, attention, LM head
+template <int N>
+struct SweepTerms {
+    double F[N], B[N];          // terms that change sides within the samples (0, 0 in lanes where they do not)
+    double a_F, a_B, fixed;     // the other terms' sums; transfers
+    uint32_t active;            // wave-uniform: terms that change sides in some lane
+    __device__ void init() {
+        a_F = a_B = fixed = 0.0;
+        active = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) F[i] = B[i] = 0.0;
+    }
+    template <bool ADDITIVE>
+    __device__ void add(int i, double f, double b, double rho_lo, double rho_hi) {
+        const bool compute = ADDITIVE || f * rho_lo >= b, read = ADDITIVE || f * rho_hi <= b;
+        a_F += compute ? f : 0.0;
+        a_B += read && (ADDITIVE || !compute) ? b : 0.0;
+        if (!ADDITIVE) {
+            const bool both = !compute && !read;
+            F[i] = both ? f : 0.0;
+            B[i] = both ? b : 0.0;
+        }
+    }
+    // `times` passes of T tokens with attention workload Q, K context tokens and n_lm LM-head rows; att: attention counts
+    template <bool ADDITIVE>
+    __device__ void add_pass(int i0, const TimeCoef &t, double times, double T, double Q, double K, double n_lm, bool att,
+                             double rho_lo, double rho_hi) {
+        const double w = times * t.L, wT = w * T, eld = fmin(t.E, t.k * T);
+#pragma unroll
+        for (int i = 0; i < N_LINEAR; ++i) {
+            const bool experts = i == OP_UP || i == OP_DOWN;
+            add<ADDITIVE>(i0 + i, wT * t.c[i], w * fma(T, t.m1[i], experts ? eld * t.m0[i] : t.m0[i]), rho_lo, rho_hi);
+        }
+        if (att) add<ADDITIVE>(i0 + N_LINEAR, w * (Q * t.c_att), w * fma(K, t.m_att_k, T * t.m_att_t), rho_lo, rho_hi);
+        if (n_lm > 0.0)
+            add<ADDITIVE>(i0 + N_LINEAR + 1, times * (n_lm * t.c_lm), times * fma(n_lm, t.m1_lm, t.m0_lm), rho_lo, rho_hi);
+        a_B += wT * t.m_nm;
+        fixed += 2.0 * w * fma(T, t.ar1, t.ar0);
+    }
+    // to be called by all lanes in action together, after the last add
+    __device__ void settle() {
+        uint32_t m = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) m |= __ballot(F[i] != 0.0) ? 1u << i : 0u;     // (a term that changes sides has F > 0)
+        active = (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
+    }
+    template <int G>
+    __device__ void evaluate(const double (&x)[G], const double (&y)[G], double (&v)[G]) const {
+#pragma unroll
+        for (int q = 0; q < G; ++q) v[q] = fma(x[q], a_F, fma(y[q], a_B, fixed));
+#pragma unroll
+        for (int i0 = 0; i0 < N; i0 += kPassTerms) {
+            if (((active >> i0) & ((1u << kPassTerms) - 1u)) == 0u) continue;       // no term of the pass
+#pragma unroll
+            for (int i = i0; i < i0 + kPassTerms; ++i) {
+                if ((active >> i) & 1u) {
+#pragma unroll
+                    for (int q = 0; q < G; ++q) v[q] += fmax(F[i] * x[q], B[i] * y[q]);
+                }
+            }
+        }
+    }
+};
+
+__device__ inline double uniform(double x) {
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Bound by the vector ALU (3800 instructions per lane for 64 samples, 22 of the 35 per sample are the sorting).  Two
+// waves per SIMD.  1.9 million configurations x 64 samples: 141 us; with every task's two sides, the split of the
+// series and the coefficients worked out per sample, 371 us.
+template <bool ADDITIVE>
+__global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const DevTables *__restrict__ tab,
+                                                            uint32_t first, uint32_t count, uint32_t n_eff,
+                                                            guide_stats out, const TileLds *__restrict__ derived) {
+    __shared__ TileLds s;
+    __shared__ double2 s_eff[GUIDE_MAX_EFF];            // (1 / e_c, 1 / e_b)
+    __shared__ double s_rho[GUIDE_MAX_EFF];
+    const uint32_t n_rows = g.div[AX_MODEL].d * g.div[AX_TP].d * g.div[AX_WBITS].d;
+    const bool coef_in_lds = n_rows <= kCoefRows;
+    {
+        const uint32_t vecs = (uint32_t)(offsetof(TileLds, coef) + (coef_in_lds ? n_rows : 0u) * sizeof(Coef) + 15) / 16;
+        for (uint32_t i = threadIdx.x; i < vecs; i += kBlock) ((uint4 *)&s)[i] = ((const uint4 *)derived)[i];
+    }
+    for (uint32_t i = threadIdx.x; i < n_eff; i += blockDim.x) {
+        s_eff[i] = double2{1.0 / tab->eff_c[i], 1.0 / tab->eff_b[i]};
+        s_rho[i] = tab->eff_b[i] / tab->eff_c[i];
+    }
+    __syncthreads();
+    double rho_lo = s_rho[0], rho_hi = rho_lo;                      // least and largest x / y
+    for (uint32_t e = 1; e < n_eff; ++e) {
+        rho_lo = fmin(rho_lo, s_rho[e]);
+        rho_hi = fmax(rho_hi, s_rho[e]);
+    }
+    // (a rounding of rho decides a term only where both sides are equal to rounding)
+    // nearest rank: p10 = sorted[ceil(n/10) - 1]; p90 = sorted[ceil(9n/10) - 1] = (n - ceil(9n/10))-th largest, 0-based
+    const uint32_t r_lo = (n_eff + 9) / 10 - 1;
+    const uint32_t r_hi = n_eff - (9 * n_eff + 9) / 10;
+    // work item u = (index with the kv_block digit removed): rows (hi * NB + k) * NM + m for k < NB
+    const uint32_t NB = g.div[AX_BLK].d, NM = g.div[AX_MBT].d, TS = NB * NM;
+    const uint32_t t_first = first / TS;
+    const uint32_t n_items = ((first + count - 1) / TS - t_first + 1) * NM;
+    const uint32_t last = first + count;
+    for (uint32_t u = blockIdx.x * kBlock + threadIdx.x; u < n_items; u += gridDim.x * kBlock) {
+        const uint32_t hi = t_first + u / NM, m_digit = u % NM;
+        const uint32_t row0 = hi * TS + m_digit;                  // the row with kv_block digit 0
+        // none of this item's rows inside [first, last)?  (only at the ragged ends)
+        if (row0 + (NB - 1) * NM < first || row0 >= last) continue;
+        const ExpandTile tl = expand_tile(s.g, g, hi);
+        const uint32_t mbt = s.g.axis[AX_MBT][m_digit];
+        const HwRecip hw = s.g.hw[tl.hw];
+        TimeCoef tc;
+        double w_gpu, kv_tok;
+        if (coef_in_lds) {
+            const Coef &cf = s.coef[tl.row];
+            tc = make_time_coef(cf, hw.r_peak, hw.r_bw, hw.r_link, hw.lat);
+            w_gpu = cf.w_gpu;
+            kv_tok = cf.kv_tok;
+        } else {
+            const Coef cf = make_coef(s.g.models[tl.model], tl.p, tl.wbits, s.r_tp[tl.d_tp]);
+            tc = make_time_coef(cf, hw.r_peak, hw.r_bw, hw.r_link, hw.lat);
+            w_gpu = cf.w_gpu;
+            kv_tok = cf.kv_tok;
+        }
+        const PrefillPlan plan = make_prefill_plan(tl.b, tl.s_in, mbt, s.r_sin[tl.d_sin], s.r_mbt[m_digit]);
+        SweepTerms<2 * kPassTerms> pre;
+        SweepTerms<kPassTerms> dec;
+        pre.init();
+        dec.init();
+        // attention over the full segments of a long prompt, or over the decode steps, is a series of terms; where it
+        // changes sides within the samples it is summed per sample
+        double p_al = 0.0, p_be = 0.0, p_ga = 0.0, d_al = 0.0, d_be = 0.0, d_ga = 0.0;
+        bool p_series = false, d_series = false;
+        const double b = (double)tl.b, n = (double)(tl.s_out - 1), S = plan.S;
+        {
+            // sum over contexts first, 2 first, .. or s + 1, .., s + n: both sides are linear in the context, so the ends decide
+            auto series = [&](auto &terms, double w, double al, double be, double ga, double c_lo, double c_hi, double all,
+                              double steps, double &o_al, double &o_be, double &o_ga) {
+                const bool read = ADDITIVE || al * rho_hi * c_hi <= fma(be, c_hi, ga);
+                const bool compute = ADDITIVE || al * rho_lo * c_lo >= fma(be, c_lo, ga);
+                terms.a_F += compute ? w * (al * all) : 0.0;
+                terms.a_B += read && (ADDITIVE || !compute) ? w * fma(be, all, steps * ga) : 0.0;
+                const bool both = !read && !compute;
+                o_al = both ? w * al : 0.0;
+                o_be = both ? w * be : 0.0;
+                o_ga = both ? w * ga : 0.0;
+                return both;
+            };
+            const bool seg = plan.segmented;
+            const double R = plan.R;
+            pre.add_pass<ADDITIVE>(0, tc, seg ? b * plan.n_fs : plan.n_full, seg ? plan.M : R * S, R * S * S, R * S, R, !seg,
+                                   rho_lo, rho_hi);
+            if (seg || plan.rem > 0.0)
+                pre.add_pass<ADDITIVE>(kPassTerms, tc, seg ? b : 1.0, seg ? plan.c_last : plan.rem * S,
+                                       seg ? plan.c_last * S : plan.rem * S * S, seg ? S : plan.rem * S, seg ? 1.0 : plan.rem, true,
+                                       rho_lo, rho_hi);
+            if (seg)
+                p_series = series(pre, b * tc.L, plan.M * tc.c_att, tc.m_att_k, plan.M * tc.m_att_t, plan.M,
+                                  plan.n_fs * plan.M, plan.M * (0.5 * plan.n_fs * (plan.n_fs + 1.0)), plan.n_fs, p_al, p_be, p_ga);
+            if (n > 0.0) {
+                dec.add_pass<ADDITIVE>(0, tc, n, b, 0.0, 0.0, b, false, rho_lo, rho_hi);
+                d_series = series(dec, tc.L, b * tc.c_att, b * tc.m_att_k, b * tc.m_att_t, S + 1.0, S + n,
+                                  fma(n, S, 0.5 * n * (n + 1.0)), n, d_al, d_be, d_ga);
+            }
+        }
+        pre.settle();
+        dec.settle();
+        const bool any_p = __ballot(p_series) != 0, any_d = __ballot(d_series) != 0;    // wave-uniform
+        ExtremeK<false> lo_p, lo_b;
+        ExtremeK<true> hi_p, hi_b;
+        lo_p.init(); hi_p.init(); lo_b.init(); hi_b.init();
+        double sum_p = 0.0, sum_b = 0.0;
+        auto samples = [&](uint32_t e, auto &tp, auto &tb) {
+            constexpr int G = sizeof(tp) / sizeof(double);
+            double x[G], y[G];
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                const double2 ef = s_eff[e + q];        // the same in every lane: kept in scalar registers
+                x[q] = uniform(ef.x);
+                y[q] = uniform(ef.y);
+            }
+            pre.evaluate(x, y, tp);
+            if (any_p) {
+#pragma unroll
+                for (int q = 0; q < G; ++q)
+                    tp[q] += attention_series<ADDITIVE>(p_al * x[q], p_be * y[q], p_ga * y[q], 0.0, plan.M, plan.r_mbt, plan.n_fs);
+            }
+            dec.evaluate(x, y, tb);
+            if (any_d) {
+#pragma unroll
+                for (int q = 0; q < G; ++q)
+                    tb[q] += attention_series<ADDITIVE>(d_al * x[q], d_be * y[q], d_ga * y[q], S, 1.0, 1.0, n);
+            }
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                tb[q] += tp[q];
+                sum_p += tp[q];
+                sum_b += tb[q];
+            }
+        };
+        // Whole groups of eight samples are sorted once (shared by the list of the smallest and the list of
+        // the largest) and merged into the lists: 12.5 instead of 28 minimum / maximum operations per sample
+        // and metric.
+        uint32_t e = 0;
+        for (; e + kSweepGroup <= n_eff; e += kSweepGroup) {
+            double a[kSweepGroup], bb[kSweepGroup];
+            samples(e, a, bb);
+            sort_group(a);
+            lo_p.merge(a);
+            hi_p.merge(a);
+            sort_group(bb);
+            lo_b.merge(bb);
+            hi_b.merge(bb);
+        }
+        for (; e < n_eff; ++e) {
+            double tp[1], tb[1];
+            samples(e, tp, tb);
+            lo_p.push(tp[0]); hi_p.push(tp[0]);
+            lo_b.push(tb[0]); hi_b.push(tb[0]);
+        }
+        const double mean_p = sum_p / (double)n_eff, mean_b = sum_b / (double)n_eff;
+        const double p10_p = lo_p.at(r_lo), p90_p = hi_p.at(r_hi), p10_b = lo_b.at(r_lo), p90_b = hi_b.at(r_hi);
+        const double cost = (double)tl.p * mean_b / 3600.0 * 1.0e6 / (b * (double)tl.s_out);
+        for (uint32_t k = 0; k < NB; ++k) {
+            const uint32_t row = row0 + k * NM;
+            if (row < first || row >= last) continue;
+            const uint32_t i = row - first;
+            if (out.ttft_mean) out.ttft_mean[i] = mean_p;
+            if (out.ttft_p10) out.ttft_p10[i] = p10_p;
+            if (out.ttft_p90) out.ttft_p90[i] = p90_p;
+            if (out.t_batch_mean) out.t_batch_mean[i] = mean_b;
+            if (out.t_batch_p10) out.t_batch_p10[i] = p10_b;
+            if (out.t_batch_p90) out.t_batch_p90[i] = p90_b;
+            if (out.cost) out.cost[i] = cost;
+            if (out.b_max || out.feasible) {
+                const MemResult mem = memory_check(w_gpu, kv_tok, hw.cap, tl.b, tl.s_in, tl.s_out, s.g.axis[AX_BLK][k]);
+                if (out.b_max) out.b_max[i] = mem.b_max;
+                if (out.feasible) out.feasible[i] = mem.feasible ? 1 : 0;
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------- expanded variants
+//
+// Where a lane cannot own a whole tile (more than four values on one of the two fastest axes) or hardly any column varies
+// inside one (the cluster-level columns), a block takes a run of tiles, works out into LDS what depends on the tile,
+// on (tile, token budget) and on (tile, block size), and then writes the rows from there, each wave 64 consecutive
+// rows of every column.
+
+constexpr uint32_t kExpandTiles = 256;          // most tiles of a run
+constexpr uint32_t kExpandParts = 1024;         // most (tile, block size) and (tile, token budget) pairs of a run
 template <bool STREAM, typename T>
 __device__ inline void put(T *col, uint32_t i, T v) {
     if (STREAM) __builtin_nontemporal_store(v, &col[i]);
@@ -849,12 +1019,6 @@ static ExpandPlan expand_plan(const GridDesc &g, uint32_t first, uint32_t count)
     return ExpandPlan{per_run, runs < most ? runs : most};
 }
 
-static uint32_t blocks_for(uint32_t count) {
-    const uint32_t need = (count + kBlock - 1) / kBlock;
-    const uint32_t cap = device_cus() * 8;
-    return need < cap ? need : cap;
-}
-
 static uint32_t tile_blocks(uint32_t first, uint32_t count, uint32_t ts) {
     const uint32_t n_tiles = (first + count - 1) / ts - first / ts + 1;
     // two persistent blocks per compute unit: every wave loops over several batches of 64 tiles, so the
@@ -1013,15 +1177,17 @@ hipError_t launch_eval_extras(const GridDesc &g, const DevTables *tab, uint32_t 
     return hipGetLastError();
 }
 
-hipError_t launch_eval_sweep(const GridDesc &g, const DevTables *tab, uint32_t first, uint32_t count, uint32_t n_eff,
-                             bool additive, const guide_stats &out, hipStream_t stream) {
+hipError_t launch_eval_sweep(const GridDesc &g, const DevTables *tab, const void *tile_tables, uint32_t first,
+                             uint32_t count, uint32_t n_eff, bool additive, const guide_stats &out, hipStream_t stream) {
     const uint32_t ts = g.div[AX_BLK].d * g.div[AX_MBT].d;
     const uint32_t n_items = ((first + count - 1) / ts - first / ts + 1) * g.div[AX_MBT].d;
-    const dim3 grid(blocks_for(n_items)), block(kBlock);
+    const uint32_t need = (n_items + kBlock - 1) / kBlock, most = 2 * device_cus();     // resident blocks: two per compute unit
+    const dim3 grid(need < most ? need : most), block(kBlock);
+    const TileLds *tables = (const TileLds *)tile_tables;
     if (additive)
-        hipLaunchKernelGGL(eval_sweep_kernel<true>, grid, block, 0, stream, g, tab, first, count, n_eff, out);
+        hipLaunchKernelGGL(eval_sweep_kernel<true>, grid, block, 0, stream, g, tab, first, count, n_eff, out, tables);
     else
-        hipLaunchKernelGGL(eval_sweep_kernel<false>, grid, block, 0, stream, g, tab, first, count, n_eff, out);
+        hipLaunchKernelGGL(eval_sweep_kernel<false>, grid, block, 0, stream, g, tab, first, count, n_eff, out, tables);
     return hipGetLastError();
 }
 

@@ -417,11 +417,11 @@ int guide_eval_grid(guide_ctx *ctx, const guide_grid *grid, uint64_t first, uint
         ctx->host_tab.eff_c[i] = eff->e_c[i];
         ctx->host_tab.eff_b[i] = eff->e_b[i];
     }
-    rc = n_eff > 1 ? upload_tables(ctx, stream) : upload_grid_tables(ctx, desc, stream);
+    rc = upload_grid_tables(ctx, desc, stream);
     if (rc) return rc;
     hipError_t e;
     if (n_eff > 1) {
-        e = launch_eval_sweep(desc, ctx->dev_tab, (uint32_t)first, (uint32_t)count, n_eff,
+        e = launch_eval_sweep(desc, ctx->dev_tab, ctx->dev_tile, (uint32_t)first, (uint32_t)count, n_eff,
                               time_model == GUIDE_TIME_ADDITIVE, *stats, stream);
     } else {
         const double e_c = n_eff ? eff->e_c[0] : 1.0, e_b = n_eff ? eff->e_b[0] : 1.0;

@@ -14,8 +14,8 @@ hipError_t launch_tile_tables(const GridDesc &g, const DevTables *tab, void *til
 struct LaunchTiming {
     hipEvent_t start = nullptr, stop = nullptr;
 };
-hipError_t launch_eval_sweep(const GridDesc &g, const DevTables *tab, uint32_t first, uint32_t count, uint32_t n_eff,
-                             bool additive, const guide_stats &out, hipStream_t stream);
+hipError_t launch_eval_sweep(const GridDesc &g, const DevTables *tab, const void *tile_tables, uint32_t first,
+                             uint32_t count, uint32_t n_eff, bool additive, const guide_stats &out, hipStream_t stream);
 
 // Selections folded into the grid evaluation (guide_eval_select): while a row's values are still
 // in registers the evaluation feeds a per-lane top-K list and / or the row sample that fixes the

@@ -326,13 +326,13 @@ struct MemResult {
 };
 
 // available = capacity - weights / p; KV per request over block-rounded s_in + s_out.
-__device__ inline MemResult memory_check(const Coef &c, double cap, uint32_t b, uint32_t s_in, uint32_t s_out,
+__device__ inline MemResult memory_check(double w_gpu, double kv_tok, double cap, uint32_t b, uint32_t s_in, uint32_t s_out,
                                          uint32_t blk) {
     MemResult r;
-    const double c_avail = cap - c.w_gpu;
+    const double c_avail = cap - w_gpu;
     const uint32_t tok = s_in + s_out;
     const uint32_t tok_req = (tok + blk - 1) / blk * blk;
-    const double kv_req = (double)tok_req * c.kv_tok;
+    const double kv_req = (double)tok_req * kv_tok;
     if (c_avail > 0.0) {
         r.feasible = (double)b * kv_req <= c_avail;
         const double q = floor(c_avail / kv_req);
@@ -342,6 +342,11 @@ __device__ inline MemResult memory_check(const Coef &c, double cap, uint32_t b, 
         r.b_max = 0u;
     }
     return r;
+}
+
+__device__ inline MemResult memory_check(const Coef &c, double cap, uint32_t b, uint32_t s_in, uint32_t s_out,
+                                         uint32_t blk) {
+    return memory_check(c.w_gpu, c.kv_tok, cap, b, s_in, s_out, blk);
 }
 
 struct Knobs {
