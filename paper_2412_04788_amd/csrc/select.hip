@@ -282,13 +282,6 @@ constexpr uint32_t kGroupThreads = 512, kGroupWaves = kGroupThreads / kWave;
 // Bound by latency at this size (one batch per block): 1.9 million rows, ten groups, k = 3 and one constraint (40 MB)
 // take 17.3 us + 5.2 us for the merge; k rounds over all rows took 15.7 + 4.1 us a round.  Blocks of 512 threads:
 // 23.0 us with 256 (twice the batches); lists that start from nothing: 35 us (every row is inserted at first).
-constexpr uint32_t kGroupThreads = 512, kGroupWaves = kGroupThreads / kWave;
-// One pass over the rows for any number of groups and k.  Every wave keeps a sorted list of k (key, row) pairs per
-// group in LDS, and the block a bound per group: some wave's k-th key.  Nearly all rows lie above the bound of
-// their group and cost a compare; the others are inserted one after the other, the list's places side by side in
-// lanes 0 .. k - 1.  Bound by the read of the columns and the inserts of the start: 1.9 million rows, ten groups,
-// k = 3 and one constraint (40 MB) take 13 us with the merge's 6; k rounds over all rows with a pass and a merge
-// each took 15.7 + 4.1 us a round.
 template <uint32_t MAXC>
 __global__ __launch_bounds__(kGroupThreads) void topk_group_kernel(const double *__restrict__ obj, RowFilter f,
                                                             const uint32_t *__restrict__ group, uint32_t G, uint32_t k,
