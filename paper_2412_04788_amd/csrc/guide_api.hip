@@ -550,7 +550,7 @@ int guide_eval_select(guide_ctx *ctx, const guide_grid *grid, uint64_t first, ui
             }
             e = launch_eval_grid_fused(desc, ctx->dev_tab, ctx->dev_tile, (uint32_t)first, (uint32_t)count, e_c, e_b,
                                        additive, *out, fs, stream, &n_blocks, timing);
-        } else if (pareto) {
+        } else if (pareto && !(select_is_small(count) && (!topk || topk->k <= 4))) {
             // the row sample of the Pareto selection is taken by extra blocks of the evaluation kernel
             FusedSelect fs;
             memset(&fs, 0, sizeof fs);
@@ -572,7 +572,7 @@ int guide_eval_select(guide_ctx *ctx, const guide_grid *grid, uint64_t first, ui
         // both selections read stored columns: the small kernels ride along with the large ones
         // with a timed evaluation kernel, the two passes are timed as well (when the pairs suffice)
         LaunchTiming passes[2];
-        const bool timed = eval_timed && pass_timing(ctx, passes);
+        const bool timed = eval_timed && !select_is_small(count) && pass_timing(ctx, passes);
         e = launch_select_both(spec_of(*topk, *out), topk->out, ws_of[topk - sel], spec_of(*pareto, *out), pareto->out,
                                ws_of[pareto - sel], count, ctx->select_scratch, stream, sampled, row_chunk,
                                timed ? passes : nullptr);

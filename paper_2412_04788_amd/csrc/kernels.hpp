@@ -70,6 +70,8 @@ hipError_t launch_select_both(const guide_select_spec &topk, const guide_select_
 // kernel deals its rows to blocks the same way, so that a row is read through the L2 that wrote it.
 uint32_t eval_grid_row_chunk(const GridDesc &g);
 
+// Selections over so few rows that one launch without a row sample does them (k <= 4 for a top-k).
+bool select_is_small(uint64_t n);
 size_t select_workspace_bytes(const guide_select_spec &spec, uint64_t n);
 hipError_t launch_eval_extras(const GridDesc &g, const DevTables *tab, uint32_t first, uint32_t count, uint32_t n_gpus,
                               bool additive, const guide_extras &out, hipStream_t stream);

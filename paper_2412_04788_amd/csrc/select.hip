@@ -1192,61 +1192,16 @@ __device__ void pareto_large_front(FinishLds &L, const ParetoWs &w, SelectScratc
     }
 }
 
-// Blocks of the launch: 0 finishes the front; 1 runs a waiting top-k merge (only launched with one); the
-// others return at once unless more than kStage rows survived, and then share the large front with block 0.
-__global__ __launch_bounds__(kFinishThreads) void pareto_finish_kernel(ParetoWs w, uint32_t n, SelectScratch *sc,
-                                                                        uint64_t *out_idx,
-                                                                        uint64_t capacity, uint64_t *out_count,
-                                                                        MergeRider rider) {
-    const uint32_t first_helper = rider.n_blocks ? 2 : 1;
-    if (rider.n_blocks && blockIdx.x == 1) {
-        if (rider.K == 1)
-            topk_merge_body<1, kFinishThreads>(rider.w, rider.n_blocks, rider.k, rider.out_idx, rider.out_val, rider.out_cnt);
-        else if (rider.K == 2)
-            topk_merge_body<2, kFinishThreads>(rider.w, rider.n_blocks, rider.k, rider.out_idx, rider.out_val, rider.out_cnt);
-        else if (rider.K == 3)
-            topk_merge_body<3, kFinishThreads>(rider.w, rider.n_blocks, rider.k, rider.out_idx, rider.out_val, rider.out_cnt);
-        else
-            topk_merge_body<4, kFinishThreads>(rider.w, rider.n_blocks, rider.k, rider.out_idx, rider.out_val, rider.out_cnt);
-        return;
-    }
+// The front among up to kStage records held by the threads of the finishing block (record q of thread t is there when
+// live[q]); L.lower, L.rep and L.cur are in their neutral states and the block has met since.
+__device__ inline void finish_in_lds(FinishLds &L, const Binning &bin, const uint64_t (&rx)[kStage / kFinishThreads],
+                                     const uint64_t (&ry)[kStage / kFinishThreads],
+                                     const uint32_t (&rr)[kStage / kFinishThreads],
+                                     const bool (&live)[kStage / kFinishThreads], uint64_t *out_idx, uint64_t capacity,
+                                     uint64_t *out_count) {
     static_assert(kFinishThreads == 1024, "kPerFinish assumes 1024 threads");
-    constexpr uint32_t P = kPerFinish;
-    __shared__ FinishLds L;
+    constexpr uint32_t P = kPerFinish, kPer = kStage / kFinishThreads;
     const uint32_t t = threadIdx.x;
-    const bool helper = blockIdx.x >= first_helper;     // block-uniform
-    if (helper && sc->counters[0] <= kStage) return;
-    if (threadIdx.x == 0) L.nfront = 0;
-    // Everything the finishing block reads from global memory is requested at once, before the survivor
-    // count is known: the first kStage survivor records (index clamped to the workspace's n rows; entries
-    // at or beyond the count are ignored later), the count and the sample partials.
-    constexpr uint32_t kPer = kStage / kFinishThreads;
-    uint64_t rx[kPer], ry[kPer];
-    uint32_t rr[kPer];
-    if (!helper) {
-#pragma unroll
-        for (uint32_t q = 0; q < kPer; ++q) {
-            const uint32_t j = q * kFinishThreads + t, jc = j < n ? j : n - 1;
-            rx[q] = w.skx[jc];
-            ry[q] = w.sky[jc];
-            rr[q] = w.surv[jc];
-        }
-    }
-    const uint32_t m = sc->counters[0];
-    // the tables of the staged path are put into their neutral state while the loads are under way
-    for (uint32_t i = t; i < padded_size<P>(); i += kFinishThreads) L.lower[i] = kNone;
-#pragma unroll
-    for (uint32_t q = 0; q < kPerFinish; ++q) {
-        const uint32_t i = q * kFinishThreads + t;
-        L.rep[i] = kNone;
-        L.cur[i] = 0;
-    }
-    const Binning bin = sampled_binning(sc, L.rng);     // its barrier also covers the tables above
-    if (m > kStage) {
-        pareto_large_front(L, w, sc, bin, m, helper ? blockIdx.x - first_helper + 1 : 0, gridDim.x - first_helper + 1,
-                           out_idx, capacity, out_count);
-        return;
-    }
     // Survivors that are dominated for sure are dropped first (after the staircase and survivors kernels there
     // are few; the filter pass leaves more): those with a survivor of a strictly lower bin at or below their y,
     // and those that their own bin's representative dominates -- the survivor with the bin's least y (of those,
@@ -1254,11 +1209,9 @@ __global__ __launch_bounds__(kFinishThreads) void pareto_finish_kernel(ParetoWs 
     // Tables: least y per bin in the LDS that the records are staged in afterwards, then its exclusive
     // prefix-min; the representatives' x in the LDS of the bin counts.
     uint32_t rb[kPer];
-    bool live[kPer];
 #pragma unroll
     for (uint32_t q = 0; q < kPer; ++q) {
         rb[q] = bin(rx[q]);
-        live[q] = q * kFinishThreads + t < m;
         if (live[q]) atomicMin((unsigned long long *)&L.lower[padded<P>(rb[q])], (unsigned long long)ry[q]);
     }
     __syncthreads();
@@ -1304,6 +1257,168 @@ __global__ __launch_bounds__(kFinishThreads) void pareto_finish_kernel(ParetoWs 
         if (pos < capacity) out_idx[pos] = row;
     });
     if (t == 0) out_count[0] = n_front;
+}
+
+__device__ inline void finish_tables_neutral(FinishLds &L) {
+    constexpr uint32_t P = kPerFinish;
+    for (uint32_t i = threadIdx.x; i < padded_size<P>(); i += kFinishThreads) L.lower[i] = kNone;
+#pragma unroll
+    for (uint32_t q = 0; q < kPerFinish; ++q) {
+        const uint32_t i = q * kFinishThreads + threadIdx.x;
+        L.rep[i] = kNone;
+        L.cur[i] = 0;
+    }
+    if (threadIdx.x == 0) L.nfront = 0;
+}
+
+// Blocks of the launch: 0 finishes the front; 1 runs a waiting top-k merge (only launched with one); the
+// others return at once unless more than kStage rows survived, and then share the large front with block 0.
+__global__ __launch_bounds__(kFinishThreads) void pareto_finish_kernel(ParetoWs w, uint32_t n, SelectScratch *sc,
+                                                                        uint64_t *out_idx,
+                                                                        uint64_t capacity, uint64_t *out_count,
+                                                                        MergeRider rider) {
+    const uint32_t first_helper = rider.n_blocks ? 2 : 1;
+    if (rider.n_blocks && blockIdx.x == 1) {
+        if (rider.K == 1)
+            topk_merge_body<1, kFinishThreads>(rider.w, rider.n_blocks, rider.k, rider.out_idx, rider.out_val, rider.out_cnt);
+        else if (rider.K == 2)
+            topk_merge_body<2, kFinishThreads>(rider.w, rider.n_blocks, rider.k, rider.out_idx, rider.out_val, rider.out_cnt);
+        else if (rider.K == 3)
+            topk_merge_body<3, kFinishThreads>(rider.w, rider.n_blocks, rider.k, rider.out_idx, rider.out_val, rider.out_cnt);
+        else
+            topk_merge_body<4, kFinishThreads>(rider.w, rider.n_blocks, rider.k, rider.out_idx, rider.out_val, rider.out_cnt);
+        return;
+    }
+    __shared__ FinishLds L;
+    const uint32_t t = threadIdx.x;
+    const bool helper = blockIdx.x >= first_helper;     // block-uniform
+    if (helper && sc->counters[0] <= kStage) return;
+    // Everything the finishing block reads from global memory is requested at once, before the survivor
+    // count is known: the first kStage survivor records (index clamped to the workspace's n rows; entries
+    // at or beyond the count are ignored later), the count and the sample partials.
+    constexpr uint32_t kPer = kStage / kFinishThreads;
+    uint64_t rx[kPer], ry[kPer];
+    uint32_t rr[kPer];
+    if (!helper) {
+#pragma unroll
+        for (uint32_t q = 0; q < kPer; ++q) {
+            const uint32_t j = q * kFinishThreads + t, jc = j < n ? j : n - 1;
+            rx[q] = w.skx[jc];
+            ry[q] = w.sky[jc];
+            rr[q] = w.surv[jc];
+        }
+    }
+    const uint32_t m = sc->counters[0];
+    finish_tables_neutral(L);                           // while the loads are under way
+    const Binning bin = sampled_binning(sc, L.rng);     // its barrier also covers the tables above
+    if (m > kStage) {
+        pareto_large_front(L, w, sc, bin, m, helper ? blockIdx.x - first_helper + 1 : 0, gridDim.x - first_helper + 1,
+                           out_idx, capacity, out_count);
+        return;
+    }
+    bool live[kPer];
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) live[q] = q * kFinishThreads + t < m;
+    finish_in_lds(L, bin, rx, ry, rr, live, out_idx, capacity, out_count);
+}
+
+// Selections over at most kStage rows: one launch without sample, filter pass and block partials.  Block 0 takes the
+// Pareto selection (sel.pareto) with every passing row as a record; the next one (or block 0) the top-k of one group.
+// Bound by latency.  1080 rows, both selections: 12.5 us, with the evaluation 16.3 us a call; filter pass and finishing
+// kernel took 10.2 + 8.3 us, 25.4 us a call.  A front of 155 among 4096 rows alone: 15.6 us (22.6 in three launches), so
+// the line lies where the records stop fitting the finishing block.
+struct SmallSelect {
+    uint32_t pareto, k;                 // k = 0: no top-k
+    const double *x, *y;
+    RowFilter f;
+    uint64_t *out_idx, capacity, *out_count;
+    const double *obj;
+    RowFilter top_f;
+    uint64_t *top_idx;
+    double *top_val;
+    uint64_t *top_cnt;
+};
+template <int K>
+__device__ inline void small_topk(const SmallSelect &s, uint32_t n) {
+    constexpr int kNW = kFinishThreads / kWave;
+    __shared__ Pair s_pairs[kNW][K];
+    __shared__ uint32_t s_cnt[kNW];
+    TopList<K> l;
+    l.init();
+    uint32_t cnt = 0;
+    constexpr uint32_t kPer = kStage / kFinishThreads;
+    Row r[kPer];
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q)
+        r[q] = load_row<false, GUIDE_MAX_CONSTRAINTS>(s.obj, nullptr, s.top_f, q * kFinishThreads + threadIdx.x, n);
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+        if (r[q].pass) {
+            ++cnt;
+            l.insert_ascending(Pair{key_of(r[q].x), (uint64_t)(q * kFinishThreads + threadIdx.x)});
+        }
+    }
+    const uint32_t wave_cnt = wave_sum(cnt);
+    if (threadIdx.x % kWave == 0) s_cnt[threadIdx.x / kWave] = wave_cnt;
+    block_topk<K, kNW>(l, s_pairs, [&](int j, const Pair &p) {
+        if ((uint32_t)j < s.k) {
+            s.top_idx[j] = p.idx;
+            s.top_val[j] = p.idx == kNone ? INFINITY : value_of(p.key);
+        }
+    });                                                 // (contains the barrier that publishes s_cnt)
+    if (threadIdx.x == 0) {
+        uint64_t c = 0;
+        for (int wv = 0; wv < kNW; ++wv) c += s_cnt[wv];
+        s.top_cnt[0] = c;
+    }
+}
+__global__ __launch_bounds__(kFinishThreads) void small_select_kernel(SmallSelect s, uint32_t n) {
+    if (!s.pareto || blockIdx.x == 1) {                 // block-uniform
+        if (s.k == 1) small_topk<1>(s, n);
+        else if (s.k == 2) small_topk<2>(s, n);
+        else if (s.k == 3) small_topk<3>(s, n);
+        else small_topk<4>(s, n);
+        return;
+    }
+    __shared__ FinishLds L;
+    __shared__ Pair s_best[kFinishThreads / kWave];
+    constexpr uint32_t kPer = kStage / kFinishThreads;
+    const uint32_t t = threadIdx.x;
+    Row r[kPer];
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q)
+        r[q] = load_row<true, GUIDE_MAX_CONSTRAINTS>(s.x, s.y, s.f, q * kFinishThreads + t, n);
+    finish_tables_neutral(L);
+    uint64_t rx[kPer], ry[kPer], lo = kNone;
+    uint32_t rr[kPer];
+    bool live[kPer];
+    Pair best = {kNone, kNone};                         // (y key, x key) of the least y
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+        live[q] = r[q].pass;
+        rx[q] = live[q] ? key_of(r[q].x) : 0;
+        ry[q] = live[q] ? key_of(r[q].y) : 0;
+        rr[q] = q * kFinishThreads + t;
+        lo = live[q] ? min_u64(lo, rx[q]) : lo;
+        if (live[q]) best = pair_min(best, Pair{ry[q], rx[q]});
+    }
+    lo = wave_min(lo);
+    best = wave_min(best);
+    if (t % kWave == 0) {
+        L.tmp64[t / kWave] = lo;
+        s_best[t / kWave] = best;
+    }
+    __syncthreads();
+    for (uint32_t w = 0; w < kFinishThreads / kWave; ++w) {
+        lo = min_u64(lo, L.tmp64[w]);
+        best = pair_min(best, s_best[w]);
+    }
+    if (lo == kNone) {                                  // no row passes (uniform)
+        if (t == 0) s.out_count[0] = 0;
+        return;
+    }
+    __syncthreads();                                    // L.tmp64 is used again below
+    finish_in_lds(L, binning_of(lo, best.idx), rx, ry, rr, live, s.out_idx, s.capacity, s.out_count);
 }
 
 __global__ void pareto_empty_kernel(uint64_t *out_count) { out_count[0] = 0; }
@@ -1365,9 +1480,39 @@ size_t select_workspace_bytes(const guide_select_spec &spec, uint64_t n) {
     return a > b ? a : b;
 }
 
+// Up to kStage rows (what the finishing block holds in LDS) and k <= 4 (wider lists of 16 waves do not fit the block
+// merge): one launch.  1000 .. 4096 rows: a front 12.8 - 21.0 us against 20.5 - 30.1 us in three launches, a top-k 5.0 - 8.7
+// against 6.5 - 11.5 us in two.
+bool select_is_small(uint64_t n) { return n > 0 && n <= kStage; }
+static hipError_t launch_small(const guide_select_spec *topk, const guide_select_out *topk_out, const guide_select_spec *pareto,
+                               const guide_select_out *pareto_out, uint64_t n, hipStream_t stream) {
+    SmallSelect s;
+    memset(&s, 0, sizeof s);
+    if (pareto) {
+        s.pareto = 1;
+        s.x = pareto->objective;
+        s.y = pareto->objective_y;
+        s.f = make_filter(*pareto);
+        s.out_idx = pareto_out->idx;
+        s.capacity = pareto_out->capacity;
+        s.out_count = pareto_out->count;
+    }
+    if (topk) {
+        s.k = topk->k;
+        s.obj = topk->objective;
+        s.top_f = make_filter(*topk);
+        s.top_idx = topk_out->idx;
+        s.top_val = topk_out->val;
+        s.top_cnt = topk_out->count;
+    }
+    hipLaunchKernelGGL(small_select_kernel, dim3(pareto && topk ? 2 : 1), dim3(kFinishThreads), 0, stream, s, (uint32_t)n);
+    return hipGetLastError();
+}
+
 hipError_t launch_select_topk(const guide_select_spec &spec, uint64_t n, const guide_select_out &out, void *ws,
                               void *scratch, hipStream_t stream) {
     (void)scratch;
+    if (!spec.group && select_is_small(n) && spec.k <= 4) return launch_small(&spec, &out, nullptr, nullptr, n, stream);
     if (!spec.group) {
         launch_top1_pass(spec, n, ws, SampleRider{}, stream);
         launch_top1_merge(partial_width(spec.k), ws, blocks_for(n), spec.k, out, stream);
@@ -1442,6 +1587,7 @@ hipError_t launch_select_pareto(const guide_select_spec &spec, uint64_t n, const
         hipLaunchKernelGGL(pareto_empty_kernel, dim3(1), dim3(1), 0, stream, out.count);
         return hipGetLastError();
     }
+    if (select_is_small(n)) return launch_small(nullptr, nullptr, &spec, &out, n, stream);
     SelectScratch *sc = (SelectScratch *)scratch;
     hipLaunchKernelGGL(pareto_prepare_kernel, dim3(kSampleBlocks), dim3(kBlock), 0, stream, spec.objective,
                        spec.objective_y, make_filter(spec), (uint32_t)n, sc);
@@ -1478,6 +1624,7 @@ hipError_t launch_select_both(const guide_select_spec &topk, const guide_select_
                               const guide_select_spec &pareto, const guide_select_out &pareto_out, void *pareto_ws_,
                               uint64_t n, void *scratch, hipStream_t stream, bool sampled,
                               uint32_t row_chunk, const LaunchTiming *pass_timing) {
+    if (select_is_small(n) && topk.k <= 4) return launch_small(&topk, &topk_out, &pareto, &pareto_out, n, stream);
     SelectScratch *sc = (SelectScratch *)scratch;
     const int K = partial_width(topk.k);
     SharedTopk shared;
