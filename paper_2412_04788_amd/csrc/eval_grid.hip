@@ -998,6 +998,78 @@ __global__ __launch_bounds__(kBlock) void eval_extras_kernel(GridDesc g, const D
     }
 }
 
+// Cluster-level columns for few rows, one index per lane: no phases to wait for.
+template <bool ADDITIVE>
+__global__ __launch_bounds__(kBlock) void eval_extras_rows_kernel(GridDesc g, const DevTables *__restrict__ tab,
+                                                             uint32_t first, uint32_t count, uint32_t n_gpus,
+                                                             guide_extras out) {
+    __shared__ GridLds s;
+    stage_grid_tables(s, g, tab);
+    __syncthreads();
+    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < count; i += gridDim.x * kBlock) {
+        const Candidate c = decode_index(s, g, first + i);
+        const HwRecip hw = s.hw[c.hw];
+        const Coef cf = make_coef(s.models[c.model], c.kn.p, c.kn.wbits);
+        const uint32_t dp = n_gpus / c.kn.p;
+        const double n = (double)(c.kn.s_out - 1);
+        double tok_s = 0.0, tok_s1 = 0.0;
+        if (c.kn.s_out > 1 && (out.cluster_tok_s || out.paper_tok_s)) {
+            const TimeCoef tc = make_time_coef(cf, hw.r_peak, hw.r_bw, hw.r_link, hw.lat);
+            tok_s = (double)c.kn.b * n / decode_time<ADDITIVE>(tc, c.kn.b, c.kn.s_in, c.kn.s_out - 1);
+            if (out.paper_tok_s) {
+                const Coef c1 = make_coef(s.models[c.model], 1u, c.kn.wbits);      // the same candidate on one GPU
+                const TimeCoef t1 = make_time_coef(c1, hw.r_peak, hw.r_bw, hw.r_link, hw.lat);
+                tok_s1 = (double)c.kn.b * n / decode_time<ADDITIVE>(t1, c.kn.b, c.kn.s_in, c.kn.s_out - 1);
+            }
+        }
+        const double c_avail = hw.cap - cf.w_gpu;
+        const double q = floor(c_avail / ((double)c.kn.b * cf.kv_tok));
+        const uint32_t s_max = !(c_avail > 0.0) ? 0u : (q >= 4294967295.0 ? 4294967295u : (uint32_t)q);
+        if (out.s_max) out.s_max[i] = s_max;
+        if (out.dp_max) out.dp_max[i] = dp;
+        const MemResult m = memory_check(cf, hw.cap, c.kn.b, c.kn.s_in, c.kn.s_out, c.kn.blk);
+        if (out.max_parallelism) out.max_parallelism[i] = (uint64_t)dp * (uint64_t)m.b_max;
+        if (out.b_adj) out.b_adj[i] = c.kn.b < m.b_max ? c.kn.b : m.b_max;
+        const bool long_prompt = c.kn.s_in > c.kn.mbt;
+        if (out.n_sub_batches) {
+            uint32_t split = c.kn.mbt / c.kn.s_in;                    // prompts per pass (0 for a long prompt)
+            split = split < c.kn.b ? split : c.kn.b;
+            out.n_sub_batches[i] = long_prompt ? c.kn.b : (c.kn.b + split - 1) / split;
+        }
+        if (out.n_segments) out.n_segments[i] = long_prompt ? (c.kn.s_in - 1) / c.kn.mbt + 1 : 1u;
+        if (out.s_adj) {
+            const uint32_t len = c.kn.s_in + c.kn.s_out;              // both below 2^31
+            out.s_adj[i] = len < s_max ? len : s_max;
+        }
+        if (out.b_max_kept || out.feasible_kept || out.s_max_kept) {
+            // a KV-cache reduction that keeps the fraction kv_keep of every request's entries
+            const double keep = out.kv_keep == 0.0 ? 1.0 : out.kv_keep;
+            const uint32_t len = c.kn.s_in + c.kn.s_out;
+            const uint64_t kept = (uint64_t)ceil(keep * (double)len);
+            const uint64_t tok_req = (kept + c.kn.blk - 1) / c.kn.blk * c.kn.blk;
+            const double kv_req = (double)tok_req * cf.kv_tok;
+            const bool room = c_avail > 0.0;
+            const double qb = floor(c_avail / kv_req), qs = floor(q / keep);
+            if (out.b_max_kept) out.b_max_kept[i] = !room ? 0u : (qb >= 4294967295.0 ? 4294967295u : (uint32_t)qb);
+            if (out.feasible_kept) out.feasible_kept[i] = (room && (double)c.kn.b * kv_req <= c_avail) ? 1 : 0;
+            if (out.s_max_kept) out.s_max_kept[i] = !room ? 0u : (qs >= 4294967295.0 ? 4294967295u : (uint32_t)qs);
+        }
+        if (out.cluster_tok_s) out.cluster_tok_s[i] = (double)dp * tok_s;
+        if (out.paper_tok_s)
+            out.paper_tok_s[i] = ((double)dp * (double)c.kn.p) * tok_s1 / (1.0 + log2((double)c.kn.p));
+    }
+}
+
+static uint32_t blocks_for(uint32_t count) {
+    const uint32_t need = (count + kBlock - 1) / kBlock;
+    const uint32_t cap = device_cus() * 8;
+    return need < cap ? need : cap;
+}
+
+// Cluster columns are expanded from 250 000 rows and six rows a tile on: 2 x 3 tiles take 10.3 us a row at a time and 10.0
+// expanded at 250 000 rows (5.2 and 6.9 at 30 000, where the phases' latency counts; 16.5 and 12.6 at 500 000), tiles of
+// one row, which share nothing, 16.3 and 21.8 at 500 000.
+constexpr uint32_t kExpandExtrasRows = 250000, kExpandExtrasTile = 6;
 // Tiles of a run and blocks of the launch.  Two blocks per compute unit (what the LDS of both kernels allows at 160 KB;
 // three with half the runs' length: 27 against 25 us for the full grid's twelve columns), every block the same number
 // of full runs, and runs of whole multiples of 64 tiles when they are that long: their rows then start on line
@@ -1161,6 +1233,14 @@ hipError_t launch_eval_grid(const GridDesc &g, const DevTables *tab, const void 
 
 hipError_t launch_eval_extras(const GridDesc &g, const DevTables *tab, uint32_t first, uint32_t count, uint32_t n_gpus,
                               bool additive, const guide_extras &out, hipStream_t stream) {
+    if (count < kExpandExtrasRows || g.div[AX_BLK].d * g.div[AX_MBT].d < kExpandExtrasTile) {
+        const dim3 grid(blocks_for(count)), block(kBlock);
+        if (additive)
+            hipLaunchKernelGGL(eval_extras_rows_kernel<true>, grid, block, 0, stream, g, tab, first, count, n_gpus, out);
+        else
+            hipLaunchKernelGGL(eval_extras_rows_kernel<false>, grid, block, 0, stream, g, tab, first, count, n_gpus, out);
+        return hipGetLastError();
+    }
     const ExpandPlan plan = expand_plan(g, first, count);
     auto bytes = [](const void *p, uint64_t width) { return p ? width : 0; };
     const uint64_t per_row = bytes(out.s_max, 4) + bytes(out.dp_max, 4) + bytes(out.max_parallelism, 8) + bytes(out.cluster_tok_s, 8) +
