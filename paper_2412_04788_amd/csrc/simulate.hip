@@ -344,9 +344,11 @@ struct TraceSums {
 // a lane with bursts takes a round per request as well, while the other lanes go on with theirs (loops over a burst
 // make the whole wave wait for every lane's bursts in turn: 7000 loop turns per 1024 requests).
 // CLOSED_RUNS: the run is advanced in closed form (GUIDE_SIM_CLOSED_FORM_RUNS); otherwise the clock walks through it.  A
-// step's time is linear in the context while attention is bound by reading the cache at any context (every lane of
-// nearly every wave), so the walk takes strides of 64 and 8 steps, whose times are in arithmetic progression, as long
+// step's time is linear in the context while attention is bound by reading the cache at any context (nearly every
+// lane), so the walk takes strides of 64 and 8 steps, whose times are in arithmetic progression, as long
 // as the last step of the stride starts before the arrival that would end the run, and single steps after that.
+// Which of the two ways a lane goes depends on its own configuration alone, never on its neighbours in the wave (which
+// differ from call to call): the results of a configuration are the same bits in every list and every call.
 // (The stride's sum has one rounding where 64 additions to a clock of hundreds of seconds have 64: against 80-bit
 // sums over runs of up to 2000 steps the clock is 2.2e-16 off, step by step 7.0e-16.)
 // What bounds the kernel: a wave is a serial stream of about 560 instructions per round, 7 cycles each with one wave
@@ -459,8 +461,10 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
         heap.lds = s_heap + off;
         heap.cap = cap;
     }
-    // attention bound by reading the cache at every context, for every lane of the wave: step times are linear
-    const bool wave_linear = ADDITIVE || __ballot(alive && !(lt.c_att <= lt.m_att_k)) == 0;
+    // attention bound by reading the cache at every context: step times are linear (in every lane: wave_linear, which only
+    // leaves work out that changes nothing in such a lane)
+    const bool lane_linear = ADDITIVE || lt.c_att <= lt.m_att_k;
+    const bool wave_linear = ADDITIVE || __ballot(alive && !lane_linear) == 0;
     if (!alive) return;
 
     heap.top = LaneHeap<KeyT>::kEmpty;
@@ -623,7 +627,7 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
             const double slope = ADDITIVE ? lt.c_att + lt.m_att_k : lt.m_att_k;
             auto step_time = [&](double ctx) {
                 const double tm = fma(ctx, slope, base_m);
-                return wave_linear ? tm : fmax(fma(ctx, lt.c_att, base), tm);
+                return wave_linear ? tm : fmax(fma(ctx, lt.c_att, base), tm);      // (tm is the larger in a linear lane)
             };
             uint32_t run = 0;
             if (CLOSED_RUNS) {
@@ -631,27 +635,30 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
                 const uint32_t r_max = total - 1;
                 if (r_max > 0 && !(arr_stop <= now)) {
                     const double h_T = 0.5 * T;
-                    auto linear_time = [&](double r) { return r * fma(slope, fma(h_T, r - 1.0, s_ctx), base_m); };
-                    auto any_time = [&](double r) {
-                        return fma(r, base, attention_series<ADDITIVE>(lt.c_att, lt.m_att_k, T * lt.m_att_t, s_ctx - T, T,
-                                                                       fast_recip(T), r));
-                    };
-                    run = r_max;
+                    float guess = 1.0f;
                     if (can_admit) {
                         // time(r) = p r + q r^2 up to rounding; its root in single precision is the first guess
                         const double rem = arr_stop - now;
                         const float q = (float)(slope * h_T), p = (float)fma(slope, s_ctx - h_T, base_m), rf = (float)rem;
-                        const float guess = ceilf(2.0f * rf * __builtin_amdgcn_rcpf(p + __builtin_amdgcn_sqrtf(fmaf(p, p, 4.0f * q * rf))));
-                        run = wave_linear ? least_steps(now, arr_stop, r_max, guess, linear_time)
-                                          : least_steps(now, arr_stop, r_max, guess, any_time);
+                        guess = ceilf(2.0f * rf * __builtin_amdgcn_rcpf(p + __builtin_amdgcn_sqrtf(fmaf(p, p, 4.0f * q * rf))));
                     }
-                    now += wave_linear ? linear_time((double)run) : any_time((double)run);
+                    auto advance = [&](auto &&time_of) {
+                        run = can_admit ? least_steps(now, arr_stop, r_max, guess, time_of) : r_max;
+                        now += time_of((double)run);
+                    };
+                    if (lane_linear)
+                        advance([&](double r) { return r * fma(slope, fma(h_T, r - 1.0, s_ctx), base_m); });
+                    else
+                        advance([&](double r) {
+                            return fma(r, base, attention_series<ADDITIVE>(lt.c_att, lt.m_att_k, T * lt.m_att_t, s_ctx - T, T,
+                                                                           fast_recip(T), r));
+                        });
                 }
                 if (run == r_max && !(arr_stop <= now)) {
                     now += step_time(fma((double)run, T, s_ctx));
                     ++run;
                 }
-            } else if (wave_linear) {
+            } else if (lane_linear) {
                 const double dt = slope * T;
                 double t0 = fma(s_ctx, slope, base_m);
                 // strides of 64, then of 8 steps, whose times are in arithmetic progression, while the last step

@@ -103,3 +103,31 @@ def test_arrival_rates_at_the_ends_of_the_range(ora, torch_cuda):
     rate[1::4] = 1e300
     rate[2::4] = 1e-130
     _check(torch_cuda, ora, g, idx, rate, tr, scheds=(0, 1))
+
+
+@pytest.mark.parametrize("sched", [0, 1, CLOSED, 1 | CLOSED])
+def test_results_do_not_depend_on_the_list(torch_cuda, sched):
+    """Which configurations share a wave differs from list to list and from call to call.  A configuration's results do
+    not: bit for bit the same in a list that mixes lanes whose attention can be bound by arithmetic with lanes whose
+    cannot, in that list once more, in the list backwards, and alone."""
+    hws = wl.hw_profiles(3, 5) + [wl.Hardware(1e13, 8e12, 900 * wl.GIB, 4e11), wl.Hardware(3e13, 4e12, 900 * wl.GIB, 4e11)]
+    g = wl.make_grid([wl.DENSE_70B, wl.DENSE_7B], hws, wl.Axis.geom2(1, 7), wl.Axis.table([1]), wl.Axis.table([1]),
+                     wl.Axis.table([1, 8]), wl.Axis.table([16, 4]), wl.Axis.table([16]), wl.Axis.table([2048]))
+    n = 8192
+    rng = np.random.default_rng(17)
+    idx = rng.integers(0, g.size, n).astype(np.uint32)
+    rate = rng.choice([0.05, 0.5, 4.0], n)
+    tr = wl.request_trace(n=70, seed=17)
+    ctx = bridge.gpu_context(g)
+
+    def run(pick):
+        return _run(torch_cuda, ctx, g, np.ascontiguousarray(idx[pick]), np.ascontiguousarray(rate[pick]), tr, scheduler=sched)
+    whole = run(np.arange(n))
+    assert (whole["status"] == 0).any()
+    for got, at in ((run(np.arange(n)), np.arange(n)), (run(np.arange(n)[::-1]), np.arange(n)[::-1])):
+        for k in whole:
+            np.testing.assert_array_equal(got[k], whole[k][at], err_msg=k)
+    for c in np.linspace(0, n - 1, 40).astype(np.int64):
+        alone = run(np.array([c]))
+        for k in whole:
+            np.testing.assert_array_equal(alone[k], whole[k][c:c + 1], err_msg=k)
