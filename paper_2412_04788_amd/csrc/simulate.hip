@@ -345,8 +345,9 @@ struct TraceSums {
 // make the whole wave wait for every lane's bursts in turn: 7000 loop turns per 1024 requests).
 // CLOSED_RUNS: the run is advanced in closed form (GUIDE_SIM_CLOSED_FORM_RUNS); otherwise the clock walks through it.  A
 // step's time is linear in the context while attention is bound by reading the cache at any context (nearly every
-// lane), so the walk takes strides of 64 and 8 steps, whose times are in arithmetic progression, as long
-// as the last step of the stride starts before the arrival that would end the run, and single steps after that.
+// lane), and in two pieces where it turns to arithmetic at some context, so the walk takes strides of 64 and 8 steps,
+// whose times are in arithmetic progression, as long as the last step of the stride starts before the arrival that
+// would end the run and lies on the same piece, and single steps after that.
 // Which of the two ways a lane goes depends on its own configuration alone, never on its neighbours in the wave (which
 // differ from call to call): the results of a configuration are the same bits in every list and every call.
 // (The stride's sum has one rounding where 64 additions to a clock of hundreds of seconds have 64: against 80-bit
@@ -686,11 +687,32 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
                     run += go ? 1u : 0u;
                 }
             } else {
-                double ctx = s_ctx;
-                while (run < total && !(arr_stop <= now)) {
-                    now += step_time(ctx);
-                    ctx += T;
-                    ++run;
+                // Attention may turn from read bound to bound by arithmetic at some context, and stays so (its slope is
+                // the greater one): strides whose first and last step lie on the same side, as above; those that
+                // do not are left to shorter ones and to single steps, after which the next round goes on.
+                auto stride = [&](auto steps) {
+                    constexpr double kS = decltype(steps)::value;
+                    while (run + (uint32_t)kS <= total) {
+                        const double ctx = fma((double)run, T, s_ctx), last = fma(kS - 1.0, T, ctx);
+                        const double t_c = fma(ctx, lt.c_att, base), t_m = fma(ctx, slope, base_m);
+                        const bool arith = t_c >= t_m;
+                        if (!arith && fma(last, lt.c_att, base) > fma(last, slope, base_m)) break;
+                        const double t0 = arith ? t_c : t_m, dt = (arith ? lt.c_att : slope) * T;
+                        const double to_last = now + fma(0.5 * (kS - 1.0) * (kS - 2.0), dt, (kS - 1.0) * t0);
+                        if (arr_stop <= to_last) break;
+                        now += fma(0.5 * kS * (kS - 1.0), dt, kS * t0);
+                        run += (uint32_t)kS;
+                    }
+                };
+                stride(std::integral_constant<int, 64>{});
+                stride(std::integral_constant<int, 8>{});
+                bool go = true;
+#pragma unroll
+                for (int j = 0; j < 7; ++j) {
+                    go = go && run < total && !(arr_stop <= now);
+                    const double n = now + step_time(fma((double)run, T, s_ctx));
+                    now = go ? n : now;
+                    run += go ? 1u : 0u;
                 }
             }
             step += run;

@@ -91,6 +91,45 @@ def test_attention_bound_by_arithmetic(ora, torch_cuda):
     _check(torch_cuda, ora, g, idx, rate, tr, time_model=1)
 
 
+def test_attention_that_turns_inside_a_stride(ora, torch_cuda):
+    """Attention turns from read bound to bound by arithmetic where context = r / (1 - r g), r = peak / bandwidth and g the
+    share of the heads that are KV heads: 99 to 10 000 tokens here, in the middle of runs, of strides and of neither."""
+    hws = [wl.Hardware(r * 2e12, 2e12, 900 * wl.GIB, 4e11) for r in (0.99, 0.998, 0.9995, 0.9999, 7.9, 7.98, 7.995)]
+    g = wl.make_grid([wl.DENSE_70B, wl.DENSE_7B], hws, wl.Axis.table([1, 2, 7, 40]), wl.Axis.table([1]), wl.Axis.table([1]),
+                     wl.Axis.table([1]), wl.Axis.table([16]), wl.Axis.table([16]), wl.Axis.table([512, 8192]))
+    tr = wl.request_trace(n=80, seed=5)
+    idx = np.arange(g.size, dtype=np.uint32)
+    _check(torch_cuda, ora, g, idx, np.where(idx % 3, 0.2, 5.0), tr)
+
+
+def test_compute_bound_lists_cost_about_as_much_as_others(torch_cuda):
+    """Stepped runs whose attention is bound by arithmetic are walked in strides like the others (step by step they took
+    eight times as long as the same list on GPUs with a hundred times the peak)."""
+    torch, times = torch_cuda, []
+    for peak in (1e13, 1e15):
+        g = wl.make_grid([wl.DENSE_70B, wl.DENSE_7B], [wl.Hardware(peak, 8e12, 900 * wl.GIB, 4e11)], wl.Axis.geom2(1, 9),
+                         wl.Axis.table([1]), wl.Axis.table([1]), wl.Axis.table([1, 8]), wl.Axis.table([16, 4]),
+                         wl.Axis.table([16]), wl.Axis.table([2048, 8192]))
+        n = 16384
+        idx = (np.arange(n) % g.size).astype(np.uint32)
+        tr = wl.request_trace(n=200, seed=7)
+        ctx, out = bridge.gpu_context(g), {k: torch.zeros(n, dtype=torch.float64, device="cuda") for k in guide.SIM_COLUMNS}
+        ws = torch.empty(ctx.simulate_workspace_bytes(n, 200), dtype=torch.uint8, device="cuda")
+        call = ctx.prepared("simulate", bridge.gpu_grid(g), torch.from_numpy(idx.view(np.int32)).cuda(),
+                            torch.full((n,), 0.02, dtype=torch.float64, device="cuda"), (tr.arrival_unit, tr.n_in, tr.n_out),
+                            out, ws)
+        t = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            call()
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        times.append(min(t))
+    assert times[0] <= 3.0 * times[1], times
+
+
 def test_arrival_rates_at_the_ends_of_the_range(ora, torch_cuda):
     """Rates that are divided instead of multiplied by a reciprocal: everything at once, and so far apart that a step
     does not move the clock at all (rates in between, such as 1e-9, lose the steps' low digits in the clock's: at
