@@ -34,7 +34,12 @@ struct RequestsLds {
 };
 
 constexpr uint32_t kHeapWidth = 4;     // children per heap node
-constexpr uint32_t kKeyBins = 1024;      // buckets of the expected-step-count ordering
+constexpr uint32_t kKeyBins = 1024;      // buckets of the expected-concurrency ordering
+// Lists are ordered where that saves more than its four launches (17 us): from 16 requests on, and when lanes share a
+// wave at all.  Ordered / as given, in us: 2000 x 8 101 / 85, 5000 x 8 136 / 129, 5000 x 16 193 / 203, 65 536 x 16 571 / 576,
+// 5000 x 32 352 / 396, 20 000 x 128 1200 / 1446 (stepped); 65 536 x 16 541 / 526, 5000 x 32 279 / 289 (closed form); one lane
+// per wave: the same 636 with 128 requests, and 31 / 13 for one configuration.
+constexpr uint32_t kOrderRequests = 16;
 
 // Workspace: heap[position][node] (u64 keys), first[cfg][req] and fin[cfg][req] (time of the first and of the
 // last token), then the launch order: perm[position] = configuration, bucket of each configuration, bucket counters.
@@ -366,7 +371,7 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
                                                              const uint32_t *__restrict__ cfg_idx,
                                                              const double *__restrict__ rate_in, uint32_t n_cfg,
                                                              guide_sim_out out, SimWs ws, TraceSums sums, uint32_t lanes,
-                                                             uint32_t heap_slots) {
+                                                             uint32_t heap_slots, bool ordered) {
     // With 32-bit keys the whole trace is below 2^30 tokens, so blocks, budgets and steps fit 32 bits as well
     using Int = typename std::conditional<sizeof(KeyT) == 4, int32_t, long long>::type;
     constexpr Int kIntMax = sizeof(KeyT) == 4 ? (Int)0x7FFFFFFF : (Int)(1ll << 62);
@@ -389,7 +394,7 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
     const uint32_t pos = wave == kSimBlock / kWave - 1 ? (wave * lanes + lane) * gridDim.x + in_part
                                                        : (wave * gridDim.x + in_part) * lanes + lane;
     const bool in_range = lane < lanes && pos < n_cfg;
-    const uint32_t c = in_range ? ws.perm[pos] : 0u;              // the lane's configuration
+    const uint32_t c = !in_range ? 0u : ordered ? ws.perm[pos] : pos;      // the lane's configuration
 
     uint32_t v[kNumAxes];
     bool alive = false;                                           // this lane has a simulation to run
@@ -434,7 +439,7 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
         const float pool = fminf(1.5f * (float)n_blk / mean_blocks + 4.0f, 2048.0f);
         auto groups = [](uint32_t x) { return (x + kHeapWidth - 1) / kHeapWidth * kHeapWidth; };
         const uint32_t bound = groups((most < (uint32_t)pool ? most : (uint32_t)pool) - 1u);
-        const uint32_t likely = groups((uint32_t)(3.0f * expected_of(alive ? ws.bucket[c] : 0u)) + 16u);
+        const uint32_t likely = ordered ? groups((uint32_t)(3.0f * expected_of(alive ? ws.bucket[c] : 0u)) + 16u) : bound;
         const uint32_t full = alive ? (bound < kHeapWidth ? kHeapWidth : bound) : 0u, want = alive && likely < full ? likely : full;
         const uint32_t wave_want = wave_sum(want), wave_full = wave_sum(full);
         if (lane == 0) s_total[wave] = uint2{wave_want, wave_full};
@@ -879,13 +884,16 @@ hipError_t launch_simulate(const GridDesc &g, const DevTables *tab, const TraceD
     const size_t lds_bytes = staged + heap_bytes;
     const dim3 grid((n_cfg + per_block - 1) / per_block), block(kSimBlock);
     const dim3 ogrid((n_cfg + kOrderBlock - 1) / kOrderBlock), oblock(kOrderBlock);
-    hipLaunchKernelGGL(sim_order_clear_kernel, dim3(1), dim3(kKeyBins), 0, stream, ws);
-    if (additive)
-        hipLaunchKernelGGL(sim_order_count_kernel<true>, ogrid, oblock, 0, stream, g, tab, n_req, cfg_idx, rate, n_cfg, ws, sum_in, sum_out);
-    else
-        hipLaunchKernelGGL(sim_order_count_kernel<false>, ogrid, oblock, 0, stream, g, tab, n_req, cfg_idx, rate, n_cfg, ws, sum_in, sum_out);
-    hipLaunchKernelGGL(sim_order_scan_kernel, dim3(1), dim3(kKeyBins), 0, stream, ws);
-    hipLaunchKernelGGL(sim_order_scatter_kernel, ogrid, oblock, 0, stream, n_cfg, ws);
+    const bool ordered = lanes > 1 && n_req >= kOrderRequests;      // (otherwise every lane's heap fits the LDS)
+    if (ordered) {
+        hipLaunchKernelGGL(sim_order_clear_kernel, dim3(1), dim3(kKeyBins), 0, stream, ws);
+        if (additive)
+            hipLaunchKernelGGL(sim_order_count_kernel<true>, ogrid, oblock, 0, stream, g, tab, n_req, cfg_idx, rate, n_cfg, ws, sum_in, sum_out);
+        else
+            hipLaunchKernelGGL(sim_order_count_kernel<false>, ogrid, oblock, 0, stream, g, tab, n_req, cfg_idx, rate, n_cfg, ws, sum_in, sum_out);
+        hipLaunchKernelGGL(sim_order_scan_kernel, dim3(1), dim3(kKeyBins), 0, stream, ws);
+        hipLaunchKernelGGL(sim_order_scatter_kernel, ogrid, oblock, 0, stream, n_cfg, ws);
+    }
     const int variant = (additive ? 8 : 0) | (prefill_first ? 4 : 0) | (closed_runs ? 2 : 0) | (key32 ? 1 : 0);
 #define GUIDE_SIM(A, P, C, K32)                                                                                    \
     case ((A ? 8 : 0) | (P ? 4 : 0) | (C ? 2 : 0) | (K32 ? 1 : 0)): {                                               \
@@ -893,7 +901,7 @@ hipError_t launch_simulate(const GridDesc &g, const DevTables *tab, const TraceD
         e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);    \
         if (e != hipSuccess) return e;                                                                              \
         hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, g, tab, trace, n_req, cfg_idx, rate, n_cfg, out, ws, \
-                           sums, lanes, heap_slots);                                                                \
+                           sums, lanes, heap_slots, ordered);                                                               \
         break;                                                                                                      \
     }
     switch (variant) {

@@ -31,10 +31,11 @@ def _check(torch, ora, g, idx, rate, tr, pick=None, scheds=(0, 1, CLOSED, 1 | CL
         _compare({k: v[pick] for k, v in got.items()}, exp)
 
 
+@pytest.mark.parametrize("n_req", [1, 15, 16, 23])                # lists are ordered from 16 requests on
 @pytest.mark.parametrize("n_cfg", [1, 63, 1024, 1025, 2048, 2049, 33000])
-def test_lanes_per_wave_by_configuration_count(ora, torch_cuda, n_cfg):
+def test_lanes_per_wave_by_configuration_count(ora, torch_cuda, n_cfg, n_req):
     g = wl.grid_full()
-    tr = wl.request_trace(n=23, seed=n_cfg)
+    tr = wl.request_trace(n=n_req, seed=n_cfg)
     idx, rate = wl.sim_configs(g, n_cfg, seed=n_cfg)
     pick = np.unique(np.linspace(0, n_cfg - 1, min(n_cfg, 96)).astype(np.int64))
     _check(torch_cuda, ora, g, idx, rate, tr, pick)
