@@ -643,9 +643,12 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
                     const double h_T = 0.5 * T;
                     float guess = 1.0f;
                     if (can_admit) {
-                        // time(r) = p r + q r^2 up to rounding; its root in single precision is the first guess
+                        // time(r) = p r + q r^2 up to rounding on the side that the run starts on; its root in single
+                        // precision is the first guess
                         const double rem = arr_stop - now;
-                        const float q = (float)(slope * h_T), p = (float)fma(slope, s_ctx - h_T, base_m), rf = (float)rem;
+                        const bool arith = !lane_linear && fma(s_ctx, lt.c_att, base) >= fma(s_ctx, slope, base_m);
+                        const double sl = arith ? lt.c_att : slope;
+                        const float q = (float)(sl * h_T), p = (float)fma(sl, s_ctx - h_T, arith ? base : base_m), rf = (float)rem;
                         guess = ceilf(2.0f * rf * __builtin_amdgcn_rcpf(p + __builtin_amdgcn_sqrtf(fmaf(p, p, 4.0f * q * rf))));
                     }
                     auto advance = [&](auto &&time_of) {
