@@ -265,13 +265,79 @@ GroupWs group_ws(void *ws, uint32_t G, uint32_t k, uint32_t n_blocks) {
 }
 constexpr uint32_t kGroupChunk = 512 * kUnroll;            // rows of a block's batch
 // Blocks of the grouped pass: two per compute unit, fewer when the partials of more would not fit the workspace
-// (8 + 12 k bytes per group and block: 512 blocks up to k = 3, 236 for k = 8).
+// (8 + 12 k bytes per group and block: 512 blocks up to k = 3, 236 for k = 8; k = 1: the 1024 of blocks_for).
 uint32_t group_blocks(uint64_t n, uint32_t k) {
     const uint64_t fit = 3 * sizeof(uint64_t) * kSelBlocks / (8 + 12 * (uint64_t)k), cap = 2 * (uint64_t)device_cus();
     uint64_t need = (n + kGroupChunk - 1) / kGroupChunk;
     need = need ? need : 1;
     need = need < cap ? need : cap;
     return (uint32_t)(need < fit ? need : fit);
+}
+
+// Counts a row of group g in every lane that is ok.  One lane does it where the rows of a wave are all of one group: 64
+// atomics on one word take 64 turns (1.9 million rows of one group: 15.5 instead of 20 us).  Every lane of the wave must call.
+__device__ inline void count_rows(uint32_t *s_cnt, uint32_t g, bool ok) {
+    const uint64_t oks = __ballot(ok);
+    if (oks == 0) return;
+    const int lead = __ffsll((long long)oks) - 1;
+    const uint32_t g0 = (uint32_t)__builtin_amdgcn_readlane((int)g, lead);
+    if (__ballot(ok && g != g0) == 0) {
+        if ((int)(threadIdx.x % kWave) == lead) atomicAdd(&s_cnt[g0], (uint32_t)__popcll(oks));
+    } else if (ok) {
+        atomicAdd(&s_cnt[g], 1u);
+    }
+}
+
+// k = 1: one pass in which the rows of a group meet in a slot per wave and group (slot_update), whatever their order.  The
+// lists below need a start and a merge inside the block, which one row per group does not pay for: 5000 rows of
+// ten groups 6.0 us and 8 million falling rows of five groups 34 us like this, 9.5 - 12.5 us and 432 us with lists of one.
+template <uint32_t MAXC>
+__global__ __launch_bounds__(kBlock) void topk_group_first_kernel(const double *__restrict__ obj, RowFilter f,
+                                                                  const uint32_t *__restrict__ group, uint32_t G, uint32_t n,
+                                                                  GroupWs w) {
+    __shared__ uint64_t s_key[kWaves][GUIDE_MAX_GROUPS], s_idx[kWaves][GUIDE_MAX_GROUPS];
+    __shared__ uint32_t s_cnt[kWaves][GUIDE_MAX_GROUPS];
+    const int wave = threadIdx.x / kWave;
+    for (uint32_t i = threadIdx.x; i < kWaves * GUIDE_MAX_GROUPS; i += kBlock) {
+        (&s_key[0][0])[i] = kNone;
+        (&s_idx[0][0])[i] = kNone;
+        (&s_cnt[0][0])[i] = 0;
+    }
+    __syncthreads();
+    constexpr uint32_t U = 4;                                   // rows per thread in flight
+    const uint64_t stride = (uint64_t)gridDim.x * kBlock;
+    for (uint64_t base = (uint64_t)blockIdx.x * kBlock; base < n; base += U * stride) {       // block-uniform trip count
+        RawRow<MAXC> raw[U];
+        uint32_t grp[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint64_t at = base + u * stride + threadIdx.x;
+            const uint32_t i = at < n ? (uint32_t)at : n;       // n: not there
+            raw[u] = load_raw<false, MAXC>(obj, nullptr, f, i, n);
+            grp[u] = group[i < n ? i : 0u];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            if (base + u * stride >= n) break;                  // (uniform)
+            const Row r = row_of<false, MAXC>(raw[u], f);
+            const bool ok = r.pass && grp[u] < G;
+            count_rows(s_cnt[wave], grp[u], ok);
+            slot_update(s_key[wave], s_idx[wave], grp[u], ok, Pair{key_of(r.x), base + u * stride + threadIdx.x});
+        }
+    }
+    __syncthreads();
+    for (uint32_t g = threadIdx.x; g < G; g += kBlock) {
+        Pair b = {s_key[0][g], s_idx[0][g]};
+        uint64_t c = s_cnt[0][g];
+        for (int wv = 1; wv < kWaves; ++wv) {
+            b = pair_min(b, Pair{s_key[wv][g], s_idx[wv][g]});
+            c += s_cnt[wv][g];
+        }
+        const size_t to = (size_t)g * gridDim.x + blockIdx.x;
+        w.key[to] = b.key;
+        w.row[to] = (uint32_t)b.idx;
+        w.cnt[to] = c;
+    }
 }
 
 constexpr uint32_t kGroupThreads = 512, kGroupWaves = kGroupThreads / kWave;
@@ -1518,7 +1584,7 @@ hipError_t launch_select_topk(const guide_select_spec &spec, uint64_t n, const g
         launch_top1_merge(partial_width(spec.k), ws, blocks_for(n), spec.k, out, stream);
         return hipGetLastError();
     }
-    const uint32_t G = spec.n_groups, k = spec.k, nb = group_blocks(n, k);
+    const uint32_t G = spec.n_groups, k = spec.k, nb = k == 1 ? blocks_for(n) : group_blocks(n, k);
     const GroupWs w = group_ws(ws, G, k, nb);
     const size_t per_group = (size_t)kGroupWaves * k;
     const size_t lds = (sizeof(uint64_t) * (1 + per_group) + sizeof(uint32_t) * (1 + per_group)) * G + sizeof(uint64_t) * 8 * G;
@@ -1526,8 +1592,12 @@ hipError_t launch_select_topk(const guide_select_spec &spec, uint64_t n, const g
                           sizeof(uint64_t) * 8 * GUIDE_MAX_GROUPS <= 65536,
                   "the lists of a block fit the default LDS limit");
     with_max_constraints(spec.n_constraints, [&](auto maxc) {
-        hipLaunchKernelGGL((topk_group_kernel<decltype(maxc)::value>), dim3(nb), dim3(kGroupThreads), lds, stream, spec.objective,
-                           make_filter(spec), spec.group, G, k, (uint32_t)n, w);
+        if (k == 1)
+            hipLaunchKernelGGL((topk_group_first_kernel<decltype(maxc)::value>), dim3(nb), dim3(kBlock), 0, stream, spec.objective,
+                               make_filter(spec), spec.group, G, (uint32_t)n, w);
+        else
+            hipLaunchKernelGGL((topk_group_kernel<decltype(maxc)::value>), dim3(nb), dim3(kGroupThreads), lds, stream,
+                               spec.objective, make_filter(spec), spec.group, G, k, (uint32_t)n, w);
     });
     const dim3 groups(G), block(kBlock);
     switch (partial_width(k)) {

@@ -32,7 +32,7 @@ def _check(ora, setup, obj, grp, G, k, feasible=None, cons=()):
 
 
 @pytest.mark.parametrize("n", [1, 7, 4095, 4096, 4097, 40_000, 600_001])
-@pytest.mark.parametrize("G,k", [(1, 1), (3, 2), (10, 3), (64, 4), (64, 8), (5, 7)])
+@pytest.mark.parametrize("G,k", [(1, 1), (64, 1), (3, 2), (10, 3), (64, 4), (64, 8), (5, 7)])
 def test_batch_edges_and_list_widths(ora, setup, n, G, k):
     rng = np.random.default_rng(n * 100 + G + k)
     obj = np.repeat(np.round(rng.standard_normal(n // 4 + 1), 3), 4)[:n]            # runs of equal values, many ties
@@ -58,3 +58,32 @@ def test_groups_without_passing_rows(ora, setup):
     _check(ora, setup, np.arange(n) * 1.0, np.full(n, 2), 4, 3)
     _check(ora, setup, np.arange(n) * 1.0, np.full(n, 2), 4, 3, np.zeros(n, dtype=np.uint8))
     _check(ora, setup, np.full(n, np.nan), np.zeros(n, dtype=np.int64), 2, 2)
+
+
+@pytest.mark.parametrize("k", [1])
+@pytest.mark.parametrize("order", ["falling", "equal"])
+def test_no_row_order_is_much_slower_than_another(setup, order, k):
+    """Columns that fall with the row number and columns of equal values cost about what random ones do (a list that every
+    row enters one after the other made them up to eighteen times as slow)."""
+    torch, ctx = setup
+    n, G = 4_000_000, 5
+    grp = torch.randint(0, G, (n,), dtype=torch.int32, device="cuda")
+    cols = {"random": torch.rand(n, dtype=torch.float64, device="cuda"), "equal": torch.zeros(n, dtype=torch.float64, device="cuda"),
+            "falling": -torch.arange(n, dtype=torch.float64, device="cuda")}
+    idx = torch.zeros(G * k, dtype=torch.int64, device="cuda")
+    val, cnt = torch.zeros(G * k, dtype=torch.float64, device="cuda"), torch.zeros(G, dtype=torch.int64, device="cuda")
+    ws = torch.empty(ctx.select_workspace_bytes(guide.SELECT_TOPK, n, G), dtype=torch.uint8, device="cuda")
+
+    def best(col):
+        call, t = ctx.prepared("select", guide.SELECT_TOPK, n, cols[col], idx, val, cnt, ws, group=grp, n_groups=G, k=k), []
+        for _ in range(10):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                call()
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        return min(t)
+    random, other = best("random"), best(order)
+    assert other <= 3.0 * random, (other, random)
