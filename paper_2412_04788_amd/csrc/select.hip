@@ -263,7 +263,7 @@ GroupWs group_ws(void *ws, uint32_t G, uint32_t k, uint32_t n_blocks) {
     w.row = (uint32_t *)(w.key + (size_t)G * n_blocks * k);
     return w;
 }
-constexpr uint32_t kGroupChunk = 512 * kUnroll;            // rows of a block's batch
+constexpr uint32_t kGroupChunk = 4096;            // rows of a block's batch
 // Blocks of the grouped pass: two per compute unit, fewer when the partials of more would not fit the workspace
 // (8 + 12 k bytes per group and block: 512 blocks up to k = 3, 236 for k = 8; k = 1: the 1024 of blocks_for).
 uint32_t group_blocks(uint64_t n, uint32_t k) {
@@ -340,35 +340,113 @@ __global__ __launch_bounds__(kBlock) void topk_group_first_kernel(const double *
     }
 }
 
-constexpr uint32_t kGroupThreads = 512, kGroupWaves = kGroupThreads / kWave;
-// One pass over the rows for any number of groups and k.  Every wave keeps a sorted list of k (key, row) pairs per
-// group in LDS, and the block a bound per group with at least k of its rows at or below it, which the first batch
-// starts from the minima of eight parts of it.  Nearly all rows lie above the bound of their group and cost a
-// compare; the others are inserted one after the other, the list's places side by side in lanes 0 .. k - 1.
-// Bound by latency at this size (one batch per block): 1.9 million rows, ten groups, k = 3 and one constraint (40 MB)
-// take 17.3 us + 5.2 us for the merge; k rounds over all rows took 15.7 + 4.1 us a round.  Blocks of 512 threads:
-// 23.0 us with 256 (twice the batches); lists that start from nothing: 35 us (every row is inserted at first).
+constexpr uint32_t kGroupThreads = 1024;
+constexpr uint32_t kGroupParts = 16;                       // parts of a batch whose least rows tighten the bounds; >= k
+constexpr uint32_t kGroupSlots = 32;                       // rows of one group that a block holds at a time; > k
+static_assert(kGroupParts >= GUIDE_MAX_TOPK && kGroupSlots >= 2 * GUIDE_MAX_TOPK, "a list of k rows must fit");
+struct GroupLds {           // 596 bytes per group
+    uint64_t *bound_key, *part_key, *slot_key;             // [G], [G][kGroupParts], [G][kGroupSlots]
+    uint32_t *bound_row, *part_row, *slot_row, *n, *cnt;   // the same, rows in the slots, passing rows
+};
+constexpr size_t kGroupLdsBytes = sizeof(uint64_t) * (1 + kGroupParts + kGroupSlots) + sizeof(uint32_t) * (3 + kGroupParts + kGroupSlots);
+static_assert(kGroupLdsBytes * GUIDE_MAX_GROUPS <= 65536, "the tables of a block fit the default LDS limit");
+
+// Keeps the k least rows of every group's slots, in order, and lowers the bounds to the k-th of them.  To be called by the
+// whole block; ends with a barrier.
+__device__ inline void group_compact(const GroupLds &L, uint32_t G, uint32_t k) {
+    constexpr uint32_t kPer = GUIDE_MAX_GROUPS * kGroupSlots / kGroupThreads;
+    uint64_t key[kPer];
+    uint32_t row[kPer], rank[kPer];
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+        const uint32_t i = q * kGroupThreads + threadIdx.x, g = i / kGroupSlots, at = i % kGroupSlots;
+        rank[q] = kGroupSlots;                              // not there
+        if (g < G) {
+            const uint32_t n = L.n[g] < kGroupSlots ? L.n[g] : kGroupSlots;
+            if (at < n) {
+                key[q] = L.slot_key[i];
+                row[q] = L.slot_row[i];
+                rank[q] = 0;
+#pragma unroll 2
+                for (uint32_t j = 0; j < n; ++j) {
+                    const uint64_t o = L.slot_key[g * kGroupSlots + j];
+                    rank[q] += (o < key[q] || (o == key[q] && L.slot_row[g * kGroupSlots + j] < row[q])) ? 1u : 0u;
+                }
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+        const uint32_t i = q * kGroupThreads + threadIdx.x, g = i / kGroupSlots;
+        if (rank[q] < k) {
+            L.slot_key[g * kGroupSlots + rank[q]] = key[q];
+            L.slot_row[g * kGroupSlots + rank[q]] = row[q];
+            if (rank[q] == k - 1 && (key[q] < L.bound_key[g] || (key[q] == L.bound_key[g] && row[q] < L.bound_row[g]))) {
+                L.bound_key[g] = key[q];
+                L.bound_row[g] = row[q];
+            }
+        }
+        if (g < G && i % kGroupSlots == 0) L.n[g] = L.n[g] < k ? L.n[g] : k;
+    }
+    __syncthreads();
+}
+
+// One pass over the rows for any number of groups and k >= 2.  The block keeps, per group, up to kGroupSlots rows in LDS and
+// a bound (key, row) with at least k of its rows at or below it.  Rows above the bound of their group, nearly all,
+// cost a compare; the others are appended, all lanes side by side, and when a group's slots are full the k least of
+// them stay.  A batch in which many rows are below their bounds (the first one; columns that fall with the row number;
+// long runs of equal values) tightens the bounds first: the least row of each of sixteen parts of the batch per group,
+// the k-th of which has k rows at or below it.  So no order of the rows makes a block append much more than k
+// rows per group and batch.
+// Bound by latency at this size (one batch per block): 1.9 million rows, ten groups, k = 3 and one constraint (40 MB) take
+// 21.5 us with the merge; k rounds over all rows 56 us.  8 million rows of 64 groups, k = 8: 81 us in random order, 108 us
+// falling, 47 us all equal (k rounds: 336 us); one list per wave and group, whose rows enter one after the other: 263,
+// 1210 and 200 us.  Blocks of 512 threads with eight rows each: 57 instead of 47 us (8 million rows, 64 groups, k = 3);
+// the next batch under way meanwhile: 74 us (four rows, one block per compute unit then).
 template <uint32_t MAXC>
-__global__ __launch_bounds__(kGroupThreads) void topk_group_kernel(const double *__restrict__ obj, RowFilter f,
+__global__ __launch_bounds__(kGroupThreads, 8) void topk_group_kernel(const double *__restrict__ obj, RowFilter f,
                                                             const uint32_t *__restrict__ group, uint32_t G, uint32_t k,
                                                             uint32_t n, GroupWs w) {
     extern __shared__ __align__(16) unsigned char s_group[];
-    uint64_t *s_bound = (uint64_t *)s_group;                    // [G]
-    uint64_t *s_part = s_bound + G;                             // [G][8]
-    uint64_t *s_key = s_part + 8 * G;                           // [wave][G][k]
-    uint32_t *s_row = (uint32_t *)(s_key + (size_t)kGroupWaves * G * k);     // the same
-    uint32_t *s_cnt = s_row + (size_t)kGroupWaves * G * k;           // [G]
-    const uint32_t wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, per_wave = G * k;
-    for (uint32_t i = threadIdx.x; i < G * 8; i += kGroupThreads) s_part[i] = kNone;
-    for (uint32_t i = threadIdx.x; i < G; i += kGroupThreads) s_cnt[i] = 0;
-    for (uint32_t i = threadIdx.x; i < kGroupWaves * per_wave; i += kGroupThreads) {
-        s_key[i] = kNone;
-        s_row[i] = ~0u;
+    __shared__ uint32_t s_any[3];
+    uint32_t turn = 0;
+    // true in every thread when any brings true; a barrier.  (Three flags in turn: the one that is cleared after a barrier
+    // was read before it by all, and is written again after the next.)
+    auto block_any = [&](bool mine) {
+        if (mine) s_any[turn] = 1;
+        __syncthreads();
+        const bool any = s_any[turn] != 0;
+        const uint32_t last = turn == 0 ? 2u : turn - 1;
+        if (threadIdx.x == 0) s_any[last] = 0;
+        turn = turn == 2 ? 0u : turn + 1;
+        return any;
+    };
+    if (threadIdx.x < 3) s_any[threadIdx.x] = 0;
+    GroupLds L;
+    L.bound_key = (uint64_t *)s_group;
+    L.part_key = L.bound_key + G;
+    L.slot_key = L.part_key + G * kGroupParts;
+    L.bound_row = (uint32_t *)(L.slot_key + G * kGroupSlots);
+    L.part_row = L.bound_row + G;
+    L.slot_row = L.part_row + G * kGroupParts;
+    L.n = L.slot_row + G * kGroupSlots;
+    L.cnt = L.n + G;
+    for (uint32_t i = threadIdx.x; i < G; i += kGroupThreads) {
+        L.bound_key[i] = kNone;
+        L.bound_row[i] = ~0u;
+        L.n[i] = 0;
+        L.cnt[i] = 0;
     }
+    auto clear_parts = [&]() {
+        for (uint32_t i = threadIdx.x; i < G * kGroupParts; i += kGroupThreads) {
+            L.part_key[i] = kNone;
+            L.part_row[i] = ~0u;
+        }
+    };
+    clear_parts();
     __syncthreads();
-    constexpr uint32_t U = kUnroll;
-    uint64_t *my_key = s_key + wave * per_wave;
-    uint32_t *my_row = s_row + wave * per_wave;
+    constexpr uint32_t U = 4;
     ChunkWalk<U * kGroupThreads / kBlock> cw(kGroupChunk, n, gridDim.x);     // batches of kGroupThreads * U rows
     RawRow<MAXC> raw[U];
     uint32_t raw_g[U];
@@ -380,109 +458,94 @@ __global__ __launch_bounds__(kGroupThreads) void topk_group_kernel(const double 
             raw_g[u] = group[i < (uint32_t)cw.end ? i : 0];
         }
     };
-    bool first = true;
-    if (cw.live()) request();
+    bool first = true;                                          // no bounds yet
     while (cw.live()) {                                         // block-uniform trip count
+        request();
         const uint32_t base = (uint32_t)cw.base + threadIdx.x;
-        Row r[U];
-        uint32_t grp[U];
+        uint64_t key[U];
+        uint32_t grp[U], in = 0;                                // in: bit u = row u may still be among the k least
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
-            r[u] = row_of<false, MAXC>(raw[u], f);
-            grp[u] = raw_g[u];
+            const Row r = row_of<false, MAXC>(raw[u], f);
+            const bool ok = r.pass && raw_g[u] < G;
+            grp[u] = ok ? raw_g[u] : 0u;
+            key[u] = key_of(r.x);
+            in |= ok ? 1u << u : 0u;
+            count_rows(L.cnt, grp[u], ok);
         }
         cw.next();
-        if (cw.live()) request();                               // the next batch is under way while this one is worked on
-        if (first) {
-            // The first batch gives the bounds a start: the least key of each of eight parts of the batch, per group;
-            // the k-th least of them has k rows at or below it.
+        auto drop = [&]() {                                     // rows above their bounds; how many of the wave's are left
+            uint32_t left = 0;
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint64_t b = L.bound_key[grp[u]];
+                const bool keep = ((in >> u) & 1u) && (key[u] < b || (key[u] == b && base + u * kGroupThreads <= L.bound_row[grp[u]]));
+                in = keep ? in : in & ~(1u << u);
+                left += (uint32_t)__popcll(__ballot(keep));
+            }
+            return left;
+        };
+        constexpr uint32_t kMany = kWave / 4;
+        if (first || block_any(drop() > kMany)) {
+            first = false;
+            // (clear_parts() has run since the last time, and a barrier)
+            auto part_of = [&](uint32_t u) {                    // scattered, so that no period of the rows lines up with it
+                return grp[u] * kGroupParts + (((base + u * kGroupThreads) * 2654435761u) >> 28);
+            };
+            static_assert(kGroupParts == 16, "four bits of the product");
 #pragma unroll
             for (uint32_t u = 0; u < U; ++u)
-                if (r[u].pass && grp[u] < G)
-                    atomicMin((unsigned long long *)&s_part[grp[u] * 8 + threadIdx.x % 8], (unsigned long long)key_of(r[u].x));
+                if ((in >> u) & 1u) atomicMin((unsigned long long *)&L.part_key[part_of(u)], (unsigned long long)key[u]);
             __syncthreads();
-            for (uint32_t g = threadIdx.x; g < G; g += kGroupThreads) {
-                uint64_t p[8], bound = kNone;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) p[j] = s_part[g * 8 + j];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    uint32_t rank = 0;
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) rank += (p[q] < p[j] || (p[q] == p[j] && q < j)) ? 1u : 0u;
-                    bound = rank == k - 1 ? p[j] : bound;
+            for (uint32_t u = 0; u < U; ++u)
+                if (((in >> u) & 1u) && L.part_key[part_of(u)] == key[u]) atomicMin(&L.part_row[part_of(u)], base + u * kGroupThreads);
+            __syncthreads();
+            for (uint32_t i = threadIdx.x; i < G * kGroupParts; i += kGroupThreads) {
+                const uint32_t g = i / kGroupParts, row = L.part_row[i];
+                const uint64_t pk = L.part_key[i];
+                uint32_t rank = 0;
+#pragma unroll 4
+                for (uint32_t j = 0; j < kGroupParts; ++j) {
+                    const uint64_t o = L.part_key[g * kGroupParts + j];
+                    rank += (o < pk || (o == pk && L.part_row[g * kGroupParts + j] < row)) ? 1u : 0u;
                 }
-                s_bound[g] = bound;
+                // (rows in the parts are at or below the old bound, so this one is not above it)
+                if (rank == k - 1 && pk != kNone) {
+                    L.bound_key[g] = pk;
+                    L.bound_row[g] = row;
+                }
             }
             __syncthreads();
-            first = false;
+            clear_parts();
+            drop();
         }
+        for (;;) {
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) {
-            const bool ok = r[u].pass && grp[u] < G;
-            const uint32_t g = ok ? grp[u] : 0u;
-            const uint64_t key = ok ? key_of(r[u].x) : kNone;
-            if (ok) atomicAdd(&s_cnt[g], 1u);
-            const uint64_t bound = __hip_atomic_load(&s_bound[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            // (of rows that tie with the bound, those that the wave's own list has no place for are left out here)
-            bool take = ok && key <= bound;
-            if (take) {
-                const uint64_t l_key = my_key[g * k + k - 1];
-                take = key < l_key || (key == l_key && base + u * kGroupThreads < my_row[g * k + k - 1]);
-            }
-            for (uint64_t todo = __ballot(take); todo; todo &= todo - 1) {
-                const int src = __ffsll((long long)todo) - 1;
-                const uint32_t c_g = (uint32_t)__builtin_amdgcn_readlane((int)g, src);
-                const uint64_t c_key = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(key >> 32), src) << 32) |
-                                       (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, src);
-                const uint32_t c_row = (uint32_t)__builtin_amdgcn_readlane((int)(base + u * kGroupThreads), src);
-                const uint32_t at = c_g * k + (lane < k ? lane : 0u);
-                const uint64_t cur = my_key[at];
-                const uint32_t cur_row = my_row[at];
-                const bool before = lane < k && (cur < c_key || (cur == c_key && cur_row < c_row));
-                const uint32_t pos = (uint32_t)__popcll(__ballot(before));      // a sorted list: the entries before come first
-                const uint64_t up = dpp_keep<0x111>(cur);                       // the left neighbour's (k <= 8 lanes of a row)
-                const uint32_t up_row = dpp_u32<0x111>(cur_row, cur_row);
-                if (lane >= pos && lane < k) {
-                    const uint64_t now = lane == pos ? c_key : up;
-                    my_key[at] = now;
-                    my_row[at] = lane == pos ? c_row : up_row;
-                    if (lane == k - 1)
-                        __hip_atomic_fetch_min(&s_bound[c_g], now, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            for (uint32_t u = 0; u < U; ++u) {
+                if (!((in >> u) & 1u)) continue;
+                const uint32_t at = atomicAdd(&L.n[grp[u]], 1u);
+                if (at < kGroupSlots) {
+                    L.slot_key[grp[u] * kGroupSlots + at] = key[u];
+                    L.slot_row[grp[u] * kGroupSlots + at] = base + u * kGroupThreads;
+                    in &= ~(1u << u);
                 }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             }
+            // full slots: at least kGroupSlots - k of the rows left are done with in the next turn
+            if (!block_any(in != 0)) break;
+            group_compact(L, G, k);
+            drop();
         }
     }
-    __syncthreads();
-    // a thread per group merges the waves' lists
-    for (uint32_t g = threadIdx.x; g < G; g += kGroupThreads) {
-        uint32_t head[kGroupWaves];
-#pragma unroll
-        for (int wv = 0; wv < kGroupWaves; ++wv) head[wv] = 0;
+    group_compact(L, G, k);
+    for (uint32_t i = threadIdx.x; i < G * k; i += kGroupThreads) {
+        const uint32_t g = i / k, j = i - g * k;
         const size_t to = ((size_t)g * gridDim.x + blockIdx.x) * k;
-        for (uint32_t j = 0; j < k; ++j) {
-            uint64_t best = kNone;
-            uint32_t best_row = ~0u;
-            int from = -1;
-#pragma unroll
-            for (int wv = 0; wv < kGroupWaves; ++wv) {
-                const uint32_t at = wv * per_wave + g * k + head[wv];   // (no list gives more than j < k entries)
-                const uint64_t c = s_key[at];
-                const uint32_t c_row = s_row[at];
-                if (c < best || (c == best && c_row < best_row)) {
-                    best = c;
-                    best_row = c_row;
-                    from = wv;
-                }
-            }
-#pragma unroll
-            for (int wv = 0; wv < kGroupWaves; ++wv) head[wv] += from == wv ? 1u : 0u;
-            w.key[to + j] = best;
-            w.row[to + j] = best_row;
-        }
-        w.cnt[(size_t)g * gridDim.x + blockIdx.x] = s_cnt[g];
+        const bool there = j < L.n[g];
+        w.key[to + j] = there ? L.slot_key[g * kGroupSlots + j] : kNone;
+        w.row[to + j] = there ? L.slot_row[g * kGroupSlots + j] : ~0u;
     }
+    for (uint32_t g = threadIdx.x; g < G; g += kGroupThreads) w.cnt[(size_t)g * gridDim.x + blockIdx.x] = L.cnt[g];
 }
 
 // One block per group: the k least of the block partials, and the count.  K >= k: places of the threads' lists.
@@ -1586,11 +1649,7 @@ hipError_t launch_select_topk(const guide_select_spec &spec, uint64_t n, const g
     }
     const uint32_t G = spec.n_groups, k = spec.k, nb = k == 1 ? blocks_for(n) : group_blocks(n, k);
     const GroupWs w = group_ws(ws, G, k, nb);
-    const size_t per_group = (size_t)kGroupWaves * k;
-    const size_t lds = (sizeof(uint64_t) * (1 + per_group) + sizeof(uint32_t) * (1 + per_group)) * G + sizeof(uint64_t) * 8 * G;
-    static_assert((sizeof(uint64_t) + sizeof(uint32_t)) * GUIDE_MAX_GROUPS * (1 + kGroupWaves * GUIDE_MAX_TOPK) +
-                          sizeof(uint64_t) * 8 * GUIDE_MAX_GROUPS <= 65536,
-                  "the lists of a block fit the default LDS limit");
+    const size_t lds = kGroupLdsBytes * G;
     with_max_constraints(spec.n_constraints, [&](auto maxc) {
         if (k == 1)
             hipLaunchKernelGGL((topk_group_first_kernel<decltype(maxc)::value>), dim3(nb), dim3(kBlock), 0, stream, spec.objective,

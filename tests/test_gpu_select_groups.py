@@ -60,7 +60,7 @@ def test_groups_without_passing_rows(ora, setup):
     _check(ora, setup, np.full(n, np.nan), np.zeros(n, dtype=np.int64), 2, 2)
 
 
-@pytest.mark.parametrize("k", [1])
+@pytest.mark.parametrize("k", [1, 3, 8])
 @pytest.mark.parametrize("order", ["falling", "equal"])
 def test_no_row_order_is_much_slower_than_another(setup, order, k):
     """Columns that fall with the row number and columns of equal values cost about what random ones do (a list that every
