@@ -855,8 +855,9 @@ __global__ __launch_bounds__(kBlock) void eval_wide_kernel(GridDesc g, uint32_t 
                 } else {
                     const double t_dec = decode_time_fast<ADDITIVE>(tc, tl.b, tl.s_in, tl.s_out - 1);
                     s_dec[t] = t_dec;
-                    s_tok[t] = tl.s_out > 1 ? (double)tl.b * (double)(tl.s_out - 1) * fast_recip(t_dec) : 0.0;
-                    s_cost[t] = (double)tl.p * (1.0e6 / 3600.0) * fast_recip((double)tl.b * (double)tl.s_out);
+                    // (divisions: their operands are exact, t_dec apart, so both columns have two roundings at most)
+                    s_tok[t] = tl.s_out > 1 ? (double)tl.b * (double)(tl.s_out - 1) / t_dec : 0.0;
+                    s_cost[t] = (double)tl.p * 1.0e6 / (3600.0 * ((double)tl.b * (double)tl.s_out));
                 }
             } else {
                 const double c_avail = hw.cap - cf.w_gpu;

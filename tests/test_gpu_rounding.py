@@ -1,0 +1,97 @@
+"""Rounding errors of the closed-form kernels against the performance model in 80 bits (numpy's long double), which is
+three decimal digits beyond what they compute in.  Bounds: an output is a sum of positive terms, each a product of a few
+rounded factors, so its relative error is a few units of 2^-53 = 1.11e-16 at most and about one in the root mean square."""
+import numpy as np
+import pytest
+
+from paper_2412_04788_amd import guide, workloads as wl
+from tests import bridge
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(np.finfo(np.longdouble).nmant < 63, reason="long double has no more bits than double here")]
+LD = np.longdouble
+ULP = 2.0 ** -53
+
+
+def _rows(g, idx):
+    """The axis values of grid rows as long doubles, with the model and hardware records spread out."""
+    v, rem = {}, np.asarray(idx, dtype=np.int64)
+    for name, axis in list(zip(("model", "hw", "b", "s", "o", "p", "bits", "blk", "mbt"), g.axes))[::-1]:
+        a = axis.array().astype(np.int64)
+        v[name] = a[rem % len(a)]
+        rem = rem // len(a)
+    m, h = wl.models_array(g.models).astype(LD)[v.pop("model")], wl.hw_array(g.hws).astype(LD)[v.pop("hw")]
+    v = {k: x.astype(LD) for k, x in v.items()}
+    v.update(zip(("L", "d", "n_h", "n_kv", "ff", "V", "E", "k"), m.T))
+    v.update(zip(("peak", "bw", "cap", "link", "lat"), h.T))
+    return v
+
+
+def _times(r, additive, e_c=1.0, e_b=1.0):
+    """(prefill, decode) times; the segments of long prompts and the decode steps are added up one by one."""
+    peak, bw, d, p, w = r["peak"] * LD(e_c), r["bw"] * LD(e_b), r["d"], r["p"], r["bits"] / 8
+    op = (lambda a, b: a + b) if additive else np.maximum
+    dh = np.floor(d / r["n_h"])
+    dq, dkv, moe = r["n_h"] * dh, r["n_kv"] * dh, (r["E"] > 1).astype(LD)
+    gkv = np.ceil(r["n_kv"] / p) * dh
+    k, E, ff = r["k"], r["E"], r["ff"]
+    ops = ((2 * d * (dq + 2 * dkv) / p, w * d * (dq + 2 * dkv) / p, 2 * d + 2 * (dq + 2 * dkv) / p, 0),
+           (2 * dq * d / p, w * dq * d / p, 2 * dq / p + 2 * d, 0), (4 * k * d * ff / p, w * 2 * d * ff / p, 2 * d + 4 * k * ff / p, 1),
+           (2 * k * ff * d / p, w * ff * d / p, 2 * k * ff / p + 2 * d, 1),
+           (2 * d * E * moe, w * d * E * moe, (2 * d + 2 * E) * moe, 0))
+
+    def one_pass(T, Q, K, n_lm, base=True):
+        t = op(4 * dq / p * Q / peak, (4 * dq / p * T + 4 * gkv * K) / bw)
+        for f, wt, a, experts in ops if base else ():
+            t = t + op(f * T / peak, (wt * (np.minimum(E, k * T) if experts else 1) + a * T) / bw)
+        if base:
+            t = t + 8 * d * T / bw + 2 * (2 * (p - 1) / p * 2 * d * T / r["link"] + 2 * (p - 1) * r["lat"])
+        lm = op(2 * d * r["V"] / p * n_lm / peak, (w * d * r["V"] / p + (2 * d + 2 * r["V"] / p) * n_lm) / bw)
+        return r["L"] * t + (n_lm > 0) * lm
+    b, s, mbt = r["b"], r["s"], r["mbt"]
+    per = np.clip(np.minimum(np.floor(mbt / s), b), 1, None)
+    full = np.floor(b / per)
+    rest, some = b - full * per, np.maximum(b - full * per, 1)
+    short = full * one_pass(per * s, per * s * s, per * s, per) + (rest > 0) * one_pass(some * s, some * s * s, some * s, some)
+    n_seg, long = np.ceil(s / mbt), 0 * s
+    for j in range(int(n_seg.max())):
+        c = np.clip(np.minimum(s - j * mbt, mbt), 0, None)
+        long = long + (c > 0) * one_pass(c, c * (j * mbt + c), j * mbt + c, (n_seg == j + 1).astype(LD))
+    n, att = r["o"] - 1, 0 * s
+    for j in range(1, int(n.max()) + 1):
+        att = att + (j <= n) * one_pass(b, b * (s + j), b * (s + j), 0 * b, base=False)
+    step = one_pass(b, 0 * b, 0 * b, b) - r["L"] * op(0 * b, 4 * dq / p * b / bw)       # without attention
+    return np.where(s <= mbt, short, b * long), n * step + att
+
+
+def _rms(got, exact):
+    e = (np.asarray(got).astype(LD) - exact) / exact
+    return float(np.sqrt((e * e).mean())) / ULP
+
+
+def _wide_grid():
+    rng = np.random.default_rng(5)
+    v = lambda lo, hi, n: sorted(set(np.rint(np.exp(rng.uniform(np.log(lo), np.log(hi), n))).astype(int).tolist()))   # noqa: E731
+    return wl.make_grid(wl.MODELS_FULL[:3], wl.hw_profiles(5, 4), wl.Axis.table(v(1, 1024, 5)), wl.Axis.table(v(64, 32768, 5)),
+                        wl.Axis.table(v(64, 2000, 4)), wl.Axis.table([1, 3, 7]), wl.Axis.table([16, 4]),
+                        wl.Axis.table(v(8, 256, 5)), wl.Axis.table(v(512, 16384, 6)))
+
+
+@pytest.mark.parametrize("tm", [0, 1])
+def test_expanded_grids(tm):
+    """Times, throughput and cost of a grid with wide fast axes."""
+    import torch
+    g = _wide_grid()
+    out = bridge.metric_buffers(g.size)
+    bridge.gpu_context(g).eval_grid(bridge.gpu_grid(g), 0, g.size, out=out, time_model=tm)
+    torch.cuda.synchronize()
+    idx = np.unique(np.linspace(0, g.size - 1, 6000).astype(np.int64))
+    r = _rows(g, idx)
+    pre, dec = _times(r, tm == 1)
+    exact = dict(t_prefill=pre, t_decode=dec, t_batch=pre + dec, decode_tok_s=r["b"] * (r["o"] - 1) / dec,
+                 cost=r["p"] * (pre + dec) / 3600 * 10 ** 6 / (r["b"] * r["o"]))
+    rms = {k: _rms(bridge.to_np(out[k])[idx], e) for k, e in exact.items()}
+    print(rms)
+    assert rms["t_prefill"] < 1.3 and rms["t_decode"] < 1.3 and rms["t_batch"] < 1.3, rms
+    # one division more than t_decode; a product with a rounded quotient more than t_batch (sqrt(1.3^2 + 2 / 3) at most)
+    assert rms["decode_tok_s"] < 1.3 and rms["cost"] < 1.4, rms
