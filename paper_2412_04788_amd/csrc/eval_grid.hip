@@ -874,7 +874,7 @@ __global__ __launch_bounds__(kBlock) void eval_wide_kernel(GridDesc g, uint32_t 
         const uint32_t row0 = (t_first + run) * TS;             // grid index of the run's first row
         const uint32_t lo = row0 > first ? row0 : first;
         const uint32_t skip = lo - row0, in_run = tiles * TS - skip, n = last - lo < in_run ? last - lo : in_run;
-        for (uint32_t j = threadIdx.x; j < n; j += kBlock) {
+        for (uint32_t j = blockIdx.y * kBlock + threadIdx.x; j < n; j += gridDim.y * kBlock) {
             const uint32_t rel = skip + j, tk = div32(rel, g.div[AX_MBT]), m = rel - tk * NM, t = div32(tk, g.div[AX_BLK]);
             const uint32_t i = lo - first + j;
             const double t_pre = s_pre[t * NM + m], t_dec = s_dec[t], t_batch = t_pre + t_dec;
@@ -979,7 +979,7 @@ __global__ __launch_bounds__(kBlock) void eval_extras_kernel(GridDesc g, const D
         const uint32_t row0 = (t_first + run) * TS;
         const uint32_t lo = row0 > first ? row0 : first;
         const uint32_t skip = lo - row0, in_run = tiles * TS - skip, n = last - lo < in_run ? last - lo : in_run;
-        for (uint32_t j = threadIdx.x; j < n; j += kBlock) {
+        for (uint32_t j = blockIdx.y * kBlock + threadIdx.x; j < n; j += gridDim.y * kBlock) {
             const uint32_t rel = skip + j, tk = div32(rel, g.div[AX_MBT]), m = rel - tk * NM, t = div32(tk, g.div[AX_BLK]);
             const uint32_t i = lo - first + j, tm = t * NM + m;
             if (out.s_max) put<STREAM>(out.s_max, i, s_smax[t]);
@@ -1075,8 +1075,11 @@ constexpr uint32_t kExpandExtrasRows = 250000, kExpandExtrasTile = 6;
 // three with half the runs' length: 27 against 25 us for the full grid's twelve columns), every block the same number
 // of full runs, and runs of whole multiples of 64 tiles when they are that long: their rows then start on line
 // boundaries of every column (2.9 TB/s when two blocks share the lines at their ends, 4.3 TB/s like this).
+// Few tiles of many rows are cut into slices of at least 512 rows, a block each, which works out all of the tile and writes its
+// own share of the rows (30 000 rows of 64 x 64: 4.6 us, with one block a tile 7.8; one index per lane 4.5).
 struct ExpandPlan {
-    uint32_t per_run, blocks;
+    uint32_t per_run;
+    dim3 grid;                          // (blocks, slices)
 };
 static ExpandPlan expand_plan(const GridDesc &g, uint32_t first, uint32_t count) {
     const uint32_t nb = g.div[AX_BLK].d, nm = g.div[AX_MBT].d, ts = nb * nm, widest = nb > nm ? nb : nm;
@@ -1089,7 +1092,12 @@ static ExpandPlan expand_plan(const GridDesc &g, uint32_t first, uint32_t count)
         per_run = up <= cap ? up : per_run / 64 * 64;
     }
     const uint32_t runs = (uint32_t)(((uint64_t)n_tiles + per_run - 1) / per_run);
-    return ExpandPlan{per_run, runs < most ? runs : most};
+    uint32_t slices = 1;
+    if (per_run == 1 && ts >= 1024 && 2 * runs <= most) {
+        const uint32_t by_rows = ts / 512, by_blocks = most / runs;
+        slices = by_rows < by_blocks ? by_rows : by_blocks;
+    }
+    return ExpandPlan{per_run, dim3(runs < most ? runs : most, slices)};
 }
 
 static uint32_t tile_blocks(uint32_t first, uint32_t count, uint32_t ts) {
@@ -1219,10 +1227,10 @@ hipError_t launch_eval_grid(const GridDesc &g, const DevTables *tab, const void 
     auto launch = [&](auto kernel) {
         const TileLds *tables = (const TileLds *)tile_tables;
         if (tm.start)
-            hipExtLaunchKernelGGL(kernel, dim3(plan.blocks), block, 0, stream, tm.start, tm.stop, 0, g, first, count, re_c, re_b,
+            hipExtLaunchKernelGGL(kernel, plan.grid, block, 0, stream, tm.start, tm.stop, 0, g, first, count, re_c, re_b,
                                   out, tables, plan.per_run);
         else
-            hipLaunchKernelGGL(kernel, dim3(plan.blocks), block, 0, stream, g, first, count, re_c, re_b, out, tables,
+            hipLaunchKernelGGL(kernel, plan.grid, block, 0, stream, g, first, count, re_c, re_b, out, tables,
                                plan.per_run);
     };
     if (additive && stream_stores) launch(eval_wide_kernel<true, true>);
@@ -1249,7 +1257,7 @@ hipError_t launch_eval_extras(const GridDesc &g, const DevTables *tab, uint32_t 
                              bytes(out.n_segments, 4) + bytes(out.s_adj, 4) + bytes(out.b_max_kept, 4) + bytes(out.s_max_kept, 4);
     const bool stream_stores = count * per_row >= kStreamBytes;
     auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(plan.blocks), dim3(kBlock), 0, stream, g, tab, first, count, n_gpus, out, plan.per_run);
+        hipLaunchKernelGGL(kernel, plan.grid, dim3(kBlock), 0, stream, g, tab, first, count, n_gpus, out, plan.per_run);
     };
     if (additive && stream_stores) launch(eval_extras_kernel<true, true>);
     else if (additive) launch(eval_extras_kernel<true, false>);
