@@ -805,6 +805,35 @@ __device__ inline void put(T *col, uint32_t i, T v) {
     else col[i] = v;
 }
 
+// What the two kernels below share, so that a row's values are the same bits in either.
+__device__ inline double tile_tok_s(const ExpandTile &tl, double t_dec) {
+    return tl.s_out > 1 ? (double)tl.b * (double)(tl.s_out - 1) / t_dec : 0.0;
+}
+// Cost per second of the batch.  (Divisions here and above: their operands are exact, t_dec apart, so both columns have
+// two roundings at most.)
+__device__ inline double tile_cost(const ExpandTile &tl) {
+    return (double)tl.p * 1.0e6 / (3600.0 * ((double)tl.b * (double)tl.s_out));
+}
+__device__ inline MemResult tile_memory(const Coef &cf, double cap, const ExpandTile &tl, uint32_t blk, double r_blk) {
+    MemResult m;
+    const double c_avail = cap - cf.w_gpu;
+    const uint32_t tok_req = floor_div(tl.s_in + tl.s_out + blk - 1, r_blk) * blk;
+    const double kv_req = (double)tok_req * cf.kv_tok;
+    const double q = floor(c_avail / kv_req);
+    const bool room = c_avail > 0.0;
+    m.b_max = !room ? 0u : (q >= 4294967295.0 ? 4294967295u : (uint32_t)q);
+    m.feasible = room && (double)tl.b * kv_req <= c_avail;
+    return m;
+}
+// What a block needs of the derived tables; the coefficients when they fit.
+__device__ inline bool stage_tile_tables(TileLds &s, const GridDesc &g, const TileLds *__restrict__ derived) {
+    const uint32_t n_rows = g.div[AX_MODEL].d * g.div[AX_TP].d * g.div[AX_WBITS].d;
+    const bool coef_in_lds = n_rows <= kCoefRows;
+    const uint32_t vecs = (uint32_t)(offsetof(TileLds, coef) + (coef_in_lds ? n_rows : 0u) * sizeof(Coef) + 15) / 16;
+    for (uint32_t i = threadIdx.x; i < vecs; i += kBlock) ((uint4 *)&s)[i] = ((const uint4 *)derived)[i];
+    return coef_in_lds;
+}
+
 // Evaluation of grids with more than four values on one of the two fastest axes.  per_run: tiles of a run.
 // Bound by arithmetic and launch at ordinary sizes: 443 211 rows of a grid with five block sizes and six token
 // budgets (20 MB), additive times: 7.5 us; one index per lane, which repeats the decode series and the prefill for
@@ -818,12 +847,7 @@ __global__ __launch_bounds__(kBlock) void eval_wide_kernel(GridDesc g, uint32_t 
     __shared__ double s_dec[kExpandTiles], s_tok[kExpandTiles], s_cost[kExpandTiles], s_pre[kExpandParts];
     __shared__ uint32_t s_bmax[kExpandParts];
     __shared__ uint8_t s_feas[kExpandParts];
-    const uint32_t n_rows = g.div[AX_MODEL].d * g.div[AX_TP].d * g.div[AX_WBITS].d;
-    const bool coef_in_lds = n_rows <= kCoefRows;
-    {
-        const uint32_t vecs = (uint32_t)(offsetof(TileLds, coef) + (coef_in_lds ? n_rows : 0u) * sizeof(Coef) + 15) / 16;
-        for (uint32_t i = threadIdx.x; i < vecs; i += kBlock) ((uint4 *)&s)[i] = ((const uint4 *)derived)[i];
-    }
+    const bool coef_in_lds = stage_tile_tables(s, g, derived);
     __syncthreads();
     const uint32_t NB = g.div[AX_BLK].d, NM = g.div[AX_MBT].d, TS = NB * NM;
     const uint32_t t_first = first / TS, last = first + count, n_tiles = (last - 1) / TS - t_first + 1;
@@ -855,19 +879,13 @@ __global__ __launch_bounds__(kBlock) void eval_wide_kernel(GridDesc g, uint32_t 
                 } else {
                     const double t_dec = decode_time_fast<ADDITIVE>(tc, tl.b, tl.s_in, tl.s_out - 1);
                     s_dec[t] = t_dec;
-                    // (divisions: their operands are exact, t_dec apart, so both columns have two roundings at most)
-                    s_tok[t] = tl.s_out > 1 ? (double)tl.b * (double)(tl.s_out - 1) / t_dec : 0.0;
-                    s_cost[t] = (double)tl.p * 1.0e6 / (3600.0 * ((double)tl.b * (double)tl.s_out));
+                    s_tok[t] = tile_tok_s(tl, t_dec);
+                    s_cost[t] = tile_cost(tl);
                 }
             } else {
-                const double c_avail = hw.cap - cf.w_gpu;
-                const uint32_t blk = s.g.axis[AX_BLK][part];
-                const uint32_t tok_req = floor_div(tl.s_in + tl.s_out + blk - 1, s.r_blk[part]) * blk;
-                const double kv_req = (double)tok_req * cf.kv_tok;
-                const double q = floor(c_avail / kv_req);
-                const bool room = c_avail > 0.0;
-                s_bmax[t * NB + part] = !room ? 0u : (q >= 4294967295.0 ? 4294967295u : (uint32_t)q);
-                s_feas[t * NB + part] = room && (double)tl.b * kv_req <= c_avail ? 1 : 0;
+                const MemResult m = tile_memory(cf, hw.cap, tl, s.g.axis[AX_BLK][part], s.r_blk[part]);
+                s_bmax[t * NB + part] = m.b_max;
+                s_feas[t * NB + part] = m.feasible ? 1 : 0;
             }
         }
         __syncthreads();
@@ -887,6 +905,39 @@ __global__ __launch_bounds__(kBlock) void eval_wide_kernel(GridDesc g, uint32_t 
             if (out.feasible) out.feasible[i] = s_feas[tk];
         }
         __syncthreads();                                        // the run's values have been read
+    }
+}
+
+// The same for few rows, one index per lane: no phases to wait for.
+template <bool ADDITIVE>
+__global__ __launch_bounds__(kBlock) void eval_wide_rows_kernel(GridDesc g, uint32_t first, uint32_t count, double re_c,
+                                                                double re_b, guide_metrics out,
+                                                                const TileLds *__restrict__ derived) {
+    __shared__ TileLds s;
+    const bool coef_in_lds = stage_tile_tables(s, g, derived);
+    __syncthreads();
+    const uint32_t NB = g.div[AX_BLK].d, NM = g.div[AX_MBT].d;
+    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < count; i += gridDim.x * kBlock) {
+        const uint32_t tk = div32(first + i, g.div[AX_MBT]), m = first + i - tk * NM, t = div32(tk, g.div[AX_BLK]), k = tk - t * NB;
+        const ExpandTile tl = expand_tile(s.g, g, t);
+        const Coef cf = coef_in_lds ? s.coef[tl.row] : make_coef(s.g.models[tl.model], tl.p, tl.wbits, s.r_tp[tl.d_tp]);
+        const HwRecip hw = s.g.hw[tl.hw];
+        const TimeCoef tc = make_time_coef(cf, hw.r_peak * re_c, hw.r_bw * re_b, hw.r_link, hw.lat);
+        const double t_pre = prefill_time_fast<ADDITIVE>(tc, tl.b, tl.s_in, s.g.axis[AX_MBT][m], s.r_sin[tl.d_sin], s.r_mbt[m]);
+        const double t_dec = decode_time_fast<ADDITIVE>(tc, tl.b, tl.s_in, tl.s_out - 1);
+        double t_batch;
+        {
+#pragma clang fp contract(off)                                  // a sum of two rounded values, as in the other kernel
+            t_batch = t_pre + t_dec;
+        }
+        const MemResult mem = tile_memory(cf, hw.cap, tl, s.g.axis[AX_BLK][k], s.r_blk[k]);
+        if (out.t_prefill) out.t_prefill[i] = t_pre;
+        if (out.t_decode) out.t_decode[i] = t_dec;
+        if (out.t_batch) out.t_batch[i] = t_batch;
+        if (out.decode_tok_s) out.decode_tok_s[i] = tile_tok_s(tl, t_dec);
+        if (out.cost) out.cost[i] = t_batch * tile_cost(tl);
+        if (out.b_max) out.b_max[i] = mem.b_max;
+        if (out.feasible) out.feasible[i] = mem.feasible ? 1 : 0;
     }
 }
 
@@ -1071,6 +1122,10 @@ static uint32_t blocks_for(uint32_t count) {
 // expanded at 250 000 rows (5.2 and 6.9 at 30 000, where the phases' latency counts; 16.5 and 12.6 at 500 000), tiles of
 // one row, which share nothing, 16.3 and 21.8 at 500 000.
 constexpr uint32_t kExpandExtrasRows = 250000, kExpandExtrasTile = 6;
+// Grids with wide fast axes are expanded beyond 131 072 rows (a row per lane of two blocks per compute unit): 3.6 us a row at
+// a time against 4.5 - 4.8 us at 3000 to 30 000 rows, 4.3 - 4.7 against 4.7 - 5.8 us at 100 000; at 500 000 rows the kernel
+// of one index per lane before took 13 - 28 us, expanded 8 - 15 us.
+constexpr uint32_t kExpandWideRows = 131072;
 // Tiles of a run and blocks of the launch.  Two blocks per compute unit (what the LDS of both kernels allows at 160 KB;
 // three with half the runs' length: 27 against 25 us for the full grid's twelve columns), every block the same number
 // of full runs, and runs of whole multiples of 64 tiles when they are that long: their rows then start on line
@@ -1222,6 +1277,19 @@ hipError_t launch_eval_grid(const GridDesc &g, const DevTables *tab, const void 
     if (additive ? dispatch_tile<true>(g, tab, tile_tables, first, count, re_c, re_b, out, fs, stream, nullptr, tm)
                  : dispatch_tile<false>(g, tab, tile_tables, first, count, re_c, re_b, out, fs, stream, nullptr, tm))
         return hipGetLastError();
+    if (count <= kExpandWideRows) {
+        const dim3 rows((count + kBlock - 1) / kBlock);
+        auto launch = [&](auto kernel) {
+            const TileLds *tables = (const TileLds *)tile_tables;
+            if (tm.start)
+                hipExtLaunchKernelGGL(kernel, rows, block, 0, stream, tm.start, tm.stop, 0, g, first, count, re_c, re_b, out, tables);
+            else
+                hipLaunchKernelGGL(kernel, rows, block, 0, stream, g, first, count, re_c, re_b, out, tables);
+        };
+        if (additive) launch(eval_wide_rows_kernel<true>);
+        else launch(eval_wide_rows_kernel<false>);
+        return hipGetLastError();
+    }
     const ExpandPlan plan = expand_plan(g, first, count);
     const bool stream_stores = (uint64_t)count * 8 * n_f64_columns(out) >= kStreamBytes;
     auto launch = [&](auto kernel) {

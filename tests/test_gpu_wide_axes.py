@@ -1,5 +1,5 @@
-"""Grids with many values on the two fastest axes, and the cluster-level columns: blocks expand runs of tiles into rows.
-Run boundaries, ragged ranges, tables beyond LDS and missing columns, against the oracle."""
+"""Grids with many values on the two fastest axes, and the cluster-level columns, at sizes that take a row per lane: ragged
+ranges, tables beyond LDS and missing columns, against the oracle."""
 import numpy as np
 import pytest
 
@@ -89,23 +89,3 @@ def test_cluster_columns(ora, torch_cuda, nb, nm, ragged):
             else:
                 np.testing.assert_array_equal(got.astype(np.int64) & (0xFFFFFFFF if got.dtype == np.int32 else -1),
                                               np.asarray(exp[k]).astype(np.int64), err_msg=k)
-
-
-def test_few_wide_tiles_use_the_chip(torch_cuda):
-    """A call over seven tiles of 64 x 64 rows costs about what the same number of rows in tiles of 8 x 8 costs (1.8 times with
-    a block per tile)."""
-    torch, times = torch_cuda, []
-    for nb, nm in ((64, 64), (8, 8)):
-        g, n = _grid(nb, nm, 0 if nb == 64 else 3), 28_000
-        ctx, out = bridge.gpu_context(g), bridge.metric_buffers(28_000)
-        call, t = ctx.prepared("eval_grid", bridge.gpu_grid(g), 0, n, out=out), []
-        for _ in range(12):
-            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            a.record()
-            for _ in range(200):
-                call()
-            b.record()
-            b.synchronize()
-            t.append(a.elapsed_time(b))
-        times.append(min(t))
-    assert times[0] <= 1.4 * times[1], times
