@@ -1118,10 +1118,24 @@ static uint32_t blocks_for(uint32_t count) {
     return need < cap ? need : cap;
 }
 
-// Cluster columns are expanded from 250 000 rows and six rows a tile on: 2 x 3 tiles take 10.3 us a row at a time and 10.0
-// expanded at 250 000 rows (5.2 and 6.9 at 30 000, where the phases' latency counts; 16.5 and 12.6 at 500 000), tiles of
-// one row, which share nothing, 16.3 and 21.8 at 500 000.
-constexpr uint32_t kExpandExtrasRows = 250000, kExpandExtrasTile = 6;
+// Cluster columns: expanded, or one index per lane?  Expanding works a value out once per tile, per (tile, block size) and per
+// (tile, token budget): `parts` of them for the tile's rows.  It pays by the work that this saves, which the throughput
+// columns need most of, and by the wider stores where many bytes of a row are asked for; against it stand the latency of
+// its phases and, with few columns, the values that nobody asked for.  Microseconds, one index per lane / expanded:
+//   all twelve columns (57 bytes)  2 x 2 15.0 / 11.8, 6 x 1 15.0 / 14.7, 5 x 6 15.0 / 9.7 (400 000 rows); 2 x 3 10.3 / 10.0,
+//                                  3 x 3 10.3 / 8.3, 6 x 1 10.2 / 10.8 (250 000); 1 x 2 14.7 / 14.9 (400 000); 2 x 3 44.7 / 25.1 (1.9 million)
+//   both throughputs, or 32 bytes  2 x 2 11.6 / 8.9 and 12.6 / 10.0, 6 x 1 11.7 / 10.8 and 12.6 / 11.9 (400 000)
+//   one throughput                 2 x 2 9.2 / 8.2, 1 x 64 9.2 / 8.1, 1 x 6 9.3 / 10.0 (400 000), 3 x 4 6.3 / 6.0, 2 x 3 6.4 / 7.4 (250 000)
+//   s_max alone                    4 x 4 7.1 / 6.2, 3 x 4 7.2 / 7.8 (400 000), 3 x 3 9.4 / 8.9, 2 x 2 9.3 / 10.7 (700 000), 2 x 3 13.7 / 14.4
+//                                  (1.3 million), 18.3 / 17.1 (1.9 million), 1 x 64 26.8 / 31.5 (3 million)
+static bool expand_extras(const GridDesc &g, uint32_t count, uint64_t row_bytes, const guide_extras &out) {
+    const uint32_t nb = g.div[AX_BLK].d, nm = g.div[AX_MBT].d, ts = nb * nm;
+    if (ts < 4) return false;
+    const double parts = (double)(1 + nb + nm) / ts;
+    if (row_bytes >= 32 || (out.cluster_tok_s && out.paper_tok_s)) return count >= (parts <= 1.04 ? 250000u : 400000u);
+    if (out.cluster_tok_s || out.paper_tok_s) return parts <= 1.3 && count >= (parts <= 0.8 ? 250000u : 400000u);
+    return parts <= 1.0 && count >= (parts <= 0.6 ? 400000u : parts <= 0.8 ? 700000u : 1800000u);
+}
 // Grids with wide fast axes are expanded beyond 131 072 rows (a row per lane of two blocks per compute unit): 3.6 us a row at
 // a time against 4.5 - 4.8 us at 3000 to 30 000 rows, 4.3 - 4.7 against 4.7 - 5.8 us at 100 000; at 500 000 rows the kernel
 // of one index per lane before took 13 - 28 us, expanded 8 - 15 us.
@@ -1310,7 +1324,11 @@ hipError_t launch_eval_grid(const GridDesc &g, const DevTables *tab, const void 
 
 hipError_t launch_eval_extras(const GridDesc &g, const DevTables *tab, uint32_t first, uint32_t count, uint32_t n_gpus,
                               bool additive, const guide_extras &out, hipStream_t stream) {
-    if (count < kExpandExtrasRows || g.div[AX_BLK].d * g.div[AX_MBT].d < kExpandExtrasTile) {
+    auto bytes = [](const void *p, uint64_t width) { return p ? width : 0; };
+    const uint64_t per_row = bytes(out.s_max, 4) + bytes(out.dp_max, 4) + bytes(out.max_parallelism, 8) + bytes(out.cluster_tok_s, 8) +
+                             bytes(out.paper_tok_s, 8) + bytes(out.b_adj, 4) + bytes(out.n_sub_batches, 4) +
+                             bytes(out.n_segments, 4) + bytes(out.s_adj, 4) + bytes(out.b_max_kept, 4) + bytes(out.s_max_kept, 4);
+    if (!expand_extras(g, count, per_row, out)) {
         const dim3 grid(blocks_for(count)), block(kBlock);
         if (additive)
             hipLaunchKernelGGL(eval_extras_rows_kernel<true>, grid, block, 0, stream, g, tab, first, count, n_gpus, out);
@@ -1319,10 +1337,6 @@ hipError_t launch_eval_extras(const GridDesc &g, const DevTables *tab, uint32_t 
         return hipGetLastError();
     }
     const ExpandPlan plan = expand_plan(g, first, count);
-    auto bytes = [](const void *p, uint64_t width) { return p ? width : 0; };
-    const uint64_t per_row = bytes(out.s_max, 4) + bytes(out.dp_max, 4) + bytes(out.max_parallelism, 8) + bytes(out.cluster_tok_s, 8) +
-                             bytes(out.paper_tok_s, 8) + bytes(out.b_adj, 4) + bytes(out.n_sub_batches, 4) +
-                             bytes(out.n_segments, 4) + bytes(out.s_adj, 4) + bytes(out.b_max_kept, 4) + bytes(out.s_max_kept, 4);
     const bool stream_stores = count * per_row >= kStreamBytes;
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, plan.grid, dim3(kBlock), 0, stream, g, tab, first, count, n_gpus, out, plan.per_run);

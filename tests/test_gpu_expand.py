@@ -111,3 +111,40 @@ def test_few_wide_tiles_use_the_chip(torch_cuda):
             t.append(a.elapsed_time(b))
         times.append(min(t))
     assert times[0] <= 1.35 * times[1], times
+
+
+EXTRAS_DT = {"max_parallelism": "int64", "cluster_tok_s": "float64", "paper_tok_s": "float64", "feasible_kept": "uint8"}
+
+
+# (56 bytes a row are stored past the caches from 1.2 million rows on where runs start on whole lines; 249 999 and 250 000
+# rows lie on either side of the rule for all columns, 699 999 and 700 000 for one narrow column of 3 x 4 tiles)
+@pytest.mark.parametrize("nb,nm,n,first,tm,names", [
+    (2, 3, 1_250_001, 0, 0, None), (2, 3, 1_900_000, 777, 1, None), (5, 6, 250_000, 41, 0, None), (5, 6, 249_999, 41, 0, None),
+    (5, 6, 3_000_000, 30, 1, None), (64, 3, 1_700_011, 192, 0, None), (1, 64, 700_003, 5, 0, None), (64, 64, 260_001, 4097, 1, None),
+    (64, 64, 1_300_000, 0, 0, None), (2, 2, 420_000, 1, 0, ("cluster_tok_s", "feasible_kept")), (6, 1, 450_000, 0, 0, None),
+    (3, 4, 700_000, 13, 0, ("s_adj",)), (3, 4, 699_999, 13, 0, ("s_adj",)), (4, 4, 500_001, 0, 0, ("n_segments", "b_max_kept")),
+    (2, 3, 1_800_005, 6, 0, ("max_parallelism",)), (1, 2, 500_000, 1, 0, None)])
+def test_cluster_columns(ora, torch_cuda, nb, nm, n, first, tm, names):
+    torch = torch_cuda
+    names, g, keep = names or guide.EXTRAS_COLUMNS, _grid(nb, nm, first + n), 0.3
+    dt = {k: getattr(torch, EXTRAS_DT.get(k, "int32")) for k in guide.EXTRAS_COLUMNS}
+    ctx, gg = bridge.gpu_context(g), bridge.gpu_grid(g)
+    full, out = _padded(torch, names, n, dt)
+    ctx.eval_extras(gg, first, n, 13, out, time_model=tm, kv_keep=keep)
+    step = 200_000                                              # a row per lane, whatever the columns
+    _, part = _padded(torch, guide.EXTRAS_COLUMNS, step, dt)
+    for at in range(0, n, step):
+        m = min(step, n - at)
+        ctx.eval_extras(gg, first + at, m, 13, {k: v[:m] for k, v in part.items()}, time_model=tm, kv_keep=keep)
+        for k in out:
+            assert torch.equal(out[k][at:at + m], part[k][:m]), (k, at)
+    assert _untouched(full, n)
+    for at in _windows(n, 12):
+        exp = ora.eval_extras_grid(bridge.ora_grid(g), 13, first + at, 200, time_model=tm, kv_keep=keep)
+        for k in out:
+            got = out[k][at:at + 200].cpu().numpy()
+            if got.dtype == np.float64:
+                assert bridge.rel_err(got, exp[k]).max() <= TOL, k
+            else:
+                np.testing.assert_array_equal(got.astype(np.int64) & (0xFFFFFFFF if got.dtype == np.int32 else -1),
+                                              np.asarray(exp[k]).astype(np.int64), err_msg=k)
