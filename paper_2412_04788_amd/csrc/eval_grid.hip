@@ -1143,12 +1143,15 @@ constexpr uint32_t kExpandWideRows = 131072;
 // Tiles of a run and blocks of the launch.  Two blocks per compute unit (what the LDS of both kernels allows at 160 KB;
 // three with half the runs' length: 27 against 25 us for the full grid's twelve columns), every block the same number
 // of full runs, and runs of whole multiples of 64 tiles when they are that long: their rows then start on line
-// boundaries of every column (2.9 TB/s when two blocks share the lines at their ends, 4.3 TB/s like this).
+// boundaries of every column unless the range itself does not.  Only then are large outputs stored past the caches, which must
+// merge the halves of a line that two blocks share: 1.9 million rows of 2 x 3 tiles, all columns, 25.1 us past them on whole
+// lines, 38.8 past and 26.9 through them on shared ones; 6 million of 4 x 4 tiles 141 and 80 us shared.
 // Few tiles of many rows are cut into slices of at least 512 rows, a block each, which works out all of the tile and writes its
-// own share of the rows (30 000 rows of 64 x 64: 4.6 us, with one block a tile 7.8; one index per lane 4.5).
+// own share of the rows (cluster columns of 250 000 rows in 64 x 64 tiles: 8.6 us, with one block a tile 14.5; one index per lane 10.3).
 struct ExpandPlan {
     uint32_t per_run;
     dim3 grid;                          // (blocks, slices)
+    bool lines;                         // every run's rows start on a line boundary of every column of four bytes or more
 };
 static ExpandPlan expand_plan(const GridDesc &g, uint32_t first, uint32_t count) {
     const uint32_t nb = g.div[AX_BLK].d, nm = g.div[AX_MBT].d, ts = nb * nm, widest = nb > nm ? nb : nm;
@@ -1166,7 +1169,8 @@ static ExpandPlan expand_plan(const GridDesc &g, uint32_t first, uint32_t count)
         const uint32_t by_rows = ts / 512, by_blocks = most / runs;
         slices = by_rows < by_blocks ? by_rows : by_blocks;
     }
-    return ExpandPlan{per_run, dim3(runs < most ? runs : most, slices)};
+    const bool lines = (first / ts * ts - first) % 32 == 0 && (uint64_t)per_run * ts % 32 == 0;
+    return ExpandPlan{per_run, dim3(runs < most ? runs : most, slices), lines};
 }
 
 static uint32_t tile_blocks(uint32_t first, uint32_t count, uint32_t ts) {
@@ -1305,7 +1309,7 @@ hipError_t launch_eval_grid(const GridDesc &g, const DevTables *tab, const void 
         return hipGetLastError();
     }
     const ExpandPlan plan = expand_plan(g, first, count);
-    const bool stream_stores = (uint64_t)count * 8 * n_f64_columns(out) >= kStreamBytes;
+    const bool stream_stores = plan.lines && (uint64_t)count * 8 * n_f64_columns(out) >= kStreamBytes;
     auto launch = [&](auto kernel) {
         const TileLds *tables = (const TileLds *)tile_tables;
         if (tm.start)
@@ -1337,7 +1341,7 @@ hipError_t launch_eval_extras(const GridDesc &g, const DevTables *tab, uint32_t 
         return hipGetLastError();
     }
     const ExpandPlan plan = expand_plan(g, first, count);
-    const bool stream_stores = count * per_row >= kStreamBytes;
+    const bool stream_stores = plan.lines && count * per_row >= kStreamBytes;
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, plan.grid, dim3(kBlock), 0, stream, g, tab, first, count, n_gpus, out, plan.per_run);
     };

@@ -148,3 +148,23 @@ def test_cluster_columns(ora, torch_cuda, nb, nm, n, first, tm, names):
             else:
                 np.testing.assert_array_equal(got.astype(np.int64) & (0xFFFFFFFF if got.dtype == np.int32 else -1),
                                               np.asarray(exp[k]).astype(np.int64), err_msg=k)
+
+
+def test_ragged_ranges_cost_about_as_much_as_whole_ones(torch_cuda):
+    """Blocks whose runs share lines at their ends store through the caches (stores past them: 1.55 times the time)."""
+    torch, times, n = torch_cuda, [], 1_900_000
+    dt = {k: getattr(torch, EXTRAS_DT.get(k, "int32")) for k in guide.EXTRAS_COLUMNS}
+    g = _grid(2, 3, n + 777)
+    ctx, out = bridge.gpu_context(g), {k: torch.zeros(n, dtype=dt[k], device="cuda") for k in guide.EXTRAS_COLUMNS}
+    for first in (0, 777):
+        call, t = ctx.prepared("eval_extras", bridge.gpu_grid(g), first, n, 8, out), []
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(50):
+                call()
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        times.append(min(t))
+    assert times[1] <= 1.25 * times[0], times
