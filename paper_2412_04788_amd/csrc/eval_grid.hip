@@ -544,6 +544,7 @@ __device__ inline ExpandTile expand_tile(const GridLds &s, const GridDesc &g, ui
 // configuration, and a sample costs two multiply-adds for all of them.  The others (a few per wave: neighbouring
 // configurations have them in common) are kept as pairs and evaluated per sample, skipped by branches that are uniform
 // over the wave.
+constexpr double kLargest = 0x1.fffffffffffffp+1023;
 constexpr int kPassTerms = N_LINEAR + 2;                // the linear tasks, attention, LM head
 template <int N>
 struct SweepTerms {
@@ -632,8 +633,10 @@ __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const
         for (uint32_t i = threadIdx.x; i < vecs; i += kBlock) ((uint4 *)&s)[i] = ((const uint4 *)derived)[i];
     }
     for (uint32_t i = threadIdx.x; i < n_eff; i += blockDim.x) {
-        s_eff[i] = double2{1.0 / tab->eff_c[i], 1.0 / tab->eff_b[i]};
-        s_rho[i] = tab->eff_b[i] / tab->eff_c[i];
+        // (finite also for subnormal efficiencies: a sum of no terms times infinity would be no number, and would
+        // drop out of the sorting instead of coming last)
+        s_eff[i] = double2{fmin(1.0 / tab->eff_c[i], kLargest), fmin(1.0 / tab->eff_b[i], kLargest)};
+        s_rho[i] = fmin(tab->eff_b[i] / tab->eff_c[i], kLargest);
     }
     __syncthreads();
     double rho_lo = s_rho[0], rho_hi = rho_lo;                      // least and largest x / y

@@ -55,3 +55,27 @@ def test_many_coefficient_rows_and_extreme_samples(ora):
     e_c, e_b = e_c.copy(), e_b.copy()
     e_c[3], e_b[3], e_c[5], e_b[5] = 1e-150, 1e150, 1e120, 1e-120
     _check(ora, g, e_c, e_b, 0, g.size, 0)
+
+
+def test_subnormal_efficiencies_come_last(ora):
+    """A sample whose reciprocal overflows is the slowest of all, not no number: percentiles of the others are what they
+    are without it.  (Its own time, and a mean that holds it, overflow or are beyond 1e280.)"""
+    g = wl.make_grid([wl.DENSE_7B, wl.MOE_8X], [wl.Hardware(3e14, 2e12, 200 * wl.GIB, 1.6e11, 1e-6), wl.HW_TINY],
+                     wl.Axis.table([1, 3, 200]), wl.Axis.table([50, 20000]), wl.Axis.table([1, 2, 300]), wl.Axis.table([1, 8]),
+                     wl.Axis.table([16]), wl.Axis.table([16]), wl.Axis.table([2048]))
+    import torch
+    e_c, e_b = wl.efficiency_pairs(n=24)
+    for tiny_c, tiny_b in ((5e-324, 1.0), (1.0, 1e-310), (1e-309, 1e-309)):
+        c, b = e_c.copy(), e_b.copy()
+        c[5], b[5] = tiny_c, tiny_b
+        out = {k: torch.zeros(g.size, dtype={"b_max": torch.int32, "feasible": torch.uint8}.get(k, torch.float64), device="cuda")
+               for k in guide.STATS_COLUMNS}
+        bridge.gpu_context(g).eval_grid(bridge.gpu_grid(g), 0, g.size, stats=out, e_c=c, e_b=b)
+        torch.cuda.synchronize()
+        # the sample is replaced by one that is slow as well, but within the range
+        c[5], b[5] = max(tiny_c, 1e-20), max(tiny_b, 1e-20)
+        exp = ora.eval_sweep_grid(bridge.ora_grid(g), c, b, 0, g.size)
+        for k in ("ttft_p10", "ttft_p90", "t_batch_p10", "t_batch_p90"):
+            assert bridge.rel_err(bridge.to_np(out[k]), exp[k]).max() <= TOL, (k, tiny_c, tiny_b)
+        for k in ("ttft_mean", "t_batch_mean"):
+            assert (bridge.to_np(out[k]) > 1e280).all(), (k, tiny_c, tiny_b)
