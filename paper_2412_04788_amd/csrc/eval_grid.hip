@@ -539,7 +539,9 @@ __device__ inline ExpandTile expand_tile(const GridLds &s, const GridDesc &g, ui
 // only the memory check is repeated per block size.
 //
 // A sample scales every compute time by x = 1 / e_c and every read time by y = 1 / e_b.  A configuration's time is a sum of
-// terms max(F x, B y) -- one per task and pass, with the passes' counts multiplied in -- plus the transfers.  Over the
+// terms max(F x, B y) -- one per task and pass, with the passes' counts multiplied in -- plus the transfers.  F and B are
+// added up as operations and bytes, whose sums are whole numbers or nearly so, and turned into times last: the roundings
+// of a configuration's sums are common to all its samples and do not average out in the means.  Over the
 // ratios x / y of all samples most terms are bound by the same side throughout: those are added up once per
 // configuration, and a sample costs two multiply-adds for all of them.  The others (a few per wave: neighbouring
 // configurations have them in common) are kept as pairs and evaluated per sample, skipped by branches that are uniform
@@ -570,25 +572,32 @@ struct SweepTerms {
     }
     // `times` passes of T tokens with attention workload Q, K context tokens and n_lm LM-head rows; att: attention counts
     template <bool ADDITIVE>
-    __device__ void add_pass(int i0, const TimeCoef &t, double times, double T, double Q, double K, double n_lm, bool att,
-                             double rho_lo, double rho_hi) {
-        const double w = times * t.L, wT = w * T, eld = fmin(t.E, t.k * T);
+    __device__ void add_pass(int i0, const Coef &c, const HwRecip &hw, double times, double T, double Q, double K, double n_lm,
+                             bool att, double rho_lo, double rho_hi) {
+        const double w = times * c.L, wT = w * T, w_eld = w * fmin(c.E, c.k * T), lm = times * n_lm;
 #pragma unroll
         for (int i = 0; i < N_LINEAR; ++i) {
             const bool experts = i == OP_UP || i == OP_DOWN;
-            add<ADDITIVE>(i0 + i, wT * t.c[i], w * fma(T, t.m1[i], experts ? eld * t.m0[i] : t.m0[i]), rho_lo, rho_hi);
+            add<ADDITIVE>(i0 + i, wT * c.f[i], fma(wT, c.a[i], (experts ? w_eld : w) * c.w[i]), rho_lo, rho_hi);
         }
-        if (att) add<ADDITIVE>(i0 + N_LINEAR, w * (Q * t.c_att), w * fma(K, t.m_att_k, T * t.m_att_t), rho_lo, rho_hi);
-        if (n_lm > 0.0)
-            add<ADDITIVE>(i0 + N_LINEAR + 1, times * (n_lm * t.c_lm), times * fma(n_lm, t.m1_lm, t.m0_lm), rho_lo, rho_hi);
-        a_B += wT * t.m_nm;
-        fixed += 2.0 * w * fma(T, t.ar1, t.ar0);
+        if (att) add<ADDITIVE>(i0 + N_LINEAR, (w * Q) * c.f_att, fma(w * K, c.c_att, wT * c.a_att), rho_lo, rho_hi);
+        if (n_lm > 0.0) add<ADDITIVE>(i0 + N_LINEAR + 1, lm * c.f_lm, fma(lm, c.a_lm, times * c.w_lm), rho_lo, rho_hi);
+        a_B += wT * c.a_nm;
+        fixed += 2.0 * fma(wT * c.m_ar, hw.r_link, w * c.n_ar * hw.lat);
     }
-    // to be called by all lanes in action together, after the last add
-    __device__ void settle() {
+    // operations and bytes become seconds; to be called by all lanes in action together, after the last add
+    __device__ void settle(const HwRecip &hw) {
+        a_F *= hw.r_peak;
+        a_B *= hw.r_bw;
         uint32_t m = 0;
 #pragma unroll
-        for (int i = 0; i < N; ++i) m |= __ballot(F[i] != 0.0) ? 1u << i : 0u;     // (a term that changes sides has F > 0)
+        for (int i = 0; i < N; ++i) {
+            if (__ballot(F[i] != 0.0)) {                // (a term that changes sides has F > 0)
+                m |= 1u << i;
+                F[i] *= hw.r_peak;
+                B[i] *= hw.r_bw;
+            }
+        }
         active = (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
     }
     template <int G>
@@ -625,12 +634,16 @@ __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const
                                                             guide_stats out, const TileLds *__restrict__ derived) {
     __shared__ TileLds s;
     __shared__ double2 s_eff[GUIDE_MAX_EFF];            // (1 / e_c, 1 / e_b)
-    __shared__ double s_rho[GUIDE_MAX_EFF];
+    __shared__ double s_rho[GUIDE_MAX_EFF], s_balance[GUIDE_MAX_HW];
     const uint32_t n_rows = g.div[AX_MODEL].d * g.div[AX_TP].d * g.div[AX_WBITS].d;
     const bool coef_in_lds = n_rows <= kCoefRows;
     {
         const uint32_t vecs = (uint32_t)(offsetof(TileLds, coef) + (coef_in_lds ? n_rows : 0u) * sizeof(Coef) + 15) / 16;
         for (uint32_t i = threadIdx.x; i < vecs; i += kBlock) ((uint4 *)&s)[i] = ((const uint4 *)derived)[i];
+    }
+    for (uint32_t i = threadIdx.x; i < g.n_hw; i += blockDim.x) {
+        const HwRecip &hw = derived->g.hw[i];
+        s_balance[i] = hw.r_peak / hw.r_bw;
     }
     for (uint32_t i = threadIdx.x; i < n_eff; i += blockDim.x) {
         // (finite also for subnormal efficiencies: a sum of no terms times infinity would be no number, and would
@@ -661,19 +674,9 @@ __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const
         const ExpandTile tl = expand_tile(s.g, g, hi);
         const uint32_t mbt = s.g.axis[AX_MBT][m_digit];
         const HwRecip hw = s.g.hw[tl.hw];
-        TimeCoef tc;
-        double w_gpu, kv_tok;
-        if (coef_in_lds) {
-            const Coef &cf = s.coef[tl.row];
-            tc = make_time_coef(cf, hw.r_peak, hw.r_bw, hw.r_link, hw.lat);
-            w_gpu = cf.w_gpu;
-            kv_tok = cf.kv_tok;
-        } else {
-            const Coef cf = make_coef(s.g.models[tl.model], tl.p, tl.wbits, s.r_tp[tl.d_tp]);
-            tc = make_time_coef(cf, hw.r_peak, hw.r_bw, hw.r_link, hw.lat);
-            w_gpu = cf.w_gpu;
-            kv_tok = cf.kv_tok;
-        }
+        const Coef cf = coef_in_lds ? s.coef[tl.row] : make_coef(s.g.models[tl.model], tl.p, tl.wbits, s.r_tp[tl.d_tp]);
+        // the ratios in operations and bytes (finite: no operations times infinity would be no number)
+        const double lo = fmin(rho_lo * s_balance[tl.hw], kLargest), up = fmin(rho_hi * s_balance[tl.hw], kLargest);
         const PrefillPlan plan = make_prefill_plan(tl.b, tl.s_in, mbt, s.r_sin[tl.d_sin], s.r_mbt[m_digit]);
         SweepTerms<2 * kPassTerms> pre;
         SweepTerms<kPassTerms> dec;
@@ -685,38 +688,39 @@ __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const
         bool p_series = false, d_series = false;
         const double b = (double)tl.b, n = (double)(tl.s_out - 1), S = plan.S;
         {
-            // sum over contexts first, 2 first, .. or s + 1, .., s + n: both sides are linear in the context, so the ends decide
-            auto series = [&](auto &terms, double w, double al, double be, double ga, double c_lo, double c_hi, double all,
+            // sum over contexts first, 2 first, .. or s + 1, .., s + n: both sides are linear in the context, so the ends decide.
+            // n_al, n_be, n_ga: whole numbers that multiply the operations per pair, the cache and the activation bytes.
+            auto series = [&](auto &terms, double n_al, double n_be, double n_ga, double c_lo, double c_hi, double all,
                               double steps, double &o_al, double &o_be, double &o_ga) {
-                const bool read = ADDITIVE || al * rho_hi * c_hi <= fma(be, c_hi, ga);
-                const bool compute = ADDITIVE || al * rho_lo * c_lo >= fma(be, c_lo, ga);
-                terms.a_F += compute ? w * (al * all) : 0.0;
-                terms.a_B += read && (ADDITIVE || !compute) ? w * fma(be, all, steps * ga) : 0.0;
+                const double al = n_al * cf.f_att, be = n_be * cf.c_att, ga = n_ga * cf.a_att;
+                const bool read = ADDITIVE || al * up * c_hi <= fma(be, c_hi, ga);
+                const bool compute = ADDITIVE || al * lo * c_lo >= fma(be, c_lo, ga);
+                terms.a_F += compute ? (n_al * all) * cf.f_att : 0.0;
+                terms.a_B += read && (ADDITIVE || !compute) ? fma(n_be * all, cf.c_att, (n_ga * steps) * cf.a_att) : 0.0;
                 const bool both = !read && !compute;
-                o_al = both ? w * al : 0.0;
-                o_be = both ? w * be : 0.0;
-                o_ga = both ? w * ga : 0.0;
+                o_al = both ? al * hw.r_peak : 0.0;
+                o_be = both ? be * hw.r_bw : 0.0;
+                o_ga = both ? ga * hw.r_bw : 0.0;
                 return both;
             };
             const bool seg = plan.segmented;
-            const double R = plan.R;
-            pre.add_pass<ADDITIVE>(0, tc, seg ? b * plan.n_fs : plan.n_full, seg ? plan.M : R * S, R * S * S, R * S, R, !seg,
-                                   rho_lo, rho_hi);
+            const double R = plan.R, bL = b * cf.L;
+            pre.add_pass<ADDITIVE>(0, cf, hw, seg ? b * plan.n_fs : plan.n_full, seg ? plan.M : R * S, R * S * S, R * S, R, !seg,
+                                   lo, up);
             if (seg || plan.rem > 0.0)
-                pre.add_pass<ADDITIVE>(kPassTerms, tc, seg ? b : 1.0, seg ? plan.c_last : plan.rem * S,
+                pre.add_pass<ADDITIVE>(kPassTerms, cf, hw, seg ? b : 1.0, seg ? plan.c_last : plan.rem * S,
                                        seg ? plan.c_last * S : plan.rem * S * S, seg ? S : plan.rem * S, seg ? 1.0 : plan.rem, true,
-                                       rho_lo, rho_hi);
+                                       lo, up);
             if (seg)
-                p_series = series(pre, b * tc.L, plan.M * tc.c_att, tc.m_att_k, plan.M * tc.m_att_t, plan.M,
-                                  plan.n_fs * plan.M, plan.M * (0.5 * plan.n_fs * (plan.n_fs + 1.0)), plan.n_fs, p_al, p_be, p_ga);
+                p_series = series(pre, bL * plan.M, bL, bL * plan.M, plan.M, plan.n_fs * plan.M,
+                                  plan.M * (0.5 * plan.n_fs * (plan.n_fs + 1.0)), plan.n_fs, p_al, p_be, p_ga);
             if (n > 0.0) {
-                dec.add_pass<ADDITIVE>(0, tc, n, b, 0.0, 0.0, b, false, rho_lo, rho_hi);
-                d_series = series(dec, tc.L, b * tc.c_att, b * tc.m_att_k, b * tc.m_att_t, S + 1.0, S + n,
-                                  fma(n, S, 0.5 * n * (n + 1.0)), n, d_al, d_be, d_ga);
+                dec.add_pass<ADDITIVE>(0, cf, hw, n, b, 0.0, 0.0, b, false, lo, up);
+                d_series = series(dec, bL, bL, bL, S + 1.0, S + n, fma(n, S, 0.5 * n * (n + 1.0)), n, d_al, d_be, d_ga);
             }
         }
-        pre.settle();
-        dec.settle();
+        pre.settle(hw);
+        dec.settle(hw);
         const bool any_p = __ballot(p_series) != 0, any_d = __ballot(d_series) != 0;    // wave-uniform
         ExtremeK<false> lo_p, lo_b;
         ExtremeK<true> hi_p, hi_b;
@@ -785,7 +789,7 @@ __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const
             if (out.t_batch_p90) out.t_batch_p90[i] = p90_b;
             if (out.cost) out.cost[i] = cost;
             if (out.b_max || out.feasible) {
-                const MemResult mem = memory_check(w_gpu, kv_tok, hw.cap, tl.b, tl.s_in, tl.s_out, s.g.axis[AX_BLK][k]);
+                const MemResult mem = memory_check(cf.w_gpu, cf.kv_tok, hw.cap, tl.b, tl.s_in, tl.s_out, s.g.axis[AX_BLK][k]);
                 if (out.b_max) out.b_max[i] = mem.b_max;
                 if (out.feasible) out.feasible[i] = mem.feasible ? 1 : 0;
             }

@@ -95,3 +95,37 @@ def test_expanded_grids(tm):
     assert rms["t_prefill"] < 1.3 and rms["t_decode"] < 1.3 and rms["t_batch"] < 1.3, rms
     # one division more than t_decode; a product with a rounded quotient more than t_batch (sqrt(1.3^2 + 2 / 3) at most)
     assert rms["decode_tok_s"] < 1.3 and rms["cost"] < 1.4, rms
+
+
+@pytest.mark.parametrize("tm", [0, 1])
+def test_efficiency_sweep(tm):
+    """Mean, p10 and p90 over the samples, and the cost."""
+    import torch
+    rng = np.random.default_rng(8)
+    g = wl.make_grid(wl.MODELS_FULL, wl.hw_profiles(5, 4), wl.Axis.table([1, 3, 29, 200]), wl.Axis.table([70, 1000, 9001]),
+                     wl.Axis.table([2, 60, 333]), wl.Axis.table([1, 3, 8]), wl.Axis.table([16, 4]), wl.Axis.table([16]),
+                     wl.Axis.table([1000, 2048, 8192]))
+    n_eff = 20
+    e_c, e_b = np.exp(0.1 * rng.standard_normal((2, n_eff)))
+    out = {k: torch.zeros(g.size, dtype={"b_max": torch.int32, "feasible": torch.uint8}.get(k, torch.float64), device="cuda")
+           for k in guide.STATS_COLUMNS}
+    bridge.gpu_context(g).eval_grid(bridge.gpu_grid(g), 0, g.size, stats=out, e_c=e_c, e_b=e_b, time_model=tm)
+    torch.cuda.synchronize()
+    idx = np.unique(np.linspace(0, g.size - 1, 1500).astype(np.int64))
+    r = _rows(g, idx)
+    pre, bat = [], []
+    for x, y in zip(e_c, e_b):
+        p, d = _times(r, tm == 1, x, y)
+        pre.append(p)
+        bat.append(p + d)
+    rms = {}
+    for name, v in (("ttft", np.stack(pre)), ("t_batch", np.stack(bat))):
+        mean = v.sum(0) / n_eff
+        v = np.sort(v, 0)
+        exact = {"_mean": mean, "_p10": v[1], "_p90": v[17]}         # nearest ranks 2 and 18 of 20
+        rms.update({name + k: _rms(bridge.to_np(out[name + k])[idx], e) for k, e in exact.items()})
+    rms["cost"] = _rms(bridge.to_np(out["cost"])[idx], r["p"] * mean / 3600 * 10 ** 6 / (r["b"] * r["o"]))
+    print(rms)
+    # sequential sums of 20 samples: about one unit in the means by themselves; the percentiles have a few roundings each
+    assert max(v for k, v in rms.items() if "p10" in k or "p90" in k) < 1.15, rms
+    assert max(rms["ttft_mean"], rms["t_batch_mean"]) < 1.51 and rms["cost"] < 1.68, rms
