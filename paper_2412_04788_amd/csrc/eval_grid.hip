@@ -9,6 +9,10 @@
 
 namespace guide {
 
+// The next number of a loop that strides over 0 .. n - 1, n (the end) when there is none: i + stride may pass 2^32 near the
+// largest grids, and a loop that compares the wrapped sum would start over and never end.
+__device__ inline uint32_t stride_on(uint32_t i, uint32_t stride, uint32_t n) { return n - i > stride ? i + stride : n; }
+
 struct GridLds {
     uint32_t axis[kNumAxes][GUIDE_MAX_AXIS_VALUES];
     guide_model models[GUIDE_MAX_MODELS];
@@ -238,8 +242,9 @@ __global__ __launch_bounds__(kBlock) void eval_tile_kernel(GridDesc g, const Dev
     const uint32_t t_first = first / TS;
     const uint32_t n_tiles = (first + count - 1) / TS - t_first + 1;
     const uint32_t last = first + count;                       // exclusive; count > 0, no overflow (grid < 2^32)
-    for (uint32_t tb = (blockIdx.x * kWaves + wave) * kWave; tb < n_tiles; tb += n_main_blocks * kWaves * kWave) {
-        const uint32_t tl = tb + lane < n_tiles ? tb + lane : n_tiles - 1;   // idle lanes repeat the last tile
+    for (uint32_t tb = (blockIdx.x * kWaves + wave) * kWave; tb < n_tiles; tb = stride_on(tb, n_main_blocks * kWaves * kWave, n_tiles)) {
+        const uint32_t left = n_tiles - tb;
+        const uint32_t tl = (uint32_t)lane < left ? tb + lane : n_tiles - 1;   // idle lanes repeat the last tile
         // digits of the seven slow axes
         uint32_t dg[AX_BLK];
         uint32_t rem = t_first + tl;
@@ -266,7 +271,7 @@ __global__ __launch_bounds__(kBlock) void eval_tile_kernel(GridDesc g, const Dev
         // Columns leave as soon as their values exist so that stores overlap the remaining arithmetic.
         const uint32_t cfg0 = (t_first + tb) * TS;             // flat index of the wave's first element
         // every element of the wave inside [first, last): no per-element checks (wave-uniform)
-        const bool full = tb + kWave <= n_tiles && cfg0 >= first && cfg0 + kWave * TS <= last;
+        const bool full = left >= (uint32_t)kWave && cfg0 >= first && cfg0 + kWave * TS <= last;
         auto store_f64 = [&](double *col, auto value_of_slot) {
             if (!col) return;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -285,7 +290,7 @@ __global__ __launch_bounds__(kBlock) void eval_tile_kernel(GridDesc g, const Dev
                 for (int it = 0; it < TS; ++it) {
                     const uint32_t cfg = cfg0 + it * kWave + lane;
                     const double v = xw[it * kWave + lane];
-                    if (cfg >= first && cfg < last && tb + (it * kWave + lane) / TS < n_tiles) col[cfg - first] = v;
+                    if (cfg >= first && cfg < last && (uint32_t)((it * kWave + lane) / TS) < left) col[cfg - first] = v;
                 }
             }
         };
@@ -321,7 +326,7 @@ __global__ __launch_bounds__(kBlock) void eval_tile_kernel(GridDesc g, const Dev
             for (int it = 0; it < TS; ++it) {
                 const uint32_t cfg = cfg0 + it * kWave + lane;
                 const uint32_t bm = xi[it * kWave + lane], fe = xi[kWave * TS + it * kWave + lane];
-                if (full || (cfg >= first && cfg < last && tb + (it * kWave + lane) / TS < n_tiles)) {
+                if (full || (cfg >= first && cfg < last && (uint32_t)((it * kWave + lane) / TS) < left)) {
                     if (out.b_max) out.b_max[cfg - first] = bm;
                     if (out.feasible) out.feasible[cfg - first] = (uint8_t)fe;
                 }
@@ -356,7 +361,7 @@ __global__ __launch_bounds__(kBlock) void eval_tile_kernel(GridDesc g, const Dev
             // The selections see exactly the values stored above.  A column's value depends on the
             // token-budget digit m at most and feasibility on the block-size digit k only, so the
             // filters and keys are worked out once per m and each row costs a few compares.
-            const bool tile_real = tb + lane < n_tiles;
+            const bool tile_real = (uint32_t)lane < left;
             const uint32_t row0 = (t_first + tl) * TS;
             auto col = [&](uint32_t id, int m) {
                 return id == GUIDE_COL_T_PREFILL ? t_prefill[m]
@@ -666,7 +671,7 @@ __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const
     const uint32_t t_first = first / TS;
     const uint32_t n_items = ((first + count - 1) / TS - t_first + 1) * NM;
     const uint32_t last = first + count;
-    for (uint32_t u = blockIdx.x * kBlock + threadIdx.x; u < n_items; u += gridDim.x * kBlock) {
+    for (uint32_t u = blockIdx.x * kBlock + threadIdx.x; u < n_items; u = stride_on(u, gridDim.x * kBlock, n_items)) {
         const uint32_t hi = t_first + u / NM, m_digit = u % NM;
         const uint32_t row0 = hi * TS + m_digit;                  // the row with kv_block digit 0
         // none of this item's rows inside [first, last)?  (only at the ragged ends)
@@ -924,7 +929,7 @@ __global__ __launch_bounds__(kBlock) void eval_wide_rows_kernel(GridDesc g, uint
     const bool coef_in_lds = stage_tile_tables(s, g, derived);
     __syncthreads();
     const uint32_t NB = g.div[AX_BLK].d, NM = g.div[AX_MBT].d;
-    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < count; i += gridDim.x * kBlock) {
+    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < count; i = stride_on(i, gridDim.x * kBlock, count)) {
         const uint32_t tk = div32(first + i, g.div[AX_MBT]), m = first + i - tk * NM, t = div32(tk, g.div[AX_BLK]), k = tk - t * NB;
         const ExpandTile tl = expand_tile(s.g, g, t);
         const Coef cf = coef_in_lds ? s.coef[tl.row] : make_coef(s.g.models[tl.model], tl.p, tl.wbits, s.r_tp[tl.d_tp]);
@@ -1065,7 +1070,7 @@ __global__ __launch_bounds__(kBlock) void eval_extras_rows_kernel(GridDesc g, co
     __shared__ GridLds s;
     stage_grid_tables(s, g, tab);
     __syncthreads();
-    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < count; i += gridDim.x * kBlock) {
+    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < count; i = stride_on(i, gridDim.x * kBlock, count)) {
         const Candidate c = decode_index(s, g, first + i);
         const HwRecip hw = s.hw[c.hw];
         const Coef cf = make_coef(s.models[c.model], c.kn.p, c.kn.wbits);
@@ -1120,7 +1125,7 @@ __global__ __launch_bounds__(kBlock) void eval_extras_rows_kernel(GridDesc g, co
 }
 
 static uint32_t blocks_for(uint32_t count) {
-    const uint32_t need = (count + kBlock - 1) / kBlock;
+    const uint32_t need = (count - 1) / kBlock + 1;             // (count > 0)
     const uint32_t cap = device_cus() * 8;
     return need < cap ? need : cap;
 }
@@ -1187,7 +1192,7 @@ static uint32_t tile_blocks(uint32_t first, uint32_t count, uint32_t ts) {
     // (every block writes one top-k partial when a top-k is folded in)
     uint32_t cap = 2 * device_cus();
     cap = cap < kSelBlocks ? cap : kSelBlocks;
-    const uint32_t need = (n_tiles + kBlock - 1) / kBlock;
+    const uint32_t need = (n_tiles - 1) / kBlock + 1;
     return need < cap ? need : cap;
 }
 
@@ -1363,7 +1368,7 @@ hipError_t launch_eval_sweep(const GridDesc &g, const DevTables *tab, const void
                              uint32_t count, uint32_t n_eff, bool additive, const guide_stats &out, hipStream_t stream) {
     const uint32_t ts = g.div[AX_BLK].d * g.div[AX_MBT].d;
     const uint32_t n_items = ((first + count - 1) / ts - first / ts + 1) * g.div[AX_MBT].d;
-    const uint32_t need = (n_items + kBlock - 1) / kBlock, most = 2 * device_cus();     // resident blocks: two per compute unit
+    const uint32_t need = (n_items - 1) / kBlock + 1, most = 2 * device_cus();     // resident blocks: two per compute unit
     const dim3 grid(need < most ? need : most), block(kBlock);
     const TileLds *tables = (const TileLds *)tile_tables;
     if (additive)

@@ -270,3 +270,36 @@ def test_cluster_extras(ora, torch_cuda):
     torch.cuda.synchronize()
     np.testing.assert_array_equal(bridge.to_np(only["dp_max"], np.uint32),
                                   ora.eval_extras_grid(bridge.ora_grid(g), 8, 0, 16)["dp_max"])
+
+
+def test_largest_grids_end(ora):
+    """4 294 964 250 configurations, 3046 below 2^32: index arithmetic of the strided loops next to the end of 32 bits.  One byte
+    per row is stored; the last rows and windows are compared with the oracle."""
+    import torch
+    from paper_2412_04788_amd import guide, workloads as wl
+    from tests import bridge
+    span = lambda a, n, step=1: wl.Axis.table([a + i * step for i in range(n)])         # noqa: E731
+    g = wl.make_grid([wl.DENSE_7B, wl.MOE_8X], wl.hw_profiles(2, 45), span(1, 50, 3), span(30, 57, 41), span(2, 61, 7), span(1, 61),
+                     wl.Axis.table([16]), wl.Axis.table([16]), wl.Axis.table([4096]))
+    axes = [(a.values, a.geom2_start) for a in g.axes]
+    axes[0] = (tuple(i % 2 for i in range(9)), 0)                   # nine values of the model axis, two models
+    ctx, gg = bridge.gpu_context(g), guide.GridArg(axes)
+    n = gg.size
+    assert 2 ** 32 - 2 * 256 * 256 < n < 2 ** 32
+    from oracle import guide_oracle as go
+    og = go.Grid(wl.models_array(g.models), wl.hw_array(g.hws),
+                 [np.asarray(axes[0][0], dtype=np.uint64)] + [a.array() for a in g.axes[1:]])
+    out = torch.full((n,), 7, dtype=torch.uint8, device="cuda")
+    wins = [0, n // 3, n - 131_200, n - 300]
+    exp = [(at, go.eval_grid(og, at, 300)["feasible"]) for at in wins]
+    ext = [(at, ora.eval_extras_grid(og, 8, at, 300, kv_keep=0.3)["feasible_kept"]) for at in wins]
+    for name, want, call in (
+            ("tiles", exp, lambda: ctx.eval_grid(gg, 0, n, out={"feasible": out})),
+            ("sweep", exp, lambda: ctx.eval_grid(gg, 0, n, stats={"feasible": out}, e_c=[1.0, 0.9], e_b=[1.0, 1.1])),
+            ("columns", ext, lambda: ctx.eval_extras(gg, 0, n, 8, {"feasible_kept": out}, kv_keep=0.3))):
+        out.fill_(7)
+        call()
+        torch.cuda.synchronize()
+        assert int(out.max()) <= 1, name
+        for at, e in want:
+            np.testing.assert_array_equal(out[at:at + 300].cpu().numpy(), e, err_msg=name)
