@@ -271,7 +271,15 @@ int guide_eval_sampled(guide_ctx *ctx, const guide_space *space, uint64_t seed, 
  * Each loop: jump to the next arrival if idle; admit FCFS while arrived, under
  * the sequence cap and with ceil((in+out)/kv_block) free KV blocks (reserved
  * for the request's lifetime; stop at the first that cannot enter); run one
- * pass; advance time by t_pass.  The pass depends on `scheduler`, the two
+ * pass; advance time by t_pass.  (In a run of decode-only passes, whose times
+ * are in arithmetic progression while attention stays on one side of the
+ * roofline, the clock advances by the sums of 64 and of 8 passes at a time as
+ * long as the last of them starts before the next admissible arrival.  Steps and
+ * request-steps count every pass.  Times are at least as close to the exact sums
+ * as pass-by-pass addition is and differ from it by its rounding, some 1e-13 of
+ * the clock after 10^5 passes; an admission test "arrived by now?" that is
+ * decided within that can fall the other way.)  A configuration's results are
+ * the same bits in every list and call.  The pass depends on `scheduler`, the two
  * framework behaviours the paper models (Inference Engine, Step 2):
  *   GUIDE_SCHED_SPLIT_FUSE    one decode token for every prefilled request +
  *                             prompt chunks in admission order under the
@@ -292,7 +300,8 @@ int guide_eval_sampled(guide_ctx *ctx, const guide_space *space, uint64_t seed, 
  * in closed form, split where attention turns from read bound to compute
  * bound).  Engine steps and request-steps count the same passes; times differ
  * from the stepped simulation by rounding only, so a result can differ from it
- * only where an admission test "arrived by now?" is decided within rounding.
+ * only where an admission test "arrived by now?" is decided within rounding, as
+ * above.
  * Outputs (DEVICE, n_cfg each): nearest-rank p50 / p99 of TTFT, mean TPOT over
  * requests with n_out > 1, generated tokens / (last finish - first arrival),
  * status (GUIDE_SIM_INFEASIBLE when weights or one request do not fit,

@@ -129,3 +129,41 @@ def test_efficiency_sweep(tm):
     # sequential sums of 20 samples: about one unit in the means by themselves; the percentiles have a few roundings each
     assert max(v for k, v in rms.items() if "p10" in k or "p90" in k) < 1.15, rms
     assert max(rms["ttft_mean"], rms["t_batch_mean"]) < 1.51 and rms["cost"] < 1.68, rms
+
+
+@pytest.mark.parametrize("sched", [guide.SCHED_SPLIT_FUSE, guide.SCHED_PREFILL_FIRST])
+@pytest.mark.parametrize("closed", [0, guide.SIM_CLOSED_FORM_RUNS])
+def test_simulation_clock(ora, sched, closed):
+    """One sequence at a time and everything there from the start: the clock is the sum of all prefills and decode steps.  The
+    kernel adds runs of steps in strides (or in closed form), fewer additions than one per step: at most 40 a request against
+    up to 1500, so it has to be at least as close to the 80-bit sum as step-by-step addition is, which the oracle does."""
+    import torch
+    rng = np.random.default_rng(21)
+    n = 150
+    n_in, n_out = rng.integers(16, 1900, n).astype(np.uint32), rng.integers(1, 1500, n).astype(np.uint32)
+    hws = wl.hw_profiles(5, 3) + [wl.Hardware(q * 2e12, 2e12, 900 * wl.GIB, 4e11) for q in (0.9, 0.999, 7.98)]
+    g = wl.make_grid([wl.DENSE_7B, wl.DENSE_70B, wl.MOE_8X], hws, wl.Axis.table([1]), wl.Axis.table([1]), wl.Axis.table([1]),
+                     wl.Axis.table([1, 4]), wl.Axis.table([16, 8]), wl.Axis.table([16]), wl.Axis.table([700, 8192]))
+    idx = np.arange(g.size, dtype=np.uint32)
+    rate = np.full(g.size, np.inf)
+    tr = wl.Trace(np.arange(n) * 1.0, n_in, n_out)
+    from tests.test_gpu_simulate import _run
+    got = _run(torch, bridge.gpu_context(g), g, idx, rate, tr, scheduler=sched | closed)
+    seq = ora.simulate_grid(bridge.ora_grid(g), idx, rate, tr.arrival_unit, n_in, n_out, scheduler=sched)
+    ok = np.nonzero(got["status"] == 0)[0]
+    assert len(ok) > 20
+    r = {k: np.repeat(v, n) for k, v in _rows(g, ok).items()}
+    r.update(b=np.ones(len(ok) * n, dtype=LD), s=np.tile(n_in, len(ok)).astype(LD), o=np.tile(n_out, len(ok)).astype(LD))
+    if sched == guide.SCHED_PREFILL_FIRST:
+        r["mbt"] = r["mbt"] * 0 + 2 ** 20                           # prompts stay whole
+    pre, dec = (x.reshape(len(ok), n) for x in _times(r, False))
+    first = np.cumsum(pre + dec, axis=1) - dec
+    ttft = np.sort(first, axis=1)
+    long = n_out > 1
+    exact = dict(ttft_p50=ttft[:, (n + 1) // 2 - 1], ttft_p99=ttft[:, (99 * n + 99) // 100 - 1],
+                 mean_tpot=(dec[:, long] / (n_out[long] - 1).astype(LD)).mean(1), tokens_s=LD(n_out.sum()) / (first + dec)[:, -1])
+    err = {k: [float(np.abs((a[k][ok].astype(LD) - e) / e).max()) for a in (got, seq)] for k, e in exact.items()}
+    print(err)
+    for k, (here, stepped) in err.items():
+        assert here <= max(1.05 * stepped, 1e-15), (k, here, stepped)
+        assert here <= 40 * n * 2.0 ** -53, (k, here)               # one rounding of the clock per addition
