@@ -305,19 +305,6 @@ __device__ inline PrefillPlan make_prefill_plan(uint32_t b, uint32_t s, uint32_t
     }
     return p;
 }
-template <bool ADDITIVE>
-__device__ inline double prefill_time_plan(const TimeCoef &t, const PrefillPlan &p, uint32_t b) {
-    if (!p.segmented) {
-        double total = p.n_full * pass_time<ADDITIVE>(t, p.R * p.S, p.R * p.S * p.S, p.R * p.S, p.R);
-        if (p.rem > 0.0) total += pass_time<ADDITIVE>(t, p.rem * p.S, p.rem * p.S * p.S, p.rem * p.S, p.rem);
-        return total;
-    }
-    const double att = attention_series<ADDITIVE>(p.M * t.c_att, t.m_att_k, p.M * t.m_att_t, 0.0, p.M, p.r_mbt, p.n_fs);
-    const double one = fma(t.L, fma(p.n_fs, layer_base<ADDITIVE>(t, p.M), att),
-                           pass_time<ADDITIVE>(t, p.c_last, p.c_last * p.S, p.S, 1.0));
-    return (double)b * one;
-}
-
 template <bool ADDITIVE, bool DENSE = false>
 __device__ inline double decode_time_fast(const TimeCoef &t, uint32_t b_, uint32_t s_, uint32_t n_) {
     if (n_ == 0) return 0.0;

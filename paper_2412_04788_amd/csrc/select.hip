@@ -801,7 +801,7 @@ __device__ inline void scan_sum_excl(uint32_t *io, uint32_t *s_tmp) {
 }
 
 // A top-k selection over the same rows that reads nothing but the Pareto selection's two columns and its
-// flag column: the staircase kernel has those values in registers anyway and keeps the per-lane lists
+// flag column: the filter pass has those values in registers anyway and keeps the per-lane lists
 // beside its own work, so the top-k needs no pass of its own.
 struct SharedTopk {
     uint32_t obj_is_y;             // objective: 0 = the x column, 1 = the y column
@@ -817,9 +817,8 @@ struct SharedTopk {
 // exclusive prefix-min) and keeps a row when no sample row of a strictly lower bin has a y at or below its
 // own.  Every row of the front is kept, and every other kept row is dominated by a kept one (its
 // dominators are themselves dominated by a front row, and domination is transitive).  Kept rows are appended
-// as (row, keys), counted per bin, and their least y per bin goes to the global table, whose exclusive
-// prefix-min tells the finishing kernel which kept rows a kept row of a lower bin dominates.
-// KT: pairs per block partial of a top-k that shares the columns (0 = none), as in the staircase kernel.
+// as (row, keys); the finishing kernel makes the bins' tables from them.
+// KT: pairs per block partial of a top-k that shares the columns (0 = none).
 template <uint32_t MAXC, int KT, uint32_t U>
 __global__ __launch_bounds__(kBlock) void pareto_filter_kernel(const double *__restrict__ x, const double *__restrict__ y,
                                                                RowFilter f, uint32_t n, ParetoWs w, SelectScratch *sc,
@@ -1331,8 +1330,7 @@ __device__ inline void finish_in_lds(FinishLds &L, const Binning &bin, const uin
     static_assert(kFinishThreads == 1024, "kPerFinish assumes 1024 threads");
     constexpr uint32_t P = kPerFinish, kPer = kStage / kFinishThreads;
     const uint32_t t = threadIdx.x;
-    // Survivors that are dominated for sure are dropped first (after the staircase and survivors kernels there
-    // are few; the filter pass leaves more): those with a survivor of a strictly lower bin at or below their y,
+    // Survivors that are dominated for sure are dropped first: those with a survivor of a strictly lower bin at or below their y,
     // and those that their own bin's representative dominates -- the survivor with the bin's least y (of those,
     // the least x); rows often tie in x, and then the representative settles all of them but the ties in y.
     // Tables: least y per bin in the LDS that the records are staged in afterwards, then its exclusive
@@ -1724,7 +1722,7 @@ hipError_t launch_select_pareto(const guide_select_spec &spec, uint64_t n, const
 }
 
 // True when the top-k selection reads only the Pareto selection's x, y and flag columns (and the Pareto
-// selection has no constraint columns); fills the description for the staircase kernel.
+// selection has no constraint columns); fills the description for the filter pass.
 static bool shares_columns(const guide_select_spec &topk, const guide_select_spec &pareto, SharedTopk *t) {
     const double *x = pareto.objective, *y = pareto.objective_y;
     if (pareto.n_constraints != 0 || topk.n_constraints > 2 || topk.k > 4) return false;
