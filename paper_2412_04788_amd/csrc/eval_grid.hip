@@ -630,9 +630,10 @@ __device__ inline double uniform(double x) {
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// Bound by the vector ALU (3800 instructions per lane for 64 samples, 22 of the 35 per sample are the sorting).  Two
-// waves per SIMD.  1.9 million configurations x 64 samples: 141 us; with every task's two sides, the split of the
-// series and the coefficients worked out per sample, 371 us.
+// Bound by the vector ALU: 4280 vector instructions per lane for 64 samples, two waves per SIMD, 44 bytes of scratch.
+// 1.9 million configurations x 64 samples: 160 us, of which the set-up and the stores are 50 (two samples take 54) and a
+// sample 1.7, most of it sorting; with every task's two sides, the split of the series and the coefficients worked
+// out per sample, 405 us.
 template <bool ADDITIVE>
 __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const DevTables *__restrict__ tab,
                                                             uint32_t first, uint32_t count, uint32_t n_eff,
@@ -847,9 +848,9 @@ __device__ inline bool stage_tile_tables(TileLds &s, const GridDesc &g, const Ti
 }
 
 // Evaluation of grids with more than four values on one of the two fastest axes.  per_run: tiles of a run.
-// Bound by arithmetic and launch at ordinary sizes: 443 211 rows of a grid with five block sizes and six token
-// budgets (20 MB), additive times: 7.5 us; one index per lane, which repeats the decode series and the prefill for
-// every row: 20.1 us.
+// Bound by latency and launch at ordinary sizes: 443 211 rows of a grid with five block sizes and six token
+// budgets (20 MB), additive times: 8.6 us (124 vector instructions per row); one index per lane, which repeats the decode
+// series and the prefill for every row: 22.9 us.
 template <bool ADDITIVE, bool STREAM>
 __global__ __launch_bounds__(kBlock) void eval_wide_kernel(GridDesc g, uint32_t first, uint32_t count, double re_c,
                                                            double re_b, guide_metrics out,
@@ -955,7 +956,7 @@ __global__ __launch_bounds__(kBlock) void eval_wide_rows_kernel(GridDesc g, uint
 
 // Cluster-level columns under a GPU budget: every one depends on the tile, on (tile, block size) or on (tile, token
 // budget) alone, so the rows are copies.  Bound by the stores: the full grid's twelve columns (57 bytes a row, 108 MB)
-// take 25 us; one index per lane with everything worked out per row (571 instructions) took 44 us.
+// take 26 us (227 vector instructions per row); one index per lane with everything worked out per row (571) took 49 us.
 template <bool ADDITIVE, bool STREAM>
 __global__ __launch_bounds__(kBlock) void eval_extras_kernel(GridDesc g, const DevTables *__restrict__ tab,
                                                              uint32_t first, uint32_t count, uint32_t n_gpus,

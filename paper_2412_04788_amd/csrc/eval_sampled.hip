@@ -75,8 +75,8 @@ __global__ void sampled_init_kernel(guide_sampled_out out) {
 // 16-bit field j of the block (lowest field of word 0 first).
 __device__ inline uint32_t field(const Block256 &b, int j) { return (uint32_t)(b.v[j >> 2] >> (16 * (j & 3))) & 0xFFFFu; }
 
-// Bound by the vector ALU: about 700 instructions per candidate, a third of them the generator.  2^28 candidates: 4.58 ms;
-// 6.26 ms with the products' low words multiplied once more, divisions by table entries (tp, block size, head count)
+// Bound by the vector ALU: 655 instructions per candidate.  2^28 candidates: 4.84 ms;
+// 6.23 ms (895 instructions) with the products' low words multiplied once more, divisions by table entries (tp, block size, head count)
 // and the router's terms that a dense model does not have.
 template <bool ADDITIVE>
 __global__ __launch_bounds__(kBlock) void eval_sampled_kernel(const SpaceTables *__restrict__ tab, uint64_t seed,

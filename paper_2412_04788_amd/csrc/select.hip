@@ -400,7 +400,7 @@ __device__ inline void group_compact(const GroupLds &L, uint32_t G, uint32_t k) 
 // the k-th of which has k rows at or below it.  So no order of the rows makes a block append much more than k
 // rows per group and batch.
 // Bound by latency at this size (one batch per block): 1.9 million rows, ten groups, k = 3 and one constraint (40 MB) take
-// 21.5 us with the merge; k rounds over all rows 56 us.  8 million rows of 64 groups, k = 8: 81 us in random order, 108 us
+// 16.3 us + 5.6 us for the merge; k rounds over all rows 56 us a call.  8 million rows of 64 groups, k = 8: 81 us in random order, 108 us
 // falling, 47 us all equal (k rounds: 336 us); one list per wave and group, whose rows enter one after the other: 263,
 // 1210 and 200 us.  Blocks of 512 threads with eight rows each: 57 instead of 47 us (8 million rows, 64 groups, k = 3);
 // the next batch under way meanwhile: 74 us (four rows, one block per compute unit then).

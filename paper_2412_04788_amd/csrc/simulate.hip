@@ -357,9 +357,9 @@ struct TraceSums {
 // differ from call to call): the results of a configuration are the same bits in every list and every call.
 // (The stride's sum has one rounding where 64 additions to a clock of hundreds of seconds have 64: against 80-bit
 // sums the first-token times of 150 requests of up to 1500 tokens, one after the other, are 5e-15 off, step by step 7.5e-14.)
-// What bounds the kernel: a wave is a serial stream of about 560 instructions per round, 7 cycles each with one wave
-// per SIMD (40 % of the cycles wait for LDS, 55 % issue), and the longest wave takes 2000 - 3200 rounds.
-// 65 536 configurations x 1024 requests: 7.1 ms stepped, 5.8 ms with closed-form runs; 1999 x 97: 0.69 ms.
+// What bounds the kernel: with one wave per SIMD a wave is a serial stream of 970 000 vector instructions (700 000 with
+// closed-form runs) on average, and 40 % of its cycles are waits; the longest wave, which takes 3200 rounds, sets the time.
+// 65 536 configurations x 1024 requests: 7.55 ms stepped, 5.98 ms with closed-form runs; 1999 x 97: 0.74 ms.
 // Before (loops over every kind of event, two rounds per request, four predicated steps of 65 instructions at a time,
 // heap segments by sequence cap, finishing times waited for by every heap read): 41.9, 13.9 and 4.1 ms.
 // heap_slots: keys that the LDS behind the staged trace holds for the whole block (whole groups of siblings); they are
