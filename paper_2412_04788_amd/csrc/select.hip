@@ -596,7 +596,7 @@ __global__ __launch_bounds__(kBlock) void topk_group_merge_kernel(GroupWs w, uin
 // columns; a top-k over the same columns can ride along with the second, and a top-k merge with the last.
 // Sample: kSampleBlocks blocks take a scattered sample of rows.  It fixes the stretch of x that the bins
 // slice (kBins equal slices of key space, clamped at both ends, so a lower bin means a strictly smaller x),
-// and every wave hands over the front of its sample rows.  The block that takes sample 0 also resets the
+// and every block hands over rows of the front of its sample.  The block that takes sample 0 also resets the
 // counters that the next two kernels accumulate into.
 // Filter: every block bins the handed-over sample rows (least y per bin, exclusive prefix-min) and keeps a
 // row when no sample row of a strictly lower bin has a y at or below its own.  The kept rows contain the
@@ -605,7 +605,22 @@ __global__ __launch_bounds__(kBlock) void topk_group_merge_kernel(GroupWs w, uin
 // over the kept rows, exclusive prefix-min) or that their own bin's representative dominates are dropped,
 // the rest are grouped by bin and tested exactly inside their bin, and front members are written at (front
 // members of lower bins) + (rank inside the bin), which orders the output by (x, y, row).  One block does
-// this in LDS for up to kStage kept rows; more are shared out among kLargeParts blocks by runs of bins.
+// this in LDS for up to kStage kept rows; more are shared out among kLargeParts blocks by runs of bins, each of which does the
+// same with what is left of its share, in bins of its own.
+
+// Sample rows per thread of the row sample's blocks, and the row that sample number k stands for (n: none): all of them when the
+// sample is larger than the selection, otherwise one at a scrambled place in each of as many stretches, so that no period of
+// the rows' layout lines up with the sample.  Four rows a thread halve what the filter pass keeps, but 64 compute units take
+// 4 us longer to fetch four columns' worth of scattered lines: 400 000 rows 29 - 49 us a call with one and 31 - 49 us with
+// four, 1.2 million rows 48 - 74 and 50 - 72 us, 1.9 million rows 57 - 95 and 55 - 91 us.
+constexpr uint32_t kSampleDeep = 4, kDeepSampleRows = 1500000;
+__device__ inline uint32_t sample_deep(uint32_t n) { return n > kDeepSampleRows ? kSampleDeep : 1u; }
+__device__ inline uint32_t sample_of(uint32_t k, uint32_t n) {
+    const uint32_t total = kSampleBlocks * kBlock * sample_deep(n);
+    if (n <= total) return k < n ? k : n;
+    const uint32_t stride = n / total, rest = n - stride * total;           // stretches of stride or stride + 1 rows
+    return k * stride + (uint32_t)((uint64_t)k * rest / total) + ((k * 2654435761u) >> 8) % stride;
+}
 
 constexpr uint32_t kStage = 4096;        // survivors whose records the finishing block holds in LDS
 constexpr uint32_t kFinishThreads = 1024;
@@ -615,12 +630,12 @@ struct ParetoWs {
     uint64_t *skx, *sky;  // [n]: keys of surviving rows
     uint32_t *surv;       // [n]: surviving rows, arbitrary order
     // large-front path only:
-    uint32_t *staged;     // [n]: per part of the front, from its first survivor slot on: its front members' rows in order
+    uint32_t *staged;     // [n]: per part of the front, from its first survivor slot on: positions of its survivors, then its front
+                          // members' rows in order
     uint32_t *grouped;    // [n]: positions into surv, grouped by bin (parts whose survivors do not fit LDS)
     uint8_t *on_front;    // [n]: flag per grouped survivor (the same parts)
-    uint8_t *dead;        // [n]: flag per survivor slot: a survivor of a lower bin dominates it
 };
-size_t pareto_ws_bytes(uint64_t n) { return (size_t)n * (8 + 8 + 4 + 4 + 4 + 1 + 1) + 256; }
+size_t pareto_ws_bytes(uint64_t n) { return (size_t)n * (8 + 8 + 4 + 4 + 4 + 1 + 1) + 256; }   // (one byte a row to spare)
 ParetoWs pareto_ws(void *ws, uint64_t n) {
     ParetoWs w;
     w.skx = (uint64_t *)ws;
@@ -629,7 +644,6 @@ ParetoWs pareto_ws(void *ws, uint64_t n) {
     w.staged = w.surv + n;
     w.grouped = w.staged + n;
     w.on_front = (uint8_t *)(w.grouped + n);
-    w.dead = w.on_front + n;
     return w;
 }
 
@@ -654,43 +668,144 @@ __device__ inline Binning binning_of(uint64_t lo, uint64_t hi) {
     return b;
 }
 
-// Range that the bins slice, from a strided sample of rows: low end = least x of
+// kBins-entry tables in LDS that a block scans are stored with one unused slot after every PER
+// entries (PER = entries per thread of the scan): thread t's entries then start at slot t * (PER + 1),
+// and the lanes of a wave reach different banks when each reads its own j-th entry.
+template <uint32_t PER>
+__device__ inline uint32_t padded(uint32_t i) { return i + i / PER; }
+template <uint32_t PER>
+constexpr uint32_t padded_size() { return kBins + kBins / PER + 1; }
+constexpr uint32_t kPerPass = kBins / kBlock;             // table entries per thread of a streaming block
+constexpr uint32_t kPerFinish = kBins / 1024;             // ... of the finishing block
+
+// Thread t of the NT-thread block owns the `per` consecutive entries v[] of a
+// table; returns the minimum over all entries before its first one
+// (scan in the wave, wave totals through LDS; one block barrier).
+// s_tmp: NT / kWave entries.
+template <uint32_t NT, uint32_t per>
+__device__ inline uint64_t prefix_min_before(const uint64_t (&v)[per], uint64_t *s_tmp) {
+    constexpr uint32_t nw = NT / kWave;
+    const uint32_t t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+    uint64_t m = kNone;
+#pragma unroll
+    for (uint32_t j = 0; j < per; ++j) m = min_u64(m, v[j]);
+    const uint64_t inc = wave_scan_min(m);              // inclusive scan of thread minima in the wave
+    if (lane == kWave - 1) s_tmp[wave] = inc;
+    uint64_t run = __shfl_up(inc, 1, kWave);            // exclusive within the wave
+    if (lane == 0) run = kNone;
+    __syncthreads();
+    for (uint32_t wv = 0; wv < nw; ++wv)
+        if (wv < wave) run = min_u64(run, s_tmp[wv]);
+    return run;
+}
+
+// Range that the bins slice, from a scattered sample of rows: low end = least x of
 // passing sample rows, high end = x of the sample row with the least y (rows
 // beyond it are dominated by that row unless their y is smaller still; they share
 // the last bin).  Any monotone binning is correct -- the sample only decides how
 // finely the interesting stretch of x is resolved.
+// A block bins its sample rows over its own range (least y per bin, exclusive prefix-min) and
+// hands over the row of every bin whose least y is below that of all lower bins; of more than kSampleFrontPer such
+// rows, evenly spaced ones, so that every stretch of x gets its share.  Any subset of rows is valid, but what is not handed
+// over prunes nothing: 1.9 million rows whose front has 8000 (4000 and 2800) members keep 40 000 (8600) of them like this, and
+// kept 419 000 (18 300) with 256 rows a block of which each wave handed over its eight rightmost.  11 us (7 us).
+constexpr uint32_t kSampleBins = 1024;                    // of a sampling block
 __device__ void pareto_prepare_body(uint32_t block, const double *__restrict__ x, const double *__restrict__ y,
                                     const RowFilter &f, uint32_t n, SelectScratch *sc) {
-    __shared__ uint64_t s_lo[kWaves];
-    __shared__ Pair s_best[kWaves];
-    const uint32_t gid = block * kBlock + threadIdx.x;
-    const uint32_t n_samples = kSampleBlocks * kBlock;
-    if (gid == 0) sc->counters[0] = sc->counters[1] = 0;         // neutral state for the kernels that follow
-    const uint32_t stride = n > n_samples ? n / n_samples : 1;
-    const uint32_t k = sample_number(block, kSampleBlocks);
-    const Row r = load_row<true, GUIDE_MAX_CONSTRAINTS>(x, y, f, (uint64_t)k * stride < n ? sample_row(k, stride) : n, n);
-    uint64_t lo = kNone, kx = 0, ky = 0;
+    constexpr uint32_t NT = kBlock, R = kSampleDeep, P = kSampleBins / NT, NW = NT / kWave;
+    constexpr uint8_t kNoSlot = 0xFF;
+    static_assert(kSampleFrontPer < kNoSlot && kSampleFrontPer <= NT, "a slot number fits a byte, and a thread each");
+    __shared__ uint64_t s_low[kSampleBins + kSampleBins / P], s_tmp[NW], s_lo[NW];
+    __shared__ Pair s_best[NW];
+    __shared__ uint8_t s_slot[kSampleBins];
+    __shared__ uint32_t s_sum[NW];
+    const uint32_t t = threadIdx.x, lane = t % kWave, wave = t / kWave, deep = sample_deep(n);
+    if (block == 0 && t == 0) sc->counters[0] = sc->counters[1] = 0;        // neutral state for the kernels that follow
+    RawRow<GUIDE_MAX_CONSTRAINTS> raw[R];
+#pragma unroll
+    for (uint32_t q = 0; q < R; ++q) {
+        raw[q].valid = false;
+        if (q < deep) raw[q] = load_raw<true, GUIDE_MAX_CONSTRAINTS>(x, y, f, sample_of((q * NT + t) * kSampleBlocks + block, n), n);
+    }
+    for (uint32_t i = t; i < kSampleBins + kSampleBins / P; i += NT) s_low[i] = kNone;
+    uint64_t lo = kNone, kx[R], ky[R];
+    bool pass[R];
     Pair best = {kNone, kNone};                                     // (y key, x key) of the least y
-    if (r.pass) {
-        lo = kx = key_of(r.x);
-        ky = key_of(r.y);
-        best = Pair{ky, kx};
+#pragma unroll
+    for (uint32_t q = 0; q < R; ++q) {
+        pass[q] = false;
+        kx[q] = ky[q] = kNone;
+        if (q >= deep) continue;                        // (uniform)
+        const Row r = row_of<true, GUIDE_MAX_CONSTRAINTS>(raw[q], f);
+        pass[q] = r.pass;
+        kx[q] = pass[q] ? key_of(r.x) : kNone;
+        ky[q] = pass[q] ? key_of(r.y) : kNone;
+        lo = min_u64(lo, kx[q]);
+        best = pair_min(best, Pair{ky[q], kx[q]});
     }
     lo = wave_min(lo);
     best = wave_min(best);
-    if (threadIdx.x % kWave == 0) {
-        s_lo[threadIdx.x / kWave] = lo;
-        s_best[threadIdx.x / kWave] = best;
+    if (lane == 0) {
+        s_lo[wave] = lo;
+        s_best[wave] = best;
     }
-    store_sample_front(r.pass, kx, ky, sc->sample_front + block * kSampleFrontPer);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int wv = 1; wv < kWaves; ++wv) {
-            lo = s_lo[wv] < lo ? s_lo[wv] : lo;
-            best = pair_min(best, s_best[wv]);
-        }
+    for (uint32_t w = 0; w < NW; ++w) {
+        lo = min_u64(lo, s_lo[w]);
+        best = pair_min(best, s_best[w]);
+    }
+    Pair *slots = sc->sample_front + block * kSampleFrontPer;
+    if (t == 0) {
         sc->sample_lo[block] = lo;
         sc->sample_best[block] = best;
+    }
+    if (lo == kNone) {                                              // no sample row passes (block-uniform)
+        if (t < kSampleFrontPer) slots[t] = Pair{kNone, kNone};
+        return;
+    }
+    const Binning fine = binning_of(lo, best.idx);
+    auto bin = [&](uint64_t k) { return fine(k) / (kBins / kSampleBins); };
+#pragma unroll
+    for (uint32_t q = 0; q < R; ++q)
+        if (pass[q]) atomicMin((unsigned long long *)&s_low[padded<P>(bin(kx[q]))], (unsigned long long)ky[q]);
+    __syncthreads();
+    // corners: bins whose least y is below that of all lower bins, numbered from the left
+    uint64_t v[P];
+#pragma unroll
+    for (uint32_t j = 0; j < P; ++j) v[j] = s_low[t * (P + 1) + j];
+    uint64_t run = prefix_min_before<NT, P>(v, s_tmp);
+    uint32_t corners = 0;                                           // bit j: entry j is one
+#pragma unroll
+    for (uint32_t j = 0; j < P; ++j) {
+        corners |= v[j] < run ? 1u << j : 0u;
+        run = min_u64(run, v[j]);
+    }
+    const uint32_t mine = (uint32_t)__popc(corners), incl = wave_scan_sum(mine);
+    if (lane == kWave - 1) s_sum[wave] = incl;
+    __syncthreads();
+    uint32_t at = incl - mine, total = 0;
+    for (uint32_t w = 0; w < NW; ++w) {
+        at += w < wave ? s_sum[w] : 0u;
+        total += s_sum[w];
+    }
+    const uint32_t per = total < kSampleFrontPer ? total : kSampleFrontPer;     // corner r goes to slot r * per / total, the last one that would
+#pragma unroll
+    for (uint32_t j = 0; j < P; ++j) {
+        uint32_t slot = kNoSlot;
+        if ((corners >> j) & 1u) {
+            const uint32_t s0 = at * per / total, s1 = (at + 1) * per / total;
+            slot = s0 != s1 ? s0 : kNoSlot;
+            ++at;
+        }
+        s_slot[t * P + j] = (uint8_t)slot;
+    }
+    if (t < kSampleFrontPer && t >= per) slots[t] = Pair{kNone, kNone};
+    __syncthreads();
+    // (rows that tie in y inside a bin write one after the other, each a valid one: 16 bytes by one store)
+#pragma unroll
+    for (uint32_t q = 0; q < R; ++q) {
+        const uint32_t b = pass[q] ? bin(kx[q]) : 0u;
+        if (pass[q] && s_slot[b] != kNoSlot && s_low[padded<P>(b)] == ky[q]) slots[s_slot[b]] = Pair{ky[q], kx[q]};
     }
 }
 __global__ __launch_bounds__(kBlock) void pareto_prepare_kernel(const double *__restrict__ x,
@@ -721,37 +836,6 @@ __device__ inline Binning sampled_binning(const SelectScratch *sc, uint64_t *s_r
     return binning_of(s_rng[0], s_rng[1]);
 }
 
-// kBins-entry tables in LDS that a block scans are stored with one unused slot after every PER
-// entries (PER = entries per thread of the scan): thread t's entries then start at slot t * (PER + 1),
-// and the lanes of a wave reach different banks when each reads its own j-th entry.
-template <uint32_t PER>
-__device__ inline uint32_t padded(uint32_t i) { return i + i / PER; }
-template <uint32_t PER>
-constexpr uint32_t padded_size() { return kBins + kBins / PER + 1; }
-constexpr uint32_t kPerPass = kBins / kBlock;             // table entries per thread of a streaming block
-constexpr uint32_t kPerFinish = kBins / 1024;             // ... of the finishing block
-
-// Thread t of the NT-thread block owns the kBins / NT consecutive entries v[] of a
-// kBins-entry table; returns the minimum over all entries before its first one
-// (scan in the wave, wave totals through LDS; one block barrier).
-// s_tmp: NT / kWave entries.
-template <uint32_t NT>
-__device__ inline uint64_t prefix_min_before(const uint64_t (&v)[kBins / NT], uint64_t *s_tmp) {
-    constexpr uint32_t per = kBins / NT, nw = NT / kWave;
-    const uint32_t t = threadIdx.x, lane = t % kWave, wave = t / kWave;
-    uint64_t m = kNone;
-#pragma unroll
-    for (uint32_t j = 0; j < per; ++j) m = min_u64(m, v[j]);
-    const uint64_t inc = wave_scan_min(m);              // inclusive scan of thread minima in the wave
-    if (lane == kWave - 1) s_tmp[wave] = inc;
-    uint64_t run = __shfl_up(inc, 1, kWave);            // exclusive within the wave
-    if (lane == 0) run = kNone;
-    __syncthreads();
-    for (uint32_t wv = 0; wv < nw; ++wv)
-        if (wv < wave) run = min_u64(run, s_tmp[wv]);
-    return run;
-}
-
 // Exclusive prefix-min over a (padded) kBins-entry table in LDS, in place, by the NT threads of the block.
 template <uint32_t NT>
 __device__ inline void scan_min_excl(uint64_t *s_io, uint64_t *s_tmp) {
@@ -760,7 +844,7 @@ __device__ inline void scan_min_excl(uint64_t *s_io, uint64_t *s_tmp) {
     uint64_t v[per];
 #pragma unroll
     for (uint32_t j = 0; j < per; ++j) v[j] = s_io[t * (per + 1) + j];
-    uint64_t run = prefix_min_before<NT>(v, s_tmp);
+    uint64_t run = prefix_min_before<NT, per>(v, s_tmp);
 #pragma unroll
     for (uint32_t j = 0; j < per; ++j) {
         s_io[t * (per + 1) + j] = run;
@@ -851,7 +935,12 @@ __global__ __launch_bounds__(kBlock) void pareto_filter_kernel(const double *__r
             atomicMin((unsigned long long *)&s_lower[padded<kPerPass>(bin(sf[j].idx))], (unsigned long long)sf[j].key);
     __syncthreads();
     scan_min_excl<kBlock>(s_lower, s_tmp);              // least y of the sample rows in strictly lower bins
-    // wave-uniform trip count: the ballots below need every lane
+    // Kept rows are appended once per block and batch: the counts of the waves meet in LDS (alternating tables: a wave may count
+    // the next batch while another still reads this one), one thread takes room for all.  An atomic per wave, on one counter, is a
+    // queue of 3700 where kept rows are spread over the columns: 1.9 million rows took 38 us that way, 18 300 kept.
+    __shared__ uint32_t s_kept[2][kWaves], s_at;
+    uint32_t turn = 0;
+    // block-uniform trip count: the ballots and barriers below need every lane
     while (cw.live()) {
         const uint32_t base = (uint32_t)cw.base;
         // the next batch is requested before this one is worked on
@@ -863,8 +952,6 @@ __global__ __launch_bounds__(kBlock) void pareto_filter_kernel(const double *__r
             for (uint32_t u = 0; u < U; ++u)
                 rn[u] = load_raw<true, MAXC>(x, y, f, (uint32_t)cw.base + threadIdx.x + u * kBlock, (uint32_t)cw.end);
         }
-        // Kept rows are rare and come in clusters: the wave counts them over the whole batch and appends them
-        // with one atomic (a wave that waits for one atomic per row slot waits several memory round trips).
         uint32_t keep_bits = 0, total = 0, before[U];
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
@@ -875,10 +962,19 @@ __global__ __launch_bounds__(kBlock) void pareto_filter_kernel(const double *__r
             total += (uint32_t)__popcll(mask);
             keep_bits |= keep ? 1u << u : 0u;
         }
-        if (total) {                                    // wave-uniform
-            uint32_t at = 0;
-            if (lane == 0) at = atomicAdd(&sc->counters[0], total);
-            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        if (lane == 0) s_kept[turn][threadIdx.x / kWave] = total;
+        __syncthreads();
+        uint32_t at = 0, block_total = 0;
+#pragma unroll
+        for (uint32_t wv = 0; wv < kWaves; ++wv) {
+            at += wv < threadIdx.x / kWave ? s_kept[turn][wv] : 0u;
+            block_total += s_kept[turn][wv];
+        }
+        turn ^= 1u;
+        if (block_total) {                              // block-uniform
+            if (threadIdx.x == 0) s_at = atomicAdd(&sc->counters[0], block_total);
+            __syncthreads();
+            at += s_at;
 #pragma unroll
             for (uint32_t u = 0; u < U; ++u) {
                 if ((keep_bits >> u) & 1u) {
@@ -935,33 +1031,29 @@ __global__ __launch_bounds__(kBlock) void pareto_filter_kernel(const double *__r
 }
 
 // LDS of the finishing kernel.
-constexpr uint16_t kDeadBit = 0x8000;
-static_assert(kBins <= kDeadBit, "a bin number and the flag share 16 bits");
 struct FinishLds {
-    union {
-        struct {
-            uint32_t off[padded_size<kPerFinish>()];    // first survivor slot per bin (exclusive scan of the bin counts)
-            uint32_t foff[padded_size<kPerFinish>()];   // front members per bin, then their exclusive scan
-        };
-        // before the bins are counted: per bin, the least x among its survivors with the bin's least y
-        uint64_t rep[kBins];
-    };
+    uint32_t off[padded_size<kPerFinish>()];    // first survivor slot per bin (exclusive scan of the bin counts)
+    uint32_t foff[padded_size<kPerFinish>()];   // front members per bin, then their exclusive scan
     uint32_t cur[kBins];                        // fill level per bin while grouping; then the list of front members
     uint32_t tmp[kFinishThreads / kWave];
     uint64_t tmp64[kFinishThreads / kWave];
     union {
         struct {
             uint64_t kx[kStage], ky[kStage];    // staged survivor records, grouped by bin
+            uint32_t row[kStage];
         };
-        // before anything is staged: per bin, the least y among the survivors of strictly lower bins (padded table)
-        uint64_t lower[padded_size<kPerFinish>()];
+        // before anything is staged: per bin, the least y among the survivors of strictly lower bins (padded table), and the
+        // least x among its survivors with the bin's least y
+        struct {
+            uint64_t lower[padded_size<kPerFinish>()], rep[kBins];
+        };
     };
-    uint32_t row[kStage];
-    uint16_t bin[kStage];                       // bin of the record; kDeadBit: a survivor of a lower bin dominates it
+    uint16_t bin[kStage];
     uint8_t flag[kStage];
-    uint32_t nfront, first, last, is_last;
+    uint32_t nfront, first, last, alive, is_last;
     uint32_t part_base[kWave], part_lo[kWave], part_cnt[kWave];
     uint64_t rng[2];
+    Pair range[kFinishThreads / kWave];
 };
 
 // The front among `cnt` survivor records staged in LDS, grouped by bin: record i of bin b sits at
@@ -983,9 +1075,9 @@ __device__ inline uint32_t staged_front_by(FinishLds &L, uint32_t cnt, uint32_t 
     for (uint32_t q = t / group; q < cnt_pad; q += q_step) {
         const bool live = q < cnt;
         const uint64_t kx = live ? L.kx[q] : 0, ky = live ? L.ky[q] : 0;
-        const uint32_t bq = live ? L.bin[q] : 0, b = bq & (kDeadBit - 1);
-        bool dom = (bq & kDeadBit) != 0;            // then its own bin need not be searched
-        const uint32_t beg = live ? L.off[padded<P>(b)] - base : 0, end = live && !dom ? L.off[padded<P>(b + 1)] - base : beg;
+        const uint32_t b = live ? L.bin[q] : 0;
+        bool dom = false;
+        const uint32_t beg = live ? L.off[padded<P>(b)] - base : 0, end = live ? L.off[padded<P>(b + 1)] - base : beg;
         for (uint32_t j = beg + sub; j < end; j += 4 * group) {
             uint64_t jx[4], jy[4];
 #pragma unroll
@@ -1015,7 +1107,7 @@ __device__ inline uint32_t staged_front_by(FinishLds &L, uint32_t cnt, uint32_t 
         const bool live = qf < nf;
         const uint32_t q = live ? L.cur[qf] : 0;
         const uint64_t kx = live ? L.kx[q] : 0, ky = live ? L.ky[q] : 0;
-        const uint32_t b = live ? L.bin[q] & (kDeadBit - 1) : 0, i = live ? L.row[q] : 0;
+        const uint32_t b = live ? L.bin[q] : 0, i = live ? L.row[q] : 0;
         const uint32_t beg = live ? L.off[padded<P>(b)] - base : 0, end = live ? L.off[padded<P>(b + 1)] - base : 0;
         uint32_t rank = 0;                          // front members of the bin that come before this one
         for (uint32_t j = beg + sub; j < end; j += 4 * group) {
@@ -1082,9 +1174,8 @@ __device__ inline uint32_t unstaged_front(FinishLds &L, const ParetoWs &w, const
         const bool live = k < cnt;
         const uint32_t g = g_lo + (live ? k : 0), q = w.grouped[g];
         const uint64_t kx = w.skx[q], ky = w.sky[q];
-        const uint32_t b = bin(kx), beg = L.off[padded<P>(b)];
-        bool dom = w.dead[q] != 0;                      // then its own bin need not be searched
-        const uint32_t end = dom ? beg : L.off[padded<P>(b + 1)];
+        const uint32_t b = bin(kx), beg = L.off[padded<P>(b)], end = L.off[padded<P>(b + 1)];
+        bool dom = false;
         for (uint32_t j = beg + sub; j < end; j += 2 * group) {
             const uint32_t j1 = j + group < end ? j + group : beg;       // past the end: the first member again
             const uint32_t q0 = w.grouped[j], q1 = w.grouped[j1];
@@ -1121,56 +1212,131 @@ __device__ inline uint32_t unstaged_front(FinishLds &L, const ParetoWs &w, const
     return L.foff[padded<P>(kBins)];
 }
 
-// A front of more than kStage survivors, finished by the n_parts blocks of the launch that call this (part =
-// 0 .. n_parts - 1).  Bins are independent until positions in the output are handed out, so each part takes a
-// run of consecutive bins that holds about m / n_parts survivors (bin b belongs to part floor(first survivor
-// slot of b * n_parts / m)), finds the front members among them, and writes their rows, in order, to the
-// workspace from its first survivor slot on.  No part waits for
-// another: each ends by taking a ticket, and the part that draws the last one lines the parts' runs up in
-// the output.
-constexpr uint32_t kLargeParts = 64;                    // blocks that finish a large front (the finishing block is one)
-static_assert(kLargeParts <= kWave, "the last part scans the parts' counts in one wave");
-static_assert(kLargeParts <= sizeof(SelectScratch::part_cnt) / sizeof(uint32_t), "one scratch entry per part");
-__device__ void pareto_large_front(FinishLds &L, const ParetoWs &w, SelectScratch *sc, const Binning &bin, uint32_t m,
-                                   uint32_t part, uint32_t n_parts, uint64_t *out_idx, uint64_t capacity,
-                                   uint64_t *out_count) {
-    constexpr uint32_t P = kPerFinish, NT = kFinishThreads;
+// The front among up to kStage records held by the threads of the finishing block (record q of thread t is
+// there when bit q of live is set; its row is row_of(q)); the tables are in their neutral states and the
+// block has met since.  Any binning will do that is fine where the records are.  Calls emit(position, row) for every front
+// member, position = its rank by (x, y, row), and returns their number.
+template <typename RowOf, typename Emit>
+__device__ inline uint32_t finish_in_lds(FinishLds &L, const Binning &bin, const uint64_t (&rx)[kStage / kFinishThreads],
+                                         const uint64_t (&ry)[kStage / kFinishThreads], RowOf &&row_of, uint32_t live,
+                                         Emit &&emit) {
+    static_assert(kFinishThreads == 1024, "kPerFinish assumes 1024 threads");
+    constexpr uint32_t P = kPerFinish, PER = kStage / kFinishThreads;
     const uint32_t t = threadIdx.x;
-    // One pass over all survivors: survivors per bin and the least y per bin, both in LDS (the latter where
-    // records are staged afterwards).  Four records are requested at a time.
+    // Survivors that are dominated for sure are dropped first: those with a survivor of a strictly lower bin at or below their y,
+    // and those that their own bin's representative dominates -- the survivor with the bin's least y (of those,
+    // the least x); rows often tie in x, and then the representative settles all of them but the ties in y.
+    // Tables: least y per bin in the LDS that the records are staged in afterwards, then its exclusive
+    // prefix-min; the representatives' x in the LDS of the bin counts.
 #pragma unroll
-    for (uint32_t q = 0; q < P; ++q) {
-        const uint32_t i = q * NT + t;
+    for (uint32_t q = 0; q < PER; ++q)
+        if ((live >> q) & 1u) atomicMin((unsigned long long *)&L.lower[padded<P>(bin(rx[q]))], (unsigned long long)ry[q]);
+    __syncthreads();
+    uint32_t least = 0;                                 // bit q: the record has its own bin's least y
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q) {
+        const uint32_t b = bin(rx[q]);
+        const bool is = ((live >> q) & 1u) && ry[q] == L.lower[padded<P>(b)];
+        if (is) atomicMin((unsigned long long *)&L.rep[b], (unsigned long long)rx[q]);
+        least |= is ? 1u << q : 0u;
+    }
+    __syncthreads();
+    scan_min_excl<kFinishThreads>(L.lower, L.tmp64);
+    uint32_t alive = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q) {
+        const uint32_t b = bin(rx[q]);
+        const uint64_t rep_x = L.rep[b];
+        const bool by_rep = rep_x <= rx[q] && (rep_x < rx[q] || !((least >> q) & 1u));
+        const bool is = ((live >> q) & 1u) && ry[q] < L.lower[padded<P>(b)] && !by_rep;
+        if (is) atomicAdd(&L.off[padded<P>(b)], 1u);
+        alive |= is ? 1u << q : 0u;
+    }
+    __syncthreads();                                    // both tables have been read by everyone: records may be staged from here on
+    scan_sum_excl<kFinishThreads, true>(L.off, L.tmp);
+    const uint32_t m_alive = L.off[padded<P>(kBins)];
+    // records staged in LDS, grouped by bin
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q) {
+        if ((alive >> q) & 1u) {
+            const uint32_t b = bin(rx[q]), pos = L.off[padded<P>(b)] + atomicAdd(&L.cur[b], 1u);
+            L.kx[pos] = rx[q]; L.ky[pos] = ry[q]; L.row[pos] = row_of(q); L.bin[pos] = (uint16_t)b;
+        }
+    }
+    return staged_front(L, m_alive, 0, 0, kBins - 1, emit);
+}
+
+__device__ inline void finish_tables_neutral(FinishLds &L) {
+    constexpr uint32_t P = kPerFinish;
+    for (uint32_t i = threadIdx.x; i < padded_size<P>(); i += kFinishThreads) L.lower[i] = kNone;
+#pragma unroll
+    for (uint32_t q = 0; q < kPerFinish; ++q) {
+        const uint32_t i = q * kFinishThreads + threadIdx.x;
+        L.rep[i] = kNone;
+        L.cur[i] = 0;
         L.off[padded<P>(i)] = 0;
         L.foff[padded<P>(i)] = 0;
-        L.cur[i] = 0;
     }
-    for (uint32_t i = t; i < padded_size<P>(); i += NT) L.lower[i] = kNone;
+    if (threadIdx.x == 0) L.nfront = 0;
+}
+
+// More kept rows than one block takes alone are finished by the n_parts blocks of the launch (part =
+// 0 .. n_parts - 1).  Bins are independent until positions in the output are handed out, so each part takes a
+// run of consecutive bins that holds about m / n_parts kept rows (bin b belongs to part floor(first kept-row
+// slot of b * n_parts / m)), drops what a kept row of a lower bin dominates (large_survivors), finds the front members among
+// the rest, and writes their rows, in order, to the workspace from its first slot on.  No part waits for
+// another: each ends by taking a ticket, and the part that draws the last one lines the parts' runs up in
+// the output (large_gather).
+// Bound by latency: two passes over the kept rows' keys and a dozen steps between barriers.  8 500 kept rows, front of 2 820:
+// 28 us; 74 us with three passes, dominated records staged as well and the parts' runs copied one after the other.
+constexpr uint32_t kLargeParts = 64;                    // blocks that finish a large front (the finishing block is one)
+constexpr uint32_t kLargeBatch = 10;                    // records per thread requested at a time
+static_assert(kLargeParts <= kWave, "the last part scans the parts' counts in one wave");
+static_assert(kLargeParts <= sizeof(SelectScratch::part_cnt) / sizeof(uint32_t), "one scratch entry per part");
+struct LargePart {
+    uint32_t b_lo, b_hi;        // the part's bins (b_lo > b_hi: none; non-empty ones in between are all its own)
+    uint32_t g_lo;              // its first slot
+    uint32_t n_alive;           // its survivors: their positions are at w.staged[g_lo ..], their counts per bin in L.cur
+};
+// The tables must be in their neutral states, and the block has met since.
+__device__ inline LargePart large_survivors(FinishLds &L, const ParetoWs &w, const Binning &bin, uint32_t m, uint32_t part,
+                                            uint32_t n_parts) {
+    constexpr uint32_t P = kPerFinish, NT = kFinishThreads, B = kLargeBatch;
+    const uint32_t t = threadIdx.x, lane = t % kWave;
+    const bool held = m <= B * NT;                      // one batch: the second pass finds the keys in registers
     if (t == 0) {
         L.first = kBins;
         L.last = 0;
+        L.alive = 0;
     }
-    __syncthreads();
-    for (uint32_t q0 = t; q0 < m; q0 += 4 * NT) {
-        uint64_t kx[4], ky[4];
+    uint64_t kx[B], ky[B];
+    auto request = [&](uint32_t q0) {
 #pragma unroll
-        for (uint32_t u = 0; u < 4; ++u) {
-            const uint32_t q = q0 + u * NT < m ? q0 + u * NT : q0;
+        for (uint32_t u = 0; u < B; ++u) {
+            const uint32_t q = q0 + u * NT < m ? q0 + u * NT : 0u;
             kx[u] = w.skx[q];
             ky[u] = w.sky[q];
         }
+    };
+    request(t);
+    __syncthreads();
+    // One pass over all kept rows: rows per bin and the least y per bin, both in LDS (the latter where
+    // records are staged afterwards).
+    for (uint32_t q0 = t; q0 < m;) {
 #pragma unroll
-        for (uint32_t u = 0; u < 4; ++u) {
+        for (uint32_t u = 0; u < B; ++u) {
             if (q0 + u * NT < m) {
                 const uint32_t b = padded<P>(bin(kx[u]));
                 atomicAdd(&L.off[b], 1u);
                 atomicMin((unsigned long long *)&L.lower[b], (unsigned long long)ky[u]);
             }
         }
+        q0 += B * NT;
+        if (q0 < m) request(q0);
     }
     __syncthreads();
     scan_sum_excl<NT, true>(L.off, L.tmp);              // entry kBins = m
-    scan_min_excl<NT>(L.lower, L.tmp64);                // least y among the survivors of strictly lower bins
+    scan_min_excl<NT>(L.lower, L.tmp64);                // least y among the kept rows of strictly lower bins
 #pragma unroll
     for (uint32_t q = 0; q < P; ++q) {
         const uint32_t i = q * NT + t, off = L.off[padded<P>(i)];
@@ -1180,101 +1346,109 @@ __device__ void pareto_large_front(FinishLds &L, const ParetoWs &w, SelectScratc
         }
     }
     __syncthreads();
-    const uint32_t b_lo = L.first, b_hi = L.last;       // this part's bins (non-empty ones in between are all its own)
-    // Which of the part's survivors a survivor of a lower bin dominates: a second pass, before anything is
-    // staged over the table.
-    if (b_lo <= b_hi) {
-        for (uint32_t q0 = t; q0 < m; q0 += 4 * NT) {
-            uint64_t kx[4];
+    LargePart r{L.first, L.last, 0, 0};
+    if (r.b_lo > r.b_hi) return r;                      // block-uniform
+    r.g_lo = L.off[padded<P>(r.b_lo)];
+    // The part's kept rows that no kept row of a lower bin dominates: listed in the workspace, counted per bin.
+    auto own = [&](uint32_t b) { return b >= r.b_lo && b <= r.b_hi; };
+    for (uint32_t q0 = t; q0 < (m + NT - 1) / NT * NT; q0 += B * NT) {          // wave-uniform trip count for the ballots
+        if (!held) {                                    // block-uniform
 #pragma unroll
-            for (uint32_t u = 0; u < 4; ++u) kx[u] = w.skx[q0 + u * NT < m ? q0 + u * NT : q0];
+            for (uint32_t u = 0; u < B; ++u) kx[u] = w.skx[q0 + u * NT < m ? q0 + u * NT : 0u];
 #pragma unroll
-            for (uint32_t u = 0; u < 4; ++u) {
-                const uint32_t q = q0 + u * NT, b = bin(kx[u]);
-                if (q < m && b >= b_lo && b <= b_hi) w.dead[q] = w.sky[q] >= L.lower[padded<P>(b)] ? 1 : 0;
+            for (uint32_t u = 0; u < B; ++u)
+                if (q0 + u * NT < m && own(bin(kx[u]))) ky[u] = w.sky[q0 + u * NT];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < B; ++u) {
+            const uint32_t b = bin(kx[u]);
+            const bool alive = q0 + u * NT < m && own(b) && ky[u] < L.lower[padded<P>(b)];
+            const uint64_t mask = __ballot(alive);
+            if (mask == 0) continue;                    // wave-uniform
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&L.alive, (uint32_t)__popcll(mask));
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(mask & ((1ull << lane) - 1));
+            if (alive) {
+                w.staged[r.g_lo + at] = q0 + u * NT;
+                atomicAdd(&L.cur[b], 1u);
             }
         }
     }
     __syncthreads();
-    uint32_t g_lo = 0, n_front = 0;
-    if (b_lo <= b_hi) {
-        g_lo = L.off[padded<P>(b_lo)];
-        auto emit = [&](uint32_t pos, uint32_t row) { w.staged[g_lo + n_front + pos] = row; };
-        // In rounds: each takes as many of the part's bins as fit the staging arrays (a single bin that does
-        // not fit is finished in the workspace instead).  A part with one round picks its survivors out of
-        // one pass over all of them; a part with more first groups its survivors by bin in the workspace, in
-        // one such pass, and every round then copies its stretch.  Four keys are requested at a time: the
-        // pass is a chain of load latencies otherwise.
-        const bool grouped = L.off[padded<P>(b_hi + 1)] - g_lo > kStage;
-        if (grouped) {
-            for (uint32_t q0 = t; q0 < m; q0 += 4 * NT) {
-                uint64_t kx[4];
+    r.n_alive = L.alive;
+    return r;
+}
+
+// The part's front when its survivors do not fit the staging arrays: they are grouped by bin in the workspace, and then
+// finished in rounds that take as many of the part's bins as fit (a single bin that does not fit is finished in the workspace
+// instead).  Returns the number of members, whose rows are at w.staged[g_lo ..] in order.
+__device__ inline uint32_t large_rounds(FinishLds &L, const ParetoWs &w, const Binning &bin, const LargePart &part) {
+    constexpr uint32_t P = kPerFinish, NT = kFinishThreads;
+    const uint32_t t = threadIdx.x, g_lo = part.g_lo, b_hi = part.b_hi;
+    uint32_t n_front = 0;
+    // slots per bin, of the survivors: slot 0 is the part's first
 #pragma unroll
-                for (uint32_t u = 0; u < 4; ++u) kx[u] = w.skx[q0 + u * NT < m ? q0 + u * NT : q0];
-#pragma unroll
-                for (uint32_t u = 0; u < 4; ++u) {
-                    const uint32_t q = q0 + u * NT, b = bin(kx[u]);
-                    if (q < m && b >= b_lo && b <= b_hi) w.grouped[L.off[padded<P>(b)] + atomicAdd(&L.cur[b], 1u)] = q;
-                }
-            }
-        }
-        for (uint32_t r_lo = b_lo; r_lo <= b_hi;) {
-            __syncthreads();                            // the previous round is done with the tables
-            if (t == 0) {
-                L.last = r_lo;
-                L.nfront = 0;
-            }
-            const uint32_t base = L.off[padded<P>(r_lo)];
-#pragma unroll
-            for (uint32_t q = 0; q < P; ++q) {
-                const uint32_t i = q * NT + t;
-                L.foff[padded<P>(i)] = 0;
-                L.cur[i] = 0;
-            }
-            __syncthreads();
-#pragma unroll
-            for (uint32_t q = 0; q < P; ++q) {
-                const uint32_t i = q * NT + t;
-                if (i > r_lo && i <= b_hi && L.off[padded<P>(i + 1)] - base <= kStage) atomicMax(&L.last, i);
-            }
-            __syncthreads();
-            const uint32_t r_hi = L.last, cnt = L.off[padded<P>(r_hi + 1)] - base;
-            uint32_t nf;
-            if (cnt <= kStage && grouped) {
-                for (uint32_t i = t; i < cnt; i += NT) {
-                    const uint32_t q = w.grouped[base + i];
-                    const uint64_t kx = w.skx[q];
-                    L.kx[i] = kx;
-                    L.ky[i] = w.sky[q];
-                    L.row[i] = w.surv[q];
-                    L.bin[i] = (uint16_t)(bin(kx) | (w.dead[q] ? kDeadBit : 0));
-                }
-                nf = staged_front(L, cnt, base, r_lo, r_hi, emit);
-            } else if (cnt <= kStage) {
-                for (uint32_t q0 = t; q0 < m; q0 += 4 * NT) {
-                    uint64_t kx[4];
-#pragma unroll
-                    for (uint32_t u = 0; u < 4; ++u) kx[u] = w.skx[q0 + u * NT < m ? q0 + u * NT : q0];
-#pragma unroll
-                    for (uint32_t u = 0; u < 4; ++u) {
-                        const uint32_t q = q0 + u * NT, b = bin(kx[u]);
-                        if (q < m && b >= r_lo && b <= r_hi) {
-                            const uint32_t pos = L.off[padded<P>(b)] - base + atomicAdd(&L.cur[b], 1u);
-                            L.kx[pos] = kx[u];
-                            L.ky[pos] = w.sky[q];
-                            L.row[pos] = w.surv[q];
-                            L.bin[pos] = (uint16_t)(b | (w.dead[q] ? kDeadBit : 0));
-                        }
-                    }
-                }
-                nf = staged_front(L, cnt, base, r_lo, r_hi, emit);
-            } else {
-                nf = unstaged_front(L, w, bin, r_lo, r_hi, emit);
-            }
-            n_front += nf;
-            r_lo = r_hi + 1;
-        }
+    for (uint32_t q = 0; q < P; ++q) {
+        const uint32_t i = q * NT + t;
+        L.off[padded<P>(i)] = L.cur[i];
+        L.cur[i] = 0;
     }
+    __syncthreads();
+    scan_sum_excl<NT, true>(L.off, L.tmp);
+    for (uint32_t i = t; i < part.n_alive; i += NT) {
+        const uint32_t q = w.staged[g_lo + i], b = bin(w.skx[q]);
+        w.grouped[g_lo + L.off[padded<P>(b)] + atomicAdd(&L.cur[b], 1u)] = q;
+    }
+    const ParetoWs part_ws{w.skx, w.sky, w.surv, w.staged, w.grouped + g_lo, w.on_front + g_lo};
+    auto emit = [&](uint32_t pos, uint32_t row) { w.staged[g_lo + n_front + pos] = row; };
+    for (uint32_t r_lo = part.b_lo; r_lo <= b_hi;) {
+        __syncthreads();                                // the list has been read; the previous round is done with the tables
+        if (t == 0) {
+            L.last = r_lo;
+            L.nfront = 0;
+        }
+        const uint32_t base = L.off[padded<P>(r_lo)];
+#pragma unroll
+        for (uint32_t q = 0; q < P; ++q) {
+            const uint32_t i = q * NT + t;
+            L.foff[padded<P>(i)] = 0;
+            L.cur[i] = 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < P; ++q) {
+            const uint32_t i = q * NT + t;
+            if (i > r_lo && i <= b_hi && L.off[padded<P>(i + 1)] - base <= kStage) atomicMax(&L.last, i);
+        }
+        __syncthreads();
+        const uint32_t r_hi = L.last, cnt = L.off[padded<P>(r_hi + 1)] - base;
+        uint32_t nf;
+        if (cnt <= kStage) {
+            for (uint32_t i = t; i < cnt; i += NT) {
+                const uint32_t q = part_ws.grouped[base + i];
+                const uint64_t kx = w.skx[q];
+                const uint32_t b = bin(kx), pos = L.off[padded<P>(b)] - base + atomicAdd(&L.cur[b], 1u);
+                L.kx[pos] = kx;
+                L.ky[pos] = w.sky[q];
+                L.row[pos] = w.surv[q];
+                L.bin[pos] = (uint16_t)b;
+            }
+            nf = staged_front(L, cnt, base, r_lo, r_hi, emit);
+        } else {
+            nf = unstaged_front(L, part_ws, bin, r_lo, r_hi, emit);
+        }
+        n_front += nf;
+        r_lo = r_hi + 1;
+    }
+    return n_front;
+}
+
+// Draws the part's ticket; the block with the last one copies all parts' runs to the output.
+__device__ inline void large_gather(FinishLds &L, const ParetoWs &w, SelectScratch *sc, uint32_t part, uint32_t n_parts,
+                                    uint32_t g_lo, uint32_t n_front, uint64_t *out_idx, uint64_t capacity,
+                                    uint64_t *out_count) {
+    constexpr uint32_t NT = kFinishThreads;
+    const uint32_t t = threadIdx.x, lane = t % kWave;
     if (t == 0) {
         sc->part_lo[part] = g_lo;
         sc->part_cnt[part] = n_front;
@@ -1304,98 +1478,35 @@ __device__ void pareto_large_front(FinishLds &L, const ParetoWs &w, SelectScratc
         }
     }
     __syncthreads();
-    for (uint32_t p = 0; p < n_parts; ++p) {
-        const uint32_t c = L.part_cnt[p], lo = L.part_lo[p];
-        const uint64_t base = L.part_base[p];
-        for (uint32_t i0 = t; i0 < c; i0 += 8 * NT) {   // eight loads in flight per thread
-            uint32_t v[8];
+    // Every wave copies the runs of kPerWave parts side by side, eight loads in flight (one part after the other is a chain of 64
+    // memory latencies: 36 of 62 us for a front of 2800 rows).
+    constexpr uint32_t kPerWave = kLargeParts / (NT / kWave), kDeep = 8 / kPerWave;
+    static_assert(kPerWave * (NT / kWave) == kLargeParts && kPerWave * kDeep == 8, "all parts, eight loads");
+    uint32_t most = 0;
 #pragma unroll
-            for (uint32_t u = 0; u < 8; ++u) v[u] = w.staged[lo + (i0 + u * NT < c ? i0 + u * NT : i0)];
+    for (uint32_t j = 0; j < kPerWave; ++j) {
+        const uint32_t c = L.part_cnt[t / kWave * kPerWave + j];
+        most = c > most ? c : most;
+    }
+    for (uint32_t i0 = lane; i0 < most; i0 += kDeep * kWave) {
+        uint32_t v[kPerWave][kDeep];
 #pragma unroll
-            for (uint32_t u = 0; u < 8; ++u) {
-                const uint32_t i = i0 + u * NT;
-                if (i < c && base + i < capacity) out_idx[base + i] = v[u];
+        for (uint32_t j = 0; j < kPerWave; ++j) {
+            const uint32_t p = t / kWave * kPerWave + j, c = L.part_cnt[p], lo = L.part_lo[p];
+#pragma unroll
+            for (uint32_t u = 0; u < kDeep; ++u) v[j][u] = c ? w.staged[lo + (i0 + u * kWave < c ? i0 + u * kWave : c - 1)] : 0u;
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < kPerWave; ++j) {
+            const uint32_t p = t / kWave * kPerWave + j, c = L.part_cnt[p];
+            const uint64_t base = L.part_base[p];
+#pragma unroll
+            for (uint32_t u = 0; u < kDeep; ++u) {
+                const uint32_t i = i0 + u * kWave;
+                if (i < c && base + i < capacity) out_idx[base + i] = v[j][u];
             }
         }
     }
-}
-
-// The front among up to kStage records held by the threads of the finishing block (record q of thread t is there when
-// live[q]); L.lower, L.rep and L.cur are in their neutral states and the block has met since.
-__device__ inline void finish_in_lds(FinishLds &L, const Binning &bin, const uint64_t (&rx)[kStage / kFinishThreads],
-                                     const uint64_t (&ry)[kStage / kFinishThreads],
-                                     const uint32_t (&rr)[kStage / kFinishThreads],
-                                     const bool (&live)[kStage / kFinishThreads], uint64_t *out_idx, uint64_t capacity,
-                                     uint64_t *out_count) {
-    static_assert(kFinishThreads == 1024, "kPerFinish assumes 1024 threads");
-    constexpr uint32_t P = kPerFinish, kPer = kStage / kFinishThreads;
-    const uint32_t t = threadIdx.x;
-    // Survivors that are dominated for sure are dropped first: those with a survivor of a strictly lower bin at or below their y,
-    // and those that their own bin's representative dominates -- the survivor with the bin's least y (of those,
-    // the least x); rows often tie in x, and then the representative settles all of them but the ties in y.
-    // Tables: least y per bin in the LDS that the records are staged in afterwards, then its exclusive
-    // prefix-min; the representatives' x in the LDS of the bin counts.
-    uint32_t rb[kPer];
-#pragma unroll
-    for (uint32_t q = 0; q < kPer; ++q) {
-        rb[q] = bin(rx[q]);
-        if (live[q]) atomicMin((unsigned long long *)&L.lower[padded<P>(rb[q])], (unsigned long long)ry[q]);
-    }
-    __syncthreads();
-    uint64_t bin_y[kPer];                               // least y of the record's own bin
-#pragma unroll
-    for (uint32_t q = 0; q < kPer; ++q) {
-        bin_y[q] = L.lower[padded<P>(rb[q])];
-        if (live[q] && ry[q] == bin_y[q]) atomicMin((unsigned long long *)&L.rep[rb[q]], (unsigned long long)rx[q]);
-    }
-    __syncthreads();
-    scan_min_excl<kFinishThreads>(L.lower, L.tmp64);
-    bool alive[kPer];
-#pragma unroll
-    for (uint32_t q = 0; q < kPer; ++q) {
-        const uint64_t rep_x = L.rep[rb[q]];
-        const bool by_rep = rep_x <= rx[q] && (rep_x < rx[q] || bin_y[q] < ry[q]);     // bin_y <= ry always
-        alive[q] = live[q] && ry[q] < L.lower[padded<P>(rb[q])] && !by_rep;
-    }
-    __syncthreads();                                    // both tables have been read by everyone
-#pragma unroll
-    for (uint32_t q = 0; q < kPerFinish; ++q) {
-        const uint32_t i = q * kFinishThreads + t;
-        L.off[padded<P>(i)] = 0;
-        L.foff[padded<P>(i)] = 0;
-    }
-    if (t == 0) L.off[padded<P>(kBins)] = 0;
-    __syncthreads();
-#pragma unroll
-    for (uint32_t q = 0; q < kPer; ++q)
-        if (alive[q]) atomicAdd(&L.off[padded<P>(rb[q])], 1u);
-    __syncthreads();                                    // records may be staged from here on
-    scan_sum_excl<kFinishThreads, true>(L.off, L.tmp);
-    const uint32_t m_alive = L.off[padded<P>(kBins)];
-    // records staged in LDS, grouped by bin
-#pragma unroll
-    for (uint32_t q = 0; q < kPer; ++q) {
-        if (alive[q]) {
-            const uint32_t pos = L.off[padded<P>(rb[q])] + atomicAdd(&L.cur[rb[q]], 1u);
-            L.kx[pos] = rx[q]; L.ky[pos] = ry[q]; L.row[pos] = rr[q]; L.bin[pos] = (uint16_t)rb[q];
-        }
-    }
-    const uint32_t n_front = staged_front(L, m_alive, 0, 0, kBins - 1, [&](uint32_t pos, uint32_t row) {
-        if (pos < capacity) out_idx[pos] = row;
-    });
-    if (t == 0) out_count[0] = n_front;
-}
-
-__device__ inline void finish_tables_neutral(FinishLds &L) {
-    constexpr uint32_t P = kPerFinish;
-    for (uint32_t i = threadIdx.x; i < padded_size<P>(); i += kFinishThreads) L.lower[i] = kNone;
-#pragma unroll
-    for (uint32_t q = 0; q < kPerFinish; ++q) {
-        const uint32_t i = q * kFinishThreads + threadIdx.x;
-        L.rep[i] = kNone;
-        L.cur[i] = 0;
-    }
-    if (threadIdx.x == 0) L.nfront = 0;
 }
 
 // Blocks of the launch: 0 finishes the front; 1 runs a waiting top-k merge (only launched with one); the
@@ -1438,15 +1549,58 @@ __global__ __launch_bounds__(kFinishThreads) void pareto_finish_kernel(ParetoWs 
     const uint32_t m = sc->counters[0];
     finish_tables_neutral(L);                           // while the loads are under way
     const Binning bin = sampled_binning(sc, L.rng);     // its barrier also covers the tables above
-    if (m > kStage) {
-        pareto_large_front(L, w, sc, bin, m, helper ? blockIdx.x - first_helper + 1 : 0, gridDim.x - first_helper + 1,
-                           out_idx, capacity, out_count);
-        return;
-    }
-    bool live[kPer];
+    const bool large = m > kStage;                      // block-uniform
+    const uint32_t part = helper ? blockIdx.x - first_helper + 1 : 0, n_parts = gridDim.x - first_helper + 1;
+    Binning own = bin;
+    LargePart p{0, 0, 0, m};
+    if (large) {
+        p = large_survivors(L, w, bin, m, part, n_parts);
+        if (p.n_alive <= kStage) {
+            // The records, and bins of the part's own for them: its share of the common ones is few, and one of those may hold
+            // hundreds (the lowest ones, for want of lower bins that would prune them).
+            uint64_t lo = kNone, hi = 0;
 #pragma unroll
-    for (uint32_t q = 0; q < kPer; ++q) live[q] = q * kFinishThreads + t < m;
-    finish_in_lds(L, bin, rx, ry, rr, live, out_idx, capacity, out_count);
+            for (uint32_t q = 0; q < kPer; ++q) rr[q] = q * kFinishThreads + t < p.n_alive ? w.staged[p.g_lo + q * kFinishThreads + t] : 0u;
+#pragma unroll
+            for (uint32_t q = 0; q < kPer; ++q) {
+                rx[q] = w.skx[rr[q]];
+                ry[q] = w.sky[rr[q]];
+                rr[q] = w.surv[rr[q]];
+            }
+#pragma unroll
+            for (uint32_t q = 0; q < kPer; ++q) {
+                if (q * kFinishThreads + t >= p.n_alive) continue;
+                lo = min_u64(lo, rx[q]);
+                hi = hi < rx[q] ? rx[q] : hi;
+            }
+            lo = wave_min(lo);
+            hi = ~wave_min(~hi);
+            if (t % kWave == 0) L.range[t / kWave] = Pair{lo, hi};
+            finish_tables_neutral(L);                   // (the tables have been read by everybody)
+            __syncthreads();
+#pragma unroll 1
+            for (uint32_t wv = 0; wv < kFinishThreads / kWave; ++wv) {
+                const Pair o = L.range[wv];
+                lo = min_u64(lo, o.key);
+                hi = hi < o.idx ? o.idx : hi;
+            }
+            if (lo <= hi) own = binning_of(lo, hi);
+        }
+    }
+    uint32_t n_front;
+    if (p.n_alive <= kStage) {                          // (a part without survivors goes through with no live record)
+        uint32_t live = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < kPer; ++q) live |= q * kFinishThreads + t < p.n_alive ? 1u << q : 0u;
+        n_front = finish_in_lds(L, own, rx, ry, [&](uint32_t q) { return rr[q]; }, live, [&](uint32_t pos, uint32_t row) {
+            if (large) w.staged[p.g_lo + pos] = row;
+            else if (pos < capacity) out_idx[pos] = row;
+        });
+    } else {
+        n_front = large_rounds(L, w, bin, p);
+    }
+    if (large) large_gather(L, w, sc, part, n_parts, p.g_lo, n_front, out_idx, capacity, out_count);
+    else if (t == 0) out_count[0] = n_front;
 }
 
 // Selections over at most kStage rows: one launch without sample, filter pass and block partials.  Block 0 takes the
@@ -1517,17 +1671,16 @@ __global__ __launch_bounds__(kFinishThreads) void small_select_kernel(SmallSelec
         r[q] = load_row<true, GUIDE_MAX_CONSTRAINTS>(s.x, s.y, s.f, q * kFinishThreads + t, n);
     finish_tables_neutral(L);
     uint64_t rx[kPer], ry[kPer], lo = kNone;
-    uint32_t rr[kPer];
-    bool live[kPer];
+    uint32_t live = 0;
     Pair best = {kNone, kNone};                         // (y key, x key) of the least y
 #pragma unroll
     for (uint32_t q = 0; q < kPer; ++q) {
-        live[q] = r[q].pass;
-        rx[q] = live[q] ? key_of(r[q].x) : 0;
-        ry[q] = live[q] ? key_of(r[q].y) : 0;
-        rr[q] = q * kFinishThreads + t;
-        lo = live[q] ? min_u64(lo, rx[q]) : lo;
-        if (live[q]) best = pair_min(best, Pair{ry[q], rx[q]});
+        const bool there = r[q].pass;
+        live |= there ? 1u << q : 0u;
+        rx[q] = there ? key_of(r[q].x) : 0;
+        ry[q] = there ? key_of(r[q].y) : 0;
+        lo = there ? min_u64(lo, rx[q]) : lo;
+        if (there) best = pair_min(best, Pair{ry[q], rx[q]});
     }
     lo = wave_min(lo);
     best = wave_min(best);
@@ -1545,7 +1698,9 @@ __global__ __launch_bounds__(kFinishThreads) void small_select_kernel(SmallSelec
         return;
     }
     __syncthreads();                                    // L.tmp64 is used again below
-    finish_in_lds(L, binning_of(lo, best.idx), rx, ry, rr, live, s.out_idx, s.capacity, s.out_count);
+    const uint32_t n_front = finish_in_lds(L, binning_of(lo, best.idx), rx, ry, [&](uint32_t q) { return q * kFinishThreads + t; },
+                                           live, [&](uint32_t pos, uint32_t row) { if (pos < s.capacity) s.out_idx[pos] = row; });
+    if (t == 0) s.out_count[0] = n_front;
 }
 
 __global__ void pareto_empty_kernel(uint64_t *out_count) { out_count[0] = 0; }

@@ -1,0 +1,99 @@
+"""Pareto selections whose kept rows one block does not hold: row samples of either depth, parts with a few survivors, with
+several rounds of them and with one bin too large for LDS, against the oracle (indices: exact)."""
+import numpy as np
+import pytest
+
+from paper_2412_04788_amd import workloads as wl
+from tests import bridge
+from tests.test_gpu_select import _dev, _pareto
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def setup():
+    import torch
+    assert torch.cuda.is_available()
+    return torch, bridge.gpu_context(wl.grid_tiny())
+
+
+def _sample_rows(n):
+    """The rows of the standalone row sample: 16 384 of up to 1.5 million rows, 65 536 of more."""
+    total = 65536 if n > 1_500_000 else 16384
+    k = np.arange(min(total, n), dtype=np.uint64)
+    if n <= total:
+        return k.astype(np.int64)
+    stride = n // total
+    jitter = (((k * np.uint64(2654435761)) & np.uint64(0xFFFFFFFF)) >> np.uint64(8)) % np.uint64(stride)
+    return (k * np.uint64(stride) + k * np.uint64(n - stride * total) // np.uint64(total) + jitter).astype(np.int64)
+
+
+def _check(ora, setup, x, y, fe=None, cons=(), capacity=None):
+    torch, ctx = setup
+    got, m = _pareto(torch, ctx, _dev(torch, x), _dev(torch, y), None if fe is None else _dev(torch, fe),
+                     [(_dev(torch, c), cap) for c, cap in cons], capacity)
+    ok = np.ones(len(x), np.uint8) if fe is None else fe.copy()
+    for c, cap in cons:
+        ok &= (c <= cap).astype(np.uint8)
+    exp = ora.pareto_sweep(x, y, ok)
+    assert m == len(exp)
+    np.testing.assert_array_equal(got, exp if capacity is None else exp[:capacity])
+    return m
+
+
+# one more than a block stages, the rows that a part's threads hold between its passes (10 240) and one more, the sample's depths
+@pytest.mark.parametrize("n, kind", [(n, kind) for n in (4097, 10240, 10241, 16385, 65537) for kind in ("front", "triples", "near", "far")] +
+                         [(400_000, "front"), (400_000, "triples"), (1_500_000, "near"), (1_500_001, "near")])
+def test_fronts_by_size(ora, setup, n, kind):
+    rng = np.random.default_rng(n)
+    if kind == "front":                                 # every row: parts of n / 64 survivors, beyond 262 144 in rounds
+        x = rng.permutation(n) + 1.0
+        y = -x
+    elif kind == "triples":                             # equal points in threes
+        x = (rng.permutation(n) // 3) + 1.0
+        y = 1.0 / x
+    elif kind == "near":                                # a thin front before a cloud, ties in runs
+        u = np.repeat(rng.random(n // 5 + 1), 5)[:n]
+        x = np.exp(9.0 * u - 5.0)
+        y = np.exp(2.0 - 4.0 * u + 0.4 * np.abs(np.repeat(rng.standard_normal(n // 5 + 1), 5)[:n]))
+    else:                                               # most of x in a sliver of its range
+        x = 1.0 + rng.random(n) ** 40
+        y = 2.0 - x + 1e-3 * rng.random(n)
+    _check(ora, setup, x, y)
+    fe = (rng.random(n) < 0.7).astype(np.uint8)
+    c, d = rng.random(n), rng.random(n)
+    _check(ora, setup, x, y, fe, [(c, 0.8)])
+    _check(ora, setup, x, y, fe, [(c, 0.8), (d, 0.9)], capacity=1000)
+
+
+@pytest.mark.parametrize("n", [200_000, 1_600_000])
+def test_survivors_of_one_bin_beyond_the_staging_arrays(ora, setup, n):
+    rng = np.random.default_rng(n + 1)
+    x, y = rng.random(n) * 100.0, rng.random(n) * 100.0
+    odd = np.setdiff1d(np.arange(n), _sample_rows(n))
+    odd = rng.choice(odd, 12_000, replace=False)        # a staircase right of everything that is sampled
+    x[odd] = 1000.0 + odd
+    y[odd] = -1.0 * odd
+    assert _check(ora, setup, x, y) > 8000
+
+
+@pytest.mark.parametrize("n", [100_000, 1_600_000])
+def test_no_sample_row_passes(ora, setup, n):
+    rng = np.random.default_rng(n + 2)
+    x, y = np.round(rng.random(n) * 1000.0, 1), np.round(rng.random(n) * 1000.0, 1)
+    fe = np.ones(n, np.uint8)
+    fe[_sample_rows(n)] = 0
+    _check(ora, setup, x, y, fe)
+    _check(ora, setup, x, y, np.zeros(n, np.uint8))
+
+
+def test_all_rows_in_one_bin_of_an_unsampled_range(ora, setup):
+    # 13 600 kept rows that nothing prunes: tested pair by pair, so not more of them
+    n = 30_000
+    rng = np.random.default_rng(4)
+    fe = np.ones(n, np.uint8)
+    fe[_sample_rows(n)] = 0
+    x = np.round(rng.random(n) * 1000.0, 1)
+    _check(ora, setup, x, 1e6 - 7.0 * x, fe)            # all of them on the front, many equal
+    for x in (np.full(n, np.inf), np.full(n, -np.inf), np.round(rng.random(n), 3)):
+        _check(ora, setup, x, np.round(rng.random(n) * 1000.0, 1), fe)
