@@ -273,11 +273,12 @@ int guide_eval_sampled(guide_ctx *ctx, const guide_space *space, uint64_t seed, 
  * for the request's lifetime; stop at the first that cannot enter); run one
  * pass; advance time by t_pass.  (In a run of decode-only passes, whose times
  * are in arithmetic progression while attention stays on one side of the
- * roofline, the clock advances by the sums of 64 and of 8 passes at a time as
- * long as the last of them starts before the next admissible arrival.  Steps and
- * request-steps count every pass.  Times are at least as close to the exact sums
- * as pass-by-pass addition is and differ from it by its rounding, some 1e-13 of
- * the clock after 10^5 passes; an admission test "arrived by now?" that is
+ * roofline, the clock advances by the sum of all of them at once, up to the pass
+ * that retires a decoder or the least one after which the next admissible
+ * request has arrived.  Steps and request-steps count every pass.  Times are at
+ * least as close to the exact sums as pass-by-pass addition is and differ from
+ * it by its rounding, some 1e-13 of the clock after 10^5 passes; an admission
+ * test "arrived by now?" that is
  * decided within that can fall the other way.)  A configuration's results are
  * the same bits in every list and call.  The pass depends on `scheduler`, the two
  * framework behaviours the paper models (Inference Engine, Step 2):
@@ -290,18 +291,16 @@ int guide_eval_sampled(guide_ctx *ctx, const guide_space *space, uint64_t seed, 
  *                             one decode token for every running request
  *                             (dynamic batching without chunking).
  * With GUIDE_SIM_CLOSED_FORM_RUNS OR-ed into `scheduler`, a run of decode-only
- * passes (every running request decoding, none waiting for prompt chunks) is
- * not stepped: until the first decoder emits its last token or a request that
- * could be admitted has arrived, every pass has the same tokens and a context
- * that grows by one per decoder, so the r passes the stepped loop would run
- * (r = passes before the one that retires a decoder, or the least r whose
- * starting time now + time(r passes) has reached that arrival) are advanced at
- * once with time(r) = r * (pass without attention) + L * (the attention series
- * in closed form, split where attention turns from read bound to compute
- * bound).  Engine steps and request-steps count the same passes; times differ
- * from the stepped simulation by rounding only, so a result can differ from it
- * only where an admission test "arrived by now?" is decided within rounding, as
- * above.
+ * passes (every running request decoding, none waiting for prompt chunks) is by
+ * definition not stepped: until the first decoder emits its last token or a
+ * request that could be admitted has arrived, every pass has the same tokens and
+ * a context that grows by one per decoder, so the r passes the stepped loop would
+ * run are advanced at once with time(r) = r * (pass without attention) + L * (the
+ * attention series in closed form, split where attention turns from read bound
+ * to compute bound).  Engine steps and request-steps count the same passes, and
+ * times differ from the stepped definition by rounding only.  The library
+ * advances runs like this in either case: results are the same bits with and
+ * without the flag.
  * Outputs (DEVICE, n_cfg each): nearest-rank p50 / p99 of TTFT, mean TPOT over
  * requests with n_out > 1, generated tokens / (last finish - first arrival),
  * status (GUIDE_SIM_INFEASIBLE when weights or one request do not fit,

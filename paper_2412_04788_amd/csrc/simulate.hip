@@ -9,11 +9,10 @@
 //     the prefill queue [comp, next) is partially prefilled;
 //   - a request that finished its prompt decodes on every later step, so its
 //     finishing step is known when its prompt completes: decoders live in a
-//     per-lane 4-ary min-heap keyed by finishing step (root in registers, the
-//     rest in LDS as far as it goes), and their number and total context are
-//     two running numbers.
-// A request therefore costs a few pass-time evaluations and O(log n) heap
-// traffic; the steps in between cost an addition to the clock or less.
+//     per-lane queue keyed by finishing step, in LDS as far as it goes, and
+//     their number and total context are two running numbers.
+// A request therefore costs a few pass-time evaluations, a push and a pop;
+// the steps in between are advanced at once.
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -24,21 +23,27 @@ namespace guide {
 
 namespace {
 
-constexpr uint32_t kSimBlock = 256;      // one block per compute unit: the trace is staged once, the rest of LDS holds heaps
+constexpr uint32_t kSimWaves = 8;        // most waves of a block; a block stages the trace once, the rest of its LDS holds queues
+constexpr uint32_t kSimBlock = kSimWaves * kWave;
 constexpr uint32_t kPctBlock = 256;
-constexpr size_t kSimStaticLds = 64;     // the simulation kernel's own static LDS (wave totals)
+constexpr size_t kSimStaticLds = 128;    // the simulation kernel's own static LDS (wave totals)
 
+// A request as the simulation kernel keeps it in LDS; two entries past the last one stand for `none left` (arrival: no
+// number, which compares false with everything).
+struct alignas(16) Request {
+    double arrival;              // at unit rate
+    uint32_t in, out;            // prompt and generated tokens
+};
 struct RequestsLds {
-    double arrival[GUIDE_MAX_REQUESTS];      // at unit rate
-    uint2 len[GUIDE_MAX_REQUESTS];           // prompt and generated tokens
+    Request r[GUIDE_MAX_REQUESTS + 2];
 };
 
 constexpr uint32_t kHeapWidth = 4;     // children per heap node
 constexpr uint32_t kKeyBins = 1024;      // buckets of the expected-concurrency ordering
 // Lists are ordered where that saves more than its four launches (17 us): from 16 requests on, and when lanes share a
-// wave at all.  Ordered / as given, in us: 2000 x 8 101 / 85, 5000 x 8 136 / 129, 5000 x 16 193 / 203, 65 536 x 16 571 / 576,
-// 5000 x 32 352 / 396, 20 000 x 128 1200 / 1446 (stepped); 65 536 x 16 541 / 526, 5000 x 32 279 / 289 (closed form); one lane
-// per wave: the same 636 with 128 requests, and 31 / 13 for one configuration.
+// wave at all.  Ordered / as given, in us, when a heap held the decoders: 5000 x 8 136 / 129, 5000 x 16 193 / 203, 65 536 x 16 571 / 576,
+// 5000 x 32 352 / 396, 20 000 x 128 1200 / 1446; 65 536 x 16 541 / 526, 5000 x 32 279 / 289 under the other scheduler; one lane
+// per wave: the same.
 constexpr uint32_t kOrderRequests = 16;
 
 // Workspace: heap[position][node] (u64 keys), first[cfg][req] and fin[cfg][req] (time of the first and of the
@@ -94,7 +99,8 @@ __global__ __launch_bounds__(kOrderBlock) void sim_order_count_kernel(GridDesc g
                                                                       uint32_t n_req,
                                                                       const uint32_t *__restrict__ cfg_idx,
                                                                       const double *__restrict__ rate_in, uint32_t n_cfg,
-                                                                      SimWs ws, double sum_in, double sum_out) {
+                                                                      SimWs ws, double sum_in, double sum_out,
+                                                                      double unit_rate) {
     __shared__ uint32_t s_n[kKeyBins];
     s_n[threadIdx.x] = 0;
     __syncthreads();
@@ -103,7 +109,7 @@ __global__ __launch_bounds__(kOrderBlock) void sim_order_count_kernel(GridDesc g
         uint32_t v[kNumAxes];
         const bool bad = decode_sim_index(tab->axis_vals, g, cfg_idx[c], v);
         uint32_t b = 0;
-        const double rate = rate_in[c];
+        const double rate = rate_in[c] * unit_rate;                 // requests per second
         if (!bad && rate > 0.0) {
             const guide_hw hw = tab->hw[v[AX_HW]];
             const Coef cf = make_coef(tab->models[v[AX_MODEL]], v[AX_TP], v[AX_WBITS]);
@@ -280,6 +286,188 @@ struct LaneHeap {
     }
 };
 
+// A lane's keys that found no room in LDS: a 4-ary min-heap in global memory, its root in a register; the children of node i
+// are nodes D i + 1 .. D i + D, node j at mem[j - 1].
+struct MemHeap {
+    static constexpr uint32_t kEmpty = ~0u, D = kHeapWidth;
+    uint32_t top, *mem, n;
+    __device__ void push(uint32_t key) {
+        const uint32_t old = top;
+        top = key < old ? key : old;
+        key = key < old ? old : key;
+        uint32_t i = n++;
+        if (i == 0) return;                             // (key is kEmpty then)
+        while (i > D) {
+            const uint32_t par = (i - 1) / D, pk = mem[par - 1];
+            LaneHeap<uint32_t>::wait_here();
+            if (pk <= key) break;
+            mem[i - 1] = pk;
+            i = par;
+        }
+        mem[i - 1] = key;
+    }
+    __device__ void pop() {                             // the last node sinks from the root
+        top = kEmpty;
+        if (--n == 0) return;
+        const uint32_t end = n - 1, last = mem[end];    // positions 0 .. end - 1 are left
+        top = last;
+        uint32_t hole = ~0u;                            // the root
+        for (uint32_t g = 0; g < end;) {
+            uint32_t k[D], at = 0, best;
+#pragma unroll
+            for (uint32_t j = 0; j < D; ++j) k[j] = g + j < end ? mem[g + j] : kEmpty;
+            LaneHeap<uint32_t>::wait_here();
+            best = k[0];
+#pragma unroll
+            for (uint32_t j = 1; j < D; ++j) best = k[j] < best ? k[j] : best;
+#pragma unroll
+            for (uint32_t j = 1; j < D; ++j) at = k[j] == best ? j : at;       // (keys differ; 0 when none of the others is it)
+            if (!(best < last)) break;
+            if (hole == ~0u) top = best; else mem[hole] = best;
+            hole = g + at;
+            g = D * hole + D;
+        }
+        if (hole != ~0u) mem[hole] = last;
+    }
+};
+
+// The decoders of a lane by finishing step when keys have 32 bits.  Keys (step << 10 | slot) lie in slots of the lane's LDS
+// segment in any order, sixteen to a block; the least key of every block is kept beside them, the least of all in a
+// register, and the request of a slot in a table of its own.  A push is two stores and a minimum that nothing waits for;
+// a pop reads the sixteen keys of the block it leaves a hole in and the least keys of the blocks around it, all at once, and
+// takes minima (with more than sixteen blocks, their least keys by sixteens make a third level): an LDS latency or two and no
+// loop, whatever the lane's neighbours do: 700 - 950 cycles a round with the retirement, the push 350 (a 4-ary heap: a latency
+// per level, and every lane waited for the deepest: 700 - 1570 and 430 - 730).  Free slots form a list through the request table.
+// Decoders beyond the segment go to a heap in global memory (MemHeap).
+// Segment: keys[cap], then the blocks' least keys (a multiple of four of them), then those of sixteen blocks each (none or
+// four), then the requests (16 bits each); cap is a multiple of 16, and 0 only in lanes that have nothing to simulate.
+struct SlotQueue {
+    static constexpr uint32_t kEmpty = ~0u, kPer = 16, kNoSlot = 0xFFFFu;
+    // LDS bytes of n blocks, and what each block after the first takes at most beside the first one's
+    static constexpr uint32_t kFirstBytes = kPer * 6 + 16, kMoreBytes = kPer * 6 + 5;
+    static __host__ __device__ uint32_t bytes(uint32_t n) { return n * kPer * 6 + (n + 3) / 4 * 16 + (n > kPer ? 16u : 0u); }
+    static_assert(GUIDE_MAX_REQUESTS <= 4 * kPer * kPer, "four superblocks");
+    uint32_t top;                     // kEmpty when there is none: above every key
+    uint32_t keys, low, req;          // byte offsets of the segment's parts
+    uint32_t cap, used, free_;        // slots; slots ever taken; first of the list of free slots below `used`
+    uint32_t last_group;              // byte offset of the last group of four blocks' least keys
+    uint32_t super_;                  // ... of the least keys of sixteen blocks each; 0: no more than sixteen blocks
+    MemHeap over;                     // the decoders that found no slot: keys step << 10 | request
+    __device__ void init(uint32_t offset, uint32_t blocks, uint32_t *mem) {
+        top = kEmpty;
+        cap = blocks * kPer;
+        keys = offset;
+        low = keys + cap * 4;
+        const uint32_t groups = (blocks + 3) / 4;
+        last_group = low + (groups - 1) * 16;
+        super_ = blocks > kPer ? low + groups * 16 : 0u;
+        req = low + groups * 16 + (blocks > kPer ? 16u : 0u);
+        used = 0;
+        free_ = kNoSlot;
+        over = MemHeap{kEmpty, mem, 0};
+    }
+    __device__ uint32_t due() const { return (top < over.top ? top : over.top) >> 10; }
+    template <typename T>
+    static __device__ T &at(unsigned char *lds, uint32_t offset) { return *(T *)(lds + offset); }
+    // The request of the least key in a slot (anything when there is none).
+    __device__ uint32_t first_request(unsigned char *lds) const {
+        return at<uint16_t>(lds, req + (top == kEmpty ? 0u : (top & 1023u) * 2));
+    }
+    // supers: some lane of the wave has more than sixteen blocks (uniform).
+    __device__ void put(unsigned char *lds, uint32_t step, uint32_t r, bool supers) {
+        const bool reuse = free_ != kNoSlot;
+        const uint32_t slot = reuse ? free_ : used;
+        auto store = [&]() {
+            const uint32_t next = at<uint16_t>(lds, req + slot * 2), key = step << 10 | slot;
+            asm volatile("" ::: "memory");              // a wave's LDS operations are done in program order
+            at<uint32_t>(lds, keys + slot * 4) = key;
+            at<uint16_t>(lds, req + slot * 2) = (uint16_t)r;
+            __hip_atomic_fetch_min(&at<uint32_t>(lds, low + slot / kPer * 4), key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            if (supers && super_)
+                __hip_atomic_fetch_min(&at<uint32_t>(lds, super_ + slot / (kPer * kPer) * 4), key, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WAVEFRONT);
+            free_ = reuse ? next : kNoSlot;
+            used += reuse ? 0u : 1u;
+            top = key < top ? key : top;
+        };
+        if (__ballot(slot == cap) == 0) store();
+        else if (slot == cap) over.push(step << 10 | r);
+        else store();
+    }
+    // Takes the least key out of the slots.  few: no lane of the wave has used more than four blocks (uniform).
+    __device__ void take_slot(unsigned char *lds, bool few, bool supers) {
+        const uint32_t slot = top & 1023u, block = slot / kPer;
+        const uint32_t block_keys = keys + block * (kPer * 4), block_low = low + block * 4;
+        at<uint32_t>(lds, keys + slot * 4) = kEmpty;
+        at<uint32_t>(lds, block_low) = kEmpty;
+        at<uint16_t>(lds, req + slot * 2) = (uint16_t)free_;
+        asm volatile("" ::: "memory");
+        auto min2 = [](uint32_t a, uint32_t b) { return a < b ? a : b; };
+        auto least = [&](const uint4 &v, uint32_t m) { return min2(min2(min2(min2(m, v.x), v.y), v.z), v.w); };
+        uint4 k[kPer / 4];
+#pragma unroll
+        for (uint32_t i = 0; i < kPer / 4; ++i) k[i] = at<uint4>(lds, block_keys + i * 16);
+        uint32_t others;                                // of the other blocks of the superblock
+        if (few) {
+            others = least(at<uint4>(lds, low), kEmpty);
+        } else {
+            const uint32_t group = low + block / kPer * 64;
+            uint4 v[4];
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i) v[i] = at<uint4>(lds, min2(group + i * 16, last_group));
+            others = min2(least(v[1], least(v[0], kEmpty)), least(v[3], least(v[2], kEmpty)));
+        }
+        const uint32_t mine = min2(least(k[1], least(k[0], kEmpty)), least(k[3], least(k[2], kEmpty)));
+        top = min2(mine, others);
+        asm volatile("" ::: "memory");
+        at<uint32_t>(lds, block_low) = mine;
+        if (supers && super_) {
+            at<uint32_t>(lds, super_ + block / kPer * 4) = top;
+            asm volatile("" ::: "memory");
+            top = least(at<uint4>(lds, super_), kEmpty);
+            asm volatile("" ::: "memory");
+        }
+        free_ = slot;
+    }
+    // Takes the decoder out that leaves next and returns its request.  first: first_request() of this moment; spilled: some lane
+    // of the wave has decoders beyond its slots (uniform).
+    __device__ uint32_t take(unsigned char *lds, uint32_t first, bool few, bool supers, bool spilled) {
+        if (!spilled) {
+            take_slot(lds, few, supers);
+            return first;
+        }
+        uint32_t r = first;
+        if (top > over.top) {
+            r = over.top & 1023u;
+            over.pop();
+        } else {
+            take_slot(lds, few, supers);
+        }
+        return r;
+    }
+};
+
+// The same as a heap, its first levels in LDS: for 64-bit keys, and for blocks whose lanes expect more decoders than LDS has
+// slots for.
+template <typename KeyT>
+struct HeapQueue {
+    LaneHeap<KeyT> heap;
+    __device__ void init(unsigned char *lds, uint32_t groups, KeyT *mem) {
+        heap.top = LaneHeap<KeyT>::kEmpty;
+        heap.lds = (KeyT *)lds;
+        heap.mem = mem;
+        heap.cap = groups * kHeapWidth;
+        heap.n = 0;
+    }
+    __device__ KeyT due() const { return heap.top >> 10; }
+    __device__ void put(unsigned char *, KeyT step, uint32_t r, bool) { heap.push(step << 10 | r); }
+    __device__ uint32_t take(unsigned char *, uint32_t, bool, bool, bool) {
+        const uint32_t r = (uint32_t)(heap.top & 1023u);
+        heap.pop();
+        return r;
+    }
+};
+
 // Pass times of one configuration with the number of layers multiplied into the layers' coefficients once.
 struct LaneTimes {
     double c[N_LINEAR], m0[N_LINEAR], m1[N_LINEAR];
@@ -340,59 +528,51 @@ struct TraceSums {
     uint32_t longest;       // most prompt + generated tokens of one request
 };
 
-// One configuration per lane, `lanes` of them per wave (64, or fewer when there are not enough configurations for
-// the chip's waves: the paths of the lanes of a wave are executed one after the other, so fewer lanes make a
-// shorter instruction stream, which is what bounds the kernel: every SIMD holds one wave).
+// One configuration per lane, `lanes` of them per wave (64 or 1).
 // A round of the loop does at most one of each kind of thing: one decoder leaves, one request enters, one prompt chunk is
 // scheduled, a pass with prompts runs, one prompt turns into a decoder, a run of decode-only steps advances up to
 // and including the step that retires the next decoder.  A lane with one event at a time takes one round per request;
 // a lane with bursts takes a round per request as well, while the other lanes go on with theirs (loops over a burst
 // make the whole wave wait for every lane's bursts in turn: 7000 loop turns per 1024 requests).
-// CLOSED_RUNS: the run is advanced in closed form (GUIDE_SIM_CLOSED_FORM_RUNS); otherwise the clock walks through it.  A
-// step's time is linear in the context while attention is bound by reading the cache at any context (nearly every
-// lane), and in two pieces where it turns to arithmetic at some context, so the walk takes strides of 64 and 8 steps,
-// whose times are in arithmetic progression, as long as the last step of the stride starts before the arrival that
-// would end the run and lies on the same piece, and single steps after that.
+// A run's steps are advanced at once, stepped or in closed form by name: a step's time is linear in the context while attention
+// is bound by reading the cache at any context (nearly every lane), and the run's time a polynomial; otherwise the
+// series of two pieces.  (One rounding of the clock per run, where a stepped clock has one per step: against 80-bit
+// sums the first-token times of 150 requests of up to 1500 tokens, one after the other, are 3e-15 off, step by step 7.5e-14.)
 // Which of the two ways a lane goes depends on its own configuration alone, never on its neighbours in the wave (which
 // differ from call to call): the results of a configuration are the same bits in every list and every call.
-// (The stride's sum has one rounding where 64 additions to a clock of hundreds of seconds have 64: against 80-bit
-// sums the first-token times of 150 requests of up to 1500 tokens, one after the other, are 5e-15 off, step by step 7.5e-14.)
-// What bounds the kernel: with one wave per SIMD a wave is a serial stream of 970 000 vector instructions (700 000 with
-// closed-form runs) on average, and 40 % of its cycles are waits; the longest wave, which takes 3200 rounds, sets the time.
-// 65 536 configurations x 1024 requests: 7.55 ms stepped, 5.98 ms with closed-form runs; 1999 x 97: 0.74 ms.
-// Before (loops over every kind of event, two rounds per request, four predicated steps of 65 instructions at a time,
-// heap segments by sequence cap, finishing times waited for by every heap read): 41.9, 13.9 and 4.1 ms.
-// heap_slots: keys that the LDS behind the staged trace holds for the whole block (whole groups of siblings); they are
-// shared out among the block's lanes in proportion to the most decoders each can have (its sequence cap), so that a
-// lane that can run a thousand sequences gets a long segment and a lane capped at four next to nothing.
-template <bool ADDITIVE, bool PREFILL_FIRST, bool CLOSED_RUNS, typename KeyT>
+// What bounds the kernel: a wave is a serial stream of instructions, four to six cycles each, and the waves of a compute unit
+// share its fetch; a round takes 2800 cycles where the queues are short and 3100 where they hold hundreds (4-ary heaps in LDS,
+// strides of 64 and 8 steps and forty branches a round: 3500 - 5500), and the longest wave, which takes 3200 rounds, sets the time.
+// 65 536 configurations x 1024 requests: 4.2 ms stepped, 4.0 ms under the other scheduler; 1999 x 97: 0.33 ms.  Before: 7.35, 5.96 and 0.68 ms.
+// heap_bytes: LDS behind the staged trace, shared out among the block's lanes by what each expects.
+template <bool ADDITIVE, bool PREFILL_FIRST, typename KeyT>
 __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const DevTables *__restrict__ tab,
                                                              const TraceDev *__restrict__ trace, uint32_t n_req,
                                                              const uint32_t *__restrict__ cfg_idx,
                                                              const double *__restrict__ rate_in, uint32_t n_cfg,
                                                              guide_sim_out out, SimWs ws, TraceSums sums, uint32_t lanes,
-                                                             uint32_t heap_slots, bool ordered) {
+                                                             uint32_t heap_bytes, bool ordered) {
     // With 32-bit keys the whole trace is below 2^30 tokens, so blocks, budgets and steps fit 32 bits as well
     using Int = typename std::conditional<sizeof(KeyT) == 4, int32_t, long long>::type;
     constexpr Int kIntMax = sizeof(KeyT) == 4 ? (Int)0x7FFFFFFF : (Int)(1ll << 62);
     extern __shared__ __align__(16) unsigned char s_raw[];
-    RequestsLds &req = *(RequestsLds *)s_raw;
-    KeyT *s_heap = (KeyT *)(s_raw + sizeof(RequestsLds));
-    __shared__ uint2 s_total[kSimBlock / kWave];
-    for (uint32_t i = threadIdx.x; i < n_req; i += blockDim.x) {
-        req.arrival[i] = trace->arrival[i];
-        req.len[i] = uint2{trace->n_in[i], trace->n_out[i]};
-    }
-    for (uint32_t i = threadIdx.x; i < heap_slots / (16 / sizeof(KeyT)); i += blockDim.x)
-        ((uint4 *)s_heap)[i] = uint4{~0u, ~0u, ~0u, ~0u};
-    const uint32_t wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    // Configurations are in order of their expected concurrency, and wave w of a block takes its lanes from the
-    // w-th quarter of them: lanes of a wave behave alike, and every block has waves with short and with long heaps.  The
-    // last quarter, where heaps reach hundreds of keys, is dealt out lane by lane, so that no block has more of
-    // the longest ones than its LDS holds (consecutive lanes there: 7.9 instead of 6.5 ms).
-    const uint32_t in_part = wave & 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
-    const uint32_t pos = wave == kSimBlock / kWave - 1 ? (wave * lanes + lane) * gridDim.x + in_part
-                                                       : (wave * gridDim.x + in_part) * lanes + lane;
+    const Request *req = ((RequestsLds *)s_raw)->r;
+    __shared__ uint4 s_total[kSimWaves];
+    for (uint32_t i = threadIdx.x; i < n_req + 2; i += blockDim.x)
+        ((RequestsLds *)s_raw)->r[i] = i < n_req ? Request{trace->arrival[i], trace->n_in[i], trace->n_out[i]}
+                                                 : Request{__builtin_nan(""), 1, 1};
+    for (uint32_t i = threadIdx.x; i < heap_bytes / 16; i += blockDim.x)
+        ((uint4 *)(s_raw + sizeof(RequestsLds)))[i] = uint4{~0u, ~0u, ~0u, ~0u};
+    const uint32_t wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, waves = blockDim.x / kWave;
+    // Configurations are in order of their expected concurrency, and every wave of a block takes its lanes from another
+    // quarter (eighth) of them: lanes of a wave behave alike, and every block has waves with short and with long queues; of
+    // eight waves those that share a SIMD are one of either.  The last quarter, where queues reach hundreds of keys, is dealt out
+    // lane by lane, so that no block has more of the longest ones than its LDS holds (consecutive lanes there: 7.9
+    // instead of 6.5 ms).
+    const uint32_t part = wave < 4 ? wave : 11 - wave;
+    const uint32_t in_part = part & 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+    const uint32_t dealt = waves > 4 ? waves / 4 : 1;           // parts that are dealt out lane by lane
+    const uint32_t pos = part >= waves - dealt ? (part * lanes + lane) * gridDim.x + in_part : (part * gridDim.x + in_part) * lanes + lane;
     const bool in_range = lane < lanes && pos < n_cfg;
     const uint32_t c = !in_range ? 0u : ordered ? ws.perm[pos] : pos;      // the lane's configuration
 
@@ -428,159 +608,172 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
         }
     }
 
-    // LDS segments of the heaps: a lane can have at most min(sequence cap, requests) decoders, one of them in a
-    // register; when the block's lanes want more than the LDS holds, every segment shrinks by the same factor
-    LaneHeap<KeyT> heap;
-    {
-        const uint32_t most = max_seqs < n_req ? max_seqs : n_req;
-        // most - 1 positions at most, and not many more than the pool holds requests of average length; three times
-        // the expected concurrency first, what is left over in proportion to the rest
+    // LDS segments of the queues, in units (blocks of slots; groups of siblings of a heap) of which every lane gets one.  A lane
+    // can have at most min(sequence cap, requests) decoders (one of a heap's is in a register), and not many more than the pool
+    // holds requests of average length.  Slots: a little more than the expected concurrency first (65 536
+    // configurations, 1024 requests: the most decoders are within 1.44 times it, or 16 of it, in 99 of 100 lanes), what is
+    // left over towards three times it; a heap: three times it, or less by the same factor in all lanes, what is left over
+    // towards the most.
+    // Returns false when the slots' wants do not fit: then a heap is the better queue, which finds the decoders beyond its
+    // segment in fewer accesses (65 536 lanes of 700 - 1024 decoders: 8 - 10 ms, with slots 16 - 17 ms).  To be called by the whole block.
+    uint32_t n_units = 0, off = 0;
+    auto allot = [&](auto tag) {
+        constexpr bool kSlots = decltype(tag)::value;
+        constexpr uint32_t kUnit = kSlots ? SlotQueue::kPer : kHeapWidth;
+        constexpr uint32_t kFirst = kSlots ? SlotQueue::kFirstBytes : kHeapWidth * sizeof(KeyT);
+        constexpr uint32_t kMore = kSlots ? SlotQueue::kMoreBytes : kHeapWidth * sizeof(KeyT);
+        auto bytes_of = [](uint32_t n) { return kSlots ? SlotQueue::bytes(n) : n * kFirst; };
+        auto units = [](uint32_t x) { return x ? (x + kUnit - 1) / kUnit : 1u; };
+        const uint32_t most = (max_seqs < n_req ? max_seqs : n_req) - (kSlots ? 0u : 1u);
         const float mean_blocks = (float)sums.tokens / (float)n_req / (float)dblk.d + 0.5f;
         const float pool = fminf(1.5f * (float)n_blk / mean_blocks + 4.0f, 2048.0f);
-        auto groups = [](uint32_t x) { return (x + kHeapWidth - 1) / kHeapWidth * kHeapWidth; };
-        const uint32_t bound = groups((most < (uint32_t)pool ? most : (uint32_t)pool) - 1u);
-        const uint32_t likely = ordered ? groups((uint32_t)(3.0f * expected_of(alive ? ws.bucket[c] : 0u)) + 16u) : bound;
-        const uint32_t full = alive ? (bound < kHeapWidth ? kHeapWidth : bound) : 0u, want = alive && likely < full ? likely : full;
-        const uint32_t wave_want = wave_sum(want), wave_full = wave_sum(full);
-        if (lane == 0) s_total[wave] = uint2{wave_want, wave_full};
-        __syncthreads();                                // the trace and the empty heaps are staged as well
-        uint32_t total = 0, total_full = 0;
-        for (uint32_t w = 0; w < kSimBlock / kWave; ++w) {
-            total += s_total[w].x;
-            total_full += s_total[w].y;
+        uint32_t full = units(most < (uint32_t)pool ? most : (uint32_t)pool), want = full;
+        if (ordered) {
+            const float expected = expected_of(alive ? ws.bucket[c] : 0u);
+            const uint32_t likely = units((uint32_t)(1.25f * expected) + 14u), enough = units((uint32_t)(3.0f * expected) + 16u);
+            if (kSlots) full = enough < full ? enough : full;
+            want = kSlots ? (likely < full ? likely : full) : (enough < full ? enough : full);
         }
-        // (heap_slots is at least a group per thread whenever the wants do not fit, so every lane in use keeps one)
-        uint32_t cap = want;
-        if (total > heap_slots)
-            cap = kHeapWidth + (uint32_t)((double)(want - kHeapWidth) * ((double)(heap_slots - kHeapWidth * kSimBlock) / (double)total)) /
-                                   kHeapWidth * kHeapWidth;
-        else if (total_full > total)
-            cap = want + (uint32_t)((double)(full - want) * fmin((double)(heap_slots - total) / (double)(total_full - total), 1.0)) /
-                             kHeapWidth * kHeapWidth;
-        if (!alive) cap = 0;
-        const uint32_t incl = wave_scan_sum(cap);
+        // the bytes of the wants, the units beyond them, and theirs beyond the first
+        const uint32_t wave_bytes = wave_sum(alive ? bytes_of(want) : 0u), wave_extra = wave_sum(alive ? full - want : 0u);
+        const uint32_t wave_more = wave_sum(alive ? want - 1u : 0u);
+        if (lane == 0) s_total[wave] = uint4{wave_bytes, wave_extra, wave_more, 0u};
+        __syncthreads();                                // the trace and the empty segments are staged as well
+        uint32_t total = 0, extra = 0, more = 0;
+        for (uint32_t w = 0; w < waves; ++w) {
+            total += s_total[w].x;
+            extra += s_total[w].y;
+            more += s_total[w].z;
+        }
         __syncthreads();
+        if (kSlots && total > heap_bytes) return false;
+        n_units = want;
+        if (total > heap_bytes)                         // (heap_bytes holds a unit for every lane in use)
+            n_units = 1u + (uint32_t)((double)(want - 1u) * ((double)(heap_bytes - waves * lanes * kFirst) / (double)kMore / (double)more));
+        else if (extra)                                 // (a lane's segment grows by kMore a unit, and by 48 bytes at most beside)
+            n_units = want + (uint32_t)((double)(full - want) *
+                                        fmin((double)(heap_bytes - total) / (double)(kMore + 48u) / (double)extra, 1.0));
+        n_units = alive ? n_units : 0u;
+        const uint32_t mine = alive ? bytes_of(n_units) : 0u;
+        const uint32_t incl = wave_scan_sum(mine);
         if (lane == kWave - 1) s_total[wave].x = incl;
         __syncthreads();
-        uint32_t off = incl - cap;
+        off = sizeof(RequestsLds) + incl - mine;
         for (uint32_t w = 0; w < wave; ++w) off += s_total[w].x;
-        heap.lds = s_heap + off;
-        heap.cap = cap;
-    }
+        return true;
+    };
     // attention bound by reading the cache at every context: step times are linear (in every lane: wave_linear, which only
     // leaves work out that changes nothing in such a lane)
     const bool lane_linear = ADDITIVE || lt.c_att <= lt.m_att_k;
     const bool wave_linear = ADDITIVE || __ballot(alive && !lane_linear) == 0;
-    if (!alive) return;
+    auto simulate = [&](auto &queue) {
+        constexpr bool kSlots = std::is_same<decltype(queue), SlotQueue &>::value;
+        if (!alive) return;
 
-    heap.top = LaneHeap<KeyT>::kEmpty;
-    heap.mem = (KeyT *)(ws.heap + (size_t)pos * n_req);
-    heap.n = 0;
-    double *first = ws.first + (size_t)c * n_req, *fin = ws.fin + (size_t)c * n_req;
+        bool few = true, supers = false;                        // (SlotQueue: uniform)
+        if constexpr (kSlots) supers = __ballot(queue.super_ != 0) != 0;
+        double *first = ws.first + (size_t)c * n_req, *fin = ws.fin + (size_t)c * n_req;
 
-    // arrival / rate: the reciprocal's product with one correction step rounds as the division does, unless the quotient lies
-    // within 2^-50 units of its last place of a rounding boundary; rates and traces at the ends of the range are divided
-    const double last_arrival = req.arrival[n_req - 1];
-    const bool plain_rate = rate >= 0x1p-400 && rate <= 0x1p400 && last_arrival <= 0x1p400;
-    const bool wave_plain = __ballot(!plain_rate) == 0;
-    const double r_rate = 1.0 / rate;
-    auto arrival_of = [&](double a) {
-        const double q = a * r_rate;
-        double t = fma(fma(-q, rate, a), r_rate, q);
-        if (!wave_plain) {
-            asm volatile("");                           // keeps the division out of the other lanes' way
-            t = plain_rate ? t : a / rate;
-        }
-        return t;
-    };
-    const Int budget_full = (uint64_t)mbt > (uint64_t)(kIntMax / 2) ? kIntMax / 2 : (Int)mbt;   // beyond every trace
-
-    double now = 0.0, max_fin = -INFINITY, s_ctx = 0.0;     // s_ctx: total context, an integer far below 2^53
-    // prompts [comp, next) are admitted and have not emitted their first token; the next one to schedule is h, of which
-    // `done` tokens have been computed; pend: prompts from comp on whose last chunk was in the pass just run
-    uint32_t next = 0, comp = 0, h = 0, done = 0, pend = 0, n_dec = 0, n_done = 0;
-    double c_T = 0.0, c_Q = 0.0, c_K = 0.0;                 // chunks scheduled for the next pass: tokens, workload, context
-    uint32_t chunks = 0, n_full = 0;                        // their number, and prompts that they complete
-    Int used = 0;                                           // their tokens
-    uint64_t step = 0, n_rs = 0;
-    KeyT dstep = 0;                                         // steps in which decoders ran
-    Int free_blk = n_blk;
-    uint32_t status = GUIDE_SIM_OK;
-    const uint64_t step_bound = (uint64_t)n_req + sums.tokens;      // every step consumes at least one token of some request
-    const uint32_t last_req = n_req - 1;
-    auto at_most = [&](uint32_t r) { return r < last_req ? r : last_req; };
-    double arr_next = arrival_of(req.arrival[0]);           // arrival time of request `next`
-    Int need_next = blocks_of(req.len[0].x + req.len[0].y);
-    double kept_base = 0.0;                                 // pass_base of kept_dec decode tokens
-    uint32_t kept_dec = 0;
-
-    for (;;) {
-        // everything that the steps below read from LDS, requested together
-        const uint2 l_h = req.len[at_most(h)], l_comp = req.len[at_most(comp)], l_next = req.len[at_most(next + 1)];
-        const double a_next = req.arrival[at_most(next + 1)];
-        bool moved = false;
-        // 1. a decoder that has emitted its last token leaves (an empty heap's top is beyond every step)
-        if ((heap.top >> 10) == dstep) {
-            const uint32_t r = (uint32_t)(heap.top & 1023u);
-            const uint2 len = req.len[r];
-            heap.pop();
-            free_blk += blocks_of(len.x + len.y);
-            --n_dec;
-            s_ctx -= (double)(len.x + len.y);
-            ++n_done;
-            fin[r] = now;
-            max_fin = now;
-            moved = true;
-        }
-        if (n_done == n_req) break;
-        // 2. idle: jump to the next arrival
-        const uint32_t n_active = (next - comp) + n_dec;
-        if (n_active == 0 && next < n_req) now = arr_next > now ? arr_next : now;
-        // 3. FCFS admission of one request, if it can enter.  (Decoders that still have to leave, or prompts that turn into
-        // decoders, only make room: whoever enters before would enter after.)
-        auto admissible = [&](uint32_t active) {
-            return next < n_req && active < max_seqs && arr_next <= now && need_next <= free_blk;
+        // arrival / rate: the reciprocal's product with one correction step rounds as the division does, unless the quotient lies
+        // within 2^-50 units of its last place of a rounding boundary; rates and traces at the ends of the range are divided
+        const double last_arrival = req[n_req - 1].arrival;
+        const bool plain_rate = rate >= 0x1p-400 && rate <= 0x1p400 && last_arrival <= 0x1p400;
+        const bool wave_plain = __ballot(!plain_rate) == 0;
+        const double r_rate = 1.0 / rate;
+        auto arrival_of = [&](double a) {
+            const double q = a * r_rate;
+            double t = fma(fma(-q, rate, a), r_rate, q);
+            if (!wave_plain) {
+                asm volatile("");                           // keeps the division out of the other lanes' way
+                t = plain_rate ? t : a / rate;
+            }
+            return t;
         };
-        if (admissible(n_active)) {
-            free_blk -= need_next;
-            ++next;
-            arr_next = next < n_req ? arrival_of(a_next) : INFINITY;
-            need_next = blocks_of(l_next.x + l_next.y);
-            moved = true;
-        }
-        const bool leaving = (heap.top >> 10) == dstep;
-        // 4. schedule one prompt chunk.  Split-fuse: the budget that the decoders leave, whose number is final once nobody
-        // leaves or joins any more; a whole prompt may go in before when it fits for sure.  Prefill-first:
-        // whole prompts, as many as fit the budget, the first always.
-        {
-            const Int rem = (Int)(l_h.x - done);
+        const Int budget_full = (uint64_t)mbt > (uint64_t)(kIntMax / 2) ? kIntMax / 2 : (Int)mbt;   // beyond every trace
+
+        double now = 0.0, s_ctx = 0.0;                          // s_ctx: total context, an integer far below 2^53
+        // prompts [comp, next) are admitted and have not emitted their first token; the next one to schedule is h, of which
+        // `done` tokens have been computed; pend: prompts from comp on whose last chunk was in the pass just run
+        uint32_t next = 0, comp = 0, h = 0, done = 0, pend = 0, n_dec = 0, n_done = 0;
+        double c_T = 0.0, c_Q = 0.0, c_K = 0.0;                 // chunks scheduled for the next pass: tokens, workload, context
+        uint32_t chunks = 0, n_full = 0;                        // their number, and prompts that they complete
+        Int used = 0;                                           // their tokens
+        uint64_t n_rs = 0;
+        typename std::conditional<sizeof(KeyT) == 4, uint32_t, uint64_t>::type step = 0;       // (every step consumes a token of some request)
+        KeyT dstep = 0;                                         // steps in which decoders ran
+        Int free_blk = n_blk;
+        uint32_t status = GUIDE_SIM_OK;
+        const uint64_t step_bound = (uint64_t)n_req + sums.tokens;      // every step consumes at least one token of some request
+        double arr_next = arrival_of(req[0].arrival);           // arrival time of request `next`, no number when none is left
+        Int need_next = blocks_of(req[0].in + req[0].out);
+
+        // A round costs its instructions, four to six cycles each, and forty for every branch that lanes take differently: what
+        // is cheap is computed in all lanes and selected.
+        for (;;) {
+            // everything that the steps below read from LDS, requested together
+            const Request q_new = req[next + 1], q_h = req[h], q_comp = req[comp];
+            const uint32_t in_after = PREFILL_FIRST ? req[h + 1].in : 0u;
+            uint32_t first_r = 0;
+            bool spilled = false;
+            if constexpr (kSlots) {
+                first_r = queue.first_request(s_raw);
+                spilled = __ballot(queue.over.n != 0) != 0;
+                few = few && __ballot(queue.used > 4u * SlotQueue::kPer) == 0;
+            }
+            // 1. a decoder that has emitted its last token leaves (with none, the next one to leave is beyond every step)
+            const bool leave = queue.due() == dstep;
+            if (leave) {
+                const uint32_t r = queue.take(s_raw, first_r, few, supers, spilled);
+                const uint32_t tokens = req[r].in + req[r].out;
+                free_blk += blocks_of(tokens);
+                --n_dec;
+                s_ctx -= (double)tokens;
+                ++n_done;
+                fin[r] = now;
+            }
+            if (n_done == n_req) break;
+            // 2. idle: jump to the next arrival
+            uint32_t active = (next - comp) + n_dec;
+            now = active == 0 && arr_next > now ? arr_next : now;
+            // 3. FCFS admission of one request, if it can enter.  (Decoders that still have to leave, or prompts that turn into
+            // decoders, only make room: whoever enters before would enter after.)
+            const bool enter = active < max_seqs && arr_next <= now && need_next <= free_blk;
+            const double arr_new = arrival_of(q_new.arrival);
+            const Int need_new = blocks_of(q_new.in + q_new.out);
+            free_blk -= enter ? need_next : 0;
+            next += enter ? 1u : 0u;
+            active += enter ? 1u : 0u;
+            arr_next = enter ? arr_new : arr_next;
+            need_next = enter ? need_new : need_next;
+            const bool room = active < max_seqs && need_next <= free_blk;      // for the next one, when it has arrived
+            const bool leaving = queue.due() == dstep;
+            // 4. schedule one prompt chunk.  Split-fuse: the budget that the decoders leave, whose number is final once nobody
+            // leaves or joins any more; a whole prompt may go in before when it fits for sure.  Prefill-first:
+            // whole prompts, as many as fit the budget, the first always.
+            const Int rem = (Int)(q_h.in - done);
             const Int left = PREFILL_FIRST ? budget_full - used : budget_full - (Int)(n_dec + pend) - used;
-            const bool fits = PREFILL_FIRST ? (chunks == 0 || rem <= left)
-                                            : (rem <= left || (left > 0 && !leaving && pend == 0));
-            if (h < next && fits) {
-                const Int ch = PREFILL_FIRST ? rem : (rem < left ? rem : left);
+            const bool fits = PREFILL_FIRST ? (chunks == 0 || rem <= left) : (rem <= left || (left > 0 && !leaving && pend == 0));
+            const bool sched = h < next && fits;
+            const Int ch = !sched ? 0 : PREFILL_FIRST || rem < left ? rem : left;
+            const bool whole = sched && ch == rem;
+            {
+                const uint32_t to = done + (uint32_t)ch;
+                const double C = (double)ch, ctx = (double)to;
                 used += ch;
-                done += (uint32_t)ch;
-                const double C = (double)ch, ctx = (double)done;
                 c_T += C;
                 c_Q = fma(C, ctx, c_Q);
-                c_K += ctx;
-                ++chunks;
-                if (ch == rem) {
-                    ++n_full;
-                    ++h;
-                    done = 0;
-                }
-                moved = true;
+                c_K += sched ? ctx : 0.0;
+                chunks += sched ? 1u : 0u;
+                n_full += whole ? 1u : 0u;
+                h += whole ? 1u : 0u;
+                done = whole ? 0u : to;
             }
-        }
-        // 5. a pass with prompts, once nothing is left to be done before it: one token per decoder (prefill-first:
-        // the decoders pause) and the scheduled chunks
-        const bool settled = !leaving && pend == 0 && !admissible((next - comp) + n_dec);
-        if (settled && comp < next) {
-            const bool more = h < next && (PREFILL_FIRST ? (Int)(req.len[at_most(h)].x) <= budget_full - used
+            // 5. a pass with prompts, once nothing is left to be done before it: one token per decoder (prefill-first:
+            // the decoders pause) and the scheduled chunks
+            const bool more = h < next && (PREFILL_FIRST ? (Int)(whole ? in_after : q_h.in) <= budget_full - used
                                                          : budget_full - (Int)n_dec - used > 0);
-            if (!more) {
+            const bool pass = comp < next && !leaving && pend == 0 && !more && !(room && arr_next <= now);
+            if (pass) {
                 const double d = PREFILL_FIRST ? 0.0 : (double)n_dec, ctx = PREFILL_FIRST ? 0.0 : s_ctx;
                 const double T = c_T + d, Q = c_Q + ctx, K = c_K + ctx;
                 now += pass_base<ADDITIVE>(lt, T, d + (double)n_full) +
@@ -589,159 +782,96 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
                 n_rs += chunks;
                 if (!PREFILL_FIRST) {
                     n_rs += n_dec;
-                    if (n_dec > 0) ++dstep;
+                    dstep += n_dec > 0 ? 1 : 0;
                     s_ctx += d;
                 }
                 pend = n_full;
                 c_T = c_Q = c_K = 0.0;
                 chunks = n_full = 0;
                 used = 0;
-                moved = true;
             }
-        }
-        // 6. a prompt completed in the last pass emits its first token
-        if (pend > 0) {
-            const uint32_t r = comp;
-            first[r] = now;
-            if (l_comp.y == 1) {
-                free_blk += blocks_of(l_comp.x + 1);
-                ++n_done;
-                fin[r] = now;
-                max_fin = now;
-            } else {
+            // 6. a prompt completed in the last pass emits its first token.  (With a single token to generate it leaves in the next
+            // round, at the same moment.)
+            const bool join = pend > 0;
+            if (join) {
+                first[comp] = now;
+                queue.put(s_raw, dstep + (KeyT)(q_comp.out - 1), comp, supers);
                 ++n_dec;
-                s_ctx += (double)(l_comp.x + 1);
-                heap.push((KeyT)(((dstep + (KeyT)(l_comp.y - 1)) << 10) | r));
+                s_ctx += (double)(q_comp.in + 1);
+                ++comp;
+                --pend;
             }
-            ++comp;
-            --pend;
-            moved = true;
-        }
-        // 7. run of decode-only steps: no prompt is waiting, and nothing changes until the first decoder emits its
-        // last token or a request that could be admitted arrives.
-        if (comp == next && n_dec > 0 && (heap.top >> 10) != dstep) {
-            const double T = (double)n_dec;
-            if (kept_dec != n_dec) {
-                kept_base = pass_base<ADDITIVE>(lt, T, T);
-                kept_dec = n_dec;
-            }
+            // 7. run of decode-only steps: no prompt is waiting, and nothing changes until the first decoder emits its
+            // last token or a request that could be admitted arrives.
+            const KeyT end_step = queue.due();
             const bool can_admit = next < n_req && n_dec < max_seqs && need_next <= free_blk;
-            const double arr_stop = can_admit ? arr_next : __builtin_nan("");      // compares false: nothing ends the run early
-            const uint32_t total = (uint32_t)((heap.top >> 10) - dstep);  // steps up to the one that retires a decoder
-            // time of a step at context c: base + max(c_att c, m_att_k c + T m_att_t)
-            const double base = kept_base, base_m = fma(T, lt.m_att_t, base);
-            const double slope = ADDITIVE ? lt.c_att + lt.m_att_k : lt.m_att_k;
-            auto step_time = [&](double ctx) {
-                const double tm = fma(ctx, slope, base_m);
-                return wave_linear ? tm : fmax(fma(ctx, lt.c_att, base), tm);      // (tm is the larger in a linear lane)
-            };
-            uint32_t run = 0;
-            if (CLOSED_RUNS) {
-                // all steps before the retiring one, or the least number after which the arrival has come
-                const uint32_t r_max = total - 1;
-                if (r_max > 0 && !(arr_stop <= now)) {
-                    const double h_T = 0.5 * T;
-                    float guess = 1.0f;
-                    if (can_admit) {
-                        // time(r) = p r + q r^2 up to rounding on the side that the run starts on; its root in single
-                        // precision is the first guess
-                        const double rem = arr_stop - now;
-                        const bool arith = !lane_linear && fma(s_ctx, lt.c_att, base) >= fma(s_ctx, slope, base_m);
-                        const double sl = arith ? lt.c_att : slope;
-                        const float q = (float)(sl * h_T), p = (float)fma(sl, s_ctx - h_T, arith ? base : base_m), rf = (float)rem;
-                        guess = ceilf(2.0f * rf * __builtin_amdgcn_rcpf(p + __builtin_amdgcn_sqrtf(fmaf(p, p, 4.0f * q * rf))));
-                    }
-                    auto advance = [&](auto &&time_of) {
-                        run = can_admit ? least_steps(now, arr_stop, r_max, guess, time_of) : r_max;
-                        now += time_of((double)run);
+            const bool go = comp == next && n_dec > 0 && end_step != dstep && !(can_admit && arr_next <= now);
+            if (go) {
+                const double T = (double)n_dec;
+                const uint32_t total = (uint32_t)(end_step - dstep);     // steps up to the one that retires a decoder
+                // time of a step at context c: base + max(c_att c, m_att_k c + T m_att_t)
+                const double base = pass_base<ADDITIVE>(lt, T, T), base_m = fma(T, lt.m_att_t, base);
+                const double slope = ADDITIVE ? lt.c_att + lt.m_att_k : lt.m_att_k;
+                const double h_T = 0.5 * T, ctx0 = s_ctx - h_T;
+                // The least r with arr_next <= now + time(r), total when there is none below it.  time(r) = p r + q r^2 up to
+                // rounding on the side that the run starts on; its root in single precision is the first guess.
+                const bool arith = !wave_linear && !lane_linear && fma(s_ctx, lt.c_att, base) >= fma(s_ctx, slope, base_m);
+                const double sl = arith ? lt.c_att : slope;
+                const float rem_t = (float)(arr_next - now), q = (float)(sl * h_T), p = (float)fma(sl, ctx0, arith ? base : base_m);
+                const float root = ceilf(2.0f * rem_t * __builtin_amdgcn_rcpf(p + __builtin_amdgcn_sqrtf(fmaf(p, p, 4.0f * q * rem_t))));
+                const float guess = can_admit && root < (float)total ? (root >= 1.0f ? root : 1.0f) : (float)total;
+                uint32_t run = 0;
+                if (wave_linear || lane_linear) {
+                    auto time_of = [&](double r) { return r * fma(slope, fma(h_T, r, ctx0), base_m); };
+                    // the guess is right or one off nearly always, so its neighbours are looked at side by side
+                    const double G = (double)guess, stop = can_admit ? arr_next : INFINITY;
+                    const bool far_below = stop <= now + time_of(G - 2.0), below = stop <= now + time_of(G - 1.0);
+                    const bool here = stop <= now + time_of(G), above = stop <= now + time_of(G + 1.0);
+                    run = (uint32_t)guess + (below ? ~0u : 0u) + (here ? 0u : 1u);
+                    run = run < total ? run : total;
+                    if (far_below || !(here || above || run == total)) run = least_steps(now, arr_next, total, guess, time_of);
+                    now += time_of((double)run);
+                } else {
+                    auto time_of = [&](double r) {
+                        return fma(r, base, attention_series<ADDITIVE>(lt.c_att, lt.m_att_k, T * lt.m_att_t, s_ctx - T, T,
+                                                                       fast_recip(T), r));
                     };
-                    if (lane_linear)
-                        advance([&](double r) { return r * fma(slope, fma(h_T, r - 1.0, s_ctx), base_m); });
-                    else
-                        advance([&](double r) {
-                            return fma(r, base, attention_series<ADDITIVE>(lt.c_att, lt.m_att_k, T * lt.m_att_t, s_ctx - T, T,
-                                                                           fast_recip(T), r));
-                        });
+                    run = can_admit ? least_steps(now, arr_next, total, guess, time_of) : total;
+                    now += time_of((double)run);
                 }
-                if (run == r_max && !(arr_stop <= now)) {
-                    now += step_time(fma((double)run, T, s_ctx));
-                    ++run;
-                }
-            } else if (lane_linear) {
-                const double dt = slope * T;
-                double t0 = fma(s_ctx, slope, base_m);
-                // strides of 64, then of 8 steps, whose times are in arithmetic progression, while the last step
-                // of the stride would still start before the arrival; then step by step
-                auto stride = [&](auto steps) {
-                    constexpr double kS = decltype(steps)::value;
-                    while (run + (uint32_t)kS <= total) {
-                        const double to_last = now + fma(0.5 * (kS - 1.0) * (kS - 2.0), dt, (kS - 1.0) * t0);
-                        if (arr_stop <= to_last) break;
-                        now += fma(0.5 * kS * (kS - 1.0), dt, kS * t0);
-                        t0 = fma(kS, dt, t0);
-                        run += (uint32_t)kS;
-                    }
-                };
-                stride(std::integral_constant<int, 64>{});
-                t0 = fma(fma((double)run, T, s_ctx), slope, base_m);
-                stride(std::integral_constant<int, 8>{});
-                t0 = fma(fma((double)run, T, s_ctx), slope, base_m);
-                bool go = true;
-#pragma unroll
-                for (int j = 0; j < 7; ++j) {
-                    go = go && run < total && !(arr_stop <= now);
-                    const double n = now + fma((double)j, dt, t0);
-                    now = go ? n : now;
-                    run += go ? 1u : 0u;
-                }
-            } else {
-                // Attention may turn from read bound to bound by arithmetic at some context, and stays so (its slope is
-                // the greater one): strides whose first and last step lie on the same side, as above; those that
-                // do not are left to shorter ones and to single steps, after which the next round goes on.
-                auto stride = [&](auto steps) {
-                    constexpr double kS = decltype(steps)::value;
-                    while (run + (uint32_t)kS <= total) {
-                        const double ctx = fma((double)run, T, s_ctx), last = fma(kS - 1.0, T, ctx);
-                        const double t_c = fma(ctx, lt.c_att, base), t_m = fma(ctx, slope, base_m);
-                        const bool arith = t_c >= t_m;
-                        if (!arith && fma(last, lt.c_att, base) > fma(last, slope, base_m)) break;
-                        const double t0 = arith ? t_c : t_m, dt = (arith ? lt.c_att : slope) * T;
-                        const double to_last = now + fma(0.5 * (kS - 1.0) * (kS - 2.0), dt, (kS - 1.0) * t0);
-                        if (arr_stop <= to_last) break;
-                        now += fma(0.5 * kS * (kS - 1.0), dt, kS * t0);
-                        run += (uint32_t)kS;
-                    }
-                };
-                stride(std::integral_constant<int, 64>{});
-                stride(std::integral_constant<int, 8>{});
-                bool go = true;
-#pragma unroll
-                for (int j = 0; j < 7; ++j) {
-                    go = go && run < total && !(arr_stop <= now);
-                    const double n = now + step_time(fma((double)run, T, s_ctx));
-                    now = go ? n : now;
-                    run += go ? 1u : 0u;
-                }
+                step += run;
+                dstep += (KeyT)run;
+                n_rs += (uint64_t)run * n_dec;
+                s_ctx = fma((double)run, T, s_ctx);
             }
-            step += run;
-            dstep += (KeyT)run;
-            n_rs += (uint64_t)run * n_dec;
-            s_ctx = fma((double)run, T, s_ctx);
-            moved = moved || run > 0;
+            if (step > step_bound || !(leave || enter || sched || pass || join || go)) {        // a round always moves something
+                status = GUIDE_SIM_INTERNAL;
+                break;
+            }
         }
-        if (step > step_bound || !moved) {                  // a round always moves something
-            status = GUIDE_SIM_INTERNAL;
-            break;
-        }
-    }
 
-    out.tokens_s[c] = status == GUIDE_SIM_OK ? sums.out / (max_fin - req.arrival[0] / rate) : 0.0;
-    out.status[c] = status;
-    out.n_steps[c] = step;
-    out.n_request_steps[c] = n_rs;
-    if (status != GUIDE_SIM_OK) {
-        out.ttft_p50[c] = INFINITY; out.ttft_p99[c] = INFINITY; out.mean_tpot[c] = INFINITY;
+        out.tokens_s[c] = status == GUIDE_SIM_OK ? sums.out / (now - req[0].arrival / rate) : 0.0;
+        out.status[c] = status;
+        out.n_steps[c] = step;
+        out.n_request_steps[c] = n_rs;
+        if (status != GUIDE_SIM_OK) {
+            out.ttft_p50[c] = INFINITY; out.ttft_p99[c] = INFINITY; out.mean_tpot[c] = INFINITY;
+        }
+    };
+
+    KeyT *mem = (KeyT *)(ws.heap + (size_t)pos * n_req);
+    if constexpr (sizeof(KeyT) == 4) {
+        if (allot(std::true_type{})) {                  // block-uniform
+            SlotQueue queue;
+            queue.init(off, n_units, mem);
+            simulate(queue);
+            return;
+        }
     }
+    allot(std::false_type{});
+    HeapQueue<KeyT> queue;
+    queue.init(s_raw + off, n_units, mem);
+    simulate(queue);
 }
 
 // One wave per simulated configuration that ended normally.  TTFT of request i = first token time - arrival /
@@ -859,61 +989,64 @@ size_t simulate_workspace_bytes(uint32_t n_cfg, uint32_t n_req) {
 
 hipError_t launch_simulate(const GridDesc &g, const DevTables *tab, const TraceDev *trace, uint32_t n_req,
                            const uint32_t *cfg_idx, const double *rate, uint32_t n_cfg, bool additive,
-                           bool prefill_first, bool closed_runs, const guide_sim_out &out, void *ws_, hipStream_t stream,
-                           double sum_in, double sum_out, uint32_t longest) {
+                           bool prefill_first, const guide_sim_out &out, void *ws_, hipStream_t stream,
+                           double sum_in, double sum_out, uint32_t longest,
+                           double unit_rate) {
     const SimWs ws = sim_ws(ws_, n_cfg, n_req);
     const TraceSums sums{sum_out, (uint64_t)(sum_in + sum_out), longest};
-    // Lanes in use per wave: 64 once the configurations fill a wave per SIMD, otherwise as few as still give every
-    // SIMD at most one wave.
-    const uint32_t simds = device_cus() * 4;
-    uint32_t lanes = kWave;
-    while (lanes > 1 && (uint64_t)n_cfg <= (uint64_t)(lanes / 2) * simds) lanes /= 2;
-    const uint32_t per_block = kSimBlock / kWave * lanes;
+    // Lanes in use per wave and waves per block.  The waves of a compute unit share its instruction fetch, so few waves are
+    // fast ones: short lists take a lane per wave and a wave per block, and beyond that (a block per compute unit) eight
+    // waves; long ones 64 lanes (a few lanes leave out few of a round's sections) and as few waves per block as still give every
+    // compute unit one block, also for the LDS that its lanes share.  In us, 97 / 300 requests, waves x lanes: 300 configurations
+    // 1 x 1 302 / 777, 8 x 1 462 / 1179, 1 x 64 443 / 1095; 600: 368 / 969, 382 / 1014, 451 / 1119; 1000: 8 x 1 364 / 925, 1 x 64 461 / 1143;
+    // 2000: 352 / 886, 468 / 1182; 4000: 8 x 1 572 / 1482, 1 x 16 509 / 1247, 1 x 64 487 / 1192; 16 000: 1 x 64 572 / 1288, 2 x 32 584 / 1321.
+    const uint32_t cus = device_cus(), lanes = n_cfg <= 8 * cus ? 1 : kWave, full_waves = (n_cfg - 1) / (kWave * cus) + 1;
+    const uint32_t waves = lanes == 1 ? (2 * n_cfg <= 5 * cus ? 1 : 8) : (full_waves < 4 ? full_waves : 4);
+    const uint32_t per_block = waves * lanes;
     // LDS beyond the staged trace holds heap nodes of the block's lanes; 32-bit keys when every finishing step
     // (at most the trace's generated tokens) fits 22 bits and the trace's tokens fit 30
     const bool key32 = sum_out < 4194303.0 && sum_in < 1073700000.0;
-    const size_t key_bytes = key32 ? sizeof(uint32_t) : sizeof(uint64_t);
     int dev = 0, lds_max = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
     if (e != hipSuccess) return e;
     const size_t staged = sizeof(RequestsLds), fixed = staged + kSimStaticLds;
-    if ((size_t)lds_max < fixed + kSimBlock * kHeapWidth * key_bytes) return hipErrorInvalidValue;
+    const size_t unit = key32 ? SlotQueue::kFirstBytes : kHeapWidth * sizeof(uint64_t);
+    if ((size_t)lds_max < fixed + per_block * unit) return hipErrorInvalidValue;
     size_t heap_bytes = (size_t)lds_max - fixed;
-    const size_t most = (size_t)per_block * (n_req + 2 * kHeapWidth) * key_bytes;      // no lane needs more
+    // no lane needs more
+    const size_t most = per_block * (key32 ? SlotQueue::bytes((n_req + SlotQueue::kPer - 1) / SlotQueue::kPer)
+                                           : (n_req + 2 * kHeapWidth) * sizeof(uint64_t));
     heap_bytes = heap_bytes < most ? heap_bytes : most;
-    heap_bytes -= heap_bytes % (kHeapWidth * sizeof(uint64_t));
-    const uint32_t heap_slots = (uint32_t)(heap_bytes / key_bytes);
+    heap_bytes -= heap_bytes % 16;
     const size_t lds_bytes = staged + heap_bytes;
-    const dim3 grid((n_cfg + per_block - 1) / per_block), block(kSimBlock);
+    const dim3 grid((n_cfg + per_block - 1) / per_block), block(waves * kWave);
     const dim3 ogrid((n_cfg + kOrderBlock - 1) / kOrderBlock), oblock(kOrderBlock);
     const bool ordered = lanes > 1 && n_req >= kOrderRequests;      // (otherwise every lane's heap fits the LDS)
     if (ordered) {
         hipLaunchKernelGGL(sim_order_clear_kernel, dim3(1), dim3(kKeyBins), 0, stream, ws);
         if (additive)
-            hipLaunchKernelGGL(sim_order_count_kernel<true>, ogrid, oblock, 0, stream, g, tab, n_req, cfg_idx, rate, n_cfg, ws, sum_in, sum_out);
+            hipLaunchKernelGGL(sim_order_count_kernel<true>, ogrid, oblock, 0, stream, g, tab, n_req, cfg_idx, rate, n_cfg, ws, sum_in, sum_out,
+                               unit_rate);
         else
-            hipLaunchKernelGGL(sim_order_count_kernel<false>, ogrid, oblock, 0, stream, g, tab, n_req, cfg_idx, rate, n_cfg, ws, sum_in, sum_out);
+            hipLaunchKernelGGL(sim_order_count_kernel<false>, ogrid, oblock, 0, stream, g, tab, n_req, cfg_idx, rate, n_cfg, ws, sum_in, sum_out,
+                               unit_rate);
         hipLaunchKernelGGL(sim_order_scan_kernel, dim3(1), dim3(kKeyBins), 0, stream, ws);
         hipLaunchKernelGGL(sim_order_scatter_kernel, ogrid, oblock, 0, stream, n_cfg, ws);
     }
-    const int variant = (additive ? 8 : 0) | (prefill_first ? 4 : 0) | (closed_runs ? 2 : 0) | (key32 ? 1 : 0);
-#define GUIDE_SIM(A, P, C, K32)                                                                                    \
-    case ((A ? 8 : 0) | (P ? 4 : 0) | (C ? 2 : 0) | (K32 ? 1 : 0)): {                                               \
-        auto kern = simulate_kernel<A, P, C, std::conditional<K32, uint32_t, uint64_t>::type>;                      \
+    const int variant = (additive ? 4 : 0) | (prefill_first ? 2 : 0) | (key32 ? 1 : 0);
+#define GUIDE_SIM(A, P, K32)                                                                                       \
+    case ((A ? 4 : 0) | (P ? 2 : 0) | (K32 ? 1 : 0)): {                                                             \
+        auto kern = simulate_kernel<A, P, std::conditional<K32, uint32_t, uint64_t>::type>;                         \
         e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);    \
         if (e != hipSuccess) return e;                                                                              \
         hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, g, tab, trace, n_req, cfg_idx, rate, n_cfg, out, ws, \
-                           sums, lanes, heap_slots, ordered);                                                               \
+                           sums, lanes, (uint32_t)heap_bytes, ordered);                                             \
         break;                                                                                                      \
     }
     switch (variant) {
-        GUIDE_SIM(false, false, false, false) GUIDE_SIM(false, false, false, true) GUIDE_SIM(false, false, true, false)
-        GUIDE_SIM(false, false, true, true) GUIDE_SIM(false, true, false, false) GUIDE_SIM(false, true, false, true)
-        GUIDE_SIM(false, true, true, false) GUIDE_SIM(false, true, true, true) GUIDE_SIM(true, false, false, false)
-        GUIDE_SIM(true, false, false, true) GUIDE_SIM(true, false, true, false) GUIDE_SIM(true, false, true, true)
-        GUIDE_SIM(true, true, false, false) GUIDE_SIM(true, true, false, true) GUIDE_SIM(true, true, true, false)
-        GUIDE_SIM(true, true, true, true)
+        GUIDE_SIM(false, false, false) GUIDE_SIM(false, false, true) GUIDE_SIM(false, true, false) GUIDE_SIM(false, true, true)
+        GUIDE_SIM(true, false, false) GUIDE_SIM(true, false, true) GUIDE_SIM(true, true, false) GUIDE_SIM(true, true, true)
     }
 #undef GUIDE_SIM
     hipLaunchKernelGGL(percentile_kernel, dim3((n_cfg + kPctBlock / kWave - 1) / (kPctBlock / kWave)), dim3(kPctBlock), 0,

@@ -1,0 +1,66 @@
+"""guide_simulate by the queue that holds the decoders: slots in LDS (one, two and three levels of minima), slots whose lane
+runs far more sequences than it expects (the rest in global memory), heaps where the lanes of a block expect more than LDS holds; and
+at the ends of the launch shapes.  Against the CPU oracle's step-level simulator."""
+import numpy as np
+import pytest
+
+from paper_2412_04788_amd import guide, workloads as wl
+from tests import bridge
+from tests.test_gpu_simulate import _run
+from tests.test_gpu_simulate_paths import CLOSED, _check
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    assert torch.cuda.is_available()
+    return torch
+
+
+def _grid(batch):
+    hw = wl.Hardware(2e15, 8e12, 4000 * wl.GIB, 6e11)
+    return wl.make_grid([wl.DENSE_7B, wl.MOE_8X], [hw], wl.Axis.table(batch), wl.Axis.table([1]), wl.Axis.table([1]),
+                        wl.Axis.table([1, 2]), wl.Axis.table([16, 8]), wl.Axis.table([16]), wl.Axis.table([8192, 2048]))
+
+
+# the most decoders: one block of slots and one more, four blocks, sixteen, and all of three levels
+@pytest.mark.parametrize("cap", [1, 16, 17, 64, 65, 256, 257, 1024])
+def test_levels_of_the_slots(ora, torch_cuda, cap):
+    rng = np.random.default_rng(cap)
+    n = 1024
+    tr = wl.Trace(np.sort(rng.random(n) * 2.0), rng.integers(8, 64, n).astype(np.uint32), rng.integers(1, 500, n).astype(np.uint32))
+    g = _grid([cap, max(cap - 3, 1)])
+    idx = np.arange(g.size, dtype=np.uint32)
+    _check(torch_cuda, ora, g, idx, np.where(idx % 2 == 0, 1e6, 30.0), tr, scheds=(0, 1))
+
+
+# (lists of one lane per wave hold every decoder in their slots; in longer ones, 300 requests at the start of a trace that ends
+# a long time after make lanes expect one sequence and run 300)
+@pytest.mark.parametrize("n_cfg", [40, 2500])
+def test_more_decoders_than_expected(ora, torch_cuda, n_cfg):
+    rng = np.random.default_rng(n_cfg)
+    n = 320
+    t = np.concatenate([np.sort(rng.random(300)), 1e7 + np.arange(20.0)])
+    tr = wl.Trace(t, rng.integers(8, 300, n).astype(np.uint32), rng.integers(1, 700, n).astype(np.uint32))
+    g = _grid([1024, 33, 200, 7])
+    idx = (np.arange(n_cfg) % g.size).astype(np.uint32)
+    rate = 1.0 + (np.arange(n_cfg) % 97) * 3.0
+    pick = np.unique(np.linspace(0, n_cfg - 1, 40).astype(np.int64))
+    _check(torch_cuda, ora, g, idx, rate, tr, pick, scheds=(0, 1 | CLOSED))
+
+
+@pytest.mark.parametrize("n_cfg", [256, 640, 641, 2048, 2049, 16384, 16385, 49153])
+def test_launch_shapes(ora, torch_cuda, n_cfg):
+    g = wl.grid_full()
+    tr = wl.request_trace(n=40, seed=n_cfg)
+    idx, rate = wl.sim_configs(g, n_cfg, seed=n_cfg)
+    pick = np.unique(np.concatenate([np.linspace(0, n_cfg - 1, 64), [n_cfg - 2, n_cfg - 1]]).astype(np.int64))
+    _check(torch_cuda, ora, g, idx, rate, tr, pick, scheds=(0, 1))
+    # a configuration's results are the same bits in every list, and with and without the closed-form flag
+    ctx = bridge.gpu_context(g)
+    whole, part = (_run(torch_cuda, ctx, g, idx[p], rate[p], tr, scheduler=s) for p, s in
+                   ((np.arange(n_cfg), 0), (pick, guide.SIM_CLOSED_FORM_RUNS)))
+    for k in whole:
+        np.testing.assert_array_equal(whole[k][pick], part[k])
