@@ -875,14 +875,15 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
 }
 
 // One wave per simulated configuration that ended normally.  TTFT of request i = first token time - arrival /
-// rate; the 1024 values (absent requests count as +inf) are sorted inside the wave's registers, 16 per lane, by
-// a bitonic network in which every compare-exchange puts the smaller value at the smaller index: element
-// e = 16 * lane + register; a stage pairs e with e ^ m, which is another register of the same lane while m < 16
-// and the same-numbered (or mirrored) register of lane ^ (m / 16) otherwise.  Then nearest-rank
+// rate; the values (absent requests count as +inf) are sorted inside the wave's registers, R = 1, 2, 4, 8 or 16 per lane --
+// as few as hold the trace -- by a bitonic network in which every compare-exchange puts the smaller value at the smaller
+// index: element e = R * lane + register; a stage pairs e with e ^ m, which is another register of the same lane while m < R
+// and the same-numbered (or mirrored) register of lane ^ (m / R) otherwise.  Then nearest-rank
 // p50 = sorted[ceil(n/2) - 1] and p99 = sorted[ceil(0.99 n) - 1]; mean TPOT = mean over requests with more than
 // one token of (finish - first token) / (tokens - 1).
-constexpr uint32_t kPerLane = GUIDE_MAX_REQUESTS / kWave;       // 16
-static_assert(kPerLane == 16, "the network below is written for 16 values per lane");
+// Bound by the vector ALU with 16 values (65 536 configurations: 0.41 ms; 0.54 ms with every exchange between lanes through
+// LDS), by launch and reading with few (65 536 x 16 requests: a call 105 - 117 us, 540 - 580 us with 16 values for any trace).
+constexpr uint32_t kMostPerLane = GUIDE_MAX_REQUESTS / kWave;   // 16
 
 constexpr uint32_t top_bit(uint32_t x) { return x < 2 ? x : 2 * top_bit(x / 2); }
 // compare-exchange inside a lane: the smaller value to the smaller register
@@ -891,28 +892,46 @@ __device__ inline void cx(double &a, double &b) {
     a = lo;
     b = hi;
 }
-// One stage of the network.  MASK: the xor mask on element numbers.
+// The value of lane ^ MASK, in the vector ALU where its patterns reach (0x1B reverses four lanes, 0x128 turns a row by eight).
 template <uint32_t MASK>
-__device__ inline void sort_stage(double (&v)[kPerLane], uint32_t lane) {
-    if constexpr (MASK < kPerLane) {
+__device__ inline double lane_xor(double x) {
+    auto move = [](double y, auto ctrl) {
+        const uint64_t b = (uint64_t)__double_as_longlong(y);
+        const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
+        constexpr int kCtrl = decltype(ctrl)::value;
+        return __longlong_as_double((long long)((uint64_t)dpp_u32<kCtrl>(hi, hi) << 32 | dpp_u32<kCtrl>(lo, lo)));
+    };
+    if constexpr (MASK == 1) return move(x, std::integral_constant<int, 0xB1>{});
+    else if constexpr (MASK == 2) return move(x, std::integral_constant<int, 0x4E>{});
+    else if constexpr (MASK == 3) return move(x, std::integral_constant<int, 0x1B>{});
+    else if constexpr (MASK == 4) return move(move(x, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{});
+    else if constexpr (MASK == 7) return move(x, std::integral_constant<int, 0x141>{});
+    else if constexpr (MASK == 8) return move(x, std::integral_constant<int, 0x128>{});
+    else if constexpr (MASK == 15) return move(x, std::integral_constant<int, 0x140>{});
+    else return __shfl_xor(x, (int)MASK, kWave);
+}
+// One stage of the network.  MASK: the xor mask on element numbers.
+template <uint32_t MASK, uint32_t R>
+__device__ inline void sort_stage(double (&v)[R], uint32_t lane) {
+    if constexpr (MASK < R) {
 #pragma unroll
-        for (uint32_t r = 0; r < kPerLane; ++r)
+        for (uint32_t r = 0; r < R; ++r)
             if ((r ^ MASK) > r) cx(v[r], v[r ^ MASK]);
     } else {
-        constexpr uint32_t kLaneMask = MASK / kPerLane, kRegMask = MASK % kPerLane;     // kRegMask: 0 or 15 (mirror)
+        constexpr uint32_t kLaneMask = MASK / R, kRegMask = MASK % R;       // kRegMask: 0 or R - 1 (mirror)
         // this lane holds the smaller indices of its pairs when the top bit of the lane mask is clear in its number
         constexpr uint32_t kTop = top_bit(kLaneMask);
         const bool keep_min = (lane & kTop) == 0;
-        double o[kPerLane];
+        double o[R];
 #pragma unroll
-        for (uint32_t r = 0; r < kPerLane; ++r) o[r] = __shfl_xor(v[r ^ kRegMask], (int)kLaneMask, kWave);
+        for (uint32_t r = 0; r < R; ++r) o[r] = lane_xor<kLaneMask>(v[r ^ kRegMask]);
 #pragma unroll
-        for (uint32_t r = 0; r < kPerLane; ++r) v[r] = keep_min ? fmin(v[r], o[r]) : fmax(v[r], o[r]);
+        for (uint32_t r = 0; r < R; ++r) v[r] = (o[r] < v[r]) == keep_min ? o[r] : v[r];      // (equal values: either)
     }
 }
 // Merge of sorted runs of K / 2 elements into sorted runs of K: the mirror stage, then halving distances.
-template <uint32_t K>
-__device__ inline void sort_merge(double (&v)[kPerLane], uint32_t lane) {
+template <uint32_t K, uint32_t R>
+__device__ inline void sort_merge(double (&v)[R], uint32_t lane) {
     sort_stage<K - 1>(v, lane);
     if constexpr (K >= 4) sort_stage<K / 4>(v, lane);
     if constexpr (K >= 8) sort_stage<K / 8>(v, lane);
@@ -925,13 +944,15 @@ __device__ inline void sort_merge(double (&v)[kPerLane], uint32_t lane) {
     if constexpr (K >= 1024) sort_stage<K / 1024>(v, lane);
 }
 // element `e` of the sorted sequence, in every lane
-__device__ inline double sorted_at(const double (&v)[kPerLane], uint32_t e) {
+template <uint32_t R>
+__device__ inline double sorted_at(const double (&v)[R], uint32_t e) {
     double x = v[0];
 #pragma unroll
-    for (uint32_t r = 1; r < kPerLane; ++r) x = (e % kPerLane) == r ? v[r] : x;
-    return __shfl(x, (int)(e / kPerLane), kWave);
+    for (uint32_t r = 1; r < R; ++r) x = (e % R) == r ? v[r] : x;
+    return __shfl(x, (int)(e / R), kWave);
 }
 
+template <uint32_t R>
 __global__ __launch_bounds__(kPctBlock) void percentile_kernel(SimWs ws, const TraceDev *__restrict__ trace,
                                                                const double *__restrict__ rate_in, uint32_t n_req,
                                                                uint32_t n_cfg, guide_sim_out out) {
@@ -940,11 +961,11 @@ __global__ __launch_bounds__(kPctBlock) void percentile_kernel(SimWs ws, const T
     if (c >= n_cfg || out.status[c] != GUIDE_SIM_OK) return;
     const double rate = rate_in[c];
     const double *first = ws.first + (size_t)c * n_req, *fin = ws.fin + (size_t)c * n_req;
-    double v[kPerLane];
+    double v[R];
     double tp = 0.0;
     uint32_t n_tp = 0;
 #pragma unroll
-    for (uint32_t r = 0; r < kPerLane; ++r) {
+    for (uint32_t r = 0; r < R; ++r) {
         const uint32_t i = r * kWave + lane;                // coalesced; the sort does not care where a value starts
         double t = INFINITY;
         if (i < n_req) {
@@ -968,10 +989,10 @@ __global__ __launch_bounds__(kPctBlock) void percentile_kernel(SimWs ws, const T
     sort_merge<16>(v, lane);
     sort_merge<32>(v, lane);
     sort_merge<64>(v, lane);
-    sort_merge<128>(v, lane);
-    sort_merge<256>(v, lane);
-    sort_merge<512>(v, lane);
-    sort_merge<1024>(v, lane);
+    if constexpr (R >= 2) sort_merge<128>(v, lane);
+    if constexpr (R >= 4) sort_merge<256>(v, lane);
+    if constexpr (R >= 8) sort_merge<512>(v, lane);
+    if constexpr (R >= 16) sort_merge<1024>(v, lane);
     const double p50 = sorted_at(v, (n_req + 1) / 2 - 1);
     const double p99 = sorted_at(v, (uint32_t)((99ull * n_req + 99) / 100 - 1));
     if (lane == 0) {
@@ -1049,8 +1070,15 @@ hipError_t launch_simulate(const GridDesc &g, const DevTables *tab, const TraceD
         GUIDE_SIM(true, false, false) GUIDE_SIM(true, false, true) GUIDE_SIM(true, true, false) GUIDE_SIM(true, true, true)
     }
 #undef GUIDE_SIM
-    hipLaunchKernelGGL(percentile_kernel, dim3((n_cfg + kPctBlock / kWave - 1) / (kPctBlock / kWave)), dim3(kPctBlock), 0,
-                       stream, ws, trace, rate, n_req, n_cfg, out);
+    const dim3 pgrid((n_cfg + kPctBlock / kWave - 1) / (kPctBlock / kWave)), pblock(kPctBlock);
+    auto percentiles = [&](auto per_lane) {
+        hipLaunchKernelGGL((percentile_kernel<decltype(per_lane)::value>), pgrid, pblock, 0, stream, ws, trace, rate, n_req, n_cfg, out);
+    };
+    if (n_req <= kWave) percentiles(std::integral_constant<uint32_t, 1>{});
+    else if (n_req <= 2 * kWave) percentiles(std::integral_constant<uint32_t, 2>{});
+    else if (n_req <= 4 * kWave) percentiles(std::integral_constant<uint32_t, 4>{});
+    else if (n_req <= 8 * kWave) percentiles(std::integral_constant<uint32_t, 8>{});
+    else percentiles(std::integral_constant<uint32_t, kMostPerLane>{});
     return hipGetLastError();
 }
 

@@ -64,3 +64,12 @@ def test_launch_shapes(ora, torch_cuda, n_cfg):
                    ((np.arange(n_cfg), 0), (pick, guide.SIM_CLOSED_FORM_RUNS)))
     for k in whole:
         np.testing.assert_array_equal(whole[k][pick], part[k])
+
+
+# values per lane of the percentiles' sorting network: 1, 2, 4, 8, 16
+@pytest.mark.parametrize("n_req", [2, 63, 64, 65, 128, 129, 256, 257, 512, 513, 1000])
+def test_percentiles_by_trace_length(ora, torch_cuda, n_req):
+    g = wl.grid_full()
+    tr = wl.request_trace(n=n_req, seed=n_req)
+    idx, rate = wl.sim_configs(g, 70, seed=n_req)
+    _check(torch_cuda, ora, g, idx, rate, tr, np.arange(0, 70, 3), scheds=(0, 1))
