@@ -1222,7 +1222,6 @@ __device__ inline uint32_t finish_in_lds(FinishLds &L, const Binning &bin, const
                                          Emit &&emit) {
     static_assert(kFinishThreads == 1024, "kPerFinish assumes 1024 threads");
     constexpr uint32_t P = kPerFinish, PER = kStage / kFinishThreads;
-    const uint32_t t = threadIdx.x;
     // Survivors that are dominated for sure are dropped first: those with a survivor of a strictly lower bin at or below their y,
     // and those that their own bin's representative dominates -- the survivor with the bin's least y (of those,
     // the least x); rows often tie in x, and then the representative settles all of them but the ties in y.

@@ -529,8 +529,8 @@ struct TraceSums {
 };
 
 // One configuration per lane, `lanes` of them per wave (64 or 1).
-// A round of the loop does at most one of each kind of thing: one decoder leaves, one request enters, one prompt chunk is
-// scheduled, a pass with prompts runs, one prompt turns into a decoder, a run of decode-only steps advances up to
+// A round of the loop does at most one of each kind of thing (two of the second and third): one decoder leaves, one request
+// enters, one prompt chunk is scheduled, a pass with prompts runs, one prompt turns into a decoder, a run of decode-only steps advances up to
 // and including the step that retires the next decoder.  A lane with one event at a time takes one round per request;
 // a lane with bursts takes a round per request as well, while the other lanes go on with theirs (loops over a burst
 // make the whole wave wait for every lane's bursts in turn: 7000 loop turns per 1024 requests).
@@ -543,7 +543,8 @@ struct TraceSums {
 // What bounds the kernel: a wave is a serial stream of instructions, four to six cycles each, and the waves of a compute unit
 // share its fetch; a round takes 2800 cycles where the queues are short and 3100 where they hold hundreds (4-ary heaps in LDS,
 // strides of 64 and 8 steps and forty branches a round: 3500 - 5500), and the longest wave, which takes 3200 rounds, sets the time.
-// 65 536 configurations x 1024 requests: 4.2 ms stepped, 4.0 ms under the other scheduler; 1999 x 97: 0.33 ms.  Before: 7.35, 5.96 and 0.68 ms.
+// 65 536 configurations x 1024 requests, a call with percentiles: 3.97 ms, 3.98 ms under the other scheduler; 1999 x 97: 0.35 ms.
+// Before: 7.7, 6.4 and 0.71 ms.
 // heap_bytes: LDS behind the staged trace, shared out among the block's lanes by what each expects.
 template <bool ADDITIVE, bool PREFILL_FIRST, typename KeyT>
 __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const DevTables *__restrict__ tab,
@@ -712,7 +713,7 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
         for (;;) {
             // everything that the steps below read from LDS, requested together
             const Request q_new = req[next + 1], q_h = req[h], q_comp = req[comp];
-            const uint32_t in_after = PREFILL_FIRST ? req[h + 1].in : 0u;
+            const uint32_t in_next = PREFILL_FIRST ? req[h + 1].in : 0u;
             uint32_t first_r = 0;
             bool spilled = false;
             if constexpr (kSlots) {
@@ -735,42 +736,58 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
             // 2. idle: jump to the next arrival
             uint32_t active = (next - comp) + n_dec;
             now = active == 0 && arr_next > now ? arr_next : now;
-            // 3. FCFS admission of one request, if it can enter.  (Decoders that still have to leave, or prompts that turn into
-            // decoders, only make room: whoever enters before would enter after.)
-            const bool enter = active < max_seqs && arr_next <= now && need_next <= free_blk;
-            const double arr_new = arrival_of(q_new.arrival);
-            const Int need_new = blocks_of(q_new.in + q_new.out);
-            free_blk -= enter ? need_next : 0;
-            next += enter ? 1u : 0u;
-            active += enter ? 1u : 0u;
-            arr_next = enter ? arr_new : arr_next;
-            need_next = enter ? need_new : need_next;
-            const bool room = active < max_seqs && need_next <= free_blk;      // for the next one, when it has arrived
+            // 3. and 4. once for all lanes, and once more while some lane of the wave is in a burst of arrivals (65 536
+            // configurations: 4.12 instead of 4.65 ms; up to three more times 4.9: the other lanes wait)
+            bool enter = false, room = false, sched = false, whole = false;
             const bool leaving = queue.due() == dstep;
-            // 4. schedule one prompt chunk.  Split-fuse: the budget that the decoders leave, whose number is final once nobody
-            // leaves or joins any more; a whole prompt may go in before when it fits for sure.  Prefill-first:
-            // whole prompts, as many as fit the budget, the first always.
-            const Int rem = (Int)(q_h.in - done);
-            const Int left = PREFILL_FIRST ? budget_full - used : budget_full - (Int)(n_dec + pend) - used;
-            const bool fits = PREFILL_FIRST ? (chunks == 0 || rem <= left) : (rem <= left || (left > 0 && !leaving && pend == 0));
-            const bool sched = h < next && fits;
-            const Int ch = !sched ? 0 : PREFILL_FIRST || rem < left ? rem : left;
-            const bool whole = sched && ch == rem;
-            {
-                const uint32_t to = done + (uint32_t)ch;
-                const double C = (double)ch, ctx = (double)to;
-                used += ch;
-                c_T += C;
-                c_Q = fma(C, ctx, c_Q);
-                c_K += sched ? ctx : 0.0;
-                chunks += sched ? 1u : 0u;
-                n_full += whole ? 1u : 0u;
-                h += whole ? 1u : 0u;
-                done = whole ? 0u : to;
+            Request q_n = q_new, q_c = q_h;
+            uint32_t in_after = in_next;
+            auto admit_and_schedule = [&]() {
+                // 3. FCFS admission of one request, if it can enter.  (Decoders that still have to leave, or prompts that turn into
+                // decoders, only make room: whoever enters before would enter after.)
+                enter = active < max_seqs && arr_next <= now && need_next <= free_blk;
+                const double arr_new = arrival_of(q_n.arrival);
+                const Int need_new = blocks_of(q_n.in + q_n.out);
+                free_blk -= enter ? need_next : 0;
+                next += enter ? 1u : 0u;
+                active += enter ? 1u : 0u;
+                arr_next = enter ? arr_new : arr_next;
+                need_next = enter ? need_new : need_next;
+                room = active < max_seqs && need_next <= free_blk;      // for the next one, when it has arrived
+                // 4. schedule one prompt chunk.  Split-fuse: the budget that the decoders leave, whose number is final once nobody
+                // leaves or joins any more; a whole prompt may go in before when it fits for sure.  Prefill-first:
+                // whole prompts, as many as fit the budget, the first always.
+                const Int rem = (Int)(q_c.in - done);
+                const Int left = PREFILL_FIRST ? budget_full - used : budget_full - (Int)(n_dec + pend) - used;
+                const bool fits = PREFILL_FIRST ? (chunks == 0 || rem <= left) : (rem <= left || (left > 0 && !leaving && pend == 0));
+                sched = h < next && fits;
+                const Int ch = !sched ? 0 : PREFILL_FIRST || rem < left ? rem : left;
+                whole = sched && ch == rem;
+                {
+                    const uint32_t to = done + (uint32_t)ch;
+                    const double C = (double)ch, ctx = (double)to;
+                    used += ch;
+                    c_T += C;
+                    c_Q = fma(C, ctx, c_Q);
+                    c_K += sched ? ctx : 0.0;
+                    chunks += sched ? 1u : 0u;
+                    n_full += whole ? 1u : 0u;
+                    h += whole ? 1u : 0u;
+                    done = whole ? 0u : to;
+                }
+            };
+            admit_and_schedule();
+            bool moved = enter || sched;
+            if (__ballot((enter && room && arr_next <= now) || (whole && h < next)) != 0) {
+                q_n = req[next + 1];
+                q_c = req[h];
+                if (PREFILL_FIRST) in_after = req[h + 1].in;
+                admit_and_schedule();
+                moved = moved || enter || sched;
             }
             // 5. a pass with prompts, once nothing is left to be done before it: one token per decoder (prefill-first:
             // the decoders pause) and the scheduled chunks
-            const bool more = h < next && (PREFILL_FIRST ? (Int)(whole ? in_after : q_h.in) <= budget_full - used
+            const bool more = h < next && (PREFILL_FIRST ? (Int)(whole ? in_after : q_c.in) <= budget_full - used
                                                          : budget_full - (Int)n_dec - used > 0);
             const bool pass = comp < next && !leaving && pend == 0 && !more && !(room && arr_next <= now);
             if (pass) {
@@ -844,7 +861,7 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
                 n_rs += (uint64_t)run * n_dec;
                 s_ctx = fma((double)run, T, s_ctx);
             }
-            if (step > step_bound || !(leave || enter || sched || pass || join || go)) {        // a round always moves something
+            if (step > step_bound || !(leave || moved || pass || join || go)) {        // a round always moves something
                 status = GUIDE_SIM_INTERNAL;
                 break;
             }
