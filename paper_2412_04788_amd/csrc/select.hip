@@ -633,9 +633,8 @@ struct ParetoWs {
     uint32_t *staged;     // [n]: per part of the front, from its first survivor slot on: positions of its survivors, then its front
                           // members' rows in order
     uint32_t *grouped;    // [n]: positions into surv, grouped by bin (parts whose survivors do not fit LDS)
-    uint8_t *on_front;    // [n]: flag per grouped survivor (the same parts)
 };
-size_t pareto_ws_bytes(uint64_t n) { return (size_t)n * (8 + 8 + 4 + 4 + 4 + 1 + 1) + 256; }   // (one byte a row to spare)
+size_t pareto_ws_bytes(uint64_t n) { return (size_t)n * (8 + 8 + 4 + 4 + 4 + 1 + 1) + 256; }   // (two bytes a row to spare)
 ParetoWs pareto_ws(void *ws, uint64_t n) {
     ParetoWs w;
     w.skx = (uint64_t *)ws;
@@ -643,7 +642,6 @@ ParetoWs pareto_ws(void *ws, uint64_t n) {
     w.surv = (uint32_t *)(w.sky + n);
     w.staged = w.surv + n;
     w.grouped = w.staged + n;
-    w.on_front = (uint8_t *)(w.grouped + n);
     return w;
 }
 
@@ -1030,6 +1028,29 @@ __global__ __launch_bounds__(kBlock) void pareto_filter_kernel(const double *__r
     }
 }
 
+// A value that is the same in all lanes of the wave, kept in scalar registers.
+__device__ inline uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ inline uint64_t uniform(uint64_t v) { return (uint64_t)uniform((uint32_t)(v >> 32)) << 32 | uniform((uint32_t)v); }
+
+// threadIdx.x, formed anew at every use: what follows from it is not kept in registers across the finishing kernel's rounds.
+__device__ inline uint32_t thread_here() {
+    uint32_t t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    __builtin_assume(t < 1024);
+    return t;
+}
+
+// Least and greatest x and least y of some records.
+struct KeyRange {
+    uint64_t lo, hi, y;
+    static __device__ KeyRange none() { return KeyRange{kNone, 0, kNone}; }
+    __device__ void add(uint64_t kx, uint64_t ky) {
+        lo = min_u64(lo, kx);
+        hi = hi < kx ? kx : hi;
+        y = min_u64(y, ky);
+    }
+};
+
 // LDS of the finishing kernel.
 struct FinishLds {
     uint32_t off[padded_size<kPerFinish>()];    // first survivor slot per bin (exclusive scan of the bin counts)
@@ -1050,14 +1071,14 @@ struct FinishLds {
     };
     uint16_t bin[kStage];
     uint8_t flag[kStage];
-    uint32_t nfront, first, last, alive, is_last;
+    uint32_t nfront, first, last, alive, is_last, todo;
     uint32_t part_base[kWave], part_lo[kWave], part_cnt[kWave];
     uint64_t rng[2];
-    Pair range[kFinishThreads / kWave];
+    KeyRange range[kFinishThreads / kWave];
 };
 
 // The front among `cnt` survivor records staged in LDS, grouped by bin: record i of bin b sits at
-// L.off[b] - base + i.  L.foff must be zero and the staging complete (the function starts with a barrier).
+// L.off[b] + i.  L.foff must be zero and the staging complete (the function starts with a barrier).
 // Calls emit(position, row) for every front member, position = its rank by (bin, x, y, row) among the
 // front members staged here, and returns their number.
 // GROUP lanes per survivor (8 or 1): they share out the members of its bin, four LDS reads in flight each, and
@@ -1066,10 +1087,10 @@ struct FinishLds {
 // them but longer chains, +1 to +6 us, the fullest bin setting the pace); beyond, one lane each saves more
 // rounds (a round over 128 survivors costs about as much as one over 1024) than the chains cost.
 template <uint32_t GROUP, typename Emit>
-__device__ inline uint32_t staged_front_by(FinishLds &L, uint32_t cnt, uint32_t base, Emit &&emit) {
+__device__ inline uint32_t staged_front_by(FinishLds &L, uint32_t cnt, Emit &&emit) {
     constexpr uint32_t P = kPerFinish, group = GROUP, q_step = kFinishThreads / group;
     constexpr uint64_t group_mask = group < 64 ? (1ull << group) - 1 : ~0ull;
-    const uint32_t t = threadIdx.x, lane = t % kWave, sub = lane % group, shift = lane - sub;
+    const uint32_t t = thread_here(), lane = t % kWave, sub = lane % group, shift = lane - sub;
     __syncthreads();
     const uint32_t cnt_pad = (cnt + q_step - 1) / q_step * q_step;      // wave-uniform trip count for the ballot
     for (uint32_t q = t / group; q < cnt_pad; q += q_step) {
@@ -1077,7 +1098,7 @@ __device__ inline uint32_t staged_front_by(FinishLds &L, uint32_t cnt, uint32_t 
         const uint64_t kx = live ? L.kx[q] : 0, ky = live ? L.ky[q] : 0;
         const uint32_t b = live ? L.bin[q] : 0;
         bool dom = false;
-        const uint32_t beg = live ? L.off[padded<P>(b)] - base : 0, end = live ? L.off[padded<P>(b + 1)] - base : beg;
+        const uint32_t beg = live ? L.off[padded<P>(b)] : 0, end = live ? L.off[padded<P>(b + 1)] : beg;
         for (uint32_t j = beg + sub; j < end; j += 4 * group) {
             uint64_t jx[4], jy[4];
 #pragma unroll
@@ -1101,14 +1122,14 @@ __device__ inline uint32_t staged_front_by(FinishLds &L, uint32_t cnt, uint32_t 
     }
     __syncthreads();
     scan_sum_excl<kFinishThreads, true>(L.foff, L.tmp);
-    const uint32_t nf = L.nfront;
+    const uint32_t nf = uniform(L.nfront);
     const uint32_t f_pad = (nf + q_step - 1) / q_step * q_step;          // wave-uniform trip count for the shuffles
     for (uint32_t qf = t / group; qf < f_pad; qf += q_step) {
         const bool live = qf < nf;
         const uint32_t q = live ? L.cur[qf] : 0;
         const uint64_t kx = live ? L.kx[q] : 0, ky = live ? L.ky[q] : 0;
         const uint32_t b = live ? L.bin[q] : 0, i = live ? L.row[q] : 0;
-        const uint32_t beg = live ? L.off[padded<P>(b)] - base : 0, end = live ? L.off[padded<P>(b + 1)] - base : 0;
+        const uint32_t beg = live ? L.off[padded<P>(b)] : 0, end = live ? L.off[padded<P>(b + 1)] : 0;
         uint32_t rank = 0;                          // front members of the bin that come before this one
         for (uint32_t j = beg + sub; j < end; j += 4 * group) {
             uint64_t jx[4], jy[4];
@@ -1133,83 +1154,101 @@ __device__ inline uint32_t staged_front_by(FinishLds &L, uint32_t cnt, uint32_t 
     }
     return nf;
 }
-// b_lo .. b_hi: the bins that hold the staged survivors.  One lane per survivor only when there are more than
-// 1024 of them and a survivor's bin holds 32 members or fewer on average over the survivors (sum of squared bin
-// counts <= 32 * cnt): crowded bins want the eight lanes (400 000 front rows took 2.2 instead of 2.1 ms,
-// 1 900 800 took 32.5 instead of 31.2 ms with one lane each), sparse ones the fewer rounds (4 000 front rows:
-// 26 instead of 60 us).
+
+// The same by sorting: for records that crowd in few bins, whatever their values.  In the order of (x, y, row) a record is on
+// the front when no pair (y, x) before it is less than its own (one with a lower y, or with the same y and a lower x).
 template <typename Emit>
-__device__ inline uint32_t staged_front(FinishLds &L, uint32_t cnt, uint32_t base, uint32_t b_lo, uint32_t b_hi,
-                                        Emit &&emit) {
-    if (cnt <= 1024) return staged_front_by<8>(L, cnt, base, emit);     // block-uniform
+__device__ inline uint32_t sorted_front(FinishLds &L, uint32_t cnt, Emit &&emit) {
+    constexpr uint32_t NT = kFinishThreads, PER = kStage / NT;
+    const uint32_t t = thread_here(), lane = t % kWave, wave = t / kWave;
+    uint32_t n = 2;                                     // records and padding (which sorts behind every record)
+    while (n < cnt) n *= 2;
+    __syncthreads();
+    for (uint32_t i = cnt + t; i < n; i += NT) {
+        L.kx[i] = L.ky[i] = kNone;
+        L.row[i] = ~0u;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t k = 2; k <= n; k *= 2) {
+#pragma unroll 1
+        for (uint32_t j = k / 2; j; j /= 2) {
+#pragma unroll 1
+            for (uint32_t p = t; p < n / 2; p += NT) {
+                const uint32_t a = 2 * p - (p & (j - 1)), b = a + j;
+                const uint64_t ax = L.kx[a], bx = L.kx[b], ay = L.ky[a], by = L.ky[b];
+                const uint32_t ar = L.row[a], br = L.row[b];
+                const bool after = ax > bx || (ax == bx && (ay > by || (ay == by && ar > br)));
+                if (after == ((a & k) == 0)) {
+                    L.kx[a] = bx; L.kx[b] = ax;
+                    L.ky[a] = by; L.ky[b] = ay;
+                    L.row[a] = br; L.row[b] = ar;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    // thread t owns PER consecutive records: least pair before its first one, front members before them
+    Pair v[PER], run = {kNone, kNone};
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q) {
+        const uint32_t i = t * PER + q;
+        v[q] = i < cnt ? Pair{L.ky[i], L.kx[i]} : Pair{kNone, kNone};
+        run = pair_min(run, v[q]);
+    }
+    for (uint32_t off = 1; off < kWave; off *= 2) {
+        const Pair o = {__shfl_up(run.key, off, kWave), __shfl_up(run.idx, off, kWave)};
+        if (lane >= off) run = pair_min(run, o);
+    }
+    if (lane == kWave - 1) L.range[wave].lo = run.key, L.range[wave].hi = run.idx;
+    run = Pair{__shfl_up(run.key, 1, kWave), __shfl_up(run.idx, 1, kWave)};
+    if (lane == 0) run = Pair{kNone, kNone};
+    __syncthreads();
+    for (uint32_t wv = 0; wv < wave; ++wv) run = pair_min(run, Pair{L.range[wv].lo, L.range[wv].hi});
+    uint32_t on = 0;                                    // bit q: record q is on the front
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q) {
+        on |= t * PER + q < cnt && !less_than(run, v[q]) ? 1u << q : 0u;
+        run = pair_min(run, v[q]);
+    }
+    const uint32_t mine = (uint32_t)__popc(on), incl = wave_scan_sum(mine);
+    if (lane == kWave - 1) L.tmp[wave] = incl;
+    __syncthreads();
+    uint32_t at = incl - mine, total = 0;
+    for (uint32_t wv = 0; wv < NT / kWave; ++wv) {
+        at += wv < wave ? L.tmp[wv] : 0u;
+        total += L.tmp[wv];
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q)
+        if ((on >> q) & 1u) emit(at++, L.row[t * PER + q]);
+    return uniform(total);
+}
+
+// Up to 1024 records eight lanes for each; more of them one lane each where their bins hold kSparse members or fewer on average
+// over the records (sum of squared bin counts <= kSparse * cnt), and otherwise by sorting.  Selections of 2048 (4096) rows, all on
+// the front, in us, pairwise with one lane / by sorting: 48 members a bin 42 / 50 (74 / 87), 64 members 56 / 53 (100 / 93),
+// 96 members 71 / 50 (131 / 88), 1024 members 615 / 54 (1219 / 95).
+constexpr uint32_t kSparse = 64;
+template <typename Emit>
+__device__ inline uint32_t staged_front(FinishLds &L, uint32_t cnt, Emit &&emit) {
+    if (cnt <= 1024) return staged_front_by<8>(L, cnt, emit);           // block-uniform
     constexpr uint32_t P = kPerFinish;
+    const uint32_t t = thread_here();
     uint32_t sq = 0;                                    // at most cnt * kStage < 2^32
 #pragma unroll
     for (uint32_t q = 0; q < P; ++q) {
-        const uint32_t b = q * kFinishThreads + threadIdx.x;
-        const uint32_t n = (b >= b_lo && b <= b_hi) ? L.off[padded<P>(b + 1)] - L.off[padded<P>(b)] : 0u;
+        const uint32_t b = q * kFinishThreads + t;
+        const uint32_t n = L.off[padded<P>(b + 1)] - L.off[padded<P>(b)];
         sq += n * n;
     }
     sq = wave_sum(sq);
     __syncthreads();                                    // L.tmp may still be read by the scan before
-    if (threadIdx.x % kWave == 0) L.tmp[threadIdx.x / kWave] = sq;
+    if (t % kWave == 0) L.tmp[t / kWave] = sq;
     __syncthreads();
     uint32_t total = 0;
     for (uint32_t wv = 0; wv < kFinishThreads / kWave; ++wv) total += L.tmp[wv];
-    return total <= 32 * cnt ? staged_front_by<1>(L, cnt, base, emit) : staged_front_by<8>(L, cnt, base, emit);
-}
-
-// The same for bins b_lo .. b_hi when their survivors do not fit the staging arrays: the records stay in the
-// workspace, reached through w.grouped (already grouped by bin: slots L.off[b_lo] .. L.off[b_hi + 1]), flags
-// in w.on_front.
-template <typename Emit>
-__device__ inline uint32_t unstaged_front(FinishLds &L, const ParetoWs &w, const Binning &bin, uint32_t b_lo, uint32_t b_hi,
-                                          Emit &&emit) {
-    constexpr uint32_t P = kPerFinish, NT = kFinishThreads, group = 8, q_step = NT / group;
-    constexpr uint64_t group_mask = (1ull << group) - 1;
-    const uint32_t t = threadIdx.x, lane = t % kWave, sub = lane % group, shift = lane - sub;
-    const uint32_t g_lo = L.off[padded<P>(b_lo)], cnt = L.off[padded<P>(b_hi + 1)] - g_lo;
-    const uint32_t cnt_pad = (cnt + q_step - 1) / q_step * q_step;       // wave-uniform trip counts
-    for (uint32_t k = t / group; k < cnt_pad; k += q_step) {
-        const bool live = k < cnt;
-        const uint32_t g = g_lo + (live ? k : 0), q = w.grouped[g];
-        const uint64_t kx = w.skx[q], ky = w.sky[q];
-        const uint32_t b = bin(kx), beg = L.off[padded<P>(b)], end = L.off[padded<P>(b + 1)];
-        bool dom = false;
-        for (uint32_t j = beg + sub; j < end; j += 2 * group) {
-            const uint32_t j1 = j + group < end ? j + group : beg;       // past the end: the first member again
-            const uint32_t q0 = w.grouped[j], q1 = w.grouped[j1];
-            const uint64_t x0 = w.skx[q0], y0 = w.sky[q0], x1 = w.skx[q1], y1 = w.sky[q1];
-            dom = dom || (x0 <= kx && y0 <= ky && (x0 < kx || y0 < ky)) || (x1 <= kx && y1 <= ky && (x1 < kx || y1 < ky));
-        }
-        const bool dominated = ((__ballot(dom) >> shift) & group_mask) != 0;
-        if (live && sub == 0) {
-            w.on_front[g] = dominated ? 0 : 1;
-            if (!dominated) atomicAdd(&L.foff[padded<P>(b)], 1u);
-        }
-    }
-    __syncthreads();
-    scan_sum_excl<NT, true>(L.foff, L.tmp);
-    for (uint32_t k = t / group; k < cnt_pad; k += q_step) {
-        const bool live = k < cnt;
-        const uint32_t g = g_lo + (live ? k : 0), q = w.grouped[g];
-        const bool front = live && w.on_front[g];
-        uint32_t rank = 0, b = 0;
-        if (front) {
-            const uint64_t kx = w.skx[q], ky = w.sky[q];
-            b = bin(kx);
-            const uint32_t beg = L.off[padded<P>(b)], end = L.off[padded<P>(b + 1)];
-            for (uint32_t j = beg + sub; j < end; j += group) {
-                if (!w.on_front[j]) continue;
-                const uint32_t qj = w.grouped[j];
-                const uint64_t jx = w.skx[qj], jy = w.sky[qj];
-                if (jx < kx || (jx == kx && (jy < ky || (jy == ky && w.surv[qj] < w.surv[q])))) ++rank;
-            }
-        }
-        for (uint32_t off = 1; off < group; off <<= 1) rank += __shfl_xor(rank, off, kWave);
-        if (front && sub == 0) emit(L.foff[padded<P>(b)] + rank, w.surv[q]);
-    }
-    return L.foff[padded<P>(kBins)];
+    return total <= kSparse * cnt ? staged_front_by<1>(L, cnt, emit) : sorted_front(L, cnt, emit);
 }
 
 // The front among up to kStage records held by the threads of the finishing block (record q of thread t is
@@ -1253,7 +1292,7 @@ __device__ inline uint32_t finish_in_lds(FinishLds &L, const Binning &bin, const
     }
     __syncthreads();                                    // both tables have been read by everyone: records may be staged from here on
     scan_sum_excl<kFinishThreads, true>(L.off, L.tmp);
-    const uint32_t m_alive = L.off[padded<P>(kBins)];
+    const uint32_t m_alive = uniform(L.off[padded<P>(kBins)]);
     // records staged in LDS, grouped by bin
 #pragma unroll
     for (uint32_t q = 0; q < PER; ++q) {
@@ -1262,21 +1301,22 @@ __device__ inline uint32_t finish_in_lds(FinishLds &L, const Binning &bin, const
             L.kx[pos] = rx[q]; L.ky[pos] = ry[q]; L.row[pos] = row_of(q); L.bin[pos] = (uint16_t)b;
         }
     }
-    return staged_front(L, m_alive, 0, 0, kBins - 1, emit);
+    return staged_front(L, m_alive, emit);
 }
 
 __device__ inline void finish_tables_neutral(FinishLds &L) {
     constexpr uint32_t P = kPerFinish;
-    for (uint32_t i = threadIdx.x; i < padded_size<P>(); i += kFinishThreads) L.lower[i] = kNone;
+    const uint32_t t = thread_here();
+    for (uint32_t i = t; i < padded_size<P>(); i += kFinishThreads) L.lower[i] = kNone;
 #pragma unroll
     for (uint32_t q = 0; q < kPerFinish; ++q) {
-        const uint32_t i = q * kFinishThreads + threadIdx.x;
+        const uint32_t i = q * kFinishThreads + t;
         L.rep[i] = kNone;
         L.cur[i] = 0;
         L.off[padded<P>(i)] = 0;
         L.foff[padded<P>(i)] = 0;
     }
-    if (threadIdx.x == 0) L.nfront = 0;
+    if (t == 0) L.nfront = 0;
 }
 
 // More kept rows than one block takes alone are finished by the n_parts blocks of the launch (part =
@@ -1345,9 +1385,9 @@ __device__ inline LargePart large_survivors(FinishLds &L, const ParetoWs &w, con
         }
     }
     __syncthreads();
-    LargePart r{L.first, L.last, 0, 0};
+    LargePart r{uniform(L.first), uniform(L.last), 0, 0};
     if (r.b_lo > r.b_hi) return r;                      // block-uniform
-    r.g_lo = L.off[padded<P>(r.b_lo)];
+    r.g_lo = uniform(L.off[padded<P>(r.b_lo)]);
     // The part's kept rows that no kept row of a lower bin dominates: listed in the workspace, counted per bin.
     auto own = [&](uint32_t b) { return b >= r.b_lo && b <= r.b_hi; };
     for (uint32_t q0 = t; q0 < (m + NT - 1) / NT * NT; q0 += B * NT) {          // wave-uniform trip count for the ballots
@@ -1374,112 +1414,175 @@ __device__ inline LargePart large_survivors(FinishLds &L, const ParetoWs &w, con
         }
     }
     __syncthreads();
-    r.n_alive = L.alive;
+    r.n_alive = uniform(L.alive);
     return r;
 }
 
-// Binning over the least and the greatest of the keys that the threads bring (kNone, 0: none).  Contains a block barrier.
-__device__ inline Binning block_binning(FinishLds &L, uint64_t lo, uint64_t hi) {
-    lo = wave_min(lo);
-    hi = ~wave_min(~hi);
-    if (threadIdx.x % kWave == 0) L.range[threadIdx.x / kWave] = Pair{lo, hi};
+// The range of the records of all threads, in every thread.  Contains a block barrier.
+__device__ inline KeyRange block_range(FinishLds &L, KeyRange r) {
+    constexpr uint32_t nw = kFinishThreads / kWave;
+    const uint32_t t = thread_here();
+    auto wave_range = [](const KeyRange &v) { return KeyRange{wave_min(v.lo), ~wave_min(~v.hi), wave_min(v.y)}; };
+    r = wave_range(r);
+    if (t % kWave == 0) L.range[t / kWave] = r;
     __syncthreads();
-#pragma unroll 1
-    for (uint32_t wv = 0; wv < kFinishThreads / kWave; ++wv) {
-        const Pair o = L.range[wv];
-        lo = min_u64(lo, o.key);
-        hi = hi < o.idx ? o.idx : hi;
+    return wave_range(L.range[t % nw]);
+}
+__device__ inline Binning binning_of(const KeyRange &r) { return r.lo <= r.hi ? binning_of(r.lo, r.hi) : binning_of(0, kNone); }
+
+// The records of up to kStage survivors (row[q]: the position of record q, where bit q of live is set; 0 elsewhere), their rows
+// in the place of the positions, and bins over their range.  Resets the tables, which the block has read; contains a block barrier.
+__device__ inline Binning listed_records(FinishLds &L, const ParetoWs &w, uint64_t (&rx)[kStage / kFinishThreads],
+                                         uint64_t (&ry)[kStage / kFinishThreads], uint32_t (&row)[kStage / kFinishThreads],
+                                         uint32_t live) {
+    constexpr uint32_t PER = kStage / kFinishThreads;
+    KeyRange r = KeyRange::none();
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q) {
+        rx[q] = w.skx[row[q]];
+        ry[q] = w.sky[row[q]];
+        row[q] = w.surv[row[q]];
     }
-    return lo <= hi ? binning_of(lo, hi) : binning_of(0, kNone);
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q)
+        if ((live >> q) & 1u) r.add(rx[q], kNone);
+    finish_tables_neutral(L);
+    return binning_of(block_range(L, r));
 }
 
-// The part's front when its survivors do not fit the staging arrays: they are pruned and grouped, in the workspace, by
-// bins of the part's own, and then finished in rounds that take as many bins as fit (a single bin that does not fit is finished in
-// the workspace instead).  Returns the number of members, whose rows are at w.staged[g_lo ..] in order.
-// (With the common bins, which hold front / 4096 rows and more each, the pairwise tests inside them were most of the time: 34 ms for
-// 1.9 million front rows, 2.9 ms like this.)
-__device__ inline uint32_t large_rounds(FinishLds &L, const ParetoWs &w, const LargePart &part) {
+// A part with more survivors than the staging arrays hold (n of them, their positions listed in w.staged[g_lo ..]): prunes and
+// groups them by x, so that they can be finished in rounds of consecutive groups.  Leaves their positions in w.grouped[g_lo ..],
+// a slot each (kNoSurvivor: none, or one that was pruned), and marks in w.staged[g_lo ..] where a group begins (no mark: 0); every group
+// has fewer than kStage slots.  Returns the number of slots.
+// The survivors are pruned and grouped by 4096 bins over their own range; a bin that holds kStage or more is done likewise, with
+// bins over its range, and so on: a bin's range is 2^12 times smaller each time, so six times are the most until a
+// bin is one x.  Then only those with the least y are left, which are equal, and grouped by row.  Bins that wait for this are a
+// list, its links in the first two entries of the bins' stretches of w.staged.
+// (1.9 million front rows: 2.6 ms; 40 ms with the bins that all parts share, which hold front / 4096 rows and more each.  One row far
+// from all others collapses the first bins: 600 000 front rows 0.90 ms without one, 0.90 - 0.93 ms with one, and 4.4 - 37 ms when a
+// bin beyond LDS is tested pair by pair, which takes minutes for some hundred thousand rows of the same x.)
+constexpr uint32_t kNoSurvivor = ~0u;
+__device__ inline uint32_t large_group(FinishLds &L, const ParetoWs &w, uint32_t g_lo, uint32_t n) {
     constexpr uint32_t P = kPerFinish, NT = kFinishThreads, B = 4;
-    const uint32_t t = threadIdx.x, g_lo = part.g_lo;
-    uint32_t n_front = 0;
-    auto survivors = [&](auto &&use) {                  // use(slot, kx, ky) for the part's survivors, B of them in flight
-        for (uint32_t i0 = t; i0 < part.n_alive; i0 += B * NT) {
-            uint32_t q[B];
-            uint64_t kx[B], ky[B];
+    const uint32_t t = threadIdx.x;
+    uint32_t *list = w.staged + g_lo, *grouped = w.grouped + g_lo;
+    uint32_t slots = 0;
+    if (t == 0) L.todo = kNoSurvivor;
+    uint32_t at = 0, cnt = n;                           // in work: list[at .. at + cnt)
+    for (bool whole = true;; whole = false) {
+        auto records = [&](auto &&use) {                // use(position, kx, ky) for each of them, B in flight
+            for (uint32_t i0 = t; i0 < cnt; i0 += B * NT) {
+                uint32_t q[B];
+                uint64_t kx[B], ky[B];
 #pragma unroll
-            for (uint32_t u = 0; u < B; ++u) q[u] = w.staged[g_lo + (i0 + u * NT < part.n_alive ? i0 + u * NT : i0)];
+                for (uint32_t u = 0; u < B; ++u) q[u] = list[at + (i0 + u * NT < cnt ? i0 + u * NT : i0)];
 #pragma unroll
-            for (uint32_t u = 0; u < B; ++u) {
-                kx[u] = w.skx[q[u]];
-                ky[u] = w.sky[q[u]];
+                for (uint32_t u = 0; u < B; ++u) {
+                    kx[u] = w.skx[q[u]];
+                    ky[u] = w.sky[q[u]];
+                }
+#pragma unroll
+                for (uint32_t u = 0; u < B; ++u)
+                    if (i0 + u * NT < cnt) use(q[u], kx[u], ky[u]);
             }
-#pragma unroll
-            for (uint32_t u = 0; u < B; ++u)
-                if (i0 + u * NT < part.n_alive) use(q[u], kx[u], ky[u]);
-        }
-    };
-    uint64_t lo = kNone, hi = 0;
-    survivors([&](uint32_t, uint64_t kx, uint64_t) {
-        lo = min_u64(lo, kx);
-        hi = hi < kx ? kx : hi;
-    });
-    finish_tables_neutral(L);                           // (the tables have been read by everybody)
-    const Binning bin = block_binning(L, lo, hi);
-    survivors([&](uint32_t, uint64_t kx, uint64_t ky) {
-        atomicMin((unsigned long long *)&L.lower[padded<P>(bin(kx))], (unsigned long long)ky);
-    });
-    __syncthreads();
-    scan_min_excl<NT>(L.lower, L.tmp64);
-    survivors([&](uint32_t, uint64_t kx, uint64_t ky) {
-        const uint32_t b = bin(kx);
-        if (ky < L.lower[padded<P>(b)]) atomicAdd(&L.off[padded<P>(b)], 1u);
-    });
-    __syncthreads();
-    scan_sum_excl<NT, true>(L.off, L.tmp);
-    survivors([&](uint32_t q, uint64_t kx, uint64_t ky) {
-        const uint32_t b = bin(kx);
-        if (ky < L.lower[padded<P>(b)]) w.grouped[g_lo + L.off[padded<P>(b)] + atomicAdd(&L.cur[b], 1u)] = q;
-    });
-    const ParetoWs part_ws{w.skx, w.sky, w.surv, w.staged, w.grouped + g_lo, w.on_front + g_lo};
-    auto emit = [&](uint32_t pos, uint32_t row) { w.staged[g_lo + n_front + pos] = row; };
-    for (uint32_t r_lo = 0; r_lo < kBins;) {
-        __syncthreads();                                // the list has been read; the previous round is done with the tables
-        if (t == 0) {
-            L.last = r_lo;
-            L.nfront = 0;
-        }
-        const uint32_t base = L.off[padded<P>(r_lo)];
-#pragma unroll
-        for (uint32_t q = 0; q < P; ++q) {
-            const uint32_t i = q * NT + t;
-            L.foff[padded<P>(i)] = 0;
-            L.cur[i] = 0;
-        }
-        __syncthreads();
-#pragma unroll
-        for (uint32_t q = 0; q < P; ++q) {
-            const uint32_t i = q * NT + t;
-            if (i > r_lo && L.off[padded<P>(i + 1)] - base <= kStage) atomicMax(&L.last, i);
-        }
-        __syncthreads();
-        const uint32_t r_hi = L.last, cnt = L.off[padded<P>(r_hi + 1)] - base;
-        uint32_t nf;
-        if (cnt <= kStage) {
-            for (uint32_t i = t; i < cnt; i += NT) {
-                const uint32_t q = part_ws.grouped[base + i];
-                const uint64_t kx = w.skx[q];
-                const uint32_t b = bin(kx), pos = L.off[padded<P>(b)] - base + atomicAdd(&L.cur[b], 1u);
-                L.kx[pos] = kx;
-                L.ky[pos] = w.sky[q];
-                L.row[pos] = w.surv[q];
-                L.bin[pos] = (uint16_t)b;
-            }
-            nf = staged_front(L, cnt, base, r_lo, r_hi, emit);
+        };
+        KeyRange r = KeyRange::none();
+        records([&](uint32_t, uint64_t kx, uint64_t ky) { r.add(kx, ky); });
+        finish_tables_neutral(L);                       // (the tables have been read by everybody)
+        r = block_range(L, r);
+        const bool one_x = r.lo == r.hi;                // block-uniform
+        Binning bin = binning_of(r);
+        if (one_x) {
+            KeyRange rows = KeyRange::none();
+            records([&](uint32_t q, uint64_t, uint64_t ky) {
+                if (ky == r.y) rows.add(w.surv[q], 0);
+            });
+            __syncthreads();
+            bin = binning_of(block_range(L, rows));
         } else {
-            nf = unstaged_front(L, part_ws, bin, r_lo, r_hi, emit);
+            records([&](uint32_t, uint64_t kx, uint64_t ky) {
+                atomicMin((unsigned long long *)&L.lower[padded<P>(bin(kx))], (unsigned long long)ky);
+            });
+            __syncthreads();
+            scan_min_excl<NT>(L.lower, L.tmp64);
         }
-        n_front += nf;
-        r_lo = r_hi + 1;
+        auto kept = [&](auto &&use) {                   // use(position, bin)
+            records([&](uint32_t q, uint64_t kx, uint64_t ky) {
+                if (one_x) {
+                    if (ky == r.y) use(q, bin(w.surv[q]));
+                } else {
+                    const uint32_t b = bin(kx);
+                    if (ky < L.lower[padded<P>(b)]) use(q, b);
+                }
+            });
+        };
+        kept([&](uint32_t, uint32_t b) { atomicAdd(&L.off[padded<P>(b)], 1u); });
+        __syncthreads();
+        scan_sum_excl<NT, true>(L.off, L.tmp);
+        kept([&](uint32_t q, uint32_t b) { grouped[at + L.off[padded<P>(b)] + atomicAdd(&L.cur[b], 1u)] = q; });
+        __syncthreads();                                // the list has been read
+        const uint32_t left = uniform(L.off[padded<P>(kBins)]);
+        if (whole) slots = cnt = left;
+        for (uint32_t i = t; i < cnt; i += NT) {
+            list[at + i] = i < left ? 0u : 1u;          // (what is not left may be split anywhere)
+            if (i >= left) grouped[at + i] = kNoSurvivor;
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < P; ++q) {
+            const uint32_t b = q * NT + t, first = L.off[padded<P>(b)], members = L.off[padded<P>(b + 1)] - first;
+            if (members >= kStage) {
+                list[at + first + 1] = members;
+                list[at + first] = atomicExch(&L.todo, at + first);
+            } else if (members) {
+                list[at + first] = 1;
+            }
+        }
+        __syncthreads();
+        at = uniform(L.todo);
+        if (at == kNoSurvivor) return slots;            // block-uniform
+        const uint32_t next = list[at];
+        cnt = uniform(list[at + 1]);
+        __syncthreads();                                // everybody has read the link
+        if (t == 0) L.todo = next;
+        for (uint32_t i = t; i < cnt; i += NT) list[at + i] = grouped[at + i];
+        __syncthreads();
+    }
+}
+
+// The part's front when its survivors do not fit the staging arrays: groups of consecutive x, as many at a time as do.  Returns
+// the number of members, whose rows are at w.staged[g_lo ..] in order.
+__device__ inline uint32_t large_rounds(FinishLds &L, const ParetoWs &w, const LargePart &part) {
+    constexpr uint32_t NT = kFinishThreads, PER = kStage / NT;
+    const uint32_t slots = large_group(L, w, part.g_lo, part.n_alive);
+    const uint32_t *grouped = w.grouped + part.g_lo, *begins = w.staged + part.g_lo;
+    uint32_t n_front = 0;
+    for (uint32_t from = 0; from < slots;) {
+        const uint32_t t = thread_here(), left = slots - from;
+        uint32_t end = 0;                               // the last group that begins within kStage slots
+#pragma unroll
+        for (uint32_t q = 0; q < PER; ++q) {
+            const uint32_t i = q * NT + t;
+            if (i < left && begins[from + i]) end = i;
+        }
+        end = wave_max(end);
+        if (t % kWave == 0) L.tmp[t / kWave] = end;
+        __syncthreads();                                // (also: the round before is done with the tables)
+        end = left <= kStage ? left : wave_max(L.tmp[t % (NT / kWave)]);
+        uint64_t rx[PER], ry[PER];
+        uint32_t rr[PER], live = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < PER; ++q) {
+            const uint32_t i = q * NT + t;
+            rr[q] = i < end ? grouped[from + i] : kNoSurvivor;
+            live |= rr[q] != kNoSurvivor ? 1u << q : 0u;
+            rr[q] = rr[q] != kNoSurvivor ? rr[q] : 0u;
+        }
+        const Binning bin = listed_records(L, w, rx, ry, rr, live);
+        n_front += finish_in_lds(L, bin, rx, ry, [&](uint32_t q) { return rr[q]; }, live, [&](uint32_t pos, uint32_t row) {
+            w.staged[part.g_lo + n_front + pos] = row;  // (over marks of slots that are done with)
+        });
+        from += end;
     }
     return n_front;
 }
@@ -1592,37 +1695,21 @@ __global__ __launch_bounds__(kFinishThreads) void pareto_finish_kernel(ParetoWs 
     const Binning bin = sampled_binning(sc, L.rng);     // its barrier also covers the tables above
     const bool large = m > kStage;                      // block-uniform
     const uint32_t part = helper ? blockIdx.x - first_helper + 1 : 0, n_parts = gridDim.x - first_helper + 1;
-    Binning own = bin;
     LargePart p{0, 0, 0, m};
-    if (large) {
-        p = large_survivors(L, w, bin, m, part, n_parts);
-        if (p.n_alive <= kStage) {
-            // The records, and bins of the part's own for them: its share of the common ones is few, and one of those may hold
-            // hundreds (the lowest ones, for want of lower bins that would prune them).
-            uint64_t lo = kNone, hi = 0;
-#pragma unroll
-            for (uint32_t q = 0; q < kPer; ++q) rr[q] = q * kFinishThreads + t < p.n_alive ? w.staged[p.g_lo + q * kFinishThreads + t] : 0u;
-#pragma unroll
-            for (uint32_t q = 0; q < kPer; ++q) {
-                rx[q] = w.skx[rr[q]];
-                ry[q] = w.sky[rr[q]];
-                rr[q] = w.surv[rr[q]];
-            }
-#pragma unroll
-            for (uint32_t q = 0; q < kPer; ++q) {
-                if (q * kFinishThreads + t >= p.n_alive) continue;
-                lo = min_u64(lo, rx[q]);
-                hi = hi < rx[q] ? rx[q] : hi;
-            }
-            finish_tables_neutral(L);                   // (the tables have been read by everybody)
-            own = block_binning(L, lo, hi);
-        }
-    }
+    if (large) p = large_survivors(L, w, bin, m, part, n_parts);
     uint32_t n_front;
     if (p.n_alive <= kStage) {                          // (a part without survivors goes through with no live record)
         uint32_t live = 0;
 #pragma unroll
         for (uint32_t q = 0; q < kPer; ++q) live |= q * kFinishThreads + t < p.n_alive ? 1u << q : 0u;
+        Binning own = bin;
+        if (large) {
+            // Bins of the part's own: its share of the common ones is few, and one of those may hold hundreds of survivors (the
+            // lowest ones, for want of lower bins that would prune them).
+#pragma unroll
+            for (uint32_t q = 0; q < kPer; ++q) rr[q] = (live >> q) & 1u ? w.staged[p.g_lo + q * kFinishThreads + t] : 0u;
+            own = listed_records(L, w, rx, ry, rr, live);
+        }
         n_front = finish_in_lds(L, own, rx, ry, [&](uint32_t q) { return rr[q]; }, live, [&](uint32_t pos, uint32_t row) {
             if (large) w.staged[p.g_lo + pos] = row;
             else if (pos < capacity) out_idx[pos] = row;

@@ -88,7 +88,7 @@ def test_no_sample_row_passes(ora, setup, n):
 
 
 def test_all_rows_in_one_bin_of_an_unsampled_range(ora, setup):
-    # 13 600 kept rows that nothing prunes: tested pair by pair, so not more of them
+    # 13 600 kept rows that nothing prunes
     n = 30_000
     rng = np.random.default_rng(4)
     fe = np.ones(n, np.uint8)
@@ -97,3 +97,50 @@ def test_all_rows_in_one_bin_of_an_unsampled_range(ora, setup):
     _check(ora, setup, x, 1e6 - 7.0 * x, fe)            # all of them on the front, many equal
     for x in (np.full(n, np.inf), np.full(n, -np.inf), np.round(rng.random(n), 3)):
         _check(ora, setup, x, np.round(rng.random(n) * 1000.0, 1), fe)
+
+
+def _crowd(kind, n):
+    """Rows that crowd in a few values of x, or at a few of its scales: one bin of any equal slicing holds most of them."""
+    rng = np.random.default_rng(n)
+    if kind == "one x":
+        return np.full(n, 3.0), rng.random(n)
+    if kind == "one x, few ys":                         # ties in y by the ten thousand, all on the front
+        return np.full(n, -2.5), rng.integers(0, 7, n).astype(np.float64)
+    if kind == "one point":
+        return np.full(n, 1e-300), np.full(n, -np.inf)
+    if kind == "few xs":
+        x = rng.integers(1, 6, n).astype(np.float64)
+        return x, np.round(rng.random(n), 4) - x
+    if kind == "few points":                            # five of them, tied by the ten thousand, all on the front
+        x = rng.integers(1, 6, n).astype(np.float64)
+        return x, -x
+    # clusters inside clusters inside clusters: slices of the widest range hold one, slices of its range one of its own
+    rank = rng.permutation(n)
+    same = rank // 3 if kind == "clusters, ties" else rank
+    m = max(same.max() // 9, 1)
+    outer = np.minimum(same // (3 * m), 2)
+    x = np.ldexp(1.0, outer * 300 - 300) * (1.0 + np.ldexp(same // m - 3 * outer, -20) + np.ldexp(same % m, -51))
+    return x, -1.0 * same
+
+
+# a part's share beyond LDS, by far
+@pytest.mark.parametrize("n", [4097, 9_001, 300_007, 1_600_000])
+@pytest.mark.parametrize("kind", ["one x", "one x, few ys", "one point", "few xs", "few points", "clusters", "clusters, ties"])
+def test_rows_that_crowd_in_x(ora, setup, kind, n):
+    x, y = _crowd(kind, n)
+    _check(ora, setup, x, y)
+    fe = (np.random.default_rng(n + 1).random(n) < 0.5).astype(np.uint8)
+    _check(ora, setup, x, y, fe, capacity=n // 3)
+
+
+# records that one block stages: in a bin or two of their range, with and without ties
+@pytest.mark.parametrize("n", [1024, 1025, 2047, 2048, 2049, 4095, 4096])
+@pytest.mark.parametrize("kind", ["one x", "one x, few ys", "one point", "few xs", "few points", "clusters", "clusters, ties"])
+def test_few_rows_that_crowd_in_x(ora, setup, kind, n):
+    x, y = _crowd(kind, n)
+    _check(ora, setup, x, y)
+    x, y = x.copy(), y.copy()
+    far = n // 2
+    x[far], y[far] = np.inf, y.min() - 1.0              # the right end of the range far from all others
+    _check(ora, setup, x, y)
+    _check(ora, setup, np.append(x, 5.0)[1:], np.append(y, -np.inf)[1:])
