@@ -1348,11 +1348,13 @@ __device__ inline LargePart large_survivors(FinishLds &L, const ParetoWs &w, con
         L.last = 0;
         L.alive = 0;
     }
+    // The end of a batch can be beyond 32 bits; sums that saturate are past every row then (there are at most 2^32 - 4096).
+    auto plus = [](uint32_t q, uint32_t d) { return __builtin_elementwise_add_sat(q, d); };
     uint64_t kx[B], ky[B];
     auto request = [&](uint32_t q0) {
 #pragma unroll
         for (uint32_t u = 0; u < B; ++u) {
-            const uint32_t q = q0 + u * NT < m ? q0 + u * NT : 0u;
+            const uint32_t q = plus(q0, u * NT) < m ? q0 + u * NT : 0u;
             kx[u] = w.skx[q];
             ky[u] = w.sky[q];
         }
@@ -1364,13 +1366,13 @@ __device__ inline LargePart large_survivors(FinishLds &L, const ParetoWs &w, con
     for (uint32_t q0 = t; q0 < m;) {
 #pragma unroll
         for (uint32_t u = 0; u < B; ++u) {
-            if (q0 + u * NT < m) {
+            if (plus(q0, u * NT) < m) {
                 const uint32_t b = padded<P>(bin(kx[u]));
                 atomicAdd(&L.off[b], 1u);
                 atomicMin((unsigned long long *)&L.lower[b], (unsigned long long)ky[u]);
             }
         }
-        q0 += B * NT;
+        q0 = plus(q0, B * NT);
         if (q0 < m) request(q0);
     }
     __syncthreads();
@@ -1390,18 +1392,18 @@ __device__ inline LargePart large_survivors(FinishLds &L, const ParetoWs &w, con
     r.g_lo = uniform(L.off[padded<P>(r.b_lo)]);
     // The part's kept rows that no kept row of a lower bin dominates: listed in the workspace, counted per bin.
     auto own = [&](uint32_t b) { return b >= r.b_lo && b <= r.b_hi; };
-    for (uint32_t q0 = t; q0 < (m + NT - 1) / NT * NT; q0 += B * NT) {          // wave-uniform trip count for the ballots
+    for (uint32_t q0 = t; q0 < (m + NT - 1) / NT * NT; q0 = plus(q0, B * NT)) {      // wave-uniform trip count for the ballots
         if (!held) {                                    // block-uniform
 #pragma unroll
-            for (uint32_t u = 0; u < B; ++u) kx[u] = w.skx[q0 + u * NT < m ? q0 + u * NT : 0u];
+            for (uint32_t u = 0; u < B; ++u) kx[u] = w.skx[plus(q0, u * NT) < m ? q0 + u * NT : 0u];
 #pragma unroll
             for (uint32_t u = 0; u < B; ++u)
-                if (q0 + u * NT < m && own(bin(kx[u]))) ky[u] = w.sky[q0 + u * NT];
+                if (plus(q0, u * NT) < m && own(bin(kx[u]))) ky[u] = w.sky[q0 + u * NT];
         }
 #pragma unroll
         for (uint32_t u = 0; u < B; ++u) {
             const uint32_t b = bin(kx[u]);
-            const bool alive = q0 + u * NT < m && own(b) && ky[u] < L.lower[padded<P>(b)];
+            const bool alive = plus(q0, u * NT) < m && own(b) && ky[u] < L.lower[padded<P>(b)];
             const uint64_t mask = __ballot(alive);
             if (mask == 0) continue;                    // wave-uniform
             uint32_t at = 0;
@@ -1457,7 +1459,7 @@ __device__ inline Binning listed_records(FinishLds &L, const ParetoWs &w, uint64
 // The survivors are pruned and grouped by 4096 bins over their own range; a bin that holds kStage or more is done likewise, with
 // bins over its range, and so on: a bin's range is 2^12 times smaller each time, so six times are the most until a
 // bin is one x.  Then only those with the least y are left, which are equal, and grouped by row.  Bins that wait for this are a
-// list, its links in the first two entries of the bins' stretches of w.staged.
+// list, its links in the first two entries of the bins' stretches of w.staged.  (At most 2^32 - 4096 rows: indices below do not wrap.)
 // (1.9 million front rows: 2.6 ms; 40 ms with the bins that all parts share, which hold front / 4096 rows and more each.  One row far
 // from all others collapses the first bins: 600 000 front rows 0.90 ms without one, 0.90 - 0.93 ms with one, and 4.4 - 37 ms when a
 // bin beyond LDS is tested pair by pair, which takes minutes for some hundred thousand rows of the same x.)

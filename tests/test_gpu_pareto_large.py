@@ -144,3 +144,25 @@ def test_few_rows_that_crowd_in_x(ora, setup, kind, n):
     x[far], y[far] = np.inf, y.min() - 1.0              # the right end of the range far from all others
     _check(ora, setup, x, y)
     _check(ora, setup, np.append(x, 5.0)[1:], np.append(y, -np.inf)[1:])
+
+
+def test_most_rows_end(setup):
+    """2^32 - 4096 rows, all on the front: index arithmetic of the batched loops next to the end of 32 bits (a batch's end wraps)."""
+    torch, ctx = setup
+    from paper_2412_04788_amd import guide
+    n = 2 ** 32 - 4096
+    need = ctx.select_workspace_bytes(guide.SELECT_PARETO, n)
+    if torch.cuda.mem_get_info()[0] < need + 16 * n + 2 ** 31:
+        pytest.skip("200 GB of device memory")
+    x = torch.arange(n, dtype=torch.float64, device="cuda")
+    x += 2.0 ** 33                                      # one binade: the parts share the rows evenly
+    y = -x
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    idx = torch.full((100_000,), -7, dtype=torch.int64, device="cuda")
+    cnt = torch.full((1,), -7, dtype=torch.int64, device="cuda")
+    ctx.select(guide.SELECT_PARETO, n, x, idx, None, cnt, ws, objective_y=y, capacity=idx.numel())
+    torch.cuda.synchronize()
+    assert int(cnt[0]) == n
+    assert torch.equal(idx, torch.arange(idx.numel(), device="cuda"))
+    del x, y, ws
+    torch.cuda.empty_cache()
