@@ -665,6 +665,15 @@ __device__ inline Binning binning_of(uint64_t lo, uint64_t hi) {
     b.shift = bits > kBinBits ? bits - kBinBits : 0u;
     return b;
 }
+// The stretch of keys up to `hi` that bins b_lo .. b_hi slice (hi: the end of the binning's range, beyond which only a few rows are;
+// what is below the range is in its first bin).
+struct Stretch {
+    uint64_t lo, hi;
+};
+__device__ inline Stretch stretch_of(const Binning &bin, uint64_t hi, uint32_t b_lo, uint32_t b_hi) {
+    const uint64_t lo = bin.lo + ((uint64_t)b_lo << bin.shift), end = bin.lo + (((uint64_t)b_hi + 1) << bin.shift) - 1;
+    return Stretch{lo, end < lo ? hi : min_u64(end, hi)};           // (end < lo: it is beyond 64 bits)
+}
 
 // kBins-entry tables in LDS that a block scans are stored with one unused slot after every PER
 // entries (PER = entries per thread of the scan): thread t's entries then start at slot t * (PER + 1),
@@ -1333,7 +1342,7 @@ constexpr uint32_t kLargeBatch = 10;                    // records per thread re
 static_assert(kLargeParts <= kWave, "the last part scans the parts' counts in one wave");
 static_assert(kLargeParts <= sizeof(SelectScratch::part_cnt) / sizeof(uint32_t), "one scratch entry per part");
 struct LargePart {
-    uint32_t b_lo, b_hi;        // the part's bins (b_lo > b_hi: none; non-empty ones in between are all its own)
+    Stretch of;                 // what its bins slice
     uint32_t g_lo;              // its first slot
     uint32_t n_alive;           // its survivors: their positions are at w.staged[g_lo ..], their counts per bin in L.cur
 };
@@ -1387,11 +1396,12 @@ __device__ inline LargePart large_survivors(FinishLds &L, const ParetoWs &w, con
         }
     }
     __syncthreads();
-    LargePart r{uniform(L.first), uniform(L.last), 0, 0};
-    if (r.b_lo > r.b_hi) return r;                      // block-uniform
-    r.g_lo = uniform(L.off[padded<P>(r.b_lo)]);
+    const uint32_t b_lo = uniform(L.first), b_hi = uniform(L.last);        // the part's bins (non-empty ones in between are all its own)
+    LargePart r{stretch_of(bin, uniform(L.rng[1]), b_lo, b_hi), 0, 0};
+    if (b_lo > b_hi) return r;                          // block-uniform
+    r.g_lo = uniform(L.off[padded<P>(b_lo)]);
     // The part's kept rows that no kept row of a lower bin dominates: listed in the workspace, counted per bin.
-    auto own = [&](uint32_t b) { return b >= r.b_lo && b <= r.b_hi; };
+    auto own = [&](uint32_t b) { return b >= b_lo && b <= b_hi; };
     for (uint32_t q0 = t; q0 < (m + NT - 1) / NT * NT; q0 = plus(q0, B * NT)) {      // wave-uniform trip count for the ballots
         if (!held) {                                    // block-uniform
 #pragma unroll
@@ -1431,14 +1441,22 @@ __device__ inline KeyRange block_range(FinishLds &L, KeyRange r) {
     return wave_range(L.range[t % nw]);
 }
 __device__ inline Binning binning_of(const KeyRange &r) { return r.lo <= r.hi ? binning_of(r.lo, r.hi) : binning_of(0, kNone); }
+// Bins for a part's records: over their range inside the part's stretch of the common bins, when there are any.  A row far beyond
+// the sampled range shares the first or the last of the common bins; over its range the part's others would share one bin.
+__device__ inline Binning binning_of(const KeyRange &r, const Stretch &of) {
+    const uint64_t lo = r.lo < of.lo ? of.lo : r.lo, hi = min_u64(r.hi, of.hi);
+    return lo <= hi ? binning_of(lo, hi) : binning_of(r);
+}
 
 // The records of up to kStage survivors (row[q]: the position of record q, where bit q of live is set; 0 elsewhere), their rows
-// in the place of the positions, and bins over their range.  Resets the tables, which the block has read; contains a block barrier.
+// in the place of the positions, and bins over their range inside `of`, or over all of it when more than a sixteenth of the n are
+// outside (too many for the end bins).  Resets the tables, which the block has read; contains a block barrier.
 __device__ inline Binning listed_records(FinishLds &L, const ParetoWs &w, uint64_t (&rx)[kStage / kFinishThreads],
                                          uint64_t (&ry)[kStage / kFinishThreads], uint32_t (&row)[kStage / kFinishThreads],
-                                         uint32_t live) {
+                                         uint32_t live, uint32_t n, const Stretch &of) {
     constexpr uint32_t PER = kStage / kFinishThreads;
     KeyRange r = KeyRange::none();
+    uint32_t outside = 0;                               // records of the wave
 #pragma unroll
     for (uint32_t q = 0; q < PER; ++q) {
         rx[q] = w.skx[row[q]];
@@ -1446,17 +1464,24 @@ __device__ inline Binning listed_records(FinishLds &L, const ParetoWs &w, uint64
         row[q] = w.surv[row[q]];
     }
 #pragma unroll
-    for (uint32_t q = 0; q < PER; ++q)
-        if ((live >> q) & 1u) r.add(rx[q], kNone);
+    for (uint32_t q = 0; q < PER; ++q) {
+        const bool there = (live >> q) & 1u;
+        if (there) r.add(rx[q], kNone);
+        outside += (uint32_t)__popcll(__ballot(there && (rx[q] < of.lo || rx[q] > of.hi)));
+    }
     finish_tables_neutral(L);
-    return binning_of(block_range(L, r));
+    const uint32_t t = thread_here();
+    if (t % kWave == 0) L.tmp64[t / kWave] = outside;    // (L.tmp may still be read by a round's start)
+    r = block_range(L, r);
+    outside = wave_sum(t % kWave < kFinishThreads / kWave ? (uint32_t)L.tmp64[t % kWave] : 0u);
+    return 16 * outside <= n ? binning_of(r, of) : binning_of(r);
 }
 
-// A part with more survivors than the staging arrays hold (n of them, their positions listed in w.staged[g_lo ..]): prunes and
+// A part with more survivors than the staging arrays hold (their positions listed in w.staged[g_lo ..]): prunes and
 // groups them by x, so that they can be finished in rounds of consecutive groups.  Leaves their positions in w.grouped[g_lo ..],
 // a slot each (kNoSurvivor: none, or one that was pruned), and marks in w.staged[g_lo ..] where a group begins (no mark: 0); every group
 // has fewer than kStage slots.  Returns the number of slots.
-// The survivors are pruned and grouped by 4096 bins over their own range; a bin that holds kStage or more is done likewise, with
+// The survivors are pruned and grouped by 4096 bins over their range inside the part's stretch; a bin that holds kStage or more is done likewise, with
 // bins over its range, and so on: a bin's range is 2^12 times smaller each time, so six times are the most until a
 // bin is one x.  Then only those with the least y are left, which are equal, and grouped by row.  Bins that wait for this are a
 // list, its links in the first two entries of the bins' stretches of w.staged.  (At most 2^32 - 4096 rows: indices below do not wrap.)
@@ -1464,13 +1489,13 @@ __device__ inline Binning listed_records(FinishLds &L, const ParetoWs &w, uint64
 // from all others collapses the first bins: 600 000 front rows 0.90 ms without one, 0.90 - 0.93 ms with one, and 4.4 - 37 ms when a
 // bin beyond LDS is tested pair by pair, which takes minutes for some hundred thousand rows of the same x.)
 constexpr uint32_t kNoSurvivor = ~0u;
-__device__ inline uint32_t large_group(FinishLds &L, const ParetoWs &w, uint32_t g_lo, uint32_t n) {
+__device__ inline uint32_t large_group(FinishLds &L, const ParetoWs &w, const LargePart &part) {
     constexpr uint32_t P = kPerFinish, NT = kFinishThreads, B = 4;
     const uint32_t t = threadIdx.x;
-    uint32_t *list = w.staged + g_lo, *grouped = w.grouped + g_lo;
+    uint32_t *list = w.staged + part.g_lo, *grouped = w.grouped + part.g_lo;
     uint32_t slots = 0;
     if (t == 0) L.todo = kNoSurvivor;
-    uint32_t at = 0, cnt = n;                           // in work: list[at .. at + cnt)
+    uint32_t at = 0, cnt = part.n_alive;                // in work: list[at .. at + cnt)
     for (bool whole = true;; whole = false) {
         auto records = [&](auto &&use) {                // use(position, kx, ky) for each of them, B in flight
             for (uint32_t i0 = t; i0 < cnt; i0 += B * NT) {
@@ -1493,7 +1518,7 @@ __device__ inline uint32_t large_group(FinishLds &L, const ParetoWs &w, uint32_t
         finish_tables_neutral(L);                       // (the tables have been read by everybody)
         r = block_range(L, r);
         const bool one_x = r.lo == r.hi;                // block-uniform
-        Binning bin = binning_of(r);
+        Binning bin = whole ? binning_of(r, part.of) : binning_of(r);
         if (one_x) {
             KeyRange rows = KeyRange::none();
             records([&](uint32_t q, uint64_t, uint64_t ky) {
@@ -1556,7 +1581,7 @@ __device__ inline uint32_t large_group(FinishLds &L, const ParetoWs &w, uint32_t
 // the number of members, whose rows are at w.staged[g_lo ..] in order.
 __device__ inline uint32_t large_rounds(FinishLds &L, const ParetoWs &w, const LargePart &part) {
     constexpr uint32_t NT = kFinishThreads, PER = kStage / NT;
-    const uint32_t slots = large_group(L, w, part.g_lo, part.n_alive);
+    const uint32_t slots = large_group(L, w, part);
     const uint32_t *grouped = w.grouped + part.g_lo, *begins = w.staged + part.g_lo;
     uint32_t n_front = 0;
     for (uint32_t from = 0; from < slots;) {
@@ -1580,7 +1605,7 @@ __device__ inline uint32_t large_rounds(FinishLds &L, const ParetoWs &w, const L
             live |= rr[q] != kNoSurvivor ? 1u << q : 0u;
             rr[q] = rr[q] != kNoSurvivor ? rr[q] : 0u;
         }
-        const Binning bin = listed_records(L, w, rx, ry, rr, live);
+        const Binning bin = listed_records(L, w, rx, ry, rr, live, end, Stretch{0, kNone});
         n_front += finish_in_lds(L, bin, rx, ry, [&](uint32_t q) { return rr[q]; }, live, [&](uint32_t pos, uint32_t row) {
             w.staged[part.g_lo + n_front + pos] = row;  // (over marks of slots that are done with)
         });
@@ -1697,7 +1722,7 @@ __global__ __launch_bounds__(kFinishThreads) void pareto_finish_kernel(ParetoWs 
     const Binning bin = sampled_binning(sc, L.rng);     // its barrier also covers the tables above
     const bool large = m > kStage;                      // block-uniform
     const uint32_t part = helper ? blockIdx.x - first_helper + 1 : 0, n_parts = gridDim.x - first_helper + 1;
-    LargePart p{0, 0, 0, m};
+    LargePart p{Stretch{0, kNone}, 0, m};
     if (large) p = large_survivors(L, w, bin, m, part, n_parts);
     uint32_t n_front;
     if (p.n_alive <= kStage) {                          // (a part without survivors goes through with no live record)
@@ -1710,7 +1735,7 @@ __global__ __launch_bounds__(kFinishThreads) void pareto_finish_kernel(ParetoWs 
             // lowest ones, for want of lower bins that would prune them).
 #pragma unroll
             for (uint32_t q = 0; q < kPer; ++q) rr[q] = (live >> q) & 1u ? w.staged[p.g_lo + q * kFinishThreads + t] : 0u;
-            own = listed_records(L, w, rx, ry, rr, live);
+            own = listed_records(L, w, rx, ry, rr, live, p.n_alive, p.of);
         }
         n_front = finish_in_lds(L, own, rx, ry, [&](uint32_t q) { return rr[q]; }, live, [&](uint32_t pos, uint32_t row) {
             if (large) w.staged[p.g_lo + pos] = row;

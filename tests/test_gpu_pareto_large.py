@@ -99,6 +99,25 @@ def test_all_rows_in_one_bin_of_an_unsampled_range(ora, setup):
         _check(ora, setup, x, np.round(rng.random(n) * 1000.0, 1), fe)
 
 
+# one row, or several, far from all others, which the sample misses: the parts at the ends of x bin the others as without it
+@pytest.mark.parametrize("n", [50_000, 200_000, 600_000, 1_900_800])
+@pytest.mark.parametrize("far", ["right", "left", "both", "many"])
+def test_far_rows(ora, setup, n, far):
+    rng = np.random.default_rng(n + 3)
+    x = rng.permutation(n) + 1.0
+    y = -x
+    odd = np.setdiff1d(np.arange(n), _sample_rows(n))
+    odd = rng.choice(odd, 2000 if far == "many" else 2, replace=False)
+    if far in ("right", "both"):
+        x[odd[0]], y[odd[0]] = (np.inf if n == 200_000 else 1e300), -1e9
+    if far in ("left", "both"):
+        x[odd[1]], y[odd[1]] = (-np.inf if n == 200_000 else 0.0), 1e9
+    if far == "many":
+        x[odd] = 1e300 * (1.0 + np.arange(2000.0))
+        y[odd] = -1e9 - np.arange(2000.0)
+    assert _check(ora, setup, x, y) == n
+
+
 def _crowd(kind, n):
     """Rows that crowd in a few values of x, or at a few of its scales: one bin of any equal slicing holds most of them."""
     rng = np.random.default_rng(n)
