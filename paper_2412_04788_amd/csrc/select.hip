@@ -1344,7 +1344,7 @@ static_assert(kLargeParts <= sizeof(SelectScratch::part_cnt) / sizeof(uint32_t),
 struct LargePart {
     Stretch of;                 // what its bins slice
     uint32_t g_lo;              // its first slot
-    uint32_t n_alive;           // its survivors: their positions are at w.staged[g_lo ..], their counts per bin in L.cur
+    uint32_t n_alive;           // its survivors: their positions are at w.staged[g_lo ..]
 };
 // The tables must be in their neutral states, and the block has met since.
 __device__ inline LargePart large_survivors(FinishLds &L, const ParetoWs &w, const Binning &bin, uint32_t m, uint32_t part,
@@ -1400,7 +1400,7 @@ __device__ inline LargePart large_survivors(FinishLds &L, const ParetoWs &w, con
     LargePart r{stretch_of(bin, uniform(L.rng[1]), b_lo, b_hi), 0, 0};
     if (b_lo > b_hi) return r;                          // block-uniform
     r.g_lo = uniform(L.off[padded<P>(b_lo)]);
-    // The part's kept rows that no kept row of a lower bin dominates: listed in the workspace, counted per bin.
+    // The part's kept rows that no kept row of a lower bin dominates: listed in the workspace.
     auto own = [&](uint32_t b) { return b >= b_lo && b <= b_hi; };
     for (uint32_t q0 = t; q0 < (m + NT - 1) / NT * NT; q0 = plus(q0, B * NT)) {      // wave-uniform trip count for the ballots
         if (!held) {                                    // block-uniform
@@ -1419,10 +1419,7 @@ __device__ inline LargePart large_survivors(FinishLds &L, const ParetoWs &w, con
             uint32_t at = 0;
             if (lane == 0) at = atomicAdd(&L.alive, (uint32_t)__popcll(mask));
             at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(mask & ((1ull << lane) - 1));
-            if (alive) {
-                w.staged[r.g_lo + at] = q0 + u * NT;
-                atomicAdd(&L.cur[b], 1u);
-            }
+            if (alive) w.staged[r.g_lo + at] = q0 + u * NT;
         }
     }
     __syncthreads();
