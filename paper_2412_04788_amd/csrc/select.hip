@@ -625,7 +625,7 @@ __device__ inline uint32_t sample_of(uint32_t k, uint32_t n) {
 constexpr uint32_t kStage = 4096;        // survivors whose records the finishing block holds in LDS
 constexpr uint32_t kFinishThreads = 1024;
 
-// Caller workspace of the Pareto path.
+// Caller workspace of the Pareto path (kParetoRowBytes a row).
 struct ParetoWs {
     uint64_t *skx, *sky;  // [n]: keys of surviving rows
     uint32_t *surv;       // [n]: surviving rows, arbitrary order
@@ -634,7 +634,7 @@ struct ParetoWs {
                           // members' rows in order
     uint32_t *grouped;    // [n]: positions into surv, grouped by bin (parts whose survivors do not fit LDS)
 };
-size_t pareto_ws_bytes(uint64_t n) { return (size_t)n * (8 + 8 + 4 + 4 + 4 + 1 + 1) + 256; }   // (two bytes a row to spare)
+size_t pareto_ws_bytes(uint64_t n) { return (size_t)n * kParetoRowBytes + 256; }
 ParetoWs pareto_ws(void *ws, uint64_t n) {
     ParetoWs w;
     w.skx = (uint64_t *)ws;

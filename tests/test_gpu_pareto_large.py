@@ -165,6 +165,23 @@ def test_few_rows_that_crowd_in_x(ora, setup, kind, n):
     _check(ora, setup, np.append(x, 5.0)[1:], np.append(y, -np.inf)[1:])
 
 
+@pytest.mark.parametrize("n, kind", [(4097, "one point"), (20_011, "clusters"), (300_007, "clusters, ties"), (300_007, "one point")])
+def test_workspace_is_what_is_asked_for(setup, n, kind):
+    torch, ctx = setup
+    from paper_2412_04788_amd import guide
+    x, y = (_dev(torch, a) for a in _crowd(kind, n))
+    need = ctx.select_workspace_bytes(guide.SELECT_PARETO, n)
+    buf = torch.full((need + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    idx = torch.full((n,), -7, dtype=torch.int64, device="cuda")
+    cnt = torch.full((1,), -7, dtype=torch.int64, device="cuda")
+    with pytest.raises(guide.GuideError):
+        ctx.select(guide.SELECT_PARETO, n, x, idx, None, cnt, buf[:need - 1], objective_y=y, capacity=n)
+    ctx.select(guide.SELECT_PARETO, n, x, idx, None, cnt, buf[:need], objective_y=y, capacity=n)
+    torch.cuda.synchronize()
+    assert int(cnt[0]) == n and bool((idx >= 0).all())
+    assert bool((buf[need:] == 0xA5).all())
+
+
 def test_most_rows_end(setup):
     """2^32 - 4096 rows, all on the front: index arithmetic of the batched loops next to the end of 32 bits (a batch's end wraps)."""
     torch, ctx = setup
