@@ -892,7 +892,7 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
 }
 
 // One wave per simulated configuration that ended normally.  TTFT of request i = first token time - arrival /
-// rate; the values (absent requests count as +inf) are sorted inside the wave's registers, R = 1, 2, 4, 8 or 16 per lane --
+// rate; the values (absent requests, and those that arrive beyond the range of doubles, count as +inf) are sorted inside the wave's registers, R = 1, 2, 4, 8 or 16 per lane --
 // as few as hold the trace -- by a bitonic network in which every compare-exchange puts the smaller value at the smaller
 // index: element e = R * lane + register; a stage pairs e with e ^ m, which is another register of the same lane while m < R
 // and the same-numbered (or mirrored) register of lane ^ (m / R) otherwise.  Then nearest-rank
@@ -988,6 +988,7 @@ __global__ __launch_bounds__(kPctBlock) void percentile_kernel(SimWs ws, const T
         if (i < n_req) {
             const double f = first[i];
             t = f - trace->arrival[i] / rate;
+            t = t == t ? t : INFINITY;                      // (arrival / rate is infinite; the network cannot place a NaN)
             const uint32_t n_out = trace->n_out[i];
             if (n_out > 1) {
                 tp += (fin[i] - f) / (double)(n_out - 1);

@@ -73,3 +73,24 @@ def test_percentiles_by_trace_length(ora, torch_cuda, n_req):
     tr = wl.request_trace(n=n_req, seed=n_req)
     idx, rate = wl.sim_configs(g, 70, seed=n_req)
     _check(torch_cuda, ora, g, idx, rate, tr, np.arange(0, 70, 3), scheds=(0, 1))
+
+
+@pytest.mark.parametrize("n_req", [7, 100, 400, 1000])
+def test_percentiles_of_infinite_waits(torch_cuda, n_req):
+    """Arrivals over rate that are infinite: those requests' times to the first token (infinity less infinity) count as infinite."""
+    hw = wl.Hardware(1e15, 5e12, 1e6 * wl.GIB, 4e11)
+    g = wl.make_grid([wl.DENSE_7B], [hw], wl.Axis.table([1, 2]), wl.Axis.table([1]), wl.Axis.table([1]),
+                     wl.Axis.table([1, 4]), wl.Axis.table([16]), wl.Axis.table([16]), wl.Axis.table([512, 8192]))
+    rng = np.random.default_rng(n_req)
+    finite = (n_req + 1) // 2                           # the median is the greatest of theirs
+    t = np.concatenate([np.arange(finite) * 1e-10, np.full(n_req - finite, 1e300)])
+    n_in, n_out = rng.integers(5, 900, n_req).astype(np.uint32), rng.integers(1, 400, n_req).astype(np.uint32)
+    idx, rate = np.arange(g.size, dtype=np.uint32), np.full(g.size, 1e-10)
+    ctx = bridge.gpu_context(g)
+    for sched in (0, 1):
+        got = _run(torch_cuda, ctx, g, idx, rate, wl.Trace(t, n_in, n_out), scheduler=sched)
+        few = _run(torch_cuda, ctx, g, idx, rate, wl.Trace(t[:finite], n_in[:finite], n_out[:finite]), scheduler=sched)
+        assert np.all(got["status"] == 0) and np.all(got["ttft_p99"] == np.inf)
+        assert np.all(np.isfinite(got["ttft_p50"])) and np.all(got["ttft_p50"] >= few["ttft_p99"])
+        if finite < 100:                                # (the 99th percentile is the greatest)
+            np.testing.assert_array_equal(got["ttft_p50"], few["ttft_p99"])
