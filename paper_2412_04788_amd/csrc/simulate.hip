@@ -841,12 +841,13 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
                 if (wave_linear || lane_linear) {
                     auto time_of = [&](double r) { return r * fma(slope, fma(h_T, r, ctx0), base_m); };
                     // the guess is right or one off nearly always, so its neighbours are looked at side by side
-                    const double G = (double)guess, stop = can_admit ? arr_next : INFINITY;
-                    const bool far_below = stop <= now + time_of(G - 2.0), below = stop <= now + time_of(G - 1.0);
-                    const bool here = stop <= now + time_of(G), above = stop <= now + time_of(G + 1.0);
+                    const double G = (double)guess;
+                    const bool far_below = arr_next <= now + time_of(G - 2.0), below = arr_next <= now + time_of(G - 1.0);
+                    const bool here = arr_next <= now + time_of(G), above = arr_next <= now + time_of(G + 1.0);
                     run = (uint32_t)guess + (below ? ~0u : 0u) + (here ? 0u : 1u);
-                    run = run < total ? run : total;
-                    if (far_below || !(here || above || run == total)) run = least_steps(now, arr_next, total, guess, time_of);
+                    run = can_admit && run < total ? run : total;
+                    if (can_admit && (far_below || !(here || above || run == total)))
+                        run = least_steps(now, arr_next, total, guess, time_of);
                     now += time_of((double)run);
                 } else {
                     auto time_of = [&](double r) {

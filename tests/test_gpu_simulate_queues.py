@@ -94,3 +94,34 @@ def test_percentiles_of_infinite_waits(torch_cuda, n_req):
         assert np.all(np.isfinite(got["ttft_p50"])) and np.all(got["ttft_p50"] >= few["ttft_p99"])
         if finite < 100:                                # (the 99th percentile is the greatest)
             np.testing.assert_array_equal(got["ttft_p50"], few["ttft_p99"])
+
+
+# (32-bit and 64-bit keys)
+@pytest.mark.parametrize("n_out", [1_000_000, 1 << 24])
+def test_arrivals_beyond_the_range_of_doubles(ora, torch_cuda, n_out):
+    """Arrivals over rate that are infinite: the clock is infinite from there on, and every request still runs.  A run of decode
+    steps while others wait for a place is advanced at once (step by step it would take seconds here, a minute with 64-bit keys)."""
+    hw = wl.Hardware(1e15, 5e12, 1e6 * wl.GIB, 4e11)
+    g = wl.make_grid([wl.DENSE_7B], [hw], wl.Axis.table([1, 2]), wl.Axis.table([1]), wl.Axis.table([1]),
+                     wl.Axis.table([1, 4]), wl.Axis.table([16]), wl.Axis.table([16]), wl.Axis.table([512, 8192]))
+    idx = np.arange(g.size, dtype=np.uint32)
+    rate = np.full(g.size, 1e-10)
+    t = np.array([0.0, 1e-10, 2e-10, 3e-10, 1e300, 1e300, 1.5e300])
+    n_in, outs = np.array([700, 30, 5, 900, 8, 9, 10], dtype=np.uint32), np.array([3, 40, 1, 7, n_out, n_out, n_out], dtype=np.uint32)
+    ctx, og = bridge.gpu_context(g), bridge.ora_grid(g)
+    for sched in (0, 1):
+        _run(torch_cuda, ctx, g, idx, rate, wl.Trace(t[:4], n_in[:4], outs[:4]), scheduler=sched)          # (loads the kernel)
+        e = [torch_cuda.cuda.Event(enable_timing=True) for _ in range(2)]
+        e[0].record()
+        got = _run(torch_cuda, ctx, g, idx, rate, wl.Trace(t, n_in, outs), scheduler=sched)
+        e[1].record()
+        torch_cuda.cuda.synchronize()
+        assert e[0].elapsed_time(e[1]) < 1000.0
+        exp = ora.simulate_grid(og, idx, rate, t, n_in, outs, scheduler=sched | CLOSED)
+        few = _run(torch_cuda, ctx, g, idx, rate, wl.Trace(t[:4], n_in[:4], outs[:4]), scheduler=sched)
+        for k in ("status", "n_steps", "n_request_steps"):
+            np.testing.assert_array_equal(got[k], exp[k], err_msg=k)
+        assert np.all(got["status"] == 0) and np.all(got["tokens_s"] == 0.0)
+        # four of the seven waited for finite times; the others count as infinite
+        np.testing.assert_array_equal(got["ttft_p50"], few["ttft_p99"])
+        assert np.all(np.isfinite(few["ttft_p99"])) and np.all(got["ttft_p99"] == np.inf)
