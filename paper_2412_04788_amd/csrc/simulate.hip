@@ -40,11 +40,11 @@ struct RequestsLds {
 
 constexpr uint32_t kHeapWidth = 4;     // children per heap node
 constexpr uint32_t kKeyBins = 1024;      // buckets of the expected-concurrency ordering
-// Lists are ordered where that saves more than its four launches (17 us): from 16 requests on, and when lanes share a
-// wave at all.  Ordered / as given, in us, when a heap held the decoders: 5000 x 8 136 / 129, 5000 x 16 193 / 203, 65 536 x 16 571 / 576,
-// 5000 x 32 352 / 396, 20 000 x 128 1200 / 1446; 65 536 x 16 541 / 526, 5000 x 32 279 / 289 under the other scheduler; one lane
-// per wave: the same.
-constexpr uint32_t kOrderRequests = 16;
+// Lists are ordered where that saves more than its four launches (17 us): when lanes share a wave at all, and blocks of several
+// waves from 64 requests on, blocks of one wave when LDS does not hold a slot for every request (353 requests).  Ordered / as
+// given, in us: 5000 x 16 83 / 64, 5000 x 64 248 / 231, 5000 x 352 1300 / 1286; 65 536 x 16 114 / 98, 65 536 x 64 277 / 272,
+// 65 536 x 128 535 / 551; 40 000 x 64 270 / 269, 40 000 x 96 407 / 414; 200 000 x 48 754 / 758, 200 000 x 64 945 / 955.
+constexpr uint32_t kOrderRequests = 64;
 
 // Workspace: heap[position][node] (u64 keys), first[cfg][req] and fin[cfg][req] (time of the first and of the
 // last token), then the launch order: perm[position] = configuration, bucket of each configuration, bucket counters.
@@ -1040,6 +1040,7 @@ hipError_t launch_simulate(const GridDesc &g, const DevTables *tab, const TraceD
     // compute unit one block, also for the LDS that its lanes share.  In us, 97 / 300 requests, waves x lanes: 300 configurations
     // 1 x 1 302 / 777, 8 x 1 462 / 1179, 1 x 64 443 / 1095; 600: 368 / 969, 382 / 1014, 451 / 1119; 1000: 8 x 1 364 / 925, 1 x 64 461 / 1143;
     // 2000: 352 / 886, 468 / 1182; 4000: 8 x 1 572 / 1482, 1 x 16 509 / 1247, 1 x 64 487 / 1192; 16 000: 1 x 64 572 / 1288, 2 x 32 584 / 1321.
+    // In ms, 1024 requests: 500 1 x 1 3.0, 8 x 1 4.3, 1 x 64 3.4; 1000 8 x 1 3.7, 1 x 64 3.4; 2000 3.4, 3.5; 2500 5.9, 3.5.
     const uint32_t cus = device_cus(), lanes = n_cfg <= 8 * cus ? 1 : kWave, full_waves = (n_cfg - 1) / (kWave * cus) + 1;
     const uint32_t waves = lanes == 1 ? (2 * n_cfg <= 5 * cus ? 1 : 8) : (full_waves < 4 ? full_waves : 4);
     const uint32_t per_block = waves * lanes;
@@ -1057,12 +1058,13 @@ hipError_t launch_simulate(const GridDesc &g, const DevTables *tab, const TraceD
     // no lane needs more
     const size_t most = per_block * (key32 ? SlotQueue::bytes((n_req + SlotQueue::kPer - 1) / SlotQueue::kPer)
                                            : (n_req + 2 * kHeapWidth) * sizeof(uint64_t));
-    heap_bytes = heap_bytes < most ? heap_bytes : most;
+    const bool all_fit = most <= heap_bytes;
+    heap_bytes = all_fit ? most : heap_bytes;
     heap_bytes -= heap_bytes % 16;
     const size_t lds_bytes = staged + heap_bytes;
     const dim3 grid((n_cfg + per_block - 1) / per_block), block(waves * kWave);
     const dim3 ogrid((n_cfg + kOrderBlock - 1) / kOrderBlock), oblock(kOrderBlock);
-    const bool ordered = lanes > 1 && n_req >= kOrderRequests;      // (otherwise every lane's heap fits the LDS)
+    const bool ordered = lanes > 1 && (waves > 1 ? n_req >= kOrderRequests : !all_fit);
     if (ordered) {
         hipLaunchKernelGGL(sim_order_clear_kernel, dim3(1), dim3(kKeyBins), 0, stream, ws);
         if (additive)

@@ -31,7 +31,7 @@ def _check(torch, ora, g, idx, rate, tr, pick=None, scheds=(0, 1, CLOSED, 1 | CL
         _compare({k: v[pick] for k, v in got.items()}, exp)
 
 
-@pytest.mark.parametrize("n_req", [1, 15, 16, 23])                # lists are ordered from 16 requests on
+@pytest.mark.parametrize("n_req", [1, 15, 16, 23])
 @pytest.mark.parametrize("n_cfg", [1, 63, 1024, 1025, 2048, 2049, 33000])
 def test_lanes_per_wave_by_configuration_count(ora, torch_cuda, n_cfg, n_req):
     g = wl.grid_full()

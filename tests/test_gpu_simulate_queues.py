@@ -66,6 +66,16 @@ def test_launch_shapes(ora, torch_cuda, n_cfg):
         np.testing.assert_array_equal(whole[k][pick], part[k])
 
 
+# lists are ordered from 64 requests on where blocks have several waves, and where LDS has no slot for every request in blocks of one
+@pytest.mark.parametrize("n_cfg, n_req", [(16385, 63), (16385, 64), (2049, 352), (2049, 353)])
+def test_the_line_of_ordering(ora, torch_cuda, n_cfg, n_req):
+    g = wl.grid_full()
+    tr = wl.request_trace(n=n_req, seed=n_cfg)
+    idx, rate = wl.sim_configs(g, n_cfg, seed=n_req)
+    pick = np.unique(np.linspace(0, n_cfg - 1, 48).astype(np.int64))
+    _check(torch_cuda, ora, g, idx, rate, tr, pick, scheds=(0, 1))
+
+
 # values per lane of the percentiles' sorting network: 1, 2, 4, 8, 16
 @pytest.mark.parametrize("n_req", [2, 63, 64, 65, 128, 129, 256, 257, 512, 513, 1000])
 def test_percentiles_by_trace_length(ora, torch_cuda, n_req):
