@@ -611,8 +611,10 @@ __global__ __launch_bounds__(kBlock) void topk_group_merge_kernel(GroupWs w, uin
 // Sample rows per thread of the row sample's blocks, and the row that sample number k stands for (n: none): all of them when the
 // sample is larger than the selection, otherwise one at a scrambled place in each of as many stretches, so that no period of
 // the rows' layout lines up with the sample.  Four rows a thread halve what the filter pass keeps, but 64 compute units take
-// 4 us longer to fetch four columns' worth of scattered lines: 400 000 rows 29 - 49 us a call with one and 31 - 49 us with
-// four, 1.2 million rows 48 - 74 and 50 - 72 us, 1.9 million rows 57 - 95 and 55 - 91 us.
+// 4 us longer to fetch four columns' worth of scattered lines.  In us a call with one / four, a uniform cloud, a band along the
+// diagonal, a thin front: 400 000 rows 20.7 / 22.6, 41 / 43, 87 / 83; 1.2 million 24.7 / 25.6, 59 / 59, 182 / 158; 1.5 million
+// 26.7 / 25.7, 66 / 64, 216 / 187; 1.9 million 29.4 / 27.7, 71 / 71, 261 / 231; 4 million 40 / 32, 117 / 107, 504 / 449;
+// 16 million 91 / 68, 364 / 318, 1917 / 1597.
 constexpr uint32_t kSampleDeep = 4, kDeepSampleRows = 1500000;
 __device__ inline uint32_t sample_deep(uint32_t n) { return n > kDeepSampleRows ? kSampleDeep : 1u; }
 __device__ inline uint32_t sample_of(uint32_t k, uint32_t n) {
