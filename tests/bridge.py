@@ -130,3 +130,15 @@ def ora_eval_sampled_all(osp: go.Space, seed, first, count, edges, ttft_cap, chu
         for k in ("t_prefill", "t_batch", "cost", "b_max", "feasible", "bucket"):
             out[k] = np.concatenate([r[k] for r in res])
     return out
+
+
+def pareto_sample_rows(n):
+    """The rows that a Pareto selection of more than 4096 rows samples (sample_of in select.hip): 16 384 of up to 1.5 million
+    rows, 65 536 of more, one at a scrambled place in each of as many stretches; all of them when there are fewer."""
+    total = 65536 if n > 1_500_000 else 16384
+    k = np.arange(min(total, n), dtype=np.uint64)
+    if n <= total:
+        return k.astype(np.int64)
+    stride = n // total
+    jitter = (((k * np.uint64(2654435761)) & np.uint64(0xFFFFFFFF)) >> np.uint64(8)) % np.uint64(stride)
+    return (k * np.uint64(stride) + k * np.uint64(n - stride * total) // np.uint64(total) + jitter).astype(np.int64)

@@ -17,17 +17,6 @@ def setup():
     return torch, bridge.gpu_context(wl.grid_tiny())
 
 
-def _sample_rows(n):
-    """The rows of the standalone row sample: 16 384 of up to 1.5 million rows, 65 536 of more."""
-    total = 65536 if n > 1_500_000 else 16384
-    k = np.arange(min(total, n), dtype=np.uint64)
-    if n <= total:
-        return k.astype(np.int64)
-    stride = n // total
-    jitter = (((k * np.uint64(2654435761)) & np.uint64(0xFFFFFFFF)) >> np.uint64(8)) % np.uint64(stride)
-    return (k * np.uint64(stride) + k * np.uint64(n - stride * total) // np.uint64(total) + jitter).astype(np.int64)
-
-
 def _check(ora, setup, x, y, fe=None, cons=(), capacity=None):
     torch, ctx = setup
     got, m = _pareto(torch, ctx, _dev(torch, x), _dev(torch, y), None if fe is None else _dev(torch, fe),
@@ -70,7 +59,7 @@ def test_fronts_by_size(ora, setup, n, kind):
 def test_survivors_of_one_bin_beyond_the_staging_arrays(ora, setup, n):
     rng = np.random.default_rng(n + 1)
     x, y = rng.random(n) * 100.0, rng.random(n) * 100.0
-    odd = np.setdiff1d(np.arange(n), _sample_rows(n))
+    odd = np.setdiff1d(np.arange(n), bridge.pareto_sample_rows(n))
     odd = rng.choice(odd, 12_000, replace=False)        # a staircase right of everything that is sampled
     x[odd] = 1000.0 + odd
     y[odd] = -1.0 * odd
@@ -82,7 +71,7 @@ def test_no_sample_row_passes(ora, setup, n):
     rng = np.random.default_rng(n + 2)
     x, y = np.round(rng.random(n) * 1000.0, 1), np.round(rng.random(n) * 1000.0, 1)
     fe = np.ones(n, np.uint8)
-    fe[_sample_rows(n)] = 0
+    fe[bridge.pareto_sample_rows(n)] = 0
     _check(ora, setup, x, y, fe)
     _check(ora, setup, x, y, np.zeros(n, np.uint8))
 
@@ -92,7 +81,7 @@ def test_all_rows_in_one_bin_of_an_unsampled_range(ora, setup):
     n = 30_000
     rng = np.random.default_rng(4)
     fe = np.ones(n, np.uint8)
-    fe[_sample_rows(n)] = 0
+    fe[bridge.pareto_sample_rows(n)] = 0
     x = np.round(rng.random(n) * 1000.0, 1)
     _check(ora, setup, x, 1e6 - 7.0 * x, fe)            # all of them on the front, many equal
     for x in (np.full(n, np.inf), np.full(n, -np.inf), np.round(rng.random(n), 3)):
@@ -106,7 +95,7 @@ def test_far_rows(ora, setup, n, far):
     rng = np.random.default_rng(n + 3)
     x = rng.permutation(n) + 1.0
     y = -x
-    odd = np.setdiff1d(np.arange(n), _sample_rows(n))
+    odd = np.setdiff1d(np.arange(n), bridge.pareto_sample_rows(n))
     odd = rng.choice(odd, 2000 if far == "many" else 2, replace=False)
     if far in ("right", "both"):
         x[odd[0]], y[odd[0]] = (np.inf if n == 200_000 else 1e300), -1e9

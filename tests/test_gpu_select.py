@@ -232,18 +232,9 @@ def test_pareto_large_front_and_repeated_calls(ora, torch_cuda):
         np.testing.assert_array_equal(got, ora.pareto_brute(xs, ys))
 
 
-def _sample_rows(n):
-    """The rows that the Pareto kernels sample out of n (16 384 strides, one row at a scrambled place in each)."""
-    ns = 16384
-    stride = n // ns if n > ns else 1
-    k = np.arange(min(ns, n), dtype=np.uint64)
-    jitter = (((k * np.uint64(2654435761)) & np.uint64(0xFFFFFFFF)) >> np.uint64(8)) % np.uint64(stride)
-    return (k * np.uint64(stride) + jitter).astype(np.int64)
-
-
 def test_pareto_large_front_ties_and_one_crowded_bin(ora, torch_cuda):
     """Large fronts that the finishing blocks share out by bin: (a) rows in identical triples, all on the front
-    (order among equal points is by row); (b) a staircase of about 20000 rows that lies beyond the sampled range,
+    (order among equal points is by row); (b) a staircase of 23616 rows that lies beyond the sampled range,
     so that one bin, and with it one block, holds more survivors than fit its LDS staging; (c) a flag column that
     fails every sample row."""
     torch = torch_cuda
@@ -260,8 +251,8 @@ def test_pareto_large_front_ties_and_one_crowded_bin(ora, torch_cuda):
     n = 40000
     x = rng.random(n) * 100.0
     y = rng.random(n) * 100.0
-    odd = np.setdiff1d(np.arange(n), _sample_rows(n))     # the staircase: the rows that the kernels do not sample
-    assert 15000 < len(odd) < 25000
+    odd = np.setdiff1d(np.arange(n), bridge.pareto_sample_rows(n))     # the staircase: the rows that the kernels do not sample
+    assert len(odd) == n - 16384
     x[odd] = 1000.0 + odd
     y[odd] = -1.0 * odd
     x[odd[7::7]] = x[odd[6::7][:len(odd[7::7])]]          # some equal x in the staircase: only the lower y stays
@@ -275,7 +266,7 @@ def test_pareto_large_front_ties_and_one_crowded_bin(ora, torch_cuda):
     x = np.round(rng.random(n) * 1000.0, 1)
     y = np.round(rng.random(n) * 1000.0, 1)
     fe = np.ones(n, np.uint8)
-    fe[_sample_rows(n)] = 0
+    fe[bridge.pareto_sample_rows(n)] = 0
     got, m = _pareto(torch, ctx, _dev(torch, x), _dev(torch, y), _dev(torch, fe))
     exp = ora.pareto_sweep(x, y, fe)
     assert m == len(exp) > 3
