@@ -19,13 +19,15 @@ def torch_cuda():
     return torch
 
 
-def _check(torch, ora, g, idx, rate, tr, pick=None, scheds=(0, 1, CLOSED, 1 | CLOSED), time_model=0):
+def _check(torch, ora, g, idx, rate, tr, pick=None, scheds=(0, 1), time_model=0):
     ctx, og = bridge.gpu_context(g), bridge.ora_grid(g)
     pick = np.arange(len(idx)) if pick is None else pick
     for sched in scheds:
         got = _run(torch, ctx, g, idx, rate, tr, time_model=time_model, scheduler=sched)
-        # the closed-form option is another definition of the clock's rounding; schedules agree away from near-ties,
-        # which the oracle's two tiers confirm on these inputs
+        # the closed-form option is accepted and changes nothing
+        flagged = _run(torch, ctx, g, idx, rate, tr, time_model=time_model, scheduler=sched | CLOSED)
+        for k in got:
+            np.testing.assert_array_equal(flagged[k], got[k], err_msg=k)
         exp = ora.simulate_grid(og, idx[pick], rate[pick], tr.arrival_unit, tr.n_in, tr.n_out, scheduler=sched & 1,
                                 time_model=time_model)
         _compare({k: v[pick] for k, v in got.items()}, exp)
@@ -52,7 +54,7 @@ def test_heaps_that_do_not_fit_lds(ora, torch_cuda):
     n_cfg = 65536
     idx = (np.arange(n_cfg) % g.size).astype(np.uint32)
     rate = np.where(np.arange(n_cfg) % 3 == 0, 64.0, 1e6 + np.arange(n_cfg))
-    _check(torch_cuda, ora, g, idx, rate, tr, np.linspace(0, n_cfg - 1, 24).astype(np.int64), scheds=(0, 1 | CLOSED))
+    _check(torch_cuda, ora, g, idx, rate, tr, np.linspace(0, n_cfg - 1, 24).astype(np.int64))
 
 
 def test_long_generations_take_64_bit_keys(ora, torch_cuda):
@@ -92,9 +94,10 @@ def test_attention_bound_by_arithmetic(ora, torch_cuda):
     _check(torch_cuda, ora, g, idx, rate, tr, time_model=1)
 
 
-def test_attention_that_turns_inside_a_stride(ora, torch_cuda):
+def test_attention_that_turns_inside_a_run(ora, torch_cuda):
     """Attention turns from read bound to bound by arithmetic where context = r / (1 - r g), r = peak / bandwidth and g the
-    share of the heads that are KV heads: 99 to 10 000 tokens here, in the middle of runs, of strides and of neither."""
+    share of the heads that are KV heads: 99 to 10 000 tokens here, in the middle of runs (whose time is then the series of two
+    pieces, and whose length is found by bisection when the guess is more than one off) and outside them."""
     hws = [wl.Hardware(r * 2e12, 2e12, 900 * wl.GIB, 4e11) for r in (0.99, 0.998, 0.9995, 0.9999, 7.9, 7.98, 7.995)]
     g = wl.make_grid([wl.DENSE_70B, wl.DENSE_7B], hws, wl.Axis.table([1, 2, 7, 40]), wl.Axis.table([1]), wl.Axis.table([1]),
                      wl.Axis.table([1]), wl.Axis.table([16]), wl.Axis.table([16]), wl.Axis.table([512, 8192]))
@@ -104,7 +107,7 @@ def test_attention_that_turns_inside_a_stride(ora, torch_cuda):
 
 
 def test_compute_bound_lists_cost_about_as_much_as_others(torch_cuda):
-    """Stepped runs whose attention is bound by arithmetic are walked in strides like the others (step by step they took
+    """Runs whose attention is bound by arithmetic are advanced at once like the others (step by step they took
     eight times as long as the same list on GPUs with a hundred times the peak)."""
     torch, times = torch_cuda, []
     for peak in (1e13, 1e15):
@@ -142,10 +145,10 @@ def test_arrival_rates_at_the_ends_of_the_range(ora, torch_cuda):
     rate[::4] = np.inf
     rate[1::4] = 1e300
     rate[2::4] = 1e-130
-    _check(torch_cuda, ora, g, idx, rate, tr, scheds=(0, 1))
+    _check(torch_cuda, ora, g, idx, rate, tr)
 
 
-@pytest.mark.parametrize("sched", [0, 1, CLOSED, 1 | CLOSED])
+@pytest.mark.parametrize("sched", [0, 1])
 def test_results_do_not_depend_on_the_list(torch_cuda, sched):
     """Which configurations share a wave differs from list to list and from call to call.  A configuration's results do
     not: bit for bit the same in a list that mixes lanes whose attention can be bound by arithmetic with lanes whose

@@ -4,7 +4,7 @@ at the ends of the launch shapes.  Against the CPU oracle's step-level simulator
 import numpy as np
 import pytest
 
-from paper_2412_04788_amd import guide, workloads as wl
+from paper_2412_04788_amd import workloads as wl
 from tests import bridge
 from tests.test_gpu_simulate import _run
 from tests.test_gpu_simulate_paths import CLOSED, _check
@@ -33,7 +33,7 @@ def test_levels_of_the_slots(ora, torch_cuda, cap):
     tr = wl.Trace(np.sort(rng.random(n) * 2.0), rng.integers(8, 64, n).astype(np.uint32), rng.integers(1, 500, n).astype(np.uint32))
     g = _grid([cap, max(cap - 3, 1)])
     idx = np.arange(g.size, dtype=np.uint32)
-    _check(torch_cuda, ora, g, idx, np.where(idx % 2 == 0, 1e6, 30.0), tr, scheds=(0, 1))
+    _check(torch_cuda, ora, g, idx, np.where(idx % 2 == 0, 1e6, 30.0), tr)
 
 
 # (lists of one lane per wave hold every decoder in their slots; in longer ones, 300 requests at the start of a trace that ends
@@ -48,7 +48,7 @@ def test_more_decoders_than_expected(ora, torch_cuda, n_cfg):
     idx = (np.arange(n_cfg) % g.size).astype(np.uint32)
     rate = 1.0 + (np.arange(n_cfg) % 97) * 3.0
     pick = np.unique(np.linspace(0, n_cfg - 1, 40).astype(np.int64))
-    _check(torch_cuda, ora, g, idx, rate, tr, pick, scheds=(0, 1 | CLOSED))
+    _check(torch_cuda, ora, g, idx, rate, tr, pick)
 
 
 @pytest.mark.parametrize("n_cfg", [256, 640, 641, 2048, 2049, 16384, 16385, 49153])
@@ -57,11 +57,10 @@ def test_launch_shapes(ora, torch_cuda, n_cfg):
     tr = wl.request_trace(n=40, seed=n_cfg)
     idx, rate = wl.sim_configs(g, n_cfg, seed=n_cfg)
     pick = np.unique(np.concatenate([np.linspace(0, n_cfg - 1, 64), [n_cfg - 2, n_cfg - 1]]).astype(np.int64))
-    _check(torch_cuda, ora, g, idx, rate, tr, pick, scheds=(0, 1))
-    # a configuration's results are the same bits in every list, and with and without the closed-form flag
+    _check(torch_cuda, ora, g, idx, rate, tr, pick)
+    # a configuration's results are the same bits in every list
     ctx = bridge.gpu_context(g)
-    whole, part = (_run(torch_cuda, ctx, g, idx[p], rate[p], tr, scheduler=s) for p, s in
-                   ((np.arange(n_cfg), 0), (pick, guide.SIM_CLOSED_FORM_RUNS)))
+    whole, part = (_run(torch_cuda, ctx, g, idx[p], rate[p], tr) for p in (np.arange(n_cfg), pick))
     for k in whole:
         np.testing.assert_array_equal(whole[k][pick], part[k])
 
@@ -73,7 +72,7 @@ def test_the_line_of_ordering(ora, torch_cuda, n_cfg, n_req):
     tr = wl.request_trace(n=n_req, seed=n_cfg)
     idx, rate = wl.sim_configs(g, n_cfg, seed=n_req)
     pick = np.unique(np.linspace(0, n_cfg - 1, 48).astype(np.int64))
-    _check(torch_cuda, ora, g, idx, rate, tr, pick, scheds=(0, 1))
+    _check(torch_cuda, ora, g, idx, rate, tr, pick)
 
 
 # values per lane of the percentiles' sorting network: 1, 2, 4, 8, 16
@@ -82,7 +81,7 @@ def test_percentiles_by_trace_length(ora, torch_cuda, n_req):
     g = wl.grid_full()
     tr = wl.request_trace(n=n_req, seed=n_req)
     idx, rate = wl.sim_configs(g, 70, seed=n_req)
-    _check(torch_cuda, ora, g, idx, rate, tr, np.arange(0, 70, 3), scheds=(0, 1))
+    _check(torch_cuda, ora, g, idx, rate, tr, np.arange(0, 70, 3))
 
 
 @pytest.mark.parametrize("n_req", [7, 100, 400, 1000])
