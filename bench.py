@@ -386,39 +386,21 @@ def extra_timings(ctx, gg, g, torch, np, guide, wl, n_sampled=1 << 28, n_sim=655
     sim["n_steps"] = torch.empty(n_cfg, dtype=torch.int64, device="cuda")
     sim["n_request_steps"] = torch.empty(n_cfg, dtype=torch.int64, device="cuda")
     ws = torch.empty(ctx.simulate_workspace_bytes(n_cfg, len(tr.n_in)), dtype=torch.uint8, device="cuda")
-    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    a.record()
-    ctx.simulate(gg, d_idx, d_rate, (tr.arrival_unit, tr.n_in, tr.n_out), sim, ws)
-    b.record()
-    torch.cuda.synchronize()
-    s = a.elapsed_time(b) * 1e-3
-    rs = int(sim["n_request_steps"].sum().item())
-    steps = int(sim["n_steps"].sum().item())
-    extra["simulate"] = {"request_steps_per_s": rs / s, "engine_steps_per_s": steps / s, "seconds": s,
-                         "configs": n_cfg, "requests_per_config": len(tr.n_in), "request_steps": rs,
-                         "feasible_configs": int((sim["status"] == 0).sum().item()), "scheduler": "split-fuse",
-                         # from rocprofv3 counters, not measured in this run (profiles/extra_kernels_valu_pmc.md)
-                         "vector_issue_frac_profiled": counter_figure("simulate_vector_issue_frac")}
-    a.record()
-    ctx.simulate(gg, d_idx, d_rate, (tr.arrival_unit, tr.n_in, tr.n_out), sim, ws, scheduler=guide.SCHED_PREFILL_FIRST)
-    b.record()
-    torch.cuda.synchronize()
-    s = a.elapsed_time(b) * 1e-3
-    rs = int(sim["n_request_steps"].sum().item())
-    extra["simulate_prefill_first"] = {"request_steps_per_s": rs / s, "seconds": s, "request_steps": rs,
-                                       "engine_steps_per_s": int(sim["n_steps"].sum().item()) / s}
-    # the same simulations with runs of decode-only steps advanced in closed form (same request-steps simulated)
-    for name, sched in (("simulate_closed_form_runs", guide.SCHED_SPLIT_FUSE),
-                        ("simulate_prefill_first_closed_form_runs", guide.SCHED_PREFILL_FIRST)):
-        a.record()
-        ctx.simulate(gg, d_idx, d_rate, (tr.arrival_unit, tr.n_in, tr.n_out), sim, ws,
-                     scheduler=sched | guide.SIM_CLOSED_FORM_RUNS)
-        b.record()
-        torch.cuda.synchronize()
-        s = a.elapsed_time(b) * 1e-3
+    trace = (tr.arrival_unit, tr.n_in, tr.n_out)
+    # GUIDE_SIM_CLOSED_FORM_RUNS is accepted and changes nothing: its two fields time the same kernels as the two without it
+    for name, sched in (("simulate", guide.SCHED_SPLIT_FUSE), ("simulate_prefill_first", guide.SCHED_PREFILL_FIRST),
+                        ("simulate_closed_form_runs", guide.SCHED_SPLIT_FUSE | guide.SIM_CLOSED_FORM_RUNS),
+                        ("simulate_prefill_first_closed_form_runs", guide.SCHED_PREFILL_FIRST | guide.SIM_CLOSED_FORM_RUNS)):
+        s = _timed(torch, lambda: ctx.simulate(gg, d_idx, d_rate, trace, sim, ws, scheduler=sched))
         rs = int(sim["n_request_steps"].sum().item())
         extra[name] = {"request_steps_per_s": rs / s, "seconds": s, "request_steps": rs,
                        "engine_steps_per_s": int(sim["n_steps"].sum().item()) / s}
+        if sched & guide.SIM_CLOSED_FORM_RUNS:
+            extra[name]["same_as"] = name.replace("_closed_form_runs", "")
+    extra["simulate"].update({"configs": n_cfg, "requests_per_config": len(tr.n_in), "scheduler": "split-fuse",
+                              "feasible_configs": int((sim["status"] == 0).sum().item()),
+                              # from rocprofv3 counters, not measured in this run (profiles/cases_kernel_trace.md)
+                              "vector_issue_frac_profiled": counter_figure("simulate_vector_issue_frac")})
     return extra
 
 

@@ -88,7 +88,7 @@ enum { GUIDE_AXIS_GEOM2 = 0, GUIDE_AXIS_TABLE = 1 };
 enum { GUIDE_SELECT_TOPK = 0, GUIDE_SELECT_PARETO = 1 };
 enum { GUIDE_SIM_OK = 0, GUIDE_SIM_INFEASIBLE = 1, GUIDE_SIM_BAD_INPUT = 2, GUIDE_SIM_INTERNAL = 3 };
 enum { GUIDE_SCHED_SPLIT_FUSE = 0, GUIDE_SCHED_PREFILL_FIRST = 1 };
-enum { GUIDE_SIM_CLOSED_FORM_RUNS = 256 };   /* OR-ed into guide_simulate's scheduler argument */
+enum { GUIDE_SIM_CLOSED_FORM_RUNS = 256 };   /* may be OR-ed into guide_simulate's scheduler argument; no effect */
 
 #define GUIDE_MAX_MODELS 8
 #define GUIDE_MAX_HW 64
@@ -278,8 +278,7 @@ int guide_eval_sampled(guide_ctx *ctx, const guide_space *space, uint64_t seed, 
  * request has arrived.  Steps and request-steps count every pass.  Times are at
  * least as close to the exact sums as pass-by-pass addition is and differ from
  * it by its rounding, some 1e-13 of the clock after 10^5 passes; an admission
- * test "arrived by now?" that is
- * decided within that can fall the other way.)  A configuration's results are
+ * test "arrived by now?" that is decided within that can fall the other way.)  A configuration's results are
  * the same bits in every list and call.  The pass depends on `scheduler`, the two
  * framework behaviours the paper models (Inference Engine, Step 2):
  *   GUIDE_SCHED_SPLIT_FUSE    one decode token for every prefilled request +
@@ -290,17 +289,11 @@ int guide_eval_sampled(guide_ctx *ctx, const guide_space *space, uint64_t seed, 
  *                             always, even if longer), decoders pause; otherwise
  *                             one decode token for every running request
  *                             (dynamic batching without chunking).
- * With GUIDE_SIM_CLOSED_FORM_RUNS OR-ed into `scheduler`, a run of decode-only
- * passes (every running request decoding, none waiting for prompt chunks) is by
- * definition not stepped: until the first decoder emits its last token or a
- * request that could be admitted has arrived, every pass has the same tokens and
- * a context that grows by one per decoder, so the r passes the stepped loop would
- * run are advanced at once with time(r) = r * (pass without attention) + L * (the
- * attention series in closed form, split where attention turns from read bound
- * to compute bound).  Engine steps and request-steps count the same passes, and
- * times differ from the stepped definition by rounding only.  The library
- * advances runs like this in either case: results are the same bits with and
- * without the flag.
+ * GUIDE_SIM_CLOSED_FORM_RUNS may be OR-ed into `scheduler` and has no effect:
+ * results are the same bits with and without it.  (It asked for runs of
+ * decode-only passes to be advanced at once, which every call does: r passes take
+ * time(r) = r * (pass without attention) + L * (the attention series in closed
+ * form, split where attention turns from read bound to compute bound).)
  * Outputs (DEVICE, n_cfg each): nearest-rank p50 / p99 of TTFT, mean TPOT over
  * requests with n_out > 1, generated tokens / (last finish - first arrival),
  * status (GUIDE_SIM_INFEASIBLE when weights or one request do not fit,

@@ -596,17 +596,18 @@ __global__ __launch_bounds__(kBlock) void topk_group_merge_kernel(GroupWs w, uin
 // columns; a top-k over the same columns can ride along with the second, and a top-k merge with the last.
 // Sample: kSampleBlocks blocks take a scattered sample of rows.  It fixes the stretch of x that the bins
 // slice (kBins equal slices of key space, clamped at both ends, so a lower bin means a strictly smaller x),
-// and every block hands over rows of the front of its sample.  The block that takes sample 0 also resets the
-// counters that the next two kernels accumulate into.
+// and every block hands over rows of the front of its sample: evenly spaced ones where they are stored columns
+// (pareto_prepare_body), the rightmost of each wave where the evaluation kernel's extra blocks work them out (store_sample_front).
+// The block that takes sample 0 also resets the counters that the next two kernels accumulate into.
 // Filter: every block bins the handed-over sample rows (least y per bin, exclusive prefix-min) and keeps a
 // row when no sample row of a strictly lower bin has a y at or below its own.  The kept rows contain the
 // front, and every other kept row is dominated by a kept one.  Kept rows are appended as (row, keys).
 // Finish: kept rows are binned; those that a kept row of a strictly lower bin dominates (least y per bin
 // over the kept rows, exclusive prefix-min) or that their own bin's representative dominates are dropped,
-// the rest are grouped by bin and tested exactly inside their bin, and front members are written at (front
-// members of lower bins) + (rank inside the bin), which orders the output by (x, y, row).  One block does
+// the rest are grouped by bin and tested exactly inside their bin (or sorted, where they crowd), and front members are written at
+// (front members of lower bins) + (rank inside the bin), which orders the output by (x, y, row).  One block does
 // this in LDS for up to kStage kept rows; more are shared out among kLargeParts blocks by runs of bins, each of which does the
-// same with what is left of its share, in bins of its own.
+// same with what is left of its share, in bins of its own, bins of bins, and rounds.
 
 // Sample rows per thread of the row sample's blocks, and the row that sample number k stands for (n: none): all of them when the
 // sample is larger than the selection, otherwise one at a scrambled place in each of as many stretches, so that no period of
@@ -1480,10 +1481,11 @@ __device__ inline Binning listed_records(FinishLds &L, const ParetoWs &w, uint64
 // groups them by x, so that they can be finished in rounds of consecutive groups.  Leaves their positions in w.grouped[g_lo ..],
 // a slot each (kNoSurvivor: none, or one that was pruned), and marks in w.staged[g_lo ..] where a group begins (no mark: 0); every group
 // has fewer than kStage slots.  Returns the number of slots.
-// The survivors are pruned and grouped by 4096 bins over their range inside the part's stretch; a bin that holds kStage or more is done likewise, with
-// bins over its range, and so on: a bin's range is 2^12 times smaller each time, so six times are the most until a
-// bin is one x.  Then only those with the least y are left, which are equal, and grouped by row.  Bins that wait for this are a
-// list, its links in the first two entries of the bins' stretches of w.staged.  (At most 2^32 - 4096 rows: indices below do not wrap.)
+// The survivors are pruned and grouped by 4096 bins over their range inside the part's stretch; a bin that holds kStage or
+// more is done likewise, with bins over its range, and so on: ranges are 2^12 times smaller each time (after the first), so
+// seven times are the most until a bin is one x.  Then only those with the least y are left, which are equal, and grouped by row.
+// Bins that wait for this are a list, its links in the first two entries of the bins' stretches of w.staged.  (There are at most
+// 2^32 - 4096 rows: indices below do not wrap.)
 // (1.9 million front rows: 2.6 ms; 40 ms with the bins that all parts share, which hold front / 4096 rows and more each.  One row far
 // from all others collapses the first bins: 600 000 front rows 0.90 ms without one, 0.90 - 0.93 ms with one, and 4.4 - 37 ms when a
 // bin beyond LDS is tested pair by pair, which takes minutes for some hundred thousand rows of the same x.)

@@ -165,8 +165,7 @@ __global__ __launch_bounds__(kKeyBins) void sim_order_clear_kernel(SimWs ws) { w
 // Heap of the decoders' finishing steps, one per lane.  The root lives in a register, node i = 1, 2, .. at position i - 1
 // of the lane's LDS segment (cap positions), deeper nodes in global memory.  D-ary: the children of node i are nodes
 // D i + 1 .. D i + D at positions D i .. D i + D - 1, so siblings are aligned 16-byte reads (cap is a multiple of D and at
-// least D: siblings never straddle the segment's end).  Unused LDS positions hold the largest key.  (Eight children per
-// node, which need fewer levels of longer comparisons, measured the same: 6.43 against 6.41 ms.)
+// least D: siblings never straddle the segment's end).  Unused LDS positions hold the largest key.
 // Key = finishing step << 10 | request; 32-bit keys when every finishing step fits 22 bits (twice the nodes in LDS).
 // While the nodes of all lanes in action are in LDS, which is nearly always, the branches that look at global memory
 // are left out by a choice that is uniform over the wave.
@@ -534,17 +533,17 @@ struct TraceSums {
 // and including the step that retires the next decoder.  A lane with one event at a time takes one round per request;
 // a lane with bursts takes a round per request as well, while the other lanes go on with theirs (loops over a burst
 // make the whole wave wait for every lane's bursts in turn: 7000 loop turns per 1024 requests).
-// A run's steps are advanced at once, stepped or in closed form by name: a step's time is linear in the context while attention
+// A run's steps are advanced at once: a step's time is linear in the context while attention
 // is bound by reading the cache at any context (nearly every lane), and the run's time a polynomial; otherwise the
 // series of two pieces.  (One rounding of the clock per run, where a stepped clock has one per step: against 80-bit
 // sums the first-token times of 150 requests of up to 1500 tokens, one after the other, are 3e-15 off, step by step 7.5e-14.)
 // Which of the two ways a lane goes depends on its own configuration alone, never on its neighbours in the wave (which
 // differ from call to call): the results of a configuration are the same bits in every list and every call.
 // What bounds the kernel: a wave is a serial stream of instructions, four to six cycles each, and the waves of a compute unit
-// share its fetch; a round takes 2800 cycles where the queues are short and 3100 where they hold hundreds (4-ary heaps in LDS,
-// strides of 64 and 8 steps and forty branches a round: 3500 - 5500), and the longest wave, which takes 3200 rounds, sets the time.
-// 65 536 configurations x 1024 requests, a call with percentiles: 3.97 ms, 3.98 ms under the other scheduler; 1999 x 97: 0.35 ms.
-// Before: 7.7, 6.4 and 0.71 ms.
+// share its fetch; the longest wave sets the time (65 536 configurations x 1024 requests: 2080 rounds of 4080 cycles, second
+// admissions included; a wave has 669 000 vector, 165 000 scalar and 40 000 LDS instructions and waits a third of its cycles).
+// A call with percentiles: 3.97 ms, 3.95 ms under the other scheduler; 1999 x 97: 0.32 ms.  Before (4-ary heaps in LDS, strides of
+// 64 and 8 steps, forty branches a round): 7.7, 6.4 and 0.71 ms.
 // heap_bytes: LDS behind the staged trace, shared out among the block's lanes by what each expects.
 template <bool ADDITIVE, bool PREFILL_FIRST, typename KeyT>
 __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const DevTables *__restrict__ tab,
@@ -616,7 +615,8 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
     // left over towards three times it; a heap: three times it, or less by the same factor in all lanes, what is left over
     // towards the most.
     // Returns false when the slots' wants do not fit: then a heap is the better queue, which finds the decoders beyond its
-    // segment in fewer accesses (65 536 lanes of 700 - 1024 decoders: 8 - 10 ms, with slots 16 - 17 ms).  To be called by the whole block.
+    // segment in fewer accesses (lanes of 700 - 1024 decoders, in ms, heap / slots: 65 536 7.8 - 8.3 / 16.6 - 17.0, 16 000 3.9 - 4.4 /
+    // 5.7 - 6.2, 3000 3.8 - 4.5 / 5.0 - 5.7).  To be called by the whole block.
     uint32_t n_units = 0, off = 0;
     auto allot = [&](auto tag) {
         constexpr bool kSlots = decltype(tag)::value;
