@@ -569,8 +569,9 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
     // The last part, where queues reach hundreds of keys, is dealt out lane by lane, so that no block has more of the longest
     // ones than its LDS holds; with one wave per block, that is all of them, whose lanes do not behave alike then.  In order / dealt,
     // 1024 requests: 5000 configurations 5.3 / 3.5 ms, 20 000 (two waves per block) 5.7 / 3.8 ms; 300 requests: 5000 1.11 / 1.12 ms,
-    // 65 536 1.52 / 1.28 ms.
-    const uint32_t in_part = ordered && (wave & 1) ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+    // 65 536 1.52 / 1.28 ms.  Every other part goes backwards: lists that are not ordered often repeat a pattern (of rates, say), and
+    // the waves of a block would all meet its same place (2000 x 300 requests: 1 % more).
+    const uint32_t in_part = wave & 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
     const bool dealt = ordered && wave == waves - 1;
     const uint32_t pos = dealt ? (wave * lanes + lane) * gridDim.x + in_part : (wave * gridDim.x + in_part) * lanes + lane;
     const bool in_range = lane < lanes && pos < n_cfg;
@@ -841,13 +842,13 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
                 if (wave_linear || lane_linear) {
                     auto time_of = [&](double r) { return r * fma(slope, fma(h_T, r, ctx0), base_m); };
                     // the guess is right or one off nearly always, so its neighbours are looked at side by side
-                    const double G = (double)guess;
-                    const bool far_below = arr_next <= now + time_of(G - 2.0), below = arr_next <= now + time_of(G - 1.0);
-                    const bool here = arr_next <= now + time_of(G), above = arr_next <= now + time_of(G + 1.0);
+                    // (no number where no arrival ends the run: at or before nothing, an infinite clock included)
+                    const double G = (double)guess, stop = can_admit ? arr_next : __builtin_nan("");
+                    const bool far_below = stop <= now + time_of(G - 2.0), below = stop <= now + time_of(G - 1.0);
+                    const bool here = stop <= now + time_of(G), above = stop <= now + time_of(G + 1.0);
                     run = (uint32_t)guess + (below ? ~0u : 0u) + (here ? 0u : 1u);
-                    run = can_admit && run < total ? run : total;
-                    if (can_admit && (far_below || !(here || above || run == total)))
-                        run = least_steps(now, arr_next, total, guess, time_of);
+                    run = run < total ? run : total;
+                    if (far_below || !(here || above || run == total)) run = least_steps(now, arr_next, total, guess, time_of);
                     now += time_of((double)run);
                 } else {
                     auto time_of = [&](double r) {
