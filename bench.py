@@ -30,9 +30,8 @@ COUNTERS = {
     # launch (scales from a 512 MiB device copy): profiles/eval_tile_kernel_full_grid_pmc.md
     "eval_tile_traffic_bytes": {"value": 86_117_555, "sources": ("eval_grid.hip", "perf_model.hpp"),
                                 "sha16": "4a59863bbd70b865"},
-    # SQ_INSTS_VALU 9.738e8 x 64 / 7.55 ms / 39.32e12 for simulate_kernel, split-fuse, stepped:
-    # profiles/cases_kernel_trace.md
-    "simulate_vector_issue_frac": {"value": 0.210, "sources": ("simulate.hip", "perf_model.hpp"), "sha16": "bc23f994ddab629b"},
+    # SQ_INSTS_VALU 7.05e8 x 64 / 3.49 ms / 39.32e12 for simulate_kernel, split-fuse: profiles/cases_kernel_trace.md
+    "simulate_vector_issue_frac": {"value": 0.329, "sources": ("simulate.hip", "perf_model.hpp"), "sha16": "948f5f1cc264b3ef"},
 }
 
 

@@ -541,7 +541,7 @@ struct TraceSums {
 // differ from call to call): the results of a configuration are the same bits in every list and every call.
 // What bounds the kernel: a wave is a serial stream of instructions, four to six cycles each, and the waves of a compute unit
 // share its fetch; the longest wave sets the time (65 536 configurations x 1024 requests: 2080 rounds of 4080 cycles, second
-// admissions included; a wave has 669 000 vector, 165 000 scalar and 40 000 LDS instructions and waits a third of its cycles).
+// admissions included; a wave has 673 000 vector, 163 000 scalar and 40 000 LDS instructions and waits a third of its cycles).
 // A call with percentiles: 3.97 ms, 3.95 ms under the other scheduler; 1999 x 97: 0.32 ms.  Before (4-ary heaps in LDS, strides of
 // 64 and 8 steps, forty branches a round): 7.7, 6.4 and 0.71 ms.
 // heap_bytes: LDS behind the staged trace, shared out among the block's lanes by what each expects.
