@@ -839,7 +839,7 @@ uint64_t ora_pareto_sweep(uint64_t n, const double *x, const double *y, const ui
     while (i < m) {
         uint64_t j = i;
         double gx = f[i].x, gy = f[i].y;   /* first of an equal-x run has the run's min y */
-        if (gy < best_y) {
+        if (i == 0 || gy < best_y) {           /* nothing is left of the first run, whatever its y */
             while (j < m && f[j].x == gx && f[j].y == gy) {
                 if (nf < cap) out_idx[nf] = f[j].i;
                 ++nf; ++j;

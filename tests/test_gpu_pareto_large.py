@@ -139,6 +139,7 @@ def test_rows_that_crowd_in_x(ora, setup, kind, n):
     _check(ora, setup, x, y)
     fe = (np.random.default_rng(n + 1).random(n) < 0.5).astype(np.uint8)
     _check(ora, setup, x, y, fe, capacity=n // 3)
+    _check(ora, setup, x, np.full(n, np.inf))
 
 
 # records that one block stages: in a bin or two of their range, with and without ties
@@ -152,6 +153,7 @@ def test_few_rows_that_crowd_in_x(ora, setup, kind, n):
     x[far], y[far] = np.inf, y.min() - 1.0              # the right end of the range far from all others
     _check(ora, setup, x, y)
     _check(ora, setup, np.append(x, 5.0)[1:], np.append(y, -np.inf)[1:])
+    _check(ora, setup, x, np.full(n, np.inf))
 
 
 @pytest.mark.parametrize("n, kind", [(4097, "one point"), (20_011, "clusters"), (300_007, "clusters, ties"), (300_007, "one point")])
@@ -191,3 +193,13 @@ def test_most_rows_end(setup):
     assert torch.equal(idx, torch.arange(idx.numel(), device="cuda"))
     del x, y, ws
     torch.cuda.empty_cache()
+
+
+# members of a bin on either side of the line between pairwise tests and sorting, a third of them dominated, some equal
+@pytest.mark.parametrize("n", [1024, 1025, 2048, 4096])
+@pytest.mark.parametrize("members", [2, 63, 64, 65, 66, 512])
+def test_members_of_a_bin(ora, setup, n, members):
+    rank = np.random.default_rng(members).permutation(n)
+    x = 1.0 + (rank // members) / (-(-n // members)) + (rank % members) * 2.0 ** -50
+    _check(ora, setup, x, -1.0 * rank)
+    _check(ora, setup, x, np.where(rank % 3 == 0, 1.0 - rank, -1.0 * (rank // 2)))

@@ -602,6 +602,10 @@ def test_pareto_brute_and_sweep(ora):
         assert list(ora.pareto_brute(x, y, mask)) == exp
         assert list(ora.pareto_sweep(x, y, mask)) == exp
     assert len(ora.pareto_sweep(np.array([1.0]), np.array([1.0]), np.array([0], dtype=np.uint8))) == 0
+    for x, y, exp in (([2.0, 1.0, 1.0], [np.inf] * 3, [1, 2]), ([np.inf, 1.0], [3.0, np.inf], [1, 0]),
+                      ([np.inf] * 2, [np.inf] * 2, [0, 1]), ([-np.inf, 5.0], [-np.inf, -np.inf], [0])):
+        for f in (ora.pareto_brute, ora.pareto_sweep):          # infinities are values like others
+            assert list(f(np.array(x), np.array(y))) == exp
     x = rng.random(3000); y = rng.random(3000)
     assert list(ora.pareto_sweep(x, y)) == list(ora.pareto_brute(x, y))
 
