@@ -520,6 +520,199 @@ __device__ inline uint32_t least_steps(double now, double arr, uint32_t r_max, f
     return hi;
 }
 
+// Percentiles of simulated configurations that ended normally, a wave at a time.  TTFT of request i = first token time - arrival /
+// rate; the values (absent requests, and those that arrive beyond the range of doubles, count as +inf) are sorted inside the wave's registers, R = 1, 2, 4, 8 or 16 per lane --
+// as few as hold the trace -- by a bitonic network in which every compare-exchange puts the smaller value at the smaller
+// index: element e = R * lane + register; a stage pairs e with e ^ m, which is another register of the same lane while m < R
+// and the same-numbered (or mirrored) register of lane ^ (m / R) otherwise.  Then nearest-rank
+// p50 = sorted[ceil(n/2) - 1] and p99 = sorted[ceil(0.99 n) - 1]; mean TPOT = mean over requests with more than
+// one token of (finish - first token) / (tokens - 1).
+// Bound by the vector ALU with 16 values (0.54 ms for 65 536 configurations with every exchange between lanes through
+// LDS), by launch and reading with few (65 536 x 16 requests: a call 105 - 117 us, 540 - 580 us with 16 values for any trace).
+constexpr uint32_t kMostPerLane = GUIDE_MAX_REQUESTS / kWave;   // 16
+
+constexpr uint32_t top_bit(uint32_t x) { return x < 2 ? x : 2 * top_bit(x / 2); }
+// compare-exchange inside a lane: the smaller value to the smaller register
+__device__ inline void cx(double &a, double &b) {
+    const double lo = fmin(a, b), hi = fmax(a, b);
+    a = lo;
+    b = hi;
+}
+// The value of lane ^ MASK, in the vector ALU where its patterns reach (0x1B reverses four lanes, 0x128 turns a row by eight).
+template <uint32_t MASK>
+__device__ inline double lane_xor(double x) {
+    auto move = [](double y, auto ctrl) {
+        const uint64_t b = (uint64_t)__double_as_longlong(y);
+        const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
+        constexpr int kCtrl = decltype(ctrl)::value;
+        return __longlong_as_double((long long)((uint64_t)dpp_u32<kCtrl>(hi, hi) << 32 | dpp_u32<kCtrl>(lo, lo)));
+    };
+    if constexpr (MASK == 1) return move(x, std::integral_constant<int, 0xB1>{});
+    else if constexpr (MASK == 2) return move(x, std::integral_constant<int, 0x4E>{});
+    else if constexpr (MASK == 3) return move(x, std::integral_constant<int, 0x1B>{});
+    else if constexpr (MASK == 4) return move(move(x, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{});
+    else if constexpr (MASK == 7) return move(x, std::integral_constant<int, 0x141>{});
+    else if constexpr (MASK == 8) return move(x, std::integral_constant<int, 0x128>{});
+    else if constexpr (MASK == 15) return move(x, std::integral_constant<int, 0x140>{});
+    else return __shfl_xor(x, (int)MASK, kWave);
+}
+// One stage of the network.  MASK: the xor mask on element numbers.
+template <uint32_t MASK, uint32_t R>
+__device__ inline void sort_stage(double (&v)[R], uint32_t lane) {
+    if constexpr (MASK < R) {
+#pragma unroll
+        for (uint32_t r = 0; r < R; ++r)
+            if ((r ^ MASK) > r) cx(v[r], v[r ^ MASK]);
+    } else {
+        constexpr uint32_t kLaneMask = MASK / R, kRegMask = MASK % R;       // kRegMask: 0 or R - 1 (mirror)
+        // this lane holds the smaller indices of its pairs when the top bit of the lane mask is clear in its number
+        constexpr uint32_t kTop = top_bit(kLaneMask);
+        const bool keep_min = (lane & kTop) == 0;
+        double o[R];
+#pragma unroll
+        for (uint32_t r = 0; r < R; ++r) o[r] = lane_xor<kLaneMask>(v[r ^ kRegMask]);
+#pragma unroll
+        for (uint32_t r = 0; r < R; ++r) v[r] = (o[r] < v[r]) == keep_min ? o[r] : v[r];      // (equal values: either)
+    }
+}
+// Merge of sorted runs of K / 2 elements into sorted runs of K: the mirror stage, then halving distances.
+template <uint32_t K, uint32_t R>
+__device__ inline void sort_merge(double (&v)[R], uint32_t lane) {
+    sort_stage<K - 1>(v, lane);
+    if constexpr (K >= 4) sort_stage<K / 4>(v, lane);
+    if constexpr (K >= 8) sort_stage<K / 8>(v, lane);
+    if constexpr (K >= 16) sort_stage<K / 16>(v, lane);
+    if constexpr (K >= 32) sort_stage<K / 32>(v, lane);
+    if constexpr (K >= 64) sort_stage<K / 64>(v, lane);
+    if constexpr (K >= 128) sort_stage<K / 128>(v, lane);
+    if constexpr (K >= 256) sort_stage<K / 256>(v, lane);
+    if constexpr (K >= 512) sort_stage<K / 512>(v, lane);
+    if constexpr (K >= 1024) sort_stage<K / 1024>(v, lane);
+}
+// element `e` of the sorted sequence, in every lane
+template <uint32_t R>
+__device__ inline double sorted_at(const double (&v)[R], uint32_t e) {
+    double x = v[0];
+#pragma unroll
+    for (uint32_t r = 1; r < R; ++r) x = (e % R) == r ? v[r] : x;
+    return __shfl(x, (int)(e / R), kWave);
+}
+
+
+// The times of configuration c's requests, element r * 64 + lane in register r (coalesced; the sort does not care where a value
+// starts; past the last request: its times once more).
+template <uint32_t R>
+__device__ inline void load_times(const SimWs &ws, uint32_t n_req, uint32_t c, double (&f)[R], double (&n)[R]) {
+    const uint32_t lane = threadIdx.x % kWave;
+    const double *first = ws.first + (size_t)c * n_req, *fin = ws.fin + (size_t)c * n_req;
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+        const uint32_t i = r * kWave + lane, j = i < n_req ? i : n_req - 1;
+        f[r] = first[j];
+        n[r] = fin[j];
+    }
+}
+// TTFTs and the lane's sum of times per output token.  first(r, i), fin(r, i): times of request i, register r; request(i): request i
+// of the trace.
+template <uint32_t R, typename First, typename Fin, typename RequestOf>
+__device__ inline double divide_times(uint32_t n_req, double rate, double (&v)[R], First &&first, Fin &&fin, RequestOf &&request) {
+    double tp = 0.0;
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+        const uint32_t i = r * kWave + threadIdx.x % kWave;
+        double t = INFINITY;
+        if (i < n_req) {
+            const Request q = request(i);
+            const double f = first(r, i);
+            t = f - q.arrival / rate;
+            t = t == t ? t : INFINITY;                      // (arrival / rate is infinite; the network cannot place a NaN)
+            if (q.out > 1) tp += (fin(r, i) - f) / (double)(q.out - 1);
+        }
+        v[r] = t;
+    }
+    return tp;
+}
+// tp: the lane's sum, n_tp: the wave's requests with more than one token.
+template <uint32_t R>
+__device__ inline void sort_and_store(double (&v)[R], double tp, uint32_t n_tp, uint32_t n_req, uint32_t c, const guide_sim_out &out) {
+    const uint32_t lane = threadIdx.x % kWave;
+    for (int off = kWave / 2; off > 0; off >>= 1) tp += __shfl_xor(tp, off, kWave);
+    sort_merge<2>(v, lane);
+    sort_merge<4>(v, lane);
+    sort_merge<8>(v, lane);
+    sort_merge<16>(v, lane);
+    sort_merge<32>(v, lane);
+    sort_merge<64>(v, lane);
+    if constexpr (R >= 2) sort_merge<128>(v, lane);
+    if constexpr (R >= 4) sort_merge<256>(v, lane);
+    if constexpr (R >= 8) sort_merge<512>(v, lane);
+    if constexpr (R >= 16) sort_merge<1024>(v, lane);
+    const double p50 = sorted_at(v, (n_req + 1) / 2 - 1);
+    const double p99 = sorted_at(v, (uint32_t)((99ull * n_req + 99) / 100 - 1));
+    if (lane == 0) {
+        out.ttft_p50[c] = p50;
+        out.ttft_p99[c] = p99;
+        out.mean_tpot[c] = n_tp ? tp / (double)n_tp : 0.0;
+    }
+}
+
+// A wave of the simulation kernel works out the percentiles of its configurations one after the other: the next one's times are
+// requested while this one's are sorted.  next(c, rate): the next configuration (uniform), false when there is none.
+template <uint32_t R, typename Next, typename RequestOf>
+__device__ inline void wave_percentiles(const SimWs &ws, uint32_t n_req, const guide_sim_out &out, Next &&next, RequestOf &&request) {
+    uint32_t c, c_next = 0;
+    double rate, rate_next = 0.0;
+    if (!next(c, rate)) return;
+    double f[R], n[R];                                      // first token, last token
+    load_times<R>(ws, n_req, c, f, n);
+    for (;;) {                                              // (uniform)
+        asm volatile("" ::: "memory");                      // (the trace is read again for every configuration: registers are for the times)
+        const bool more = next(c_next, rate_next);
+        double v[R];
+        uint32_t n_tp = 0;
+        const double tp = divide_times<R>(n_req, rate, v, [&](uint32_t r, uint32_t) { return f[r]; },
+                                          [&](uint32_t r, uint32_t) {
+                                              ++n_tp;
+                                              return n[r];
+                                          }, request);
+        if (more) load_times<R>(ws, n_req, c_next, f, n);
+        sort_and_store<R>(v, tp, wave_sum(n_tp), n_req, c, out);
+        if (!more) return;
+        c = c_next;
+        rate = rate_next;
+    }
+}
+// fn(integral_constant<values per lane>) for a trace of n_req requests
+template <typename F>
+__host__ __device__ inline void with_values_per_lane(uint32_t n_req, F &&fn) {
+    if (n_req <= kWave) fn(std::integral_constant<uint32_t, 1>{});
+    else if (n_req <= 2 * kWave) fn(std::integral_constant<uint32_t, 2>{});
+    else if (n_req <= 4 * kWave) fn(std::integral_constant<uint32_t, 4>{});
+    else if (n_req <= 8 * kWave) fn(std::integral_constant<uint32_t, 8>{});
+    else fn(std::integral_constant<uint32_t, kMostPerLane>{});
+}
+
+// One wave per configuration, from position `from` of the launch order on (as given when it is not ordered).
+template <uint32_t R>
+__global__ __launch_bounds__(kPctBlock) void percentile_kernel(SimWs ws, const TraceDev *__restrict__ trace,
+                                                               const double *__restrict__ rate_in, uint32_t n_req,
+                                                               uint32_t n_cfg, guide_sim_out out, uint32_t from, bool ordered) {
+    const uint32_t pos = from + blockIdx.x * (kPctBlock / kWave) + threadIdx.x / kWave;      // wave-uniform
+    if (pos >= n_cfg) return;
+    const uint32_t c = ordered ? (uint32_t)__builtin_amdgcn_readfirstlane((int)ws.perm[pos]) : pos;
+    if (out.status[c] != GUIDE_SIM_OK) return;
+    const double *first = ws.first + (size_t)c * n_req, *fin = ws.fin + (size_t)c * n_req;
+    double v[R];
+    uint32_t n_tp = 0;
+    const double tp = divide_times<R>(n_req, rate_in[c], v, [&](uint32_t, uint32_t i) { return first[i]; },
+                                      [&](uint32_t, uint32_t i) {
+                                          ++n_tp;
+                                          return fin[i];
+                                      },
+                                      [&](uint32_t i) { return Request{trace->arrival[i], 0u, trace->n_out[i]}; });
+    sort_and_store<R>(v, tp, wave_sum(n_tp), n_req, c, out);
+}
+
 // What the host knows about the trace.
 struct TraceSums {
     double out;             // generated tokens
@@ -542,10 +735,13 @@ struct TraceSums {
 // What bounds the kernel: a wave is a serial stream of instructions, four to six cycles each, and the waves of a compute unit
 // share its fetch; the longest wave sets the time (65 536 configurations x 1024 requests: 2080 rounds of 4080 cycles, second
 // admissions included; a wave has 673 000 vector, 163 000 scalar and 40 000 LDS instructions and waits a third of its cycles).
-// A call with percentiles: 3.97 ms, 3.95 ms under the other scheduler; 1999 x 97: 0.32 ms.  Before (4-ary heaps in LDS, strides of
-// 64 and 8 steps, forty branches a round): 7.7, 6.4 and 0.71 ms.
+// A call with percentiles: 3.72 ms, 3.62 ms under the other scheduler; 1999 x 97: 0.29 ms.  With all percentiles after the last wave's end
+// 3.92, 3.95 and 0.33 ms: the waves of the first three parts of a list are done 0.5 - 1.3 ms before the dealt part's.
+// (4-ary heaps in LDS, strides of 64 and 8 steps, forty branches a round: 7.7, 6.4 and 0.71 ms.)
 // heap_bytes: LDS behind the staged trace, shared out among the block's lanes by what each expects.
-template <bool ADDITIVE, bool PREFILL_FIRST, typename KeyT>
+// OWN: waves work out the percentiles of their own configurations, but for those of the dealt part.  (A variant of its own: with
+// its registers allotted for both, the loop over the rounds takes 3 % longer.)
+template <bool ADDITIVE, bool PREFILL_FIRST, typename KeyT, bool OWN>
 __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const DevTables *__restrict__ tab,
                                                              const TraceDev *__restrict__ trace, uint32_t n_req,
                                                              const uint32_t *__restrict__ cfg_idx,
@@ -668,6 +864,7 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
     // leaves work out that changes nothing in such a lane)
     const bool lane_linear = ADDITIVE || lt.c_att <= lt.m_att_k;
     const bool wave_linear = ADDITIVE || __ballot(alive && !lane_linear) == 0;
+    bool ended = false;                                             // the lane's simulation has ended normally
     auto simulate = [&](auto &queue) {
         constexpr bool kSlots = std::is_same<decltype(queue), SlotQueue &>::value;
         if (!alive) return;
@@ -870,6 +1067,7 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
         }
 
         out.tokens_s[c] = status == GUIDE_SIM_OK ? sums.out / (now - req[0].arrival / rate) : 0.0;
+        if (OWN) ended = status == GUIDE_SIM_OK;
         out.status[c] = status;
         out.n_steps[c] = step;
         out.n_request_steps[c] = n_rs;
@@ -879,147 +1077,42 @@ __global__ __launch_bounds__(kSimBlock) void simulate_kernel(GridDesc g, const D
     };
 
     KeyT *mem = (KeyT *)(ws.heap + (size_t)pos * n_req);
+    bool slots = false;                                             // (block-uniform)
     if constexpr (sizeof(KeyT) == 4) {
-        if (allot(std::true_type{})) {                  // block-uniform
+        slots = allot(std::true_type{});
+        if (slots) {
             SlotQueue queue;
             queue.init(off, n_units, mem);
             simulate(queue);
-            return;
+            if constexpr (!OWN) return;
         }
     }
-    allot(std::false_type{});
-    HeapQueue<KeyT> queue;
-    queue.init(s_raw + off, n_units, mem);
-    simulate(queue);
-}
+    if (!slots) {
+        allot(std::false_type{});
+        HeapQueue<KeyT> queue;
+        queue.init(s_raw + off, n_units, mem);
+        simulate(queue);
+    }
+    if constexpr (!OWN) return;
 
-// One wave per simulated configuration that ended normally.  TTFT of request i = first token time - arrival /
-// rate; the values (absent requests, and those that arrive beyond the range of doubles, count as +inf) are sorted inside the wave's registers, R = 1, 2, 4, 8 or 16 per lane --
-// as few as hold the trace -- by a bitonic network in which every compare-exchange puts the smaller value at the smaller
-// index: element e = R * lane + register; a stage pairs e with e ^ m, which is another register of the same lane while m < R
-// and the same-numbered (or mirrored) register of lane ^ (m / R) otherwise.  Then nearest-rank
-// p50 = sorted[ceil(n/2) - 1] and p99 = sorted[ceil(0.99 n) - 1]; mean TPOT = mean over requests with more than
-// one token of (finish - first token) / (tokens - 1).
-// Bound by the vector ALU with 16 values (65 536 configurations: 0.41 ms; 0.54 ms with every exchange between lanes through
-// LDS), by launch and reading with few (65 536 x 16 requests: a call 105 - 117 us, 540 - 580 us with 16 values for any trace).
-constexpr uint32_t kMostPerLane = GUIDE_MAX_REQUESTS / kWave;   // 16
-
-constexpr uint32_t top_bit(uint32_t x) { return x < 2 ? x : 2 * top_bit(x / 2); }
-// compare-exchange inside a lane: the smaller value to the smaller register
-__device__ inline void cx(double &a, double &b) {
-    const double lo = fmin(a, b), hi = fmax(a, b);
-    a = lo;
-    b = hi;
-}
-// The value of lane ^ MASK, in the vector ALU where its patterns reach (0x1B reverses four lanes, 0x128 turns a row by eight).
-template <uint32_t MASK>
-__device__ inline double lane_xor(double x) {
-    auto move = [](double y, auto ctrl) {
-        const uint64_t b = (uint64_t)__double_as_longlong(y);
-        const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
-        constexpr int kCtrl = decltype(ctrl)::value;
-        return __longlong_as_double((long long)((uint64_t)dpp_u32<kCtrl>(hi, hi) << 32 | dpp_u32<kCtrl>(lo, lo)));
+    // Percentiles, by the waves that are done before the longest ones: those of the dealt part are left to a kernel
+    // that has the whole chip for them.
+    if (dealt) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");          // the lanes read each other's times
+    uint64_t left = __ballot(ended);
+    auto next_ended = [&](uint32_t &cfg, double &r) {
+        if (left == 0) return false;
+        const int j = __ffsll((long long)left) - 1;
+        left &= left - 1;
+        cfg = (uint32_t)__builtin_amdgcn_readlane((int)c, j);
+        const uint64_t bits = (uint64_t)__double_as_longlong(rate);
+        r = __longlong_as_double((long long)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(bits >> 32), j) << 32 |
+                                             (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)bits, j)));
+        return true;
     };
-    if constexpr (MASK == 1) return move(x, std::integral_constant<int, 0xB1>{});
-    else if constexpr (MASK == 2) return move(x, std::integral_constant<int, 0x4E>{});
-    else if constexpr (MASK == 3) return move(x, std::integral_constant<int, 0x1B>{});
-    else if constexpr (MASK == 4) return move(move(x, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{});
-    else if constexpr (MASK == 7) return move(x, std::integral_constant<int, 0x141>{});
-    else if constexpr (MASK == 8) return move(x, std::integral_constant<int, 0x128>{});
-    else if constexpr (MASK == 15) return move(x, std::integral_constant<int, 0x140>{});
-    else return __shfl_xor(x, (int)MASK, kWave);
-}
-// One stage of the network.  MASK: the xor mask on element numbers.
-template <uint32_t MASK, uint32_t R>
-__device__ inline void sort_stage(double (&v)[R], uint32_t lane) {
-    if constexpr (MASK < R) {
-#pragma unroll
-        for (uint32_t r = 0; r < R; ++r)
-            if ((r ^ MASK) > r) cx(v[r], v[r ^ MASK]);
-    } else {
-        constexpr uint32_t kLaneMask = MASK / R, kRegMask = MASK % R;       // kRegMask: 0 or R - 1 (mirror)
-        // this lane holds the smaller indices of its pairs when the top bit of the lane mask is clear in its number
-        constexpr uint32_t kTop = top_bit(kLaneMask);
-        const bool keep_min = (lane & kTop) == 0;
-        double o[R];
-#pragma unroll
-        for (uint32_t r = 0; r < R; ++r) o[r] = lane_xor<kLaneMask>(v[r ^ kRegMask]);
-#pragma unroll
-        for (uint32_t r = 0; r < R; ++r) v[r] = (o[r] < v[r]) == keep_min ? o[r] : v[r];      // (equal values: either)
-    }
-}
-// Merge of sorted runs of K / 2 elements into sorted runs of K: the mirror stage, then halving distances.
-template <uint32_t K, uint32_t R>
-__device__ inline void sort_merge(double (&v)[R], uint32_t lane) {
-    sort_stage<K - 1>(v, lane);
-    if constexpr (K >= 4) sort_stage<K / 4>(v, lane);
-    if constexpr (K >= 8) sort_stage<K / 8>(v, lane);
-    if constexpr (K >= 16) sort_stage<K / 16>(v, lane);
-    if constexpr (K >= 32) sort_stage<K / 32>(v, lane);
-    if constexpr (K >= 64) sort_stage<K / 64>(v, lane);
-    if constexpr (K >= 128) sort_stage<K / 128>(v, lane);
-    if constexpr (K >= 256) sort_stage<K / 256>(v, lane);
-    if constexpr (K >= 512) sort_stage<K / 512>(v, lane);
-    if constexpr (K >= 1024) sort_stage<K / 1024>(v, lane);
-}
-// element `e` of the sorted sequence, in every lane
-template <uint32_t R>
-__device__ inline double sorted_at(const double (&v)[R], uint32_t e) {
-    double x = v[0];
-#pragma unroll
-    for (uint32_t r = 1; r < R; ++r) x = (e % R) == r ? v[r] : x;
-    return __shfl(x, (int)(e / R), kWave);
-}
-
-template <uint32_t R>
-__global__ __launch_bounds__(kPctBlock) void percentile_kernel(SimWs ws, const TraceDev *__restrict__ trace,
-                                                               const double *__restrict__ rate_in, uint32_t n_req,
-                                                               uint32_t n_cfg, guide_sim_out out) {
-    const uint32_t lane = threadIdx.x % kWave;
-    const uint32_t c = blockIdx.x * (kPctBlock / kWave) + threadIdx.x / kWave;      // wave-uniform
-    if (c >= n_cfg || out.status[c] != GUIDE_SIM_OK) return;
-    const double rate = rate_in[c];
-    const double *first = ws.first + (size_t)c * n_req, *fin = ws.fin + (size_t)c * n_req;
-    double v[R];
-    double tp = 0.0;
-    uint32_t n_tp = 0;
-#pragma unroll
-    for (uint32_t r = 0; r < R; ++r) {
-        const uint32_t i = r * kWave + lane;                // coalesced; the sort does not care where a value starts
-        double t = INFINITY;
-        if (i < n_req) {
-            const double f = first[i];
-            t = f - trace->arrival[i] / rate;
-            t = t == t ? t : INFINITY;                      // (arrival / rate is infinite; the network cannot place a NaN)
-            const uint32_t n_out = trace->n_out[i];
-            if (n_out > 1) {
-                tp += (fin[i] - f) / (double)(n_out - 1);
-                ++n_tp;
-            }
-        }
-        v[r] = t;
-    }
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        tp += __shfl_xor(tp, off, kWave);
-        n_tp += __shfl_xor(n_tp, off, kWave);
-    }
-    sort_merge<2>(v, lane);
-    sort_merge<4>(v, lane);
-    sort_merge<8>(v, lane);
-    sort_merge<16>(v, lane);
-    sort_merge<32>(v, lane);
-    sort_merge<64>(v, lane);
-    if constexpr (R >= 2) sort_merge<128>(v, lane);
-    if constexpr (R >= 4) sort_merge<256>(v, lane);
-    if constexpr (R >= 8) sort_merge<512>(v, lane);
-    if constexpr (R >= 16) sort_merge<1024>(v, lane);
-    const double p50 = sorted_at(v, (n_req + 1) / 2 - 1);
-    const double p99 = sorted_at(v, (uint32_t)((99ull * n_req + 99) / 100 - 1));
-    if (lane == 0) {
-        out.ttft_p50[c] = p50;
-        out.ttft_p99[c] = p99;
-        out.mean_tpot[c] = n_tp ? tp / (double)n_tp : 0.0;
-    }
+    with_values_per_lane(n_req, [&](auto per_lane) {
+        wave_percentiles<decltype(per_lane)::value>(ws, n_req, out, next_ended, [&](uint32_t i) { return req[i]; });
+    });
 }
 
 }  // namespace
@@ -1077,10 +1170,17 @@ hipError_t launch_simulate(const GridDesc &g, const DevTables *tab, const TraceD
         hipLaunchKernelGGL(sim_order_scan_kernel, dim3(1), dim3(kKeyBins), 0, stream, ws);
         hipLaunchKernelGGL(sim_order_scatter_kernel, ogrid, oblock, 0, stream, n_cfg, ws);
     }
+    // Waves of a lane each work out their own percentiles, and so do all but the dealt part's in blocks of four waves, which wait for
+    // the longest ones otherwise: where the trace is long enough that working them out one after the other pays.  With / without, in us:
+    // 65 536 x 64 304 / 281, x 96 427 / 423, x 128 499 / 520, x 300 1241 / 1283, x 600 2418 / 2447, x 1024 3717 / 3925; 200 000 x 100 1545 /
+    // 1519, x 200 2832 / 2946; two or three waves 20 000 x 600 2375 / 2288, 49 000 x 1024 3828 / 3865; a lane a wave 1999 x 97 285 / 327,
+    // 2000 x 16 54 / 66, 1500 x 1024 3050 / 3311, 300 x 1024 2826 / 2827.
+    const bool own_percentiles = lanes == 1 || (ordered && waves > 3 && n_req >= 128);
     const int variant = (additive ? 4 : 0) | (prefill_first ? 2 : 0) | (key32 ? 1 : 0);
 #define GUIDE_SIM(A, P, K32)                                                                                       \
     case ((A ? 4 : 0) | (P ? 2 : 0) | (K32 ? 1 : 0)): {                                                             \
-        auto kern = simulate_kernel<A, P, std::conditional<K32, uint32_t, uint64_t>::type>;                         \
+        using Key = std::conditional<K32, uint32_t, uint64_t>::type;                                                \
+        auto kern = own_percentiles ? simulate_kernel<A, P, Key, true> : simulate_kernel<A, P, Key, false>;         \
         e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);    \
         if (e != hipSuccess) return e;                                                                              \
         hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, g, tab, trace, n_req, cfg_idx, rate, n_cfg, out, ws, \
@@ -1092,15 +1192,15 @@ hipError_t launch_simulate(const GridDesc &g, const DevTables *tab, const TraceD
         GUIDE_SIM(true, false, false) GUIDE_SIM(true, false, true) GUIDE_SIM(true, true, false) GUIDE_SIM(true, true, true)
     }
 #undef GUIDE_SIM
-    const dim3 pgrid((n_cfg + kPctBlock / kWave - 1) / (kPctBlock / kWave)), pblock(kPctBlock);
-    auto percentiles = [&](auto per_lane) {
-        hipLaunchKernelGGL((percentile_kernel<decltype(per_lane)::value>), pgrid, pblock, 0, stream, ws, trace, rate, n_req, n_cfg, out);
-    };
-    if (n_req <= kWave) percentiles(std::integral_constant<uint32_t, 1>{});
-    else if (n_req <= 2 * kWave) percentiles(std::integral_constant<uint32_t, 2>{});
-    else if (n_req <= 4 * kWave) percentiles(std::integral_constant<uint32_t, 4>{});
-    else if (n_req <= 8 * kWave) percentiles(std::integral_constant<uint32_t, 8>{});
-    else percentiles(std::integral_constant<uint32_t, kMostPerLane>{});
+    // Percentiles that the simulation kernel has left
+    const uint32_t from = !own_percentiles ? 0u : ordered ? (waves - 1) * lanes * grid.x : n_cfg;
+    if (from < n_cfg) {
+        const dim3 pgrid((n_cfg - from + kPctBlock / kWave - 1) / (kPctBlock / kWave));
+        with_values_per_lane(n_req, [&](auto per_lane) {
+            hipLaunchKernelGGL((percentile_kernel<decltype(per_lane)::value>), pgrid, dim3(kPctBlock), 0, stream, ws,
+                               trace, rate, n_req, n_cfg, out, from, ordered);
+        });
+    }
     return hipGetLastError();
 }
 

@@ -4,7 +4,7 @@ at the ends of the launch shapes.  Against the CPU oracle's step-level simulator
 import numpy as np
 import pytest
 
-from paper_2412_04788_amd import workloads as wl
+from paper_2412_04788_amd import guide, workloads as wl
 from tests import bridge
 from tests.test_gpu_simulate import _run
 from tests.test_gpu_simulate_paths import CLOSED, _check
@@ -134,3 +134,24 @@ def test_arrivals_beyond_the_range_of_doubles(ora, torch_cuda, n_out):
         # four of the seven waited for finite times; the others count as infinite
         np.testing.assert_array_equal(got["ttft_p50"], few["ttft_p99"])
         assert np.all(np.isfinite(few["ttft_p99"])) and np.all(got["ttft_p99"] == np.inf)
+
+
+@pytest.mark.parametrize("n_cfg,n_req", [(50_000, 127), (50_000, 128), (49_153, 129), (70_001, 64), (20_000, 512), (20_000, 513), (33_000, 600)])
+def test_percentiles_by_the_waves_and_by_their_own_kernel(torch_cuda, n_cfg, n_req):
+    """Percentiles come from the simulation's waves, but for those of the longest configurations or of short traces: the same bits as
+    in a list of one lane per wave, whose waves work out all of them."""
+    torch = torch_cuda
+    g = wl.grid_full()
+    ctx = bridge.gpu_context(g)
+    tr = wl.request_trace(n=n_req, seed=n_req)
+    idx, rate = wl.sim_configs(g, n_cfg, seed=n_req)
+    whole = _run(torch, ctx, g, idx, rate, tr)
+    assert (whole["status"] == guide.SIM_OK).sum() > n_cfg // 2
+    pick = np.unique(np.linspace(0, n_cfg - 1, 1500).astype(np.int64))
+    part = _run(torch, ctx, g, np.ascontiguousarray(idx[pick]), np.ascontiguousarray(rate[pick]), tr)
+    for k in whole:
+        np.testing.assert_array_equal(whole[k][pick], part[k], err_msg=k)
+    # every configuration that ended has its percentiles, whichever kernel wrote them
+    ok = whole["status"] == guide.SIM_OK
+    assert np.all(np.isfinite(whole["ttft_p99"][ok])) and np.all(whole["ttft_p50"][ok] <= whole["ttft_p99"][ok])
+    assert np.all(np.isinf(whole["ttft_p50"][~ok]))
