@@ -110,6 +110,39 @@ __device__ inline uint32_t wave_sum(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_sum(v), kWave - 1);
 }
 
+// The waves' totals of a block of NW <= 16 waves in LDS, put together by every wave for itself: the scan over a row of 16 lanes and
+// two lane reads.  (A loop over the totals takes every wave NW turns: in a block of 16 waves, four to a SIMD, an instruction takes 17 cycles.)
+// `wave` must be uniform (wave_number()).
+__device__ inline uint32_t wave_number() { return (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)); }
+template <uint32_t NW>
+__device__ inline uint64_t min_before_wave(const uint64_t *totals, uint32_t wave) {
+    const uint32_t at = threadIdx.x % 16;
+    uint64_t v = at < NW ? totals[at] : kNone;
+    v = min_u64(v, dpp_keep<0x111>(v));
+    v = min_u64(v, dpp_keep<0x112>(v));
+    if (NW > 4) {
+        v = min_u64(v, dpp_keep<0x114>(v));
+        v = min_u64(v, dpp_keep<0x118>(v));
+    }
+    const uint32_t from = wave ? wave - 1 : 0;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, (int)from);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), (int)from);
+    return wave ? (uint64_t)hi << 32 | lo : kNone;
+}
+template <uint32_t NW>
+__device__ inline uint32_t sum_before_wave(const uint32_t *totals, uint32_t wave, uint32_t &total) {
+    const uint32_t at = threadIdx.x % 16;
+    uint32_t v = at < NW ? totals[at] : 0u;
+    v += dpp_u32<0x111>(0u, v);
+    v += dpp_u32<0x112>(0u, v);
+    if (NW > 4) {
+        v += dpp_u32<0x114>(0u, v);
+        v += dpp_u32<0x118>(0u, v);
+    }
+    total = (uint32_t)__builtin_amdgcn_readlane((int)v, (int)NW - 1);
+    return wave ? (uint32_t)__builtin_amdgcn_readlane((int)v, (int)wave - 1) : 0u;
+}
+
 // Per-wave LDS slots holding the least (key, row) pair per group.  A wave's LDS
 // operations execute in program order for all its lanes, so one update is: read
 // the key slot, atomic-min the key, read it back; lanes that hold the new

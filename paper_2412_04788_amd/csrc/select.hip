@@ -695,7 +695,7 @@ constexpr uint32_t kPerFinish = kBins / 1024;             // ... of the finishin
 template <uint32_t NT, uint32_t per>
 __device__ inline uint64_t prefix_min_before(const uint64_t (&v)[per], uint64_t *s_tmp) {
     constexpr uint32_t nw = NT / kWave;
-    const uint32_t t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+    const uint32_t t = threadIdx.x, lane = t % kWave, wave = wave_number();
     uint64_t m = kNone;
 #pragma unroll
     for (uint32_t j = 0; j < per; ++j) m = min_u64(m, v[j]);
@@ -704,9 +704,7 @@ __device__ inline uint64_t prefix_min_before(const uint64_t (&v)[per], uint64_t 
     uint64_t run = __shfl_up(inc, 1, kWave);            // exclusive within the wave
     if (lane == 0) run = kNone;
     __syncthreads();
-    for (uint32_t wv = 0; wv < nw; ++wv)
-        if (wv < wave) run = min_u64(run, s_tmp[wv]);
-    return run;
+    return min_u64(run, min_before_wave<nw>(s_tmp, wave));
 }
 
 // Range that the bins slice, from a scattered sample of rows: low end = least x of
@@ -869,7 +867,7 @@ __device__ inline void scan_min_excl(uint64_t *s_io, uint64_t *s_tmp) {
 template <uint32_t NT, bool PAD>
 __device__ inline void scan_sum_excl(uint32_t *io, uint32_t *s_tmp) {
     constexpr uint32_t per = kBins / NT, nw = NT / kWave, pitch = PAD ? per + 1 : per;
-    const uint32_t t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+    const uint32_t t = threadIdx.x, lane = t % kWave, wave = wave_number();
     uint32_t v[per], m = 0;
 #pragma unroll
     for (uint32_t j = 0; j < per; ++j) {
@@ -878,13 +876,9 @@ __device__ inline void scan_sum_excl(uint32_t *io, uint32_t *s_tmp) {
     }
     const uint32_t inc = wave_scan_sum(m);
     if (lane == kWave - 1) s_tmp[wave] = inc;
-    uint32_t run = inc - m;
     __syncthreads();
-    uint32_t total = 0;
-    for (uint32_t wv = 0; wv < nw; ++wv) {
-        if (wv < wave) run += s_tmp[wv];
-        total += s_tmp[wv];
-    }
+    uint32_t total;
+    uint32_t run = inc - m + sum_before_wave<nw>(s_tmp, wave, total);
 #pragma unroll
     for (uint32_t j = 0; j < per; ++j) {
         io[t * pitch + j] = run;
@@ -1265,14 +1259,16 @@ __device__ inline uint32_t staged_front(FinishLds &L, uint32_t cnt, Emit &&emit)
 
 // The front among up to kStage records held by the threads of the finishing block (record q of thread t is
 // there when bit q of live is set; its row is row_of(q)); the tables are in their neutral states and the
-// block has met since.  Any binning will do that is fine where the records are.  Calls emit(position, row) for every front
+// block has met since.  end: no record is past that many (record q of thread t counts as number q * kFinishThreads + t); registers
+// without any cost a branch.  Any binning will do that is fine where the records are.  Calls emit(position, row) for every front
 // member, position = its rank by (x, y, row), and returns their number.
 template <typename RowOf, typename Emit>
 __device__ inline uint32_t finish_in_lds(FinishLds &L, const Binning &bin, const uint64_t (&rx)[kStage / kFinishThreads],
                                          const uint64_t (&ry)[kStage / kFinishThreads], RowOf &&row_of, uint32_t live,
-                                         Emit &&emit) {
+                                         uint32_t end, Emit &&emit) {
     static_assert(kFinishThreads == 1024, "kPerFinish assumes 1024 threads");
     constexpr uint32_t P = kPerFinish, PER = kStage / kFinishThreads;
+    auto there = [&](uint32_t q) { return q * kFinishThreads < end; };             // (uniform)
     // Survivors that are dominated for sure are dropped first: those with a survivor of a strictly lower bin at or below their y,
     // and those that their own bin's representative dominates -- the survivor with the bin's least y (of those,
     // the least x); rows often tie in x, and then the representative settles all of them but the ties in y.
@@ -1280,11 +1276,12 @@ __device__ inline uint32_t finish_in_lds(FinishLds &L, const Binning &bin, const
     // prefix-min; the representatives' x in the LDS of the bin counts.
 #pragma unroll
     for (uint32_t q = 0; q < PER; ++q)
-        if ((live >> q) & 1u) atomicMin((unsigned long long *)&L.lower[padded<P>(bin(rx[q]))], (unsigned long long)ry[q]);
+        if (there(q) && ((live >> q) & 1u)) atomicMin((unsigned long long *)&L.lower[padded<P>(bin(rx[q]))], (unsigned long long)ry[q]);
     __syncthreads();
     uint32_t least = 0;                                 // bit q: the record has its own bin's least y
 #pragma unroll
     for (uint32_t q = 0; q < PER; ++q) {
+        if (!there(q)) break;
         const uint32_t b = bin(rx[q]);
         const bool is = ((live >> q) & 1u) && ry[q] == L.lower[padded<P>(b)];
         if (is) atomicMin((unsigned long long *)&L.rep[b], (unsigned long long)rx[q]);
@@ -1295,6 +1292,7 @@ __device__ inline uint32_t finish_in_lds(FinishLds &L, const Binning &bin, const
     uint32_t alive = 0;
 #pragma unroll
     for (uint32_t q = 0; q < PER; ++q) {
+        if (!there(q)) break;
         const uint32_t b = bin(rx[q]);
         const uint64_t rep_x = L.rep[b];
         const bool by_rep = rep_x <= rx[q] && (rep_x < rx[q] || !((least >> q) & 1u));
@@ -1308,7 +1306,7 @@ __device__ inline uint32_t finish_in_lds(FinishLds &L, const Binning &bin, const
     // records staged in LDS, grouped by bin
 #pragma unroll
     for (uint32_t q = 0; q < PER; ++q) {
-        if ((alive >> q) & 1u) {
+        if (there(q) && ((alive >> q) & 1u)) {
             const uint32_t b = bin(rx[q]), pos = L.off[padded<P>(b)] + atomicAdd(&L.cur[b], 1u);
             L.kx[pos] = rx[q]; L.ky[pos] = ry[q]; L.row[pos] = row_of(q); L.bin[pos] = (uint16_t)b;
         }
@@ -1607,7 +1605,7 @@ __device__ inline uint32_t large_rounds(FinishLds &L, const ParetoWs &w, const L
             rr[q] = rr[q] != kNoSurvivor ? rr[q] : 0u;
         }
         const Binning bin = listed_records(L, w, rx, ry, rr, live, end, Stretch{0, kNone});
-        n_front += finish_in_lds(L, bin, rx, ry, [&](uint32_t q) { return rr[q]; }, live, [&](uint32_t pos, uint32_t row) {
+        n_front += finish_in_lds(L, bin, rx, ry, [&](uint32_t q) { return rr[q]; }, live, end, [&](uint32_t pos, uint32_t row) {
             w.staged[part.g_lo + n_front + pos] = row;  // (over marks of slots that are done with)
         });
         from += end;
@@ -1738,7 +1736,7 @@ __global__ __launch_bounds__(kFinishThreads) void pareto_finish_kernel(ParetoWs 
             for (uint32_t q = 0; q < kPer; ++q) rr[q] = (live >> q) & 1u ? w.staged[p.g_lo + q * kFinishThreads + t] : 0u;
             own = listed_records(L, w, rx, ry, rr, live, p.n_alive, p.of);
         }
-        n_front = finish_in_lds(L, own, rx, ry, [&](uint32_t q) { return rr[q]; }, live, [&](uint32_t pos, uint32_t row) {
+        n_front = finish_in_lds(L, own, rx, ry, [&](uint32_t q) { return rr[q]; }, live, p.n_alive, [&](uint32_t pos, uint32_t row) {
             if (large) w.staged[p.g_lo + pos] = row;
             else if (pos < capacity) out_idx[pos] = row;
         });
@@ -1821,6 +1819,8 @@ __global__ __launch_bounds__(kFinishThreads) void small_select_kernel(SmallSelec
     Pair best = {kNone, kNone};                         // (y key, x key) of the least y
 #pragma unroll
     for (uint32_t q = 0; q < kPer; ++q) {
+        rx[q] = ry[q] = 0;
+        if (q * kFinishThreads >= n) continue;          // (uniform)
         const bool there = r[q].pass;
         live |= there ? 1u << q : 0u;
         rx[q] = there ? key_of(r[q].x) : 0;
@@ -1835,17 +1835,23 @@ __global__ __launch_bounds__(kFinishThreads) void small_select_kernel(SmallSelec
         s_best[t / kWave] = best;
     }
     __syncthreads();
-    for (uint32_t w = 0; w < kFinishThreads / kWave; ++w) {
-        lo = min_u64(lo, L.tmp64[w]);
-        best = pair_min(best, s_best[w]);
+    if (t < kWave) {
+        constexpr uint32_t kNW = kFinishThreads / kWave;
+        lo = wave_min(t < kNW ? L.tmp64[t] : kNone);
+        best = wave_min(t < kNW ? s_best[t] : Pair{kNone, kNone});
+        if (t == 0) {
+            L.rng[0] = lo;
+            L.rng[1] = best.idx;
+        }
     }
+    __syncthreads();
+    lo = uniform(L.rng[0]);
     if (lo == kNone) {                                  // no row passes (uniform)
         if (t == 0) s.out_count[0] = 0;
         return;
     }
-    __syncthreads();                                    // L.tmp64 is used again below
-    const uint32_t n_front = finish_in_lds(L, binning_of(lo, best.idx), rx, ry, [&](uint32_t q) { return q * kFinishThreads + t; },
-                                           live, [&](uint32_t pos, uint32_t row) { if (pos < s.capacity) s.out_idx[pos] = row; });
+    const uint32_t n_front = finish_in_lds(L, binning_of(lo, uniform(L.rng[1])), rx, ry, [&](uint32_t q) { return q * kFinishThreads + t; },
+                                           live, n, [&](uint32_t pos, uint32_t row) { if (pos < s.capacity) s.out_idx[pos] = row; });
     if (t == 0) s.out_count[0] = n_front;
 }
 
