@@ -511,6 +511,31 @@ __device__ inline void sort_group(double (&a)[kSweepGroup]) {
     cx(a[3], a[4]);
 }
 
+// Mean and both percentile lists of the samples' times.  Whole groups of eight samples are sorted once (shared by the list of
+// the smallest and the list of the largest) and merged into the lists: 12.5 instead of 28 minimum / maximum operations
+// per sample.
+struct SweepStat {
+    ExtremeK<false> lo;
+    ExtremeK<true> hi;
+    double sum;
+    __device__ void init() {
+        lo.init();
+        hi.init();
+        sum = 0.0;
+    }
+    __device__ void take(double (&a)[kSweepGroup]) {
+        sum += ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+        sort_group(a);
+        lo.merge(a);
+        hi.merge(a);
+    }
+    __device__ void take_one(double a) {
+        sum += a;
+        lo.push(a);
+        hi.push(a);
+    }
+};
+
 // One setting of the seven slower axes.
 struct ExpandTile {
     uint32_t row;                               // (model, tp, precision) row of coefficients
@@ -551,6 +576,15 @@ __device__ inline ExpandTile expand_tile(const GridLds &s, const GridDesc &g, ui
 // configuration, and a sample costs two multiply-adds for all of them.  The others (a few per wave: neighbouring
 // configurations have them in common) are kept as pairs and evaluated per sample, skipped by branches that are uniform
 // over the wave.
+
+// Work items of a sweep.  The first n_prefill (a multiple of a wave, or none) are settings of all axes but s_out and kv_block, of which
+// only the prefill's columns are made, n_s_out * NB rows at a time; the others are settings of all axes but kv_block.
+struct SweepItems {
+    uint32_t n, n_prefill;          // items; those of the prefill
+    uint32_t prefill_end;           // the last ones up to n_prefill are empty
+    uint32_t first_group, inner;    // the first setting of the axes above s_out that holds rows of the range; tiles from a value of s_out to the next
+};
+
 constexpr double kLargest = 0x1.fffffffffffffp+1023;
 constexpr int kPassTerms = N_LINEAR + 2;                // the linear tasks, attention, LM head
 template <int N>
@@ -616,7 +650,7 @@ struct SweepTerms {
             for (int i = i0; i < i0 + kPassTerms; ++i) {
                 if ((active >> i) & 1u) {
 #pragma unroll
-                    for (int q = 0; q < G; ++q) v[q] += fmax(F[i] * x[q], B[i] * y[q]);
+                    for (int q = 0; q < G; ++q) v[q] = fmax(fma(F[i], x[q], v[q]), fma(B[i], y[q], v[q]));
                 }
             }
         }
@@ -630,14 +664,19 @@ __device__ inline double uniform(double x) {
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// Bound by the vector ALU: 4280 vector instructions per lane for 64 samples, two waves per SIMD, 44 bytes of scratch.
-// 1.9 million configurations x 64 samples: 160 us, of which the set-up and the stores are 50 (two samples take 54) and a
-// sample 1.7, most of it sorting; with every task's two sides, the split of the series and the coefficients worked
-// out per sample, 405 us.
-template <bool ADDITIVE>
+// SHARED: the prefill's columns, which are the same for all values of s_out, are made by items of their own; the others then sort
+// one metric instead of two.  (One lane for several values of s_out, with the prefill's columns once for all of them, is slower,
+// 145 - 170 us: the waves whose terms change sides take three times as long as the others, and fewer, longer items do not even that out.)
+// Bound by the vector ALU, two waves per SIMD.  1.9 million configurations x 64 samples: 122 us a call, of which the set-up and the
+// stores are about 50; 137 - 142 with one item for all columns (149 with products and sums of a term that changes sides apart and
+// the samples added one by one); 405 us with every task's two sides, the split of the series and the coefficients
+// worked out per sample.  Samples in the order of their ratios, so that a term changes sides in few groups of eight and is added up
+// once per group elsewhere, gain nothing: finding the groups costs what it saves.
+template <bool ADDITIVE, bool SHARED>
 __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const DevTables *__restrict__ tab,
                                                             uint32_t first, uint32_t count, uint32_t n_eff,
-                                                            guide_stats out, const TileLds *__restrict__ derived) {
+                                                            guide_stats out, const TileLds *__restrict__ derived,
+                                                            SweepItems items) {
     __shared__ TileLds s;
     __shared__ double2 s_eff[GUIDE_MAX_EFF];            // (1 / e_c, 1 / e_b)
     __shared__ double s_rho[GUIDE_MAX_EFF], s_balance[GUIDE_MAX_HW];
@@ -667,16 +706,21 @@ __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const
     // nearest rank: p10 = sorted[ceil(n/10) - 1]; p90 = sorted[ceil(9n/10) - 1] = (n - ceil(9n/10))-th largest, 0-based
     const uint32_t r_lo = (n_eff + 9) / 10 - 1;
     const uint32_t r_hi = n_eff - (9 * n_eff + 9) / 10;
-    // work item u = (index with the kv_block digit removed): rows (hi * NB + k) * NM + m for k < NB
     const uint32_t NB = g.div[AX_BLK].d, NM = g.div[AX_MBT].d, TS = NB * NM;
-    const uint32_t t_first = first / TS;
-    const uint32_t n_items = ((first + count - 1) / TS - t_first + 1) * NM;
-    const uint32_t last = first + count;
-    for (uint32_t u = blockIdx.x * kBlock + threadIdx.x; u < n_items; u = stride_on(u, gridDim.x * kBlock, n_items)) {
-        const uint32_t hi = t_first + u / NM, m_digit = u % NM;
-        const uint32_t row0 = hi * TS + m_digit;                  // the row with kv_block digit 0
+    const uint32_t last = first + count, n_s_out = g.div[AX_SOUT].d, t_first = first / TS;
+    for (uint32_t u = blockIdx.x * kBlock + threadIdx.x; u < items.n; u = stride_on(u, gridDim.x * kBlock, items.n)) {
+        const bool prefill_only = SHARED && u < items.n_prefill;                    // (the same in a whole wave)
+        const uint32_t w = SHARED && !prefill_only ? u - items.n_prefill : u;
+        const uint32_t q = w / NM, m_digit = w - q * NM;
+        uint32_t hi = t_first + q, steps = 1;                     // tile; values of s_out
+        if (prefill_only) {
+            const uint32_t group = q / items.inner;
+            hi = (items.first_group + group) * (n_s_out * items.inner) + (q - group * items.inner);
+            steps = n_s_out;
+        }
+        uint32_t row0 = hi * TS + m_digit;                        // the row with kv_block digit 0
         // none of this item's rows inside [first, last)?  (only at the ragged ends)
-        if (row0 + (NB - 1) * NM < first || row0 >= last) continue;
+        if ((prefill_only && u >= items.prefill_end) || row0 + ((steps - 1) * items.inner * NB + NB - 1) * NM < first || row0 >= last) continue;
         const ExpandTile tl = expand_tile(s.g, g, hi);
         const uint32_t mbt = s.g.axis[AX_MBT][m_digit];
         const HwRecip hw = s.g.hw[tl.hw];
@@ -687,65 +731,72 @@ __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const
         SweepTerms<2 * kPassTerms> pre;
         SweepTerms<kPassTerms> dec;
         pre.init();
-        dec.init();
         // attention over the full segments of a long prompt, or over the decode steps, is a series of terms; where it
         // changes sides within the samples it is summed per sample
         double p_al = 0.0, p_be = 0.0, p_ga = 0.0, d_al = 0.0, d_be = 0.0, d_ga = 0.0;
         bool p_series = false, d_series = false;
-        const double b = (double)tl.b, n = (double)(tl.s_out - 1), S = plan.S;
-        {
-            // sum over contexts first, 2 first, .. or s + 1, .., s + n: both sides are linear in the context, so the ends decide.
-            // n_al, n_be, n_ga: whole numbers that multiply the operations per pair, the cache and the activation bytes.
-            auto series = [&](auto &terms, double n_al, double n_be, double n_ga, double c_lo, double c_hi, double all,
-                              double steps, double &o_al, double &o_be, double &o_ga) {
-                const double al = n_al * cf.f_att, be = n_be * cf.c_att, ga = n_ga * cf.a_att;
-                const bool read = ADDITIVE || al * up * c_hi <= fma(be, c_hi, ga);
-                const bool compute = ADDITIVE || al * lo * c_lo >= fma(be, c_lo, ga);
-                terms.a_F += compute ? (n_al * all) * cf.f_att : 0.0;
-                terms.a_B += read && (ADDITIVE || !compute) ? fma(n_be * all, cf.c_att, (n_ga * steps) * cf.a_att) : 0.0;
-                const bool both = !read && !compute;
-                o_al = both ? al * hw.r_peak : 0.0;
-                o_be = both ? be * hw.r_bw : 0.0;
-                o_ga = both ? ga * hw.r_bw : 0.0;
-                return both;
-            };
-            const bool seg = plan.segmented;
-            const double R = plan.R, bL = b * cf.L;
-            pre.add_pass<ADDITIVE>(0, cf, hw, seg ? b * plan.n_fs : plan.n_full, seg ? plan.M : R * S, R * S * S, R * S, R, !seg,
+        const double b = (double)tl.b, S = plan.S;
+        double n = 0.0;                                           // decode steps
+        // sum over contexts first, 2 first, .. or s + 1, .., s + n: both sides are linear in the context, so the ends decide.
+        // n_al, n_be, n_ga: whole numbers that multiply the operations per pair, the cache and the activation bytes.
+        auto series = [&](auto &terms, double n_al, double n_be, double n_ga, double c_lo, double c_hi, double all,
+                          double steps, double &o_al, double &o_be, double &o_ga) {
+            const double al = n_al * cf.f_att, be = n_be * cf.c_att, ga = n_ga * cf.a_att;
+            const bool read = ADDITIVE || al * up * c_hi <= fma(be, c_hi, ga);
+            const bool compute = ADDITIVE || al * lo * c_lo >= fma(be, c_lo, ga);
+            terms.a_F += compute ? (n_al * all) * cf.f_att : 0.0;
+            terms.a_B += read && (ADDITIVE || !compute) ? fma(n_be * all, cf.c_att, (n_ga * steps) * cf.a_att) : 0.0;
+            const bool both = !read && !compute;
+            o_al = both ? al * hw.r_peak : 0.0;
+            o_be = both ? be * hw.r_bw : 0.0;
+            o_ga = both ? ga * hw.r_bw : 0.0;
+            return both;
+        };
+        const bool seg = plan.segmented;
+        const double R = plan.R, bL = b * cf.L;
+        pre.add_pass<ADDITIVE>(0, cf, hw, seg ? b * plan.n_fs : plan.n_full, seg ? plan.M : R * S, R * S * S, R * S, R, !seg,
+                               lo, up);
+        if (seg || plan.rem > 0.0)
+            pre.add_pass<ADDITIVE>(kPassTerms, cf, hw, seg ? b : 1.0, seg ? plan.c_last : plan.rem * S,
+                                   seg ? plan.c_last * S : plan.rem * S * S, seg ? S : plan.rem * S, seg ? 1.0 : plan.rem, true,
                                    lo, up);
-            if (seg || plan.rem > 0.0)
-                pre.add_pass<ADDITIVE>(kPassTerms, cf, hw, seg ? b : 1.0, seg ? plan.c_last : plan.rem * S,
-                                       seg ? plan.c_last * S : plan.rem * S * S, seg ? S : plan.rem * S, seg ? 1.0 : plan.rem, true,
-                                       lo, up);
-            if (seg)
-                p_series = series(pre, bL * plan.M, bL, bL * plan.M, plan.M, plan.n_fs * plan.M,
-                                  plan.M * (0.5 * plan.n_fs * (plan.n_fs + 1.0)), plan.n_fs, p_al, p_be, p_ga);
-            if (n > 0.0) {
-                dec.add_pass<ADDITIVE>(0, cf, hw, n, b, 0.0, 0.0, b, false, lo, up);
-                d_series = series(dec, bL, bL, bL, S + 1.0, S + n, fma(n, S, 0.5 * n * (n + 1.0)), n, d_al, d_be, d_ga);
-            }
-        }
+        if (seg)
+            p_series = series(pre, bL * plan.M, bL, bL * plan.M, plan.M, plan.n_fs * plan.M,
+                              plan.M * (0.5 * plan.n_fs * (plan.n_fs + 1.0)), plan.n_fs, p_al, p_be, p_ga);
         pre.settle(hw);
+        const bool any_p = __ballot(p_series) != 0;             // wave-uniform
+        dec.init();
+        if (!prefill_only && tl.s_out > 1) {
+            n = (double)(tl.s_out - 1);
+            dec.add_pass<ADDITIVE>(0, cf, hw, n, b, 0.0, 0.0, b, false, lo, up);
+            d_series = series(dec, bL, bL, bL, S + 1.0, S + n, fma(n, S, 0.5 * n * (n + 1.0)), n, d_al, d_be, d_ga);
+        }
         dec.settle(hw);
-        const bool any_p = __ballot(p_series) != 0, any_d = __ballot(d_series) != 0;    // wave-uniform
-        ExtremeK<false> lo_p, lo_b;
-        ExtremeK<true> hi_p, hi_b;
-        lo_p.init(); hi_p.init(); lo_b.init(); hi_b.init();
-        double sum_p = 0.0, sum_b = 0.0;
-        auto samples = [&](uint32_t e, auto &tp, auto &tb) {
-            constexpr int G = sizeof(tp) / sizeof(double);
-            double x[G], y[G];
+        const bool any_d = __ballot(d_series) != 0;
+        auto efficiencies = [&](uint32_t e, auto &x, auto &y) {
+            constexpr int G = sizeof(x) / sizeof(double);
 #pragma unroll
             for (int q = 0; q < G; ++q) {
                 const double2 ef = s_eff[e + q];        // the same in every lane: kept in scalar registers
                 x[q] = uniform(ef.x);
                 y[q] = uniform(ef.y);
             }
+        };
+        auto prefill_times = [&](const auto &x, const auto &y, auto &tp) {
+            constexpr int G = sizeof(tp) / sizeof(double);
             pre.evaluate(x, y, tp);
             if (any_p) {
 #pragma unroll
                 for (int q = 0; q < G; ++q)
                     tp[q] += attention_series<ADDITIVE>(p_al * x[q], p_be * y[q], p_ga * y[q], 0.0, plan.M, plan.r_mbt, plan.n_fs);
+            }
+        };
+        auto batch_times = [&](const auto &x, const auto &y, const auto &tp, auto &tb) {
+            constexpr int G = sizeof(tb) / sizeof(double);
+            if (prefill_only) {
+#pragma unroll
+                for (int q = 0; q < G; ++q) tb[q] = tp[q];
+                return;
             }
             dec.evaluate(x, y, tb);
             if (any_d) {
@@ -754,42 +805,55 @@ __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const
                     tb[q] += attention_series<ADDITIVE>(d_al * x[q], d_be * y[q], d_ga * y[q], S, 1.0, 1.0, n);
             }
 #pragma unroll
-            for (int q = 0; q < G; ++q) {
-                tb[q] += tp[q];
-                sum_p += tp[q];
-                sum_b += tb[q];
-            }
+            for (int q = 0; q < G; ++q) tb[q] += tp[q];
         };
-        // Whole groups of eight samples are sorted once (shared by the list of the smallest and the list of
-        // the largest) and merged into the lists: 12.5 instead of 28 minimum / maximum operations per sample
-        // and metric.
+        SweepStat st_p, st_b;                                     // SHARED: st_b alone, of the prefill or of the batch
+        st_p.init();
+        st_b.init();
         uint32_t e = 0;
         for (; e + kSweepGroup <= n_eff; e += kSweepGroup) {
-            double a[kSweepGroup], bb[kSweepGroup];
-            samples(e, a, bb);
-            sort_group(a);
-            lo_p.merge(a);
-            hi_p.merge(a);
-            sort_group(bb);
-            lo_b.merge(bb);
-            hi_b.merge(bb);
+            double x[kSweepGroup], y[kSweepGroup], tp[kSweepGroup], tb[kSweepGroup];
+            efficiencies(e, x, y);
+            prefill_times(x, y, tp);
+            batch_times(x, y, tp, tb);
+            if (!SHARED) st_p.take(tp);
+            st_b.take(tb);
         }
         for (; e < n_eff; ++e) {
-            double tp[1], tb[1];
-            samples(e, tp, tb);
-            lo_p.push(tp[0]); hi_p.push(tp[0]);
-            lo_b.push(tb[0]); hi_b.push(tb[0]);
+            double x[1], y[1], tp[1], tb[1];
+            efficiencies(e, x, y);
+            prefill_times(x, y, tp);
+            batch_times(x, y, tp, tb);
+            if (!SHARED) st_p.take_one(tp[0]);
+            st_b.take_one(tb[0]);
         }
-        const double mean_p = sum_p / (double)n_eff, mean_b = sum_b / (double)n_eff;
-        const double p10_p = lo_p.at(r_lo), p90_p = hi_p.at(r_hi), p10_b = lo_b.at(r_lo), p90_b = hi_b.at(r_hi);
+        const double mean_b = st_b.sum / (double)n_eff, p10_b = st_b.lo.at(r_lo), p90_b = st_b.hi.at(r_hi);
+        auto put_prefill = [&](uint32_t i, double mean, double p10, double p90) {
+            if (out.ttft_mean) out.ttft_mean[i] = mean;
+            if (out.ttft_p10) out.ttft_p10[i] = p10;
+            if (out.ttft_p90) out.ttft_p90[i] = p90;
+        };
+        if (prefill_only) {
+            for (uint32_t step = 0; step < steps; ++step, row0 += items.inner * TS) {
+                for (uint32_t k = 0; k < NB; ++k) {
+                    const uint32_t row = row0 + k * NM;
+                    if (row >= first && row < last) put_prefill(row - first, mean_b, p10_b, p90_b);
+                }
+            }
+            continue;
+        }
+        double mean_p = 0.0, p10_p = 0.0, p90_p = 0.0;
+        if (!SHARED) {
+            mean_p = st_p.sum / (double)n_eff;
+            p10_p = st_p.lo.at(r_lo);
+            p90_p = st_p.hi.at(r_hi);
+        }
         const double cost = (double)tl.p * mean_b / 3600.0 * 1.0e6 / (b * (double)tl.s_out);
         for (uint32_t k = 0; k < NB; ++k) {
             const uint32_t row = row0 + k * NM;
             if (row < first || row >= last) continue;
             const uint32_t i = row - first;
-            if (out.ttft_mean) out.ttft_mean[i] = mean_p;
-            if (out.ttft_p10) out.ttft_p10[i] = p10_p;
-            if (out.ttft_p90) out.ttft_p90[i] = p90_p;
+            if (!SHARED) put_prefill(i, mean_p, p10_p, p90_p);
             if (out.t_batch_mean) out.t_batch_mean[i] = mean_b;
             if (out.t_batch_p10) out.t_batch_p10[i] = p10_b;
             if (out.t_batch_p90) out.t_batch_p90[i] = p90_b;
@@ -1367,15 +1431,28 @@ hipError_t launch_eval_extras(const GridDesc &g, const DevTables *tab, uint32_t 
 
 hipError_t launch_eval_sweep(const GridDesc &g, const DevTables *tab, const void *tile_tables, uint32_t first,
                              uint32_t count, uint32_t n_eff, bool additive, const guide_stats &out, hipStream_t stream) {
-    const uint32_t ts = g.div[AX_BLK].d * g.div[AX_MBT].d;
-    const uint32_t n_items = ((first + count - 1) / ts - first / ts + 1) * g.div[AX_MBT].d;
-    const uint32_t need = (n_items - 1) / kBlock + 1, most = 2 * device_cus();     // resident blocks: two per compute unit
+    const uint32_t ts = g.div[AX_BLK].d * g.div[AX_MBT].d, nm = g.div[AX_MBT].d;
+    const uint32_t most = 2 * device_cus();                     // resident blocks: two per compute unit
+    SweepItems items;
+    items.inner = g.div[AX_TP].d * g.div[AX_WBITS].d;
+    const uint32_t span = items.inner * g.div[AX_SOUT].d;       // tiles of a setting of the axes above s_out
+    items.first_group = first / ts / span;
+    const uint32_t n_rest = ((first + count - 1) / ts - first / ts + 1) * nm;
+    items.prefill_end = ((first + count - 1) / ts / span - items.first_group + 1) * items.inner * nm;
+    // Items of the prefill pay where they are few (six values of s_out or more) and the others fill the chip more than once.  In us, all columns by one item / apart, 64 samples: 1.9 million rows 137 - 142 / 122, additive 92 / 78;
+    // 950 000 82 / 71; 317 000 37.4 / 33.1; 127 000 rows (half a round) 20.8 / 22.2; five values of s_out 139 / 138 - 145;
+    // 1.9 million rows of two samples 55 - 58 / 56, of eight 59.4 / 59.4, of 24 81.3 / 77.5.
+    const bool shared = n_rest > most * kBlock && items.prefill_end < n_rest / 5 && n_rest < 3u << 30;      // (the sum fits 32 bits)
+    items.n_prefill = shared ? (items.prefill_end - 1) / kWave * kWave + kWave : 0u;
+    items.n = items.n_prefill + n_rest;
+    const uint32_t need = (items.n - 1) / kBlock + 1;
     const dim3 grid(need < most ? need : most), block(kBlock);
     const TileLds *tables = (const TileLds *)tile_tables;
-    if (additive)
-        hipLaunchKernelGGL(eval_sweep_kernel<true>, grid, block, 0, stream, g, tab, first, count, n_eff, out, tables);
-    else
-        hipLaunchKernelGGL(eval_sweep_kernel<false>, grid, block, 0, stream, g, tab, first, count, n_eff, out, tables);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, g, tab, first, count, n_eff, out, tables, items); };
+    if (additive && shared) launch(eval_sweep_kernel<true, true>);
+    else if (additive) launch(eval_sweep_kernel<true, false>);
+    else if (shared) launch(eval_sweep_kernel<false, true>);
+    else launch(eval_sweep_kernel<false, false>);
     return hipGetLastError();
 }
 
