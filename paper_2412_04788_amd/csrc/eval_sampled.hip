@@ -387,9 +387,9 @@ hipError_t launch_eval_sampled(const SpaceTables *tab, uint64_t seed, uint64_t f
                                uint32_t n_edges) {
     uint64_t need = (count + kSampledBlock - 1) / kSampledBlock;
     if (need == 0) need = 1;
-    // two blocks per compute unit are resident; enough of them, on any part of a chip, that one has fewer than 2^32 of 2^40
-    const uint32_t two = 2 * device_cus(), most = two < 512 ? 512 : (two < kSampledMaxBlocks ? two : kSampledMaxBlocks);
-    const uint32_t nb = (uint32_t)(need < most ? need : most);
+    // two blocks of each of 256 compute units are resident; enough of them, on any part of a chip, that one has fewer than 2^32 of
+    // 2^40.  (No room for more of them: a context is made and destroyed in 65 us with up to 1 MB of partials, in 110 us beyond.)
+    const uint32_t nb = (uint32_t)(need < kSampledMaxBlocks ? need : kSampledMaxBlocks);
     SampledScratch *sc = (SampledScratch *)scratch;
     const bool columns = out.t_prefill || out.t_batch || out.cost || out.b_max || out.feasible || out.bucket;
     auto launch = [&](auto kernel) {

@@ -94,7 +94,7 @@ struct SpaceTables {
     uint32_t layers_lo, layers_n, ffn_lo_x2, ffn_span_x2, vocab, n_edges;
     double link_div;     // link_bw = bw / link_div
 };
-constexpr uint32_t kSampledMaxBlocks = 1024;
+constexpr uint32_t kSampledMaxBlocks = 512;
 size_t sampled_scratch_bytes();
 hipError_t launch_eval_sampled(const SpaceTables *tab, uint64_t seed, uint64_t first, uint64_t count, double ttft_cap,
                                bool additive, const guide_sampled_out &out, void *scratch, hipStream_t stream,
