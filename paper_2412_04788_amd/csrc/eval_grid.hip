@@ -657,18 +657,11 @@ struct SweepTerms {
     }
 };
 
-__device__ inline double uniform(double x) {
-    const uint64_t b = (uint64_t)__double_as_longlong(x);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
 // SHARED: the prefill's columns, which are the same for all values of s_out, are made by items of their own; the others then sort
 // one metric instead of two.  (One lane for several values of s_out, with the prefill's columns once for all of them, is slower,
 // 145 - 170 us: the waves whose terms change sides take three times as long as the others, and fewer, longer items do not even that out.)
-// Bound by the vector ALU, two waves per SIMD.  1.9 million configurations x 64 samples: 122 us a call, of which the set-up and the
-// stores are about 50; 137 - 142 with one item for all columns (149 with products and sums of a term that changes sides apart and
+// Bound by the vector ALU, two waves per SIMD.  1.9 million configurations x 64 samples: 112 - 120 us a call, of which the set-up and the
+// stores are about 50; 122 with the samples' factors in scalar registers, 137 - 142 with one item for all columns as well (149 with products and sums of a term that changes sides apart and
 // the samples added one by one); 405 us with every task's two sides, the split of the series and the coefficients
 // worked out per sample.  Samples in the order of their ratios, so that a term changes sides in few groups of eight and is added up
 // once per group elsewhere, gain nothing: finding the groups costs what it saves.
@@ -777,9 +770,9 @@ __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const
             constexpr int G = sizeof(x) / sizeof(double);
 #pragma unroll
             for (int q = 0; q < G; ++q) {
-                const double2 ef = s_eff[e + q];        // the same in every lane: kept in scalar registers
-                x[q] = uniform(ef.x);
-                y[q] = uniform(ef.y);
+                const double2 ef = s_eff[e + q];        // (moved to scalar registers, four instructions a sample: 10 % slower)
+                x[q] = ef.x;
+                y[q] = ef.y;
             }
         };
         auto prefill_times = [&](const auto &x, const auto &y, auto &tp) {
@@ -1439,9 +1432,10 @@ hipError_t launch_eval_sweep(const GridDesc &g, const DevTables *tab, const void
     items.first_group = first / ts / span;
     const uint32_t n_rest = ((first + count - 1) / ts - first / ts + 1) * nm;
     items.prefill_end = ((first + count - 1) / ts / span - items.first_group + 1) * items.inner * nm;
-    // Items of the prefill pay where they are few (six values of s_out or more) and the others fill the chip more than once.  In us, all columns by one item / apart, 64 samples: 1.9 million rows 137 - 142 / 122, additive 92 / 78;
-    // 950 000 82 / 71; 317 000 37.4 / 33.1; 127 000 rows (half a round) 20.8 / 22.2; five values of s_out 139 / 138 - 145;
-    // 1.9 million rows of two samples 55 - 58 / 56, of eight 59.4 / 59.4, of 24 81.3 / 77.5.
+    // Items of the prefill pay where they are few (six values of s_out or more) and the others fill the chip more than once.
+    // In us, all columns by one item / apart, 64 samples whose factors were still moved to scalar registers: 1.9 million rows
+    // 137 - 142 / 122, additive 92 / 78; 950 000 82 / 71; 317 000 37.4 / 33.1; 127 000 rows (half a round) 20.8 / 22.2; five
+    // values of s_out 139 / 138 - 145; 1.9 million rows of two samples 55 - 58 / 56, of eight 59.4 / 59.4, of 24 81.3 / 77.5.
     const bool shared = n_rest > most * kBlock && items.prefill_end < n_rest / 5 && n_rest < 3u << 30;      // (the sum fits 32 bits)
     items.n_prefill = shared ? (items.prefill_end - 1) / kWave * kWave + kWave : 0u;
     items.n = items.n_prefill + n_rest;
