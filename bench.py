@@ -26,10 +26,10 @@ VECTOR_ISSUE_PEAK = 256 * 4 * 16 * 2.4e9      # lane-instructions per second: 25
 # Figures taken from rocprofv3 counter runs (profiles/*.md), each with the SHA-256 (first 16 hex digits) of the
 # kernel sources it was measured on.  A figure is reported only while those sources are unchanged, else null.
 COUNTERS = {
-    # in-step launches (with the row-sample blocks): WRITE_SIZE 83607.48 KiB x 1.0 + FETCH_SIZE 245.85 KiB x 2.0 per
+    # in-step launches (with the row-sample blocks): WRITE_SIZE 83601.91 KiB x 1.0 + FETCH_SIZE 253.5 KiB x 2.0 per
     # launch (scales from a 512 MiB device copy): profiles/eval_tile_kernel_full_grid_pmc.md
-    "eval_tile_traffic_bytes": {"value": 86_117_555, "sources": ("eval_grid.hip", "perf_model.hpp"),
-                                "sha16": "4a59863bbd70b865"},
+    "eval_tile_traffic_bytes": {"value": 86_127_519, "sources": ("eval_grid.hip", "perf_model.hpp"),
+                                "sha16": "07e2fd067a92d526"},
     # SQ_INSTS_VALU 7.05e8 x 64 / 3.49 ms / 39.32e12 for simulate_kernel, split-fuse: profiles/cases_kernel_trace.md
     "simulate_vector_issue_frac": {"value": 0.329, "sources": ("simulate.hip", "perf_model.hpp"), "sha16": "948f5f1cc264b3ef"},
 }
