@@ -142,7 +142,7 @@ __device__ inline double segment_attention(double M, double n, double al, double
 }
 
 // Bound by the vector ALU: an instruction on 64-bit values takes 4.3 - 5 of a SIMD's cycles, a 64-bit reciprocal 16, and the loop
-// has about 450 (a third of them the generator's).  2^28 candidates: 3.59 ms a call; 4.58 ms with every task's coefficients
+// has 507 (a third of them the generator's).  2^28 candidates: 3.59 ms a call; 4.58 ms with every task's coefficients
 // divided out, long and short prompts as two paths and integer tables; a block of 256 threads instead of 512 would not
 // leave room for the tables four waves a SIMD deep.  148 000 candidates 33.7 us, 49.3 us with histograms added up by atomics and a
 // launch that cleared them.
