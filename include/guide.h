@@ -142,7 +142,9 @@ typedef struct {
 
 /* Outputs of an efficiency sweep (eff.n > 1): mean (index-order sum / n) and
  * nearest-rank p10 / p90 (sorted[ceil(q n) - 1]) of TTFT and batch latency over
- * the samples; cost from the mean batch latency. */
+ * the samples; cost from the mean batch latency.  A configuration's values are
+ * the same bits in every range [first, first + count) of the same grid, tables
+ * and samples. */
 typedef struct {
     double *ttft_mean, *ttft_p10, *ttft_p90, *t_batch_mean, *t_batch_p10, *t_batch_p90, *cost;
     uint32_t *b_max;

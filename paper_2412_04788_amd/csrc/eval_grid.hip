@@ -576,6 +576,10 @@ __device__ inline ExpandTile expand_tile(const GridLds &s, const GridDesc &g, ui
 // configuration, and a sample costs two multiply-adds for all of them.  The others (a few per wave: neighbouring
 // configurations have them in common) are kept as pairs and evaluated per sample, skipped by branches that are uniform
 // over the wave.
+//
+// A configuration's outputs are the same bits whichever variant of the kernel a range is given to, so sums are contracted where
+// the code says fma and nowhere else (here and in what it calls: make_coef, attention_series).  A term of a neighbour in
+// the wave adds zero.
 
 // Work items of a sweep.  The first n_prefill (a multiple of a wave, or none) are settings of all axes but s_out and kv_block, of which
 // only the prefill's columns are made, n_s_out * NB rows at a time; the others are settings of all axes but kv_block.
@@ -598,10 +602,13 @@ struct SweepTerms {
 #pragma unroll
         for (int i = 0; i < N; ++i) F[i] = B[i] = 0.0;
     }
+    // a term of n x per operations and b bytes
     template <bool ADDITIVE>
-    __device__ void add(int i, double f, double b, double rho_lo, double rho_hi) {
+    __device__ void add(int i, double n, double per, double b, double rho_lo, double rho_hi) {
+#pragma clang fp contract(off)
+        const double f = n * per;
         const bool compute = ADDITIVE || f * rho_lo >= b, read = ADDITIVE || f * rho_hi <= b;
-        a_F += compute ? f : 0.0;
+        a_F = ADDITIVE ? fma(n, per, a_F) : a_F + (compute ? f : 0.0);
         a_B += read && (ADDITIVE || !compute) ? b : 0.0;
         if (!ADDITIVE) {
             const bool both = !compute && !read;
@@ -613,16 +620,17 @@ struct SweepTerms {
     template <bool ADDITIVE>
     __device__ void add_pass(int i0, const Coef &c, const HwRecip &hw, double times, double T, double Q, double K, double n_lm,
                              bool att, double rho_lo, double rho_hi) {
+#pragma clang fp contract(off)
         const double w = times * c.L, wT = w * T, w_eld = w * fmin(c.E, c.k * T), lm = times * n_lm;
 #pragma unroll
         for (int i = 0; i < N_LINEAR; ++i) {
             const bool experts = i == OP_UP || i == OP_DOWN;
-            add<ADDITIVE>(i0 + i, wT * c.f[i], fma(wT, c.a[i], (experts ? w_eld : w) * c.w[i]), rho_lo, rho_hi);
+            add<ADDITIVE>(i0 + i, wT, c.f[i], fma(wT, c.a[i], (experts ? w_eld : w) * c.w[i]), rho_lo, rho_hi);
         }
-        if (att) add<ADDITIVE>(i0 + N_LINEAR, (w * Q) * c.f_att, fma(w * K, c.c_att, wT * c.a_att), rho_lo, rho_hi);
-        if (n_lm > 0.0) add<ADDITIVE>(i0 + N_LINEAR + 1, lm * c.f_lm, fma(lm, c.a_lm, times * c.w_lm), rho_lo, rho_hi);
-        a_B += wT * c.a_nm;
-        fixed += 2.0 * fma(wT * c.m_ar, hw.r_link, w * c.n_ar * hw.lat);
+        if (att) add<ADDITIVE>(i0 + N_LINEAR, w * Q, c.f_att, fma(w * K, c.c_att, wT * c.a_att), rho_lo, rho_hi);
+        if (n_lm > 0.0) add<ADDITIVE>(i0 + N_LINEAR + 1, lm, c.f_lm, fma(lm, c.a_lm, times * c.w_lm), rho_lo, rho_hi);
+        a_B = fma(wT, c.a_nm, a_B);
+        fixed = fma(2.0, fma(wT * c.m_ar, hw.r_link, w * c.n_ar * hw.lat), fixed);
     }
     // operations and bytes become seconds; to be called by all lanes in action together, after the last add
     __device__ void settle(const HwRecip &hw) {
@@ -670,6 +678,7 @@ __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const
                                                             uint32_t first, uint32_t count, uint32_t n_eff,
                                                             guide_stats out, const TileLds *__restrict__ derived,
                                                             SweepItems items) {
+#pragma clang fp contract(off)
     __shared__ TileLds s;
     __shared__ double2 s_eff[GUIDE_MAX_EFF];            // (1 / e_c, 1 / e_b)
     __shared__ double s_rho[GUIDE_MAX_EFF], s_balance[GUIDE_MAX_HW];
@@ -737,7 +746,7 @@ __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const
             const double al = n_al * cf.f_att, be = n_be * cf.c_att, ga = n_ga * cf.a_att;
             const bool read = ADDITIVE || al * up * c_hi <= fma(be, c_hi, ga);
             const bool compute = ADDITIVE || al * lo * c_lo >= fma(be, c_lo, ga);
-            terms.a_F += compute ? (n_al * all) * cf.f_att : 0.0;
+            terms.a_F = ADDITIVE ? fma(n_al * all, cf.f_att, terms.a_F) : terms.a_F + (compute ? (n_al * all) * cf.f_att : 0.0);
             terms.a_B += read && (ADDITIVE || !compute) ? fma(n_be * all, cf.c_att, (n_ga * steps) * cf.a_att) : 0.0;
             const bool both = !read && !compute;
             o_al = both ? al * hw.r_peak : 0.0;

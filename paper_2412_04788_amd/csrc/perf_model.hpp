@@ -63,26 +63,26 @@ __device__ inline Coef make_coef(const guide_model &md, uint32_t p_, uint32_t wb
     c.L = (double)md.L;
     c.f[OP_QKV] = 2.0 * d * (dq + 2.0 * dkv) * rp;
     c.w[OP_QKV] = w * d * (dq + 2.0 * dkv) * rp;
-    c.a[OP_QKV] = a * d + a * (dq + 2.0 * dkv) * rp;
+    c.a[OP_QKV] = fma(a * (dq + 2.0 * dkv), rp, a * d);
     c.f_att = 4.0 * dq * rp;
     c.a_att = 2.0 * a * dq * rp;
     c.c_att = 2.0 * kKvBytes * gkv;
     c.f[OP_OPROJ] = 2.0 * dq * d * rp;
     c.w[OP_OPROJ] = w * dq * d * rp;
-    c.a[OP_OPROJ] = a * dq * rp + a * d;
+    c.a[OP_OPROJ] = fma(a * dq, rp, a * d);
     c.f[OP_UP] = 2.0 * k * pf1 * rp;
     c.w[OP_UP] = w * pf1 * rp;
-    c.a[OP_UP] = a * d + 2.0 * a * k * dff * rp;
+    c.a[OP_UP] = fma(2.0 * a * k * dff, rp, a * d);
     c.f[OP_DOWN] = 2.0 * k * pf2 * rp;
     c.w[OP_DOWN] = w * pf2 * rp;
-    c.a[OP_DOWN] = a * k * dff * rp + a * d;
+    c.a[OP_DOWN] = fma(a * k * dff, rp, a * d);
     c.f[OP_ROUTER] = 2.0 * prt;                       // router is replicated on every GPU
     c.w[OP_ROUTER] = w * prt;
     c.a[OP_ROUTER] = md.E > 1 ? a * d + a * E : 0.0;
     c.a_nm = 4.0 * a * d;
     c.f_lm = 2.0 * d * V * rp;
     c.w_lm = w * d * V * rp;
-    c.a_lm = a * d + a * V * rp;
+    c.a_lm = fma(a * V, rp, a * d);
     c.m_ar = p_ > 1 ? 2.0 * (p - 1.0) * rp * (a * d) : 0.0;
     c.n_ar = p_ > 1 ? 2.0 * (p - 1.0) : 0.0;
     c.p_total = c.L * (pattn + E * (pf1 + pf2) + prt) + 2.0 * V * d;
@@ -220,7 +220,7 @@ __device__ inline double attention_series(double alpha, double beta, double gamm
     const double all = fma(u, tri, n * s);               // sum of c_j
     if (ADDITIVE) return fma(alpha + beta, all, n * gamma);
     if (alpha <= beta) return fma(beta, all, n * gamma); // bandwidth bound at every context
-    double jm = floor((gamma * fast_recip(alpha - beta) - s) * r_u);
+    double jm = floor(fma(gamma, fast_recip(alpha - beta), -s) * r_u);
     jm = fmin(fmax(jm, 0.0), n);
     const double low = fma(u, 0.5 * jm * (jm + 1.0), jm * s);
     return fma(beta, low, fma(jm, gamma, alpha * (all - low)));
