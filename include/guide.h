@@ -140,11 +140,13 @@ typedef struct {
     uint8_t *feasible;
 } guide_metrics;
 
-/* Outputs of an efficiency sweep (eff.n > 1): mean (index-order sum / n) and
- * nearest-rank p10 / p90 (sorted[ceil(q n) - 1]) of TTFT and batch latency over
- * the samples; cost from the mean batch latency.  A configuration's values are
- * the same bits in every range [first, first + count) of the same grid, tables
- * and samples. */
+/* Outputs of an efficiency sweep (eff.n > 1): mean (sum / n) and nearest-rank
+ * p10 / p90 (sorted[ceil(q n) - 1]) of TTFT and batch latency over the samples;
+ * cost from the mean batch latency.  Order of the sum: whole groups of eight
+ * samples t[i .. i + 7] first, in index order, each added to the sum as
+ * ((t0 + t1) + (t2 + t3)) + ((t4 + t5) + (t6 + t7)), then the other samples one
+ * by one, in index order.  A configuration's values are the same bits in every
+ * range [first, first + count) of the same grid, tables and samples. */
 typedef struct {
     double *ttft_mean, *ttft_p10, *ttft_p90, *t_batch_mean, *t_batch_p10, *t_batch_p90, *cost;
     uint32_t *b_max;

@@ -126,9 +126,11 @@ def test_efficiency_sweep(tm):
         rms.update({name + k: _rms(bridge.to_np(out[name + k])[idx], e) for k, e in exact.items()})
     rms["cost"] = _rms(bridge.to_np(out["cost"])[idx], r["p"] * mean / 3600 * 10 ** 6 / (r["b"] * r["o"]))
     print(rms)
-    # sequential sums of 20 samples: about one unit in the means by themselves; the percentiles have a few roundings each
+    # The percentiles have a few roundings each.  A rounding is 0.43 units in the root mean square.  The sum of 20 samples, two groups of
+    # eight as trees and four one by one: 0.91 units, each rounding weighed by the share of the sum that it is made in (one by
+    # one 1.14); the division by 20; and 0.9 units of the samples' own that all of them have in common: 1.35.  The cost has three roundings more.
     assert max(v for k, v in rms.items() if "p10" in k or "p90" in k) < 1.15, rms
-    assert max(rms["ttft_mean"], rms["t_batch_mean"]) < 1.51 and rms["cost"] < 1.68, rms
+    assert max(rms["ttft_mean"], rms["t_batch_mean"]) < 1.35 and rms["cost"] < 1.55, rms
 
 
 @pytest.mark.parametrize("sched", [guide.SCHED_SPLIT_FUSE, guide.SCHED_PREFILL_FIRST])

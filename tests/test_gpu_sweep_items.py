@@ -1,5 +1,6 @@
 """Efficiency sweeps whose prefill columns are made by items of their own (many rows, six generation lengths or more): the
-same bits as in pieces that are too small for that, whatever part of the grid is asked for."""
+same bits as in pieces that are too small for that, whatever part of the grid is asked for; and the order in which the
+samples are added up."""
 import numpy as np
 import pytest
 
@@ -49,3 +50,36 @@ def test_prefill_items(n_so, n_blk, n_mbt, first, less, n_eff, tm, tp):
         part = _sweep(ctx, g, e_c, e_b, first + at, n, tm)
         for k in guide.STATS_COLUMNS:
             np.testing.assert_array_equal(whole[k][at:at + n], part[k], err_msg=k)
+
+
+def _added_up(times):
+    """Sum over axis 0 in the documented order: groups of eight as trees, the rest one by one."""
+    total, i, n = 0.0, 0, len(times)
+    while i + 8 <= n:
+        a = times[i:i + 8]
+        total = total + (((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])))
+        i += 8
+    for t in times[i:]:
+        total = total + t
+    return total
+
+
+# One GPU (no transfers) and samples that scale both rates by the same power of two: every time is the least one times a power
+# of two, exactly, so the sums' roundings are known bit for bit.
+@pytest.mark.parametrize("n_eff", [2, 7, 8, 9, 20, 64])
+@pytest.mark.parametrize("tm", [0, 1])
+def test_order_of_the_sums(n_eff, tm):
+    g = wl.make_grid([wl.DENSE_7B, wl.MOE_8X], wl.hw_profiles(5, 2), wl.Axis.table([1, 7, 300]), wl.Axis.table([50, 3001]),
+                     wl.Axis.table([1, 30, 1000]), wl.Axis.table([1]), wl.Axis.table([16, 4]), wl.Axis.table([16]), wl.Axis.table([1000, 8192]))
+    power = (np.arange(n_eff) * 11) % 5                                   # 0 at first: sample 0 is among the fastest
+    e = 0.5 ** power
+    out = _sweep(bridge.gpu_context(g), g, e, e, 0, g.size, tm)
+    # the least time is the p10: at least a tenth of the samples are as fast
+    assert np.count_nonzero(power == 0) >= -(-n_eff // 10)
+    for name in ("ttft", "t_batch"):
+        times = out[name + "_p10"][None, :] * 2.0 ** power[:, None]
+        np.testing.assert_array_equal(out[name + "_mean"], _added_up(times) / n_eff, err_msg=name)
+    one_by_one = np.zeros(g.size)
+    for t in out["t_batch_p10"][None, :] * 2.0 ** power[:, None]:
+        one_by_one = one_by_one + t
+    assert n_eff < 8 or (one_by_one != _added_up(times)).any()            # (the test can tell the orders apart)
