@@ -6,7 +6,7 @@ import pytest
 
 from paper_2412_04788_amd import guide, workloads as wl
 from tests import bridge
-from tests.test_gpu_simulate import _run
+from tests.test_gpu_simulate import _compare, _run
 from tests.test_gpu_simulate_paths import CLOSED, _check
 
 pytestmark = pytest.mark.gpu
@@ -136,22 +136,37 @@ def test_arrivals_beyond_the_range_of_doubles(ora, torch_cuda, n_out):
         assert np.all(np.isfinite(few["ttft_p99"])) and np.all(got["ttft_p99"] == np.inf)
 
 
-@pytest.mark.parametrize("n_cfg,n_req", [(50_000, 127), (50_000, 128), (49_153, 129), (70_001, 64), (20_000, 512), (20_000, 513), (33_000, 600)])
-def test_percentiles_by_the_waves_and_by_their_own_kernel(torch_cuda, n_cfg, n_req):
+# (also the additive model, whole prompts first, and generations that take 64-bit keys)
+@pytest.mark.parametrize("n_cfg,n_req,tm,sched,longer", [(50_000, 127, 0, 0, 1), (50_000, 128, 0, 0, 1), (49_153, 129, 0, 0, 1), (70_001, 64, 0, 0, 1),
+                                                         (20_000, 512, 0, 0, 1), (20_000, 513, 0, 0, 1), (33_000, 600, 0, 0, 1),
+                                                         (49_999, 140, 1, 0, 1), (49_999, 140, 1, 1, 1), (49_999, 140, 0, 1, 1),
+                                                         (49_157, 130, 0, 0, 300), (49_157, 130, 0, 1, 300), (49_157, 130, 1, 0, 300)])
+def test_percentiles_by_the_waves_and_by_their_own_kernel(ora, torch_cuda, n_cfg, n_req, tm, sched, longer):
     """Percentiles come from the simulation's waves, but for those of the longest configurations or of short traces: the same bits as
     in a list of one lane per wave, whose waves work out all of them."""
     torch = torch_cuda
-    g = wl.grid_full()
-    ctx = bridge.gpu_context(g)
     tr = wl.request_trace(n=n_req, seed=n_req)
-    idx, rate = wl.sim_configs(g, n_cfg, seed=n_req)
-    whole = _run(torch, ctx, g, idx, rate, tr)
+    if longer == 1:
+        g = wl.grid_full()
+        idx, rate = wl.sim_configs(g, n_cfg, seed=n_req)
+    else:                                               # (a pool that holds them)
+        tr = wl.Trace(tr.arrival_unit, tr.n_in, tr.n_out * np.uint32(longer))
+        g = _grid([1, 9, 60, 700])
+        idx = (np.arange(n_cfg) * 7 % g.size).astype(np.uint32)
+        rate = 1e-4 * 1.001 ** (np.arange(n_cfg) % 5000)
+        assert int(tr.n_out.sum()) > 1 << 22
+    ctx = bridge.gpu_context(g)
+    whole = _run(torch, ctx, g, idx, rate, tr, time_model=tm, scheduler=sched)
     assert (whole["status"] == guide.SIM_OK).sum() > n_cfg // 2
     pick = np.unique(np.linspace(0, n_cfg - 1, 1500).astype(np.int64))
-    part = _run(torch, ctx, g, np.ascontiguousarray(idx[pick]), np.ascontiguousarray(rate[pick]), tr)
+    part = _run(torch, ctx, g, np.ascontiguousarray(idx[pick]), np.ascontiguousarray(rate[pick]), tr, time_model=tm, scheduler=sched)
     for k in whole:
         np.testing.assert_array_equal(whole[k][pick], part[k], err_msg=k)
     # every configuration that ended has its percentiles, whichever kernel wrote them
     ok = whole["status"] == guide.SIM_OK
     assert np.all(np.isfinite(whole["ttft_p99"][ok])) and np.all(whole["ttft_p50"][ok] <= whole["ttft_p99"][ok])
     assert np.all(np.isinf(whole["ttft_p50"][~ok]))
+    if longer == 1:                                     # (a clock of 10^6 s has no 1e-9 of a TTFT of milliseconds)
+        few = pick[::125]
+        exp = ora.simulate_grid(bridge.ora_grid(g), idx[few], rate[few], tr.arrival_unit, tr.n_in, tr.n_out, time_model=tm, scheduler=sched)
+        _compare({k: v[few] for k, v in whole.items()}, exp)
