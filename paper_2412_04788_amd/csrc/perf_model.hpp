@@ -48,11 +48,11 @@ struct HwRecip {
     double r_peak, r_bw, cap, r_link, lat;
 };
 
-// rp = 1 / p_ (correctly rounded); dh = d / n_h; kv_heads = ceil(n_kv / p_).  p_exact: p_ is a power of two, and the
-// product with rp is the division's quotient.
-__device__ inline Coef make_coef(const guide_model &md, uint32_t p_, uint32_t wbits, double rp, double dh, uint32_t kv_heads,
-                                 bool p_exact) {
+// rp = 1 / p_ (correctly rounded)
+__device__ inline Coef make_coef(const guide_model &md, uint32_t p_, uint32_t wbits, double rp) {
     Coef c;
+    const double dh = (double)(md.d / md.n_h);
+    const uint32_t kv_heads = (md.n_kv + p_ - 1) / p_;
     const double p = (double)p_, w = (double)wbits * 0.125, a = kActBytes;
     const double d = (double)md.d;
     const double dq = (double)md.n_h * dh, dkv = (double)md.n_kv * dh;
@@ -86,15 +86,11 @@ __device__ inline Coef make_coef(const guide_model &md, uint32_t p_, uint32_t wb
     c.m_ar = p_ > 1 ? 2.0 * (p - 1.0) * rp * (a * d) : 0.0;
     c.n_ar = p_ > 1 ? 2.0 * (p - 1.0) : 0.0;
     c.p_total = c.L * (pattn + E * (pf1 + pf2) + prt) + 2.0 * V * d;
-    c.w_gpu = p_exact ? w * c.p_total * rp : w * c.p_total / p;     // same operation order as a plain evaluator
+    c.w_gpu = w * c.p_total / p;                // same operation order as a plain evaluator
     c.kv_tok = 2.0 * c.L * gkv * kKvBytes;
     c.E = E;
     c.k = k;
     return c;
-}
-
-__device__ inline Coef make_coef(const guide_model &md, uint32_t p_, uint32_t wbits, double rp) {
-    return make_coef(md, p_, wbits, rp, (double)(md.d / md.n_h), (md.n_kv + p_ - 1) / p_, false);
 }
 
 __device__ inline Coef make_coef(const guide_model &md, uint32_t p_, uint32_t wbits) {
@@ -132,15 +128,14 @@ __device__ inline double op_time(double t_compute, double t_memory) {
 
 // Sum of the layer ops that do not depend on the attention workload, plus the
 // norms and the two all-reduces: everything of a layer but attention.
-// DENSE: one expert, no router (the model is known to have E = k = 1, and T >= 1).
-template <bool ADDITIVE, bool DENSE = false>
+template <bool ADDITIVE>
 __device__ inline double layer_base(const TimeCoef &t, double T) {
-    const double eld = DENSE ? 1.0 : fmin(t.E, t.k * T);   // experts whose weights are read
+    const double eld = fmin(t.E, t.k * T);   // experts whose weights are read
     double s = op_time<ADDITIVE>(T * t.c[OP_QKV], fma(T, t.m1[OP_QKV], t.m0[OP_QKV]));
     s += op_time<ADDITIVE>(T * t.c[OP_OPROJ], fma(T, t.m1[OP_OPROJ], t.m0[OP_OPROJ]));
     s += op_time<ADDITIVE>(T * t.c[OP_UP], fma(T, t.m1[OP_UP], eld * t.m0[OP_UP]));
     s += op_time<ADDITIVE>(T * t.c[OP_DOWN], fma(T, t.m1[OP_DOWN], eld * t.m0[OP_DOWN]));
-    if (!DENSE) s += op_time<ADDITIVE>(T * t.c[OP_ROUTER], fma(T, t.m1[OP_ROUTER], t.m0[OP_ROUTER]));
+    s += op_time<ADDITIVE>(T * t.c[OP_ROUTER], fma(T, t.m1[OP_ROUTER], t.m0[OP_ROUTER]));
     s += T * t.m_nm;
     s += 2.0 * fma(T, t.ar1, t.ar0);
     return s;
@@ -157,9 +152,9 @@ __device__ inline double attention(const TimeCoef &t, double T, double Q, double
 }
 
 // t_pass = L * (layer ops + 2 all-reduces) + LM head.
-template <bool ADDITIVE, bool DENSE = false>
+template <bool ADDITIVE>
 __device__ inline double pass_time(const TimeCoef &t, double T, double Q, double K, double n_lm) {
-    return fma(t.L, layer_base<ADDITIVE, DENSE>(t, T) + attention<ADDITIVE>(t, T, Q, K), lm_head<ADDITIVE>(t, n_lm));
+    return fma(t.L, layer_base<ADDITIVE>(t, T) + attention<ADDITIVE>(t, T, Q, K), lm_head<ADDITIVE>(t, n_lm));
 }
 
 // Static batch of b prompts of s tokens under a budget of mbt tokens per pass.
@@ -252,7 +247,7 @@ __device__ inline double decode_time(const TimeCoef &t, uint32_t b_, uint32_t s_
 // Same prefill with the segment loop of long prompts summed in closed form and
 // the integer divisions replaced by nudged reciprocals (r_s ~ 1/s, r_mbt ~ 1/mbt,
 // both from recip_up).
-template <bool ADDITIVE, bool DENSE = false>
+template <bool ADDITIVE>
 __device__ inline double prefill_time_fast(const TimeCoef &t, uint32_t b, uint32_t s, uint32_t mbt, double r_s,
                                            double r_mbt) {
     const double S = (double)s;
@@ -262,10 +257,10 @@ __device__ inline double prefill_time_fast(const TimeCoef &t, uint32_t b, uint32
         const uint32_t n_full = r == b ? 1u : floor_div(b, recip_up(fast_recip((double)r)));
         const uint32_t rem = b - n_full * r;
         double R = (double)r;
-        double total = (double)n_full * pass_time<ADDITIVE, DENSE>(t, R * S, R * S * S, R * S, R);
+        double total = (double)n_full * pass_time<ADDITIVE>(t, R * S, R * S * S, R * S, R);
         if (rem > 0) {
             R = (double)rem;
-            total += pass_time<ADDITIVE, DENSE>(t, R * S, R * S * S, R * S, R);
+            total += pass_time<ADDITIVE>(t, R * S, R * S * S, R * S, R);
         }
         return total;
     }
@@ -274,7 +269,7 @@ __device__ inline double prefill_time_fast(const TimeCoef &t, uint32_t b, uint32
     const double M = (double)mbt, n_fs = (double)(n_seg - 1);
     const double c_last = S - n_fs * M;
     const double att = attention_series<ADDITIVE>(M * t.c_att, t.m_att_k, M * t.m_att_t, 0.0, M, r_mbt, n_fs);
-    const double one = fma(t.L, fma(n_fs, layer_base<ADDITIVE, DENSE>(t, M), att), pass_time<ADDITIVE, DENSE>(t, c_last, c_last * S, S, 1.0));
+    const double one = fma(t.L, fma(n_fs, layer_base<ADDITIVE>(t, M), att), pass_time<ADDITIVE>(t, c_last, c_last * S, S, 1.0));
     return (double)b * one;
 }
 
@@ -305,11 +300,11 @@ __device__ inline PrefillPlan make_prefill_plan(uint32_t b, uint32_t s, uint32_t
     }
     return p;
 }
-template <bool ADDITIVE, bool DENSE = false>
+template <bool ADDITIVE>
 __device__ inline double decode_time_fast(const TimeCoef &t, uint32_t b_, uint32_t s_, uint32_t n_) {
     if (n_ == 0) return 0.0;
     const double b = (double)b_, n = (double)n_;
-    const double base = fma(t.L, layer_base<ADDITIVE, DENSE>(t, b), lm_head<ADDITIVE>(t, b));
+    const double base = fma(t.L, layer_base<ADDITIVE>(t, b), lm_head<ADDITIVE>(t, b));
     const double att = attention_series<ADDITIVE>(b * t.c_att, b * t.m_att_k, b * t.m_att_t, (double)s_, 1.0, 1.0, n);
     return fma(n, base, t.L * att);
 }
