@@ -668,11 +668,12 @@ struct SweepTerms {
 // SHARED: the prefill's columns, which are the same for all values of s_out, are made by items of their own; the others then sort
 // one metric instead of two.  (One lane for several values of s_out, with the prefill's columns once for all of them, is slower,
 // 145 - 170 us: the waves whose terms change sides take three times as long as the others, and fewer, longer items do not even that out.)
-// Bound by the vector ALU, two waves per SIMD.  1.9 million configurations x 64 samples: 112 - 120 us a call, of which the set-up and the
-// stores are about 50; 122 with the samples' factors in scalar registers, 137 - 142 with one item for all columns as well (149 with products and sums of a term that changes sides apart and
-// the samples added one by one); 405 us with every task's two sides, the split of the series and the coefficients
-// worked out per sample.  Samples in the order of their ratios, so that a term changes sides in few groups of eight and is added up
-// once per group elsewhere, gain nothing: finding the groups costs what it saves.
+// Bound by the vector ALU, two waves per SIMD.  1.9 million configurations x 64 samples: 115 - 124 us a call by inputs and device, of which the
+// set-up and the stores are about 55 (a call with three samples takes 60); 142 with one item for all columns as well (8 more with products and sums of a
+// term that changes sides apart and the samples added one by one); 405 us with every task's two sides, the split of the series and the coefficients
+// worked out per sample.  The samples' factors in scalar registers instead of vector registers: 10 % slower.  Samples in the order of
+// their ratios, so that a term changes sides in few groups of eight and is added up once per group elsewhere, gain nothing: finding
+// the groups costs what it saves.
 template <bool ADDITIVE, bool SHARED>
 __global__ __launch_bounds__(kBlock, 2) void eval_sweep_kernel(GridDesc g, const DevTables *__restrict__ tab,
                                                             uint32_t first, uint32_t count, uint32_t n_eff,
@@ -1441,11 +1442,14 @@ hipError_t launch_eval_sweep(const GridDesc &g, const DevTables *tab, const void
     items.first_group = first / ts / span;
     const uint32_t n_rest = ((first + count - 1) / ts - first / ts + 1) * nm;
     items.prefill_end = ((first + count - 1) / ts / span - items.first_group + 1) * items.inner * nm;
-    // Items of the prefill pay where they are few (six values of s_out or more) and the others fill the chip more than once.
-    // In us, all columns by one item / apart, 64 samples whose factors were still moved to scalar registers: 1.9 million rows
-    // 137 - 142 / 122, additive 92 / 78; 950 000 82 / 71; 317 000 37.4 / 33.1; 127 000 rows (half a round) 20.8 / 22.2; five
-    // values of s_out 139 / 138 - 145; 1.9 million rows of two samples 55 - 58 / 56, of eight 59.4 / 59.4, of 24 81.3 / 77.5.
-    const bool shared = n_rest > most * kBlock && items.prefill_end < n_rest / 5 && n_rest < 3u << 30;      // (the sum fits 32 bits)
+    // Items of the prefill pay where they are few (six values of s_out or more), the others fill the chip more than once, and there
+    // are samples enough to sort.  In us, all columns by one item / apart, 64 samples: 1.9 million rows 142 / 122, additive 99 / 80,
+    // without columns of the prefill 136 / 117; 950 000 75.4 / 63.3; 317 000 32.6 / 26.9; seven values of s_out 116 / 103, six 99 / 89.
+    // 1.9 million rows of two samples 54.2 / 56.7 (without columns of the prefill 52.6 / 54.3), of three 60.6 / 60.6 - 62.0, of four
+    // 63.4 / 63.6 - 65.5, additive 40.4 / 38.7, 950 000 38.0 / 36.2; of five 64.6 / 64.6, of eight 60.2 / 58.2, of 24 79.3 / 74.4 (with few
+    // samples stores are half of it, and where the columns lie makes a difference of 2 us).  The lines of lengths and rows are on the safe side: five values
+    // 89 / 78, four 76 / 71, 127 000 rows (half a round) 18.9 / 17.1.
+    const bool shared = n_eff >= 4 && n_rest > most * kBlock && items.prefill_end < n_rest / 5 && n_rest < 3u << 30;      // (the sum fits 32 bits)
     items.n_prefill = shared ? (items.prefill_end - 1) / kWave * kWave + kWave : 0u;
     items.n = items.n_prefill + n_rest;
     const uint32_t need = (items.n - 1) / kBlock + 1;

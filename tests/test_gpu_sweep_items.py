@@ -1,6 +1,6 @@
-"""Efficiency sweeps whose prefill columns are made by items of their own (many rows, six generation lengths or more): the
-same bits as in pieces that are too small for that, whatever part of the grid is asked for; and the order in which the
-samples are added up."""
+"""Efficiency sweeps whose prefill columns are made by items of their own (many rows, six generation lengths and four
+samples or more): the same bits as in pieces that are too small for that, whatever part of the grid is asked for; and the order in
+which the samples are added up."""
 import numpy as np
 import pytest
 
@@ -31,7 +31,8 @@ def _sweep(ctx, g, e_c, e_b, first, count, tm):
 # (99 rows) in lane
 @pytest.mark.parametrize("n_so,n_blk,n_mbt,first,less,n_eff,tm,tp",
                          [(6, 1, 1, 0, 0, 9, 0, (1, 2, 8)), (8, 2, 3, 1237, 5, 8, 0, (1, 2, 8)), (7, 2, 5, 31, 40_001, 3, 1, (1, 2, 8)),
-                          (64, 1, 2, 7, 0, 2, 0, (1, 2, 8)), (6, 2, 2, 77, 9, 20, 0, range(1, 12)), (6, 2, 2, 77, 9, 20, 1, range(1, 12))])
+                          (64, 1, 2, 7, 0, 2, 0, (1, 2, 8)), (64, 1, 2, 7, 0, 4, 0, (1, 2, 8)), (7, 2, 5, 31, 40_001, 5, 1, (1, 2, 8)),
+                          (6, 2, 2, 77, 9, 20, 0, range(1, 12)), (6, 2, 2, 77, 9, 20, 1, range(1, 12))])
 def test_prefill_items(n_so, n_blk, n_mbt, first, less, n_eff, tm, tp):
     items_above = -(-170_000 // (n_so * n_mbt * 3 * len(tp)))              # settings of model, hw, batch, s_in
     n_b = -(-items_above // (3 * 2 * 3))
