@@ -1170,12 +1170,19 @@ hipError_t launch_simulate(const GridDesc &g, const DevTables *tab, const TraceD
         hipLaunchKernelGGL(sim_order_scan_kernel, dim3(1), dim3(kKeyBins), 0, stream, ws);
         hipLaunchKernelGGL(sim_order_scatter_kernel, ogrid, oblock, 0, stream, n_cfg, ws);
     }
-    // Waves of a lane each work out their own percentiles, and so do all but the dealt part's in blocks of four waves, which wait for
-    // the longest ones otherwise: where the trace is long enough that working them out one after the other pays.  With / without, in us:
-    // 65 536 x 64 304 / 281, x 96 427 / 423, x 128 499 / 520, x 300 1241 / 1283, x 600 2418 / 2447, x 1024 3717 / 3925; 200 000 x 100 1545 /
-    // 1519, x 200 2832 / 2946; two or three waves 20 000 x 600 2375 / 2288, 49 000 x 1024 3828 / 3865; a lane a wave 1999 x 97 285 / 327,
-    // 2000 x 16 54 / 66, 1500 x 1024 3050 / 3311, 300 x 1024 2826 / 2827.
-    const bool own_percentiles = lanes == 1 || (ordered && waves > 3 && n_req >= 128);
+    // Who works out the percentiles.  In blocks of four waves, those that are done before the longest ones: where the trace is long enough, and
+    // fills the values that are sorted well enough (256 from 129 requests on, 512 from 257 on, ..), that working them out one after the other is done
+    // by then.  In us, by the waves / by a kernel: 65 536 x 64 304 / 281, x 96 427 / 423, x 128 557 / 580, x 129 612 / 592, x 150 and 160 as
+    // long (+1 %), x 192 5 % less, x 300 1257 / 1306, x 600 2410 / 2490, x 1024 3743 / 3930; 80 000 x 129 and 140 5 % more, x 160 1.5 % more, x 180
+    // 1 % less; 300 000 x 129 1 % more, x 150 3 % less.  With fewer blocks than compute units: 49 153 x 257 and 513 1.3 % more, x 288 and 576 1 %
+    // less.  Two or three waves: 20 000 x 600 2375 / 2288, 49 000 x 1024 3828 / 3865.  Waves of a lane each do it themselves, which saves the launch: 2000 x 16
+    // 56 / 67, 1999 x 97 285 / 327, 1500 x 1024 2967 / 3240, 300 and 512 configurations within 3 % either way from 200 requests on; but a wave that has a compute unit to itself has nobody to
+    // wait for, and the loop over the rounds is 2 - 3 % slower in this variant: 256 x 16 50 / 54, x 60 153 / 154, x 300 724 / 708, x 1024 2440 / 2334.
+    uint32_t sorted = kWave;                            // values that are sorted
+    while (sorted < n_req) sorted *= 2;
+    const uint32_t sixteenths = sorted == 4 * kWave ? 10u : sorted > 4 * kWave && grid.x < cus ? 9u : 0u;   // of them at least are requests
+    const bool own_percentiles = lanes == 1 ? n_cfg > cus || n_req <= kWave
+                                            : ordered && waves > 3 && n_req >= 128 && 16 * n_req >= sixteenths * sorted;
     const int variant = (additive ? 4 : 0) | (prefill_first ? 2 : 0) | (key32 ? 1 : 0);
 #define GUIDE_SIM(A, P, K32)                                                                                       \
     case ((A ? 4 : 0) | (P ? 2 : 0) | (K32 ? 1 : 0)): {                                                             \

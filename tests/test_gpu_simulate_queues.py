@@ -139,8 +139,10 @@ def test_arrivals_beyond_the_range_of_doubles(ora, torch_cuda, n_out):
 # (also the additive model, whole prompts first, and generations that take 64-bit keys)
 @pytest.mark.parametrize("n_cfg,n_req,tm,sched,longer", [(50_000, 127, 0, 0, 1), (50_000, 128, 0, 0, 1), (49_153, 129, 0, 0, 1), (70_001, 64, 0, 0, 1),
                                                          (20_000, 512, 0, 0, 1), (20_000, 513, 0, 0, 1), (33_000, 600, 0, 0, 1),
-                                                         (49_999, 140, 1, 0, 1), (49_999, 140, 1, 1, 1), (49_999, 140, 0, 1, 1),
-                                                         (49_157, 130, 0, 0, 300), (49_157, 130, 0, 1, 300), (49_157, 130, 1, 0, 300)])
+                                                         (66_000, 159, 0, 0, 1), (66_000, 160, 0, 0, 1), (49_153, 287, 0, 0, 1), (49_153, 288, 0, 0, 1),
+                                                         (65_537, 257, 0, 0, 1), (49_999, 170, 1, 0, 1), (49_999, 170, 1, 1, 1), (49_999, 170, 0, 1, 1),
+                                                         (49_157, 190, 0, 0, 300), (49_157, 190, 0, 1, 300), (49_157, 190, 1, 0, 300),
+                                                         (256, 64, 0, 0, 1), (256, 65, 0, 0, 1), (257, 65, 0, 0, 1)])
 def test_percentiles_by_the_waves_and_by_their_own_kernel(ora, torch_cuda, n_cfg, n_req, tm, sched, longer):
     """Percentiles come from the simulation's waves, but for those of the longest configurations or of short traces: the same bits as
     in a list of one lane per wave, whose waves work out all of them."""
