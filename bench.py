@@ -324,9 +324,11 @@ def front_timings(ctx, n, torch, np, guide, sizes=(100, 1000, 4000, 5000, 20000,
 
 
 def extra_timings(ctx, gg, g, torch, np, guide, wl, n_sampled=1 << 28, n_sim=65536):
-    """Sweep (1.9M x 64 samples), sampled space (2^28), serving simulation (65 536 x 1024 requests)."""
+    """Sweep (1.9M x 64 samples), sampled space (2^28), serving simulation (65 536 x 1024 requests).  One call each after a
+    synchronisation, so the launch and the clocks' way up are in it: among others a sweep takes 115 - 130 us instead of 140 - 160,
+    the sampled space 3.6 ms instead of 3.7 - 4.2."""
     n = g.size
-    extra = {}
+    extra = {"timing": "one call after a warm-up call and a synchronisation (cluster_extras: five calls, sweep_pipeline: three)"}
     e_c, e_b = wl.efficiency_pairs()
     dt = {"b_max": torch.int32, "feasible": torch.uint8}
     st = {k: torch.empty(n, dtype=dt.get(k, torch.float64), device="cuda") for k in guide.STATS_COLUMNS}

@@ -1749,9 +1749,9 @@ __global__ __launch_bounds__(kFinishThreads) void pareto_finish_kernel(ParetoWs 
 
 // Selections over at most kStage rows: one launch without sample, filter pass and block partials.  Block 0 takes the
 // Pareto selection (sel.pareto) with every passing row as a record; the next one (or block 0) the top-k of one group.
-// Bound by latency.  1080 rows, both selections: 12.5 us, with the evaluation 16.3 us a call; filter pass and finishing
-// kernel took 10.2 + 8.3 us, 25.4 us a call.  A front of 155 among 4096 rows alone: 15.6 us (22.6 in three launches), so
-// the line lies where the records stop fitting the finishing block.
+// Bound by latency.  1080 rows, both selections: 9.5 us, with the evaluation 13.4 us a call (12.6 and 15.7 us with the waves' totals gone
+// through by every wave); filter pass and finishing kernel took 10.2 + 8.3 us, 25.4 us a call.  A front of 155 among 4096 rows alone: 15.7 us
+// (17.6; 22.6 in three launches), so the line lies where the records stop fitting the finishing block.
 struct SmallSelect {
     uint32_t pareto, k;                 // k = 0: no top-k
     const double *x, *y;

@@ -734,9 +734,10 @@ struct TraceSums {
 // differ from call to call): the results of a configuration are the same bits in every list and every call.
 // What bounds the kernel: a wave is a serial stream of instructions, four to six cycles each, and the waves of a compute unit
 // share its fetch; the longest wave sets the time (65 536 configurations x 1024 requests: 2080 rounds of 4080 cycles, second
-// admissions included; a wave has 673 000 vector, 163 000 scalar and 40 000 LDS instructions and waits a third of its cycles).
-// A call with percentiles: 3.72 ms, 3.62 ms under the other scheduler; 1999 x 97: 0.29 ms.  With all percentiles after the last wave's end
-// 3.92, 3.95 and 0.33 ms: the waves of the first three parts of a list are done 0.5 - 1.3 ms before the dealt part's.
+// admissions included; a wave has 673 000 vector, 163 000 scalar and 40 000 LDS instructions in the mean, 841 000, 184 000 and 47 000 with
+// three quarters of the percentiles, and waits a third of its cycles).
+// A call with percentiles: 3.74 ms, 3.60 ms under the other scheduler; 1999 x 97: 0.27 - 0.36 ms by the trace.  With all percentiles after the last
+// wave's end 3.95, 3.97 and 0.31 - 0.42 ms: the waves of the first three parts of a list are done 0.5 - 1.3 ms before the dealt part's.
 // (4-ary heaps in LDS, strides of 64 and 8 steps, forty branches a round: 7.7, 6.4 and 0.71 ms.)
 // heap_bytes: LDS behind the staged trace, shared out among the block's lanes by what each expects.
 // OWN: waves work out the percentiles of their own configurations, but for those of the dealt part.  (A variant of its own: with
@@ -1172,8 +1173,8 @@ hipError_t launch_simulate(const GridDesc &g, const DevTables *tab, const TraceD
     }
     // Who works out the percentiles.  In blocks of four waves, those that are done before the longest ones: where the trace is long enough, and
     // fills the values that are sorted well enough (256 from 129 requests on, 512 from 257 on, ..), that working them out one after the other is done
-    // by then.  In us, by the waves / by a kernel: 65 536 x 64 304 / 281, x 96 427 / 423, x 128 557 / 580, x 129 612 / 592, x 150 and 160 as
-    // long (+1 %), x 192 5 % less, x 300 1257 / 1306, x 600 2410 / 2490, x 1024 3743 / 3930; 80 000 x 129 and 140 5 % more, x 160 1.5 % more, x 180
+    // by then.  In us, by the waves / by a kernel: 65 536 x 64 304 / 281, x 96 427 / 423, x 128 557 / 580, x 129 612 / 592, x 150 and 160
+    // 1 % less, x 192 5 % less, x 300 1257 / 1306, x 600 2410 / 2490, x 1024 3743 / 3930; 80 000 x 129 and 140 5 % more, x 160 1.5 % more, x 180
     // 1 % less; 300 000 x 129 1 % more, x 150 3 % less.  With fewer blocks than compute units: 49 153 x 257 and 513 1.3 % more, x 288 and 576 1 %
     // less.  Two or three waves: 20 000 x 600 2375 / 2288, 49 000 x 1024 3828 / 3865.  Waves of a lane each do it themselves, which saves the launch: 2000 x 16
     // 56 / 67, 1999 x 97 285 / 327, 1500 x 1024 2967 / 3240, 300 and 512 configurations within 3 % either way from 200 requests on; but a wave that has a compute unit to itself has nobody to
